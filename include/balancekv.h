@@ -190,8 +190,8 @@ int bkv_attend_kv(const bkv_params* p, const void* K_c, const void* V_c, const f
  * bkv_attend_kv, without `workspace`: the partial sums of a split token range go to a static device array inside the
  * library (bkv_attend_kv_static_max_bytes() bytes, 2.25 MiB, held by every GPU the library runs on until the process
  * ends).  The call allocates nothing and frees nothing.  A launch whose partials would not fit the array returns
- * BKV_EWORKSPACE (with today's launch plan -- at most 1023 (workgroup, split) pairs of 4 x (d + 2) floats whenever the
- * range is split -- every shape that bkv_attend_kv accepts fits).  All calls on one GPU share the array: calls that
+ * BKV_EWORKSPACE (with today's launch plan, which cuts a range into fewer splits where their partials would not fit, every
+ * shape that bkv_attend_kv accepts fits).  All calls on one GPU share the array: calls that
  * overlap in time on the same GPU (different streams, different threads) race; calls on one stream do not.  The
  * array keeps the last call's partials; every launch writes all partials it later reads, nothing needs clearing.  */
 size_t bkv_attend_kv_static_max_bytes(void);

@@ -315,10 +315,10 @@ size_t bkv_attend_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t co
 
 }  // extern "C"
 
-// exact_need: the workspace need only hold what this very launch writes (else: the public, count-independent bound)
+// static_scratch: the workspace is the library's own array (fewer splits where the partials would not fit it)
 static int attend_kv_impl(const bkv_params* p, const void* K_c, const void* V_c, const float* w, int64_t n_seq,
                           int64_t count, int64_t stride_tokens, const void* Q, int32_t g, int32_t nq, void* out,
-                          float* lse_out, void* workspace, size_t ws_bytes, bool exact_need, void* hip_stream) {
+                          float* lse_out, void* workspace, size_t ws_bytes, bool static_scratch, void* hip_stream) {
     int rc = check_params(p);
     if (rc) return rc;
     if (n_seq < 0 || count < 0 || stride_tokens < count || g <= 0 || nq <= 0) return BKV_EINVAL;
@@ -335,15 +335,17 @@ static int attend_kv_impl(const bkv_params* p, const void* K_c, const void* V_c,
         return BKV_OK;
     }
     if (!K_c || !V_c || !w || !aligned16(K_c) || !aligned16(V_c)) return BKV_EINVAL;
-    const size_t need = exact_need ? bkv::attend_partial_bytes(p->dtype, p->d, n_seq, count, n_q)
-                                   : bkv::attend_workspace_bytes(p->d, n_seq, n_q);
+    const size_t limit = static_scratch ? bkv::kAttendStaticPartialBytes : bkv::kAttendPartialBytes;
+    const size_t need = static_scratch ? bkv::attend_scratch_bytes(p->dtype, p->d, n_seq, count, n_q, limit)
+                                       : bkv::attend_workspace_bytes(p->d, n_seq, n_q);
     if (!workspace || ws_bytes < need || !aligned16(workspace)) return BKV_EWORKSPACE;
     bkv::AttendArgs a;
     memset(&a, 0, sizeof(a));
-    a.K = (const char*)K_c; a.V = (const char*)V_c; a.w = w; a.Q = (const char*)Q; a.out = (char*)out;
-    a.lse_out = lse_out; a.stride_tokens = stride_tokens; a.count = count; a.n_q = n_q;
+    a.set[0].K = (const char*)K_c; a.set[0].V = (const char*)V_c; a.set[0].w = w;
+    a.set[0].stride = stride_tokens; a.set[0].count = count;
+    a.Q = (const char*)Q; a.out = (char*)out; a.lse_out = lse_out; a.n_seq = n_seq; a.n_q = n_q;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
-    e = bkv::launch_attend(p->dtype, p->d, a, n_seq, workspace, st);
+    e = bkv::launch_attend(p->dtype, p->d, a, workspace, limit, st);
     return e == hipSuccess ? BKV_OK : hip_fail(e);
 }
 
@@ -365,8 +367,9 @@ int bkv_attend_kv_static(const bkv_params* p, const void* K_c, const void* V_c, 
     if (rc) return rc;
     if (n_seq < 0 || count < 0 || g <= 0 || nq <= 0) return BKV_EINVAL;
     if (n_seq > 65535 || (int64_t)g * nq > 4 * 65535) return BKV_ESHAPE;
-    // what this launch would write into the partial buffer must fit the library's static array
-    if (bkv::attend_partial_bytes(p->dtype, p->d, n_seq, count, g * nq) > bkv::kAttendStaticScratchBytes) return BKV_EWORKSPACE;
+    // what this launch would write into the scratch buffer must fit the library's static array
+    if (bkv::attend_scratch_bytes(p->dtype, p->d, n_seq, count, g * nq, bkv::kAttendStaticPartialBytes) > bkv::kAttendStaticScratchBytes)
+        return BKV_EWORKSPACE;
     void* ws = nullptr;
     const hipError_t e = bkv::attend_static_scratch(&ws);
     if (e != hipSuccess) return hip_fail(e);
@@ -441,9 +444,7 @@ int bkv_balancekv_sets(const bkv_params* p_in, int32_t which, const void* K, con
 
 size_t bkv_attend_sets_workspace_bytes(const bkv_params* p, int64_t n_seq, int32_t g, int32_t nq) {
     if (check_params(p) || n_seq < 0 || g <= 0 || nq <= 0) return 0;
-    const size_t rows = (size_t)n_seq * g * nq;
-    return align_up(bkv::attend_workspace_bytes(p->d, n_seq, g * nq), 256) + 2 * align_up(rows * 4, 256) +
-           align_up(rows * (size_t)row_bytes(p), 256);
+    return align_up(bkv::attend_workspace_bytes(p->d, n_seq, g * nq, 2), 256);
 }
 
 int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const float* w_n, int64_t count_n, int64_t stride_n,
@@ -456,31 +457,20 @@ int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const
     if (n_seq == 0) return BKV_OK;
     const size_t need = bkv_attend_sets_workspace_bytes(p, n_seq, g, nq);
     if (!workspace || ws_bytes < need || !aligned16(workspace)) return BKV_EWORKSPACE;
-    const size_t rows = (size_t)n_seq * g * nq;
-    char* ws = (char*)workspace;
-    void* att_ws = ws;
-    const size_t att_bytes = align_up(bkv::attend_workspace_bytes(p->d, n_seq, g * nq), 256);
-    ws += att_bytes;
-    float* lse_n = (float*)ws; ws += align_up(rows * 4, 256);
-    float* lse_d = (float*)ws; ws += align_up(rows * 4, 256);
-    void* scratch = ws;
-    // numerator sum / its own normaliser, then the normaliser of the denominator set (no value rows are read for it)
-    rc = bkv_attend_kv(p, K_n, V_n, w_n, n_seq, count_n, stride_n, Q, g, nq, out, lse_n, att_ws, att_bytes, hip_stream);
-    if (rc) return rc;
-    float* lse_den = lse_out ? lse_out : lse_d;
-    hipError_t e;
-    if (count_d == 0) {
-        if ((e = bkv::launch_fill_u32(lse_den, 0xff800000u, (int64_t)rows, (hipStream_t)hip_stream)) != hipSuccess) return hip_fail(e);
-    } else {
-        if (stride_d < count_d || !K_d || !w_d || !aligned16(K_d) || !Q || !aligned16(Q)) return BKV_EINVAL;
-        bkv::AttendArgs a;
-        memset(&a, 0, sizeof(a));
-        a.K = (const char*)K_d; a.V = nullptr; a.w = w_d; a.Q = (const char*)Q; a.out = (char*)scratch;
-        a.lse_out = lse_den; a.stride_tokens = stride_d; a.count = count_d; a.n_q = g * nq;
-        a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
-        if ((e = bkv::launch_attend(p->dtype, p->d, a, n_seq, att_ws, (hipStream_t)hip_stream)) != hipSuccess) return hip_fail(e);
-    }
-    e = bkv::launch_rescale(p->dtype, out, lse_n, lse_den, (int64_t)rows, p->d, (hipStream_t)hip_stream);
+    if (n_seq > 65535 || (int64_t)g * nq > 4 * 65535) return BKV_ESHAPE;
+    if (stride_n < count_n || stride_d < count_d || !Q || !out || !aligned16(Q) || !aligned16(out)) return BKV_EINVAL;
+    if (count_d == 0)                                                            // both sets empty: zeros, lse = -inf
+        return bkv_attend_kv(p, K_n, V_n, w_n, n_seq, 0, stride_n, Q, g, nq, out, lse_out, workspace, ws_bytes, hip_stream);
+    if (count_n > 0 && (!K_n || !V_n || !w_n || !aligned16(K_n) || !aligned16(V_n))) return BKV_EINVAL;
+    if (!K_d || !w_d || !aligned16(K_d)) return BKV_EINVAL;
+    // one pass over both sets: the numerator's sums, and the normaliser of the denominator set (no value rows are read for it)
+    bkv::AttendArgs a;
+    memset(&a, 0, sizeof(a));
+    a.set[0].K = (const char*)K_n; a.set[0].V = (const char*)V_n; a.set[0].w = w_n; a.set[0].stride = stride_n; a.set[0].count = count_n;
+    a.set[1].K = (const char*)K_d; a.set[1].w = w_d; a.set[1].stride = stride_d; a.set[1].count = count_d;
+    a.Q = (const char*)Q; a.out = (char*)out; a.lse_out = lse_out; a.n_seq = n_seq; a.n_q = g * nq;
+    a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
+    const hipError_t e = bkv::launch_attend(p->dtype, p->d, a, workspace, bkv::kAttendPartialBytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? BKV_OK : hip_fail(e);
 }
 

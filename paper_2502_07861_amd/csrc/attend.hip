@@ -1,361 +1,587 @@
 // Decode attention against the compressed, weighted cache (Alg. 1 output line of arXiv 2502.07861):
 //   z = sum_i w_i e^{<k_i,q>/sqrt d} v_i / sum_i w_i e^{<k_i,q>/sqrt d},  w_i = 2^level(i).
-// w_i e^x = 2^{x log2(e) + log2 w_i}: a softmax with logit bias log2 w_i, evaluated with a running
-// maximum.  The pass is one stream over K, V, w (HBM bound): every lane owns a 16-byte slice of a
-// row, a group of kSlices lanes owns a row, each wavefront covers 64/kSlices rows per step, and up to
-// QT query vectors that share the KV sequence (GQA) are served from the same loads.  The token range
-// is split over workgroups; partial (max, denominator, numerator) triples are merged by a second
-// small kernel, which also emits the log-denominator so callers can merge further partials.
+// w_i e^x = 2^{x log2(e) + log2 w_i}: a softmax with logit bias log2 w_i, evaluated with a running reference exponent.
+// Optionally numerator and denominator run over two sets of their own (Alg. 1 as listed).
+//
+// Both contractions run on the matrix cores in 16x16 tiles and nothing is staged through LDS: a wavefront takes groups
+// of kKeys keys (32 bf16, 16 fp32) straight from memory into operand registers.  With lane = 16 kg + n:
+//   S^T = K Q^T   rows = keys, columns = queries.  Lane (n, kg) holds piece kg of every 64 bytes of key row n (A) and of
+//                 query n (B): the same pieces, so the contraction meets every column once.  Result: query n, keys 4 kg + r.
+//   O^T += V^T P  the weights are already where the next product wants them (column = query n, the lane's own keys), if the
+//                 lane loads the value rows of exactly those keys.  It takes columns d = kEpn n + e, e < kEpn, of each (16
+//                 lanes cover a row): element e is operand row n of product e.  bf16 pairs two keys per register by a byte
+//                 permute; fp32 elements are operands as they are.
+// So the pass needs no transposes, and a query's weights, running reference and sums stay in its own lanes.
+// What bounds it: with few queries per sequence the stream over K, V, w (1024 sequences x 8321 tokens x 4 queries, bf16:
+// 704 us = 6.25 TB/s); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
+// tokens x 256 queries: 23 us; 113 us on the vector units, four queries per pass); short ranges the sum of two memory
+// round trips and the hand-over between workgroups (8 x 4357 tokens: 11 us in one launch; 14 us as pass + merge launches).
+#include <atomic>
+
 #include "bkv_device.h"
 #include "bkv_host.h"
 
 namespace bkv {
 
-constexpr int kQT = 4;           // query vectors per pass over the cache
-constexpr int kAttWaves = 4;
-constexpr int kUnroll = 4;       // rows in flight per lane group
-constexpr int kTargetWGs = 512;    // workgroups of the streaming pass when the token range is split (two per compute unit:
-                                   // more only lengthen the merge, measured from 8 to 256 sequences)
-constexpr float kNeg = -1.0e30f; // "minus infinity" that stays finite under subtraction
+constexpr int kTargetWaves = 2048;           // wavefronts of the pass when token ranges are split (see attend_plan)
+constexpr int kRowPad = 4;                   // floats behind the D sums of a partial row: [0] reference exponent, [1] denominator
+constexpr float kNeg = -1.0e30f;             // "minus infinity" that stays finite under subtraction
+constexpr float kSlack = 6.f;                // weights may exceed the running reference by 2^6 before it moves
 
-// HASV = false: the normaliser alone (Alg. 1's denominator sum over a set of its own): no value row is read, the
-// output columns are zero, lse_out carries the result.
-template <typename T, int D, bool HASV = true>
-__global__ __launch_bounds__(kAttWaves * 64) void attend_partial_kernel(const AttendArgs a) {
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));     // four consecutive weights, any alignment
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// ---------------------------------------------------------------------------------------------------------------------
+// "Am I the last of `total` workgroups to get here?", without anybody having cleared the counter before: the workspace is
+// the caller's and arrives with any content.  word[0] is (48-bit mark | 16-bit count); while the mark is there one
+// fetch-add per workgroup decides.  A word without it (first use of this memory) sends all workgroups of the launch to
+// word[1], a counter labelled with the launch's own number by compare-and-swap (at most `total` failed attempts each,
+// because every failure is another workgroup's success).  The last one leaves word[0] marked and zero for the next
+// launch.  Calls that share a workspace must not overlap, as before; replays of a captured launch find word[0] as the
+// previous replay left it.
+constexpr unsigned long long kMark = 0x5bd1e995a7c3ull << 16;
+__device__ __forceinline__ bool arrive_last(unsigned long long* word, unsigned int total, unsigned long long label) {
+    const unsigned long long old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned int before;
+    if ((old & ~0xffffull) == kMark) before = (unsigned int)(old & 0xffffull);
+    else {
+        unsigned long long cur = __hip_atomic_load(word + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (;;) {
+            before = (cur & ~0xffffull) == label ? (unsigned int)(cur & 0xffffull) : 0u;
+            if (__hip_atomic_compare_exchange_strong(word + 1, &cur, label | (before + 1u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) break;
+        }
+    }
+    if (before + 1u != total) return false;
+    __hip_atomic_store(word + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(word, kMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// Partial rows travel between workgroups (other XCDs, other L2s) past the caches, two floats at a time: device-scope
+// accesses, ordered by waiting for them.  A release fence per workgroup would write back its XCD's whole L2 instead, which
+// made a pass of 500 workgroups twice as long.
+__device__ __forceinline__ void put2(float* p, float x, float y) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, floatx2{x, y}), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ floatx2 get2(const float* p) {
+    return __builtin_bit_cast(floatx2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ float log2_or(float l, float m) { return m + __builtin_amdgcn_logf(l); }      // v_log_f32 = log2
+
+template <typename T> __device__ __forceinline__ void store4(char* out, size_t i, const floatx4& z) {
+    if constexpr (sizeof(T) == 2) {
+        const uintx2 p = {f32_to_bf16_bits(z[0]) | (f32_to_bf16_bits(z[1]) << 16), f32_to_bf16_bits(z[2]) | (f32_to_bf16_bits(z[3]) << 16)};
+        *reinterpret_cast<uintx2*>(out + i * 2) = p;
+    } else {
+        *reinterpret_cast<floatx4*>(out + i * 4) = z;
+    }
+}
+
+// Sum the partial rows of `nq` consecutive queries over the splits of the numerator set, divide by the denominator (of
+// the same set, or of the second one), store.  part: row 0 of split 0; consecutive splits are `sstride` floats apart; splits
+// ns0 .. ns0 + ns1 - 1 belong to the second set.  Whole workgroup of NTH threads; a thread owns four columns of a query and
+// every SR-th split, with a running reference of its own, so that one pass of independent loads is all the latency there is;
+// the order of all sums is fixed.
+template <typename T, int D, int NTH>
+__device__ __forceinline__ void merge_rows(const float* part, size_t sstride, int nq, int ns0, int ns1, char* out, float* lse_out,
+                                           size_t row0, float* red /*[NTH * 8]*/) {
+    constexpr int P = D + kRowPad, CG = D / 4;
+    const int tid = threadIdx.x;
+    const int C = nq * CG, SR = C < NTH ? NTH / C : 1;            // splits summed side by side
+    for (int c0 = 0; c0 < C; c0 += NTH) {
+        const int sg = SR > 1 ? tid / C : 0, c = SR > 1 ? tid - sg * C : c0 + tid;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        float M = kNeg, L = 0.f, Md = kNeg, Ld = 0.f;
+        const int q = c / CG, col = 4 * (c - q * CG);
+        const float* row = part + (size_t)q * P;
+        if (sg < SR && c < C) {
+// (twelve splits requested before the first is used: device-scope loads are not reordered by the compiler)
+            constexpr int U = 12;
+            for (int s = sg; s < ns0; s += U * SR) {
+                floatx2 ml[U], x[U], y[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float* r = row + (size_t)min(s + u * SR, ns0 - 1) * sstride;
+                    ml[u] = get2(r + D); x[u] = get2(r + col); y[u] = get2(r + col + 2);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (s + u * SR >= ns0) break;
+                    const float mn = fmaxf(M, ml[u][0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(ml[u][0] - mn);
+                    M = mn; L = L * f0 + ml[u][1] * f1;
+                    acc[0] = acc[0] * f0 + x[u][0] * f1; acc[1] = acc[1] * f0 + x[u][1] * f1;
+                    acc[2] = acc[2] * f0 + y[u][0] * f1; acc[3] = acc[3] * f0 + y[u][1] * f1;
+                }
+            }
+            for (int s = ns0 + sg; s < ns0 + ns1; s += U * SR) {
+                floatx2 ml[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) ml[u] = get2(row + (size_t)min(s + u * SR, ns0 + ns1 - 1) * sstride + D);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (s + u * SR >= ns0 + ns1) break;
+                    const float mn = fmaxf(Md, ml[u][0]);
+                    Ld = Ld * fast_exp2(Md - mn) + ml[u][1] * fast_exp2(ml[u][0] - mn);
+                    Md = mn;
+                }
+            }
+        }
+        if (SR > 1) {
+            float* mine = red + tid * 8;
+            *reinterpret_cast<floatx4*>(mine) = acc;
+            *reinterpret_cast<floatx4*>(mine + 4) = floatx4{M, L, Md, Ld};
+            __syncthreads();
+            if (tid >= C) return;
+            for (int r = 1; r < SR; ++r) {
+                const floatx4 x = *reinterpret_cast<const floatx4*>(red + (r * C + tid) * 8), k = *reinterpret_cast<const floatx4*>(red + (r * C + tid) * 8 + 4);
+                const float mn = fmaxf(M, k[0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(k[0] - mn);
+                M = mn; L = L * f0 + k[1] * f1;
+                acc = acc * f0 + x * f1;
+                const float dn = fmaxf(Md, k[2]);
+                Ld = Ld * fast_exp2(Md - dn) + k[3] * fast_exp2(k[2] - dn);
+                Md = dn;
+            }
+        }
+        if (c < C) {
+            float f = L > 0.f ? 1.f / L : 0.f;
+            if (ns1 > 0) {
+                f = L > 0.f && Ld > 0.f ? fast_exp2(M - Md) / Ld : 0.f;
+                M = Md; L = Ld;
+            }
+            store4<T>(out, (row0 + q) * D + col, acc * f);
+            if (lse_out && col == 0) lse_out[row0 + q] = L > 0.f ? log2_or(L, M) * 0.6931471805599453f : -INFINITY;
+        }
+    }
+}
+
+// One workgroup of W wavefronts: NQT x 16 queries of one sequence against one range of keys; its wavefronts take the
+// key groups of the range in turn.  Registers (NQT = 1, bf16, d = 128): 64 for the K and V rows in flight, 16 queries, 32
+// sums.  The rows of the next group are requested as soon as the registers of the current one are free (keys after S^T,
+// values after O^T), so that about 12 KB per wavefront are under way at any time.
+template <typename T, int D, int NQT, int W>
+__global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
+    constexpr bool B16 = sizeof(T) == 2;
     constexpr int ROWB = D * (int)sizeof(T);
-    constexpr int SL = ROWB / 16;              // lanes per row
-    constexpr int RPW = 64 / SL;               // rows per wavefront per step
-    constexpr int EPL = Elem<T>::kPerFrag;     // elements per lane
-    constexpr int ROWS_IT = kAttWaves * RPW * kUnroll;
+    constexpr int KEYS = B16 ? 32 : 16;        // keys per step of a wavefront
+    constexpr int NT = KEYS / 16;              // key tiles of a step
+    constexpr int KC = ROWB / 64;              // 16-byte pieces of a lane's quarter of a row
+    constexpr int VR = KEYS / 4;               // value rows (= weights) per lane and step
+    constexpr int EPN = D / 16;                // columns per lane of a value row
+    constexpr int VD = EPN * (int)sizeof(T) / 4;   // ... in dwords
+    constexpr int RQ = 16 * NQT;
+    constexpr int P = D + kRowPad;
 
-    __shared__ float red[kAttWaves][kQT][D + 2];
+    // the wavefronts' sums meet here
+    __shared__ __align__(16) float lds[W * RQ * P];
+    __shared__ int last_flag;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int sl = lane % SL, lg = lane / SL;
-    const int split = blockIdx.x, qg = blockIdx.y;
-    const int64_t seq = blockIdx.z;
-    const int64_t r_begin = (int64_t)split * a.rows_per_split;
-    const int64_t r_end = min(a.count, r_begin + a.rows_per_split);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kg = lane >> 4;
 
-    const char* Kb = a.K + (size_t)seq * a.stride_tokens * ROWB;
-    const char* Vb = HASV ? a.V + (size_t)seq * a.stride_tokens * ROWB : nullptr;
-    const float* wb = a.w + (size_t)seq * a.stride_tokens;
-
-    // queries of this pass: raw 16-byte slices (bf16 path: consumed by packed dot products) and, for
-    // fp32, the unpacked values; the logit scale log2(e)/sqrt(d) is applied to the reduced dot product
-    uintx4 qraw[kQT];
-#pragma unroll
-    for (int qi = 0; qi < kQT; ++qi) {
-        const int q = qg * kQT + qi;
-        qraw[qi] = (q < a.n_q) ? *reinterpret_cast<const uintx4*>(a.Q + ((size_t)seq * a.n_q + q) * ROWB + sl * 16)
-                               : uintx4{0u, 0u, 0u, 0u};
+    // workgroup -> (sequence, query group, split).  Where several query groups read the same rows, the workgroups of a
+    // sequence go to one XCD (blocks are dealt to the eight XCDs in turn), whose L2 then serves all but the first read.
+    const unsigned int ns = (unsigned int)(a.ns[0] + a.ns[1]), inner = ns * (unsigned int)a.n_qg;
+    unsigned int seq_u, rest;
+    if (a.by_xcd) {
+        const unsigned int k = blockIdx.x >> 3;
+        seq_u = (k / inner) * 8u + (blockIdx.x & 7u);
+        rest = k % inner;
+        if (seq_u >= (unsigned int)a.n_seq) return;
+    } else {
+        seq_u = blockIdx.x / inner;
+        rest = blockIdx.x % inner;
     }
-    float m[kQT], l[kQT], o[kQT][EPL];
-#pragma unroll
-    for (int qi = 0; qi < kQT; ++qi) {
-        m[qi] = kNeg; l[qi] = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[qi][e] = 0.f;
-    }
+    const int qg = (int)(rest % (unsigned int)a.n_qg);
+    const int split = (int)(rest / (unsigned int)a.n_qg);
+    const int64_t seq = seq_u;
+    const int which = split >= a.ns[0] ? 1 : 0;
+    const AttendSet S = which ? a.set[1] : a.set[0];
+    const bool has_v = S.V != nullptr;
+    const int64_t groups = (S.count + KEYS - 1) / KEYS, full = S.count / KEYS;
+    const int64_t g0 = (int64_t)(split - (which ? a.ns[0] : 0)) * S.groups_per_split;
+    const int64_t g1 = min(groups, g0 + S.groups_per_split), gf = min(full, g1);
 
-    struct Batch { uintx4 k[kUnroll], v[kUnroll]; float w[kUnroll]; };
-    auto issue = [&](Batch& t, int64_t base) {
+    const char* Kb = S.K + (size_t)seq * S.stride * ROWB;
+    const char* Vb = has_v ? S.V + (size_t)seq * S.stride * ROWB : nullptr;
+    const float* wb = S.w + (size_t)seq * S.stride;
+
+    uintx4 kf[NT][KC];
+    unsigned int vf[VR][VD];
+    float w0[VR], w1[VR];
+    const int koff = n * ROWB + kg * 16, voff = 4 * kg * ROWB + n * VD * 4;
+    auto load_w = [&](float (&w)[VR], int64_t g) {
+        const float* p = wb + g * KEYS + 4 * kg;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t row = base + (u * kAttWaves + wave) * RPW + lg;
-            const int64_t rr = row < r_end ? row : r_end - 1;          // stay in bounds; masked in consume()
-            t.k[u] = *reinterpret_cast<const uintx4*>(Kb + (size_t)rr * ROWB + sl * 16);
-            if constexpr (HASV) t.v[u] = *reinterpret_cast<const uintx4*>(Vb + (size_t)rr * ROWB + sl * 16);
-            t.w[u] = wb[rr];
+        for (int t = 0; t < NT; ++t) {
+            const floatx4_u x = *reinterpret_cast<const floatx4_u*>(p + 16 * t);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[4 * t + r] = x[r];
         }
     };
-    auto consume = [&](const Batch& t, int64_t base) {
-        float lg2[kUnroll][kQT];
-        float mb[kQT];
-#pragma unroll
-        for (int qi = 0; qi < kQT; ++qi) mb[qi] = kNeg;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t row = base + (u * kAttWaves + wave) * RPW + lg;
-            const bool live = row < r_end && t.w[u] > 0.f;
-            const float bias = live ? __builtin_amdgcn_logf(t.w[u]) : 0.f;    // v_log_f32 = log2
-#pragma unroll
-            for (int qi = 0; qi < kQT; ++qi) {
-                float part = Elem<T>::dot(qraw[qi], t.k[u]);
-                part = group_sum<SL>(part);
-                lg2[u][qi] = live ? fmaf(part, a.scale_log2, bias) : 2.f * kNeg;   // below every running maximum: weight 0
-                mb[qi] = fmaxf(mb[qi], lg2[u][qi]);
-            }
-        }
-        // a new running maximum rescales what has been accumulated; once the maxima have settled this is rare, and
-        // the whole wavefront skips it
-        bool grew = false;
-#pragma unroll
-        for (int qi = 0; qi < kQT; ++qi) grew |= mb[qi] > m[qi];
-        if (__builtin_amdgcn_ballot_w64(grew) != 0ull) {
-#pragma unroll
-            for (int qi = 0; qi < kQT; ++qi) {
-                const float mnew = fmaxf(m[qi], mb[qi]);
-                const float sc = fast_exp2(m[qi] - mnew);
-                m[qi] = mnew;
-                l[qi] *= sc;
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) o[qi][e] *= sc;
-            }
-        }
-        if constexpr (sizeof(T) == 2) {
-            // bf16 values: two rows at a time on the packed dot product.  The weights p of the two rows are rounded to
-            // bf16 (to nearest even, both in one v_cvt_pk_bf16_f32) and the denominator adds the same rounded values,
-            // so numerator and denominator stay one estimator and the rounding errors carry no bias; element e of rows
-            // a and b is paired by byte permutes, and o[e] += p_a v_a[e] + p_b v_b[e] is one v_dot2c_f32_bf16 (exact
-            // products, fp32 sum) instead of two conversions and two multiply-adds.
-            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-            static_assert(kUnroll % 2 == 0, "rows are consumed in pairs");
-            const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-            for (int u = 0; u < kUnroll; u += 2) {
-                bf16x2_t vp[EPL];
-                if constexpr (HASV)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const unsigned int wa = t.v[u][i], wb = t.v[u + 1][i];
-                    vp[2 * i] = __builtin_bit_cast(bf16x2_t, __builtin_amdgcn_perm(wb, wa, 0x05040100u));       // (a[2i], b[2i])
-                    vp[2 * i + 1] = __builtin_bit_cast(bf16x2_t, __builtin_amdgcn_perm(wb, wa, 0x07060302u));   // (a[2i+1], b[2i+1])
-                }
-#pragma unroll
-                for (int qi = 0; qi < kQT; ++qi) {
-                    const floatx2 pf = {fast_exp2(lg2[u][qi] - m[qi]),            // dead rows: 2^(2 kNeg - m) = 0, m >= kNeg
-                                        fast_exp2(lg2[u + 1][qi] - m[qi])};
-                    const bf16x2_t pp = __builtin_convertvector(pf, bf16x2_t);     // (p_a, p_b)
-                    l[qi] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l[qi], false);
-                    if constexpr (HASV) {
-#pragma unroll
-                        for (int e = 0; e < EPL; ++e) o[qi][e] = __builtin_amdgcn_fdot2_f32_bf16(pp, vp[e], o[qi][e], false);
-                    }
-                }
-            }
+    auto load_v_row = [&](int j, const char* p) {
+        if constexpr (VD == 2) {
+            const uintx2 x = *reinterpret_cast<const uintx2*>(p);
+            vf[j][0] = x[0]; vf[j][1] = x[1];
         } else {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                float vf[EPL];
-                if constexpr (HASV) Elem<T>::unpack(t.v[u], vf);
+            for (int c = 0; c < VD / 4; ++c) {
+                const uintx4 x = *reinterpret_cast<const uintx4*>(p + 16 * c);
 #pragma unroll
-                for (int qi = 0; qi < kQT; ++qi) {
-                    const float p = fast_exp2(lg2[u][qi] - m[qi]);        // dead rows: 2^(2 kNeg - m) = 0, m >= kNeg
-                    l[qi] += p;
-                    if constexpr (HASV)
+                for (int i = 0; i < 4; ++i) vf[j][4 * c + i] = x[i];
+            }
+        }
+    };
+    auto load_k = [&](int64_t g) {
+        const char* p = Kb + (size_t)g * (KEYS * ROWB) + koff;
 #pragma unroll
-                        for (int e = 0; e < EPL; ++e) o[qi][e] = fmaf(p, vf[e], o[qi][e]);
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < KC; ++c) kf[t][c] = *reinterpret_cast<const uintx4*>(p + 16 * t * ROWB + 64 * c);
+    };
+    auto load_v = [&](int64_t g) {
+        const char* p = Vb + (size_t)g * (KEYS * ROWB) + voff;
+#pragma unroll
+        for (int j = 0; j < VR; ++j) load_v_row(j, p + ((j & 3) + 16 * (j >> 2)) * ROWB);
+    };
+
+    int64_t g = g0 + wave;
+    const bool any_full = g < gf;
+    if (any_full) {
+        load_w(w0, g);
+        load_k(g);
+        if (has_v) load_v(g);
+    }
+    // queries: lane (n, kg) holds its quarter of query n of each tile (queries past the end repeat the last one)
+    uintx4 qf[NQT][KC];
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) {
+        const int q = min(qg * RQ + 16 * t + n, a.n_q - 1);
+        const char* p = a.Q + ((size_t)seq * a.n_q + q) * ROWB + kg * 16;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) qf[t][c] = *reinterpret_cast<const uintx4*>(p + 64 * c);
+    }
+    if (any_full && g + W < gf) load_w(w1, g + W);
+
+    float m[NQT], l[NQT];
+    floatx4 o[NQT][EPN];
+    const floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) {
+        m[t] = kNeg; l[t] = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPN; ++e) o[t][e] = zero4;
+    }
+    floatx4 s[NQT][NT];
+    auto qk = [&]() {
+#pragma unroll
+        for (int t = 0; t < NQT; ++t)
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt) s[t][kt] = zero4;
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+                for (int t = 0; t < NQT; ++t) {
+                    if constexpr (B16) {
+                        s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[kt][c]), __builtin_bit_cast(bf16x8_t, qf[t][c]),
+                                                                           s[t][kt], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const unsigned int ka = kf[kt][c][i], qa = qf[t][c][i];
+                            s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka), __uint_as_float(qa), s[t][kt], 0, 0, 0);
+                        }
+                    }
                 }
+    };
+    // logits -> weights 2^(logit - m), rounded to bf16 (to nearest even) on the bf16 path; the denominator adds the same
+    // rounded weights.  The reference m moves only when a logit passes it by more than kSlack (then to the largest one, for
+    // all lanes of the query): the weights are floating-point numbers, so a reference that is 2^6 too small costs nothing.
+    bf16x8_t pb[NQT];
+    auto softmax = [&](const float (&w)[VR]) {
+        float bias[VR];
+        bool dead = false;
+#pragma unroll
+        for (int x = 0; x < VR; ++x) {
+            const bool live = w[x] > 0.f;
+            dead |= !live;
+            bias[x] = live ? __builtin_amdgcn_logf(w[x]) : 2.f * kNeg;        // below every reference: weight 0
+        }
+        if (__builtin_amdgcn_ballot_w64(dead) != 0ull) {                      // (whatever an absent token's row holds)
+#pragma unroll
+            for (int t = 0; t < NQT; ++t)
+#pragma unroll
+                for (int x = 0; x < VR; ++x) s[t][x >> 2][x & 3] = w[x] > 0.f ? s[t][x >> 2][x & 3] : 0.f;
+        }
+        bool grew = false;
+        float mx[NQT];
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+            mx[t] = 2.f * kNeg;
+#pragma unroll
+            for (int x = 0; x < VR; ++x) {
+                const float lg = fmaf(s[t][x >> 2][x & 3], a.scale_log2, bias[x]);
+                s[t][x >> 2][x & 3] = lg;
+                mx[t] = fmaxf(mx[t], lg);
+            }
+            grew |= mx[t] > m[t] + kSlack;
+        }
+        if (__builtin_amdgcn_ballot_w64(grew) != 0ull) {
+#pragma unroll
+            for (int t = 0; t < NQT; ++t) {
+                float mm = fmaxf(mx[t], __shfl_xor(mx[t], 16));
+                mm = fmaxf(mm, __shfl_xor(mm, 32));
+                const float mnew = fmaxf(m[t], mm);
+                const float sc = fast_exp2(m[t] - mnew);
+                m[t] = mnew;
+                l[t] *= sc;
+#pragma unroll
+                for (int e = 0; e < EPN; ++e) o[t][e] *= sc;
+            }
+        }
+        const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+        for (int t = 0; t < NQT; ++t) {
+#pragma unroll
+            for (int x = 0; x < VR; ++x) s[t][x >> 2][x & 3] = fast_exp2(s[t][x >> 2][x & 3] - m[t]);
+            if constexpr (B16) {
+                uintx4 pk;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const floatx2 pf = {s[t][i >> 1][2 * (i & 1)], s[t][i >> 1][2 * (i & 1) + 1]};
+                    const bf16x2_t pp = __builtin_convertvector(pf, bf16x2_t);
+                    l[t] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l[t], false);
+                    pk[i] = __builtin_bit_cast(unsigned int, pp);
+                }
+                pb[t] = __builtin_bit_cast(bf16x8_t, pk);
+            } else {
+#pragma unroll
+                for (int x = 0; x < VR; ++x) l[t] += s[t][x >> 2][x & 3];
+            }
+        }
+    };
+    auto pv = [&]() {
+#pragma unroll
+        for (int e = 0; e < EPN; ++e) {
+            if constexpr (B16) {
+                uintx4 f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)       // element e of the rows of keys 2i, 2i + 1 of this lane
+                    f[i] = __builtin_amdgcn_perm(vf[2 * i + 1][e >> 1], vf[2 * i][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+                for (int t = 0; t < NQT; ++t)
+                    o[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f), pb[t], o[t][e], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int t = 0; t < NQT; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        o[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vf[j][e]), s[t][0][j], o[t][e], 0, 0, 0);
             }
         }
     };
 
-    // two batches of rows in flight: the loads of the next batch are issued before the current one is consumed
-    if (r_begin < r_end) {
-        Batch b0, b1;
-        issue(b0, r_begin);
-        for (int64_t base = r_begin; base < r_end; base += 2 * ROWS_IT) {
-            if (base + ROWS_IT < r_end) issue(b1, base + ROWS_IT);
-            consume(b0, base);
-            if (base + ROWS_IT < r_end) {
-                if (base + 2 * ROWS_IT < r_end) issue(b0, base + 2 * ROWS_IT);
-                consume(b1, base + ROWS_IT);
+    if (any_full) {
+        for (;;) {
+            // the next group with a live key (places without a token are not read); its weights arrived a step ago
+            int64_t gn = g + W;
+            bool more = false;
+            while (gn < gf) {
+                bool live = false;
+#pragma unroll
+                for (int x = 0; x < VR; ++x) live |= w1[x] > 0.f;
+                if (__builtin_amdgcn_ballot_w64(live) != 0ull) { more = true; break; }
+                gn += W;
+                if (gn < gf) load_w(w1, gn);
             }
+            float wc[VR];
+#pragma unroll
+            for (int x = 0; x < VR; ++x) { wc[x] = w0[x]; w0[x] = w1[x]; }
+            if (more && gn + W < gf) load_w(w1, gn + W);
+            qk();
+            if (more) load_k(gn);
+            softmax(wc);
+            if (has_v) {
+                pv();
+                if (more) load_v(gn);
+            }
+            if (!more) break;
+            g = gn;
         }
+    }
+    // the sequence's last group, if it is not full: one wavefront, rows past the end repeat the last row with weight 0
+    if (g1 > full && (int)((full - g0) % W) == wave) {
+        const int left = (int)(S.count - full * KEYS) - 1;           // last valid row of the group
+        const char* kp = Kb + (size_t)full * (KEYS * ROWB) + kg * 16;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < KC; ++c) kf[t][c] = *reinterpret_cast<const uintx4*>(kp + min(16 * t + n, left) * ROWB + 64 * c);
+        float wt[VR];
+#pragma unroll
+        for (int j = 0; j < VR; ++j) {
+            const int row = 4 * kg + (j & 3) + 16 * (j >> 2);
+            const float x = wb[full * KEYS + min(row, left)];
+            wt[j] = row <= left ? x : 0.f;
+            if (has_v) load_v_row(j, Vb + (size_t)full * (KEYS * ROWB) + min(row, left) * ROWB + n * VD * 4);
+        }
+        qk();
+        softmax(wt);
+        if (has_v) pv();
+    }
+#pragma unroll
+    for (int t = 0; t < NQT; ++t) {
+        l[t] += __shfl_xor(l[t], 16);
+        l[t] += __shfl_xor(l[t], 32);
     }
 
-    // merge the lane groups of a wavefront (each saw different rows)
+    // ---- the wavefronts meet in LDS; a thread then owns four columns of a query
+    const int q0 = qg * RQ, nqv = min(RQ, a.n_q - q0);
 #pragma unroll
-    for (int off = SL; off < 64; off <<= 1) {
+    for (int t = 0; t < NQT; ++t)
+        if (16 * t + n < nqv) {
+            float* row = lds + (wave * RQ + 16 * t + n) * P;
+            if (has_v) {
 #pragma unroll
-        for (int qi = 0; qi < kQT; ++qi) {
-            const float mo = __shfl_xor(m[qi], off);
-            const float lo = __shfl_xor(l[qi], off);
-            const float mn = fmaxf(m[qi], mo);
-            const float s0 = fast_exp2(m[qi] - mn), s1 = fast_exp2(mo - mn);
-            l[qi] = l[qi] * s0 + lo * s1;
+                for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) o[qi][e] = o[qi][e] * s0 + __shfl_xor(o[qi][e], off) * s1;
-            m[qi] = mn;
-        }
-    }
-    if (lg == 0) {
-#pragma unroll
-        for (int qi = 0; qi < kQT; ++qi) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) red[wave][qi][sl * EPL + e] = o[qi][e];
-            if (sl == 0) { red[wave][qi][D] = m[qi]; red[wave][qi][D + 1] = l[qi]; }
-        }
-    }
-    __syncthreads();
-    if (a.n_splits == 1) {
-        // The whole token range was one split: normalise and store the result here (the same arithmetic as partial +
-        // merge, which is not launched then).
-        for (int t = tid; t < kQT * D; t += kAttWaves * 64) {
-            const int qi = t / D, c = t - qi * D;
-            const int q = qg * kQT + qi;
-            if (q >= a.n_q) continue;
-            float M = red[0][qi][D];
-#pragma unroll
-            for (int w = 1; w < kAttWaves; ++w) M = fmaxf(M, red[w][qi][D]);
-            float val = 0.f, L = 0.f;
-#pragma unroll
-            for (int w = 0; w < kAttWaves; ++w) {
-                const float sc = fast_exp2(red[w][qi][D] - M);
-                val += red[w][qi][c] * sc;
-                L += red[w][qi][D + 1] * sc;
+                    for (int e = 0; e < EPN; e += 4) {
+                        const floatx4 x = {o[t][e][r], o[t][e + 1][r], o[t][e + 2][r], o[t][e + 3][r]};
+                        *reinterpret_cast<floatx4*>(row + EPN * (4 * kg + r) + e) = x;
+                    }
             }
-            const float z = val * (L > 0.f ? 1.f / L : 0.f);
-            const size_t oi = ((size_t)seq * a.n_q + q) * D + c;
-            if (sizeof(T) == 2) reinterpret_cast<unsigned short*>(a.out)[oi] = (unsigned short)f32_to_bf16_bits(z);
-            else reinterpret_cast<float*>(a.out)[oi] = z;
-            if (c == 0 && a.lse_out)
-                a.lse_out[(size_t)seq * a.n_q + q] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+            if (kg == 0) *reinterpret_cast<floatx2*>(row + D) = floatx2{m[t], l[t]};
         }
-        return;
-    }
-    // merge the wavefronts and store the partial: [seq][qg][split][qi][D + 2]
-    float* dst = a.partial + ((((size_t)seq * gridDim.y + qg) * a.n_splits + split) * kQT) * (D + 2);
-    for (int t = tid; t < kQT * (D + 2); t += kAttWaves * 64) {
-        const int qi = t / (D + 2), c = t - qi * (D + 2);
-        float M = red[0][qi][D];
+    __syncthreads();
+    const size_t row0 = (size_t)seq * a.n_q + q0;
+    // partial rows: [sequence][query group][split][row], a.rows rows of P floats each
+    const size_t grp = (size_t)seq * a.n_qg + qg, sstride = (size_t)a.rows * P;
+    float* part = a.partial + grp * ns * sstride;
+    for (int c = tid; c < nqv * (D / 4); c += W * 64) {
+        const int q = c / (D / 4), col = 4 * (c - q * (D / 4));
+        const float* row = lds + q * P;
+        floatx2 ml[W];
+        float M = kNeg, L = 0.f;
 #pragma unroll
-        for (int w = 1; w < kAttWaves; ++w) M = fmaxf(M, red[w][qi][D]);
-        float val;
-        if (c == D) val = M;
-        else {
-            val = 0.f;
+        for (int w = 0; w < W; ++w) { ml[w] = *reinterpret_cast<const floatx2*>(row + w * RQ * P + D); M = fmaxf(M, ml[w][0]); }
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < kAttWaves; ++w) val += red[w][qi][c] * fast_exp2(red[w][qi][D] - M);
+        for (int w = 0; w < W; ++w) {
+            const float f = fast_exp2(ml[w][0] - M);
+            L = fmaf(ml[w][1], f, L);
+            if (has_v) acc += *reinterpret_cast<const floatx4*>(row + w * RQ * P + col) * f;
         }
-        dst[qi * (D + 2) + c] = val;
+        if (ns == 1) {                          // the whole range was one split: normalise and store
+            store4<T>(a.out, (row0 + q) * D + col, acc * (L > 0.f ? 1.f / L : 0.f));
+            if (col == 0 && a.lse_out) a.lse_out[row0 + q] = L > 0.f ? log2_or(L, M) * 0.6931471805599453f : -INFINITY;
+        } else {
+            float* dst = part + split * sstride + q * P;
+            if (has_v) { put2(dst + col, acc[0], acc[1]); put2(dst + col + 2, acc[2], acc[3]); }
+            if (col == 0) put2(dst + D, M, L);
+        }
     }
+    if (ns == 1 || !a.fused) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wavefront's share of the partial has reached memory ...
+    __syncthreads();                                            // ... and so has everybody else's
+    if (tid == 0) last_flag = arrive_last(a.arrivals + 2 * grp, ns, a.label) ? 1 : 0;
+    __syncthreads();
+    if (!last_flag) return;
+    merge_rows<T, D, W * 64>(part, sstride, nqv, a.ns[0], a.ns[1], a.out, a.lse_out, row0, lds);
 }
 
-// One workgroup (4 wavefronts) per (sequence, query): merge the split partials, normalise, store.  The numerator
-// pass spreads the splits over the threads (a thread owns two columns and every SR-th split, several loads in
-// flight), so its latency does not grow with the number of splits; the partial sums meet in LDS in a fixed order.
+// Partials of many splits per query: one workgroup per (sequence, query) merges them (spread over the chip, where the last
+// workgroup of a group would have to read them all by itself).
 constexpr int kMergeThreads = 256;
-constexpr int kScaleCache = 512;
 template <typename T, int D>
-__global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(const AttendArgs a, int n_qgroups) {
-    constexpr int NW = kMergeThreads / 64;
-    constexpr int CG = D / 2;                        // column pairs (the rows of a partial are 8-byte aligned)
-    constexpr int SR = kMergeThreads / CG;           // splits summed side by side
-    __shared__ float red[2 * NW];
-    __shared__ float scale[kScaleCache];
-    __shared__ float part[SR][D];
+__global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(const AttendArgs a, int rq) {
+    __shared__ __align__(16) float red[kMergeThreads * 8];
     const int64_t seq = blockIdx.y;
-    const int q = blockIdx.x, tid = threadIdx.x, ns = a.n_splits;
-    const int qg = q / kQT, qi = q % kQT;
-    const float* src = a.partial + ((((size_t)seq * n_qgroups + qg) * ns) * kQT + qi) * (D + 2);
-    const size_t sstride = (size_t)kQT * (D + 2);                  // between consecutive splits
-    // largest running maximum over the splits
-    float m = kNeg;
-    for (int s = tid; s < ns; s += kMergeThreads) m = fmaxf(m, src[s * sstride + D]);
-    m = wave_max(m);
-    if ((tid & 63) == 0) red[tid >> 6] = m;
-    __syncthreads();
-    float M = red[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, red[w]);
-    // denominators, rescaled; the per-split factors are kept for the numerator pass
-    float l = 0.f;
-    for (int s = tid; s < ns; s += kMergeThreads) {
-        const float sc = fast_exp2(src[s * sstride + D] - M);
-        l = fmaf(src[s * sstride + D + 1], sc, l);
-        if (s < kScaleCache) scale[s] = sc;
-    }
-    l = wave_sum(l);
-    if ((tid & 63) == 0) red[NW + (tid >> 6)] = l;
-    __syncthreads();
-    float L = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) L += red[NW + w];
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    // numerators
-    const int cg = tid % CG, sg = tid / CG;
-    auto factor = [&](int s) -> float { return s < kScaleCache ? scale[s] : fast_exp2(src[s * sstride + D] - M); };
-    float acc0 = 0.f, acc1 = 0.f;
-    int s = sg;
-    for (; s + 3 * SR < ns; s += 4 * SR) {                         // four independent loads in flight
-        const floatx2 p0 = *reinterpret_cast<const floatx2*>(src + (size_t)s * sstride + 2 * cg);
-        const floatx2 p1 = *reinterpret_cast<const floatx2*>(src + (size_t)(s + SR) * sstride + 2 * cg);
-        const floatx2 p2 = *reinterpret_cast<const floatx2*>(src + (size_t)(s + 2 * SR) * sstride + 2 * cg);
-        const floatx2 p3 = *reinterpret_cast<const floatx2*>(src + (size_t)(s + 3 * SR) * sstride + 2 * cg);
-        const float f0 = factor(s), f1 = factor(s + SR), f2 = factor(s + 2 * SR), f3 = factor(s + 3 * SR);
-        acc0 = fmaf(p0[0], f0, acc0); acc1 = fmaf(p0[1], f0, acc1);
-        acc0 = fmaf(p1[0], f1, acc0); acc1 = fmaf(p1[1], f1, acc1);
-        acc0 = fmaf(p2[0], f2, acc0); acc1 = fmaf(p2[1], f2, acc1);
-        acc0 = fmaf(p3[0], f3, acc0); acc1 = fmaf(p3[1], f3, acc1);
-    }
-    for (; s < ns; s += SR) {
-        const floatx2 p0 = *reinterpret_cast<const floatx2*>(src + (size_t)s * sstride + 2 * cg);
-        const float f0 = factor(s);
-        acc0 = fmaf(p0[0], f0, acc0); acc1 = fmaf(p0[1], f0, acc1);
-    }
-    part[sg][2 * cg] = acc0; part[sg][2 * cg + 1] = acc1;
-    __syncthreads();
-    for (int c = tid; c < D; c += kMergeThreads) {
-        float z = 0.f;
-#pragma unroll
-        for (int r = 0; r < SR; ++r) z += part[r][c];
-        z *= inv;
-        const size_t oi = ((size_t)seq * a.n_q + q) * D + c;
-        if (sizeof(T) == 2) reinterpret_cast<unsigned short*>(a.out)[oi] = (unsigned short)f32_to_bf16_bits(z);
-        else reinterpret_cast<float*>(a.out)[oi] = z;
-    }
-    if (a.lse_out && tid == 0)
-        a.lse_out[(size_t)seq * a.n_q + q] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+    const int q = blockIdx.x, qg = q / rq, ns = a.ns[0] + a.ns[1];
+    const size_t sstride = (size_t)a.rows * (D + kRowPad);
+    const float* part = a.partial + ((size_t)seq * a.n_qg + qg) * ns * sstride + (size_t)(q - qg * rq) * (D + kRowPad);
+    merge_rows<T, D, kMergeThreads>(part, sstride, 1, a.ns[0], a.ns[1], a.out, a.lse_out, (size_t)seq * a.n_q + q, red);
 }
 
-static void attend_plan(int d, int dtype_bytes, int64_t n_seq, int64_t count, int n_q, int* n_qg, int* n_splits,
-                        int* rows_per_split) {
-    const int sl = d * dtype_bytes / 16;
-    const int rows_it = kAttWaves * (64 / sl) * kUnroll;
-    *n_qg = (n_q + kQT - 1) / kQT;
-    int64_t wgs = n_seq * (*n_qg);
-    int64_t want = wgs > 0 ? (kTargetWGs + wgs - 1) / wgs : 1;
-    int64_t max_splits = (count + rows_it - 1) / rows_it;      // a split is at least one batch of rows
-    if (max_splits < 1) max_splits = 1;
-    if (want > max_splits) want = max_splits;
-    if (want < 1) want = 1;
-    int64_t rps = (count + want - 1) / want;
-    rps = (rps + rows_it - 1) / rows_it * rows_it;
-    if (rps < rows_it) rps = rows_it;
-    int64_t ns = (count + rps - 1) / rps;
-    if (ns < 1) ns = 1;
-    *n_splits = (int)ns;
-    *rows_per_split = (int)rps;
+// ---------------------------------------------------------------------------------------------------------------------
+struct AttendPlan {
+    int nqt, waves, n_qg, rows;   // query tiles and wavefronts per workgroup, query groups, rows of a partial
+    int ns[2], gps[2];            // splits and key groups per split of each set
+    bool fused;                   // the last workgroup of a query group merges
+    size_t arrive_bytes, partial_bytes;
+};
+
+// Splits: eight wavefronts per compute unit, each at least one key group (twice as many: the merge takes longer than the
+// pass gains, 27.8 against 23.3 us with 256 queries, decode of 64 sequences 3 % slower); the steps of a wavefront decide a
+// workgroup's time, so the ranges are cut into equal numbers of steps.
+static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, int64_t count1, int n_q, size_t max_bytes) {
+    AttendPlan p;
+    const int keys = elem == 2 ? 32 : 16;
+    p.nqt = n_q > 16 ? 2 : 1;
+    const int rq = 16 * p.nqt;
+    p.n_qg = (n_q + rq - 1) / rq;
+    p.rows = n_q < rq ? n_q : rq;
+    const int64_t wgs = n_seq * p.n_qg;
+    const int64_t cnt[2] = {count0, count1};
+    const int64_t all = (count0 + keys - 1) / keys + (count1 + keys - 1) / keys;
+    // four wavefronts per workgroup let three workgroups share a compute unit (registers); eight mean half the splits where
+    // a wavefront has a single group anyway, and are what 32 queries take (one workgroup per compute unit, LDS)
+    p.waves = p.nqt == 1 && all * wgs > kTargetWaves ? 4 : 8;
+    const size_t row_bytes = (size_t)p.rows * (d + kRowPad) * sizeof(float);
+    int64_t most = (int64_t)(max_bytes / ((size_t)wgs * row_bytes));          // splits whose partials fit the buffer
+    int64_t steps = (all * wgs + kTargetWaves - 1) / kTargetWaves;             // per wavefront
+    if (steps < 1) steps = 1;
+    for (int k = 0; k < 2; ++k) {
+        const int64_t groups = (cnt[k] + keys - 1) / keys;
+        int64_t ns = (groups + steps * p.waves - 1) / (steps * p.waves);
+        const int64_t lim = k == 0 ? (count1 > 0 ? (most + 1) / 2 : most) : most / 2;
+        if (ns > lim) ns = lim;
+        if (ns < 1 && groups > 0) ns = 1;
+        const int64_t gps = ns > 0 ? (groups + ns - 1) / ns : 1;
+        p.ns[k] = groups > 0 ? (int)((groups + gps - 1) / gps) : 0;
+        p.gps[k] = (int)gps;
+    }
+    const int ns = p.ns[0] + p.ns[1];
+    p.partial_bytes = ns > 1 ? (size_t)wgs * ns * row_bytes : 0;
+    p.arrive_bytes = ns > 1 ? ((size_t)wgs * 16 + 255) / 256 * 256 : 0;
+    // one workgroup reads ns * rows partial rows at the end: up to 128 KB of them that is faster than one more launch (by
+    // 2 us with 18 splits of 4 rows, equal with 4 splits of 32)
+    p.fused = ns > 1 && (size_t)ns * row_bytes <= (size_t)128 * 1024;
+    return p;
 }
 
-size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q) {
-    // the split count never exceeds ceil(kTargetWGs / workgroups-without-splitting), whatever the token count
-    const int64_t n_qg = (n_q + kQT - 1) / kQT;
-    const int64_t wgs = n_seq * n_qg;
-    const int64_t ns = wgs > 0 ? (kTargetWGs + wgs - 1) / wgs : 1;
-    return (size_t)(wgs * ns) * kQT * (d + 2) * sizeof(float) + 256;
+// Upper bounds for any token count: a set is cut into at most ceil(kTargetWaves / (wavefronts per workgroup * wgs)) splits.
+size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q, int sets) {
+    const int rq = n_q > 16 ? 32 : 16;
+    const int64_t wgs = n_seq * ((n_q + rq - 1) / rq);
+    const int64_t wg_target = kTargetWaves / (n_q > 16 ? 8 : 4);
+    const int64_t per = wgs > 0 ? (wg_target + wgs - 1) / wgs + sets : 1;
+    const size_t row_bytes = (size_t)(n_q < rq ? n_q : rq) * (d + kRowPad) * sizeof(float);
+    return (size_t)(wgs * per) * row_bytes + (size_t)wgs * 16 + 512;
+}
+
+size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q, size_t max_bytes) {
+    if (n_seq <= 0 || n_q <= 0) return 0;
+    const AttendPlan p = attend_plan(d, dtype == BKV_BF16 ? 2 : 4, n_seq, count, 0, n_q, max_bytes);
+    return p.partial_bytes + p.arrive_bytes;
 }
 
 template <typename T, int D>
-static hipError_t launch_attend_t(AttendArgs& a, int64_t n_seq, int n_qg, hipStream_t st) {
-    const dim3 grid(a.n_splits, n_qg, (unsigned)n_seq);
-    const hipError_t e = a.V ? launch_timed(kProfAttend, n_seq * a.count, attend_partial_kernel<T, D, true>, grid, dim3(kAttWaves * 64), 0, st, a)
-                             : launch_timed(kProfAttend, n_seq * a.count, attend_partial_kernel<T, D, false>, grid, dim3(kAttWaves * 64), 0, st, a);
-    if (e != hipSuccess || a.n_splits == 1) return e;          // a single split stores the final result itself
-    return launch_timed(kProfAttendMerge, n_seq * a.n_q, attend_merge_kernel<T, D>, dim3(a.n_q, (unsigned)n_seq), dim3(kMergeThreads), 0, st,
-                        a, n_qg);
-}
-
-// Bytes of split partials that a launch with this shape writes (0 when the token range is a single split: the
-// streaming pass then stores the result itself).
-size_t attend_partial_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q) {
-    if (n_seq <= 0 || n_q <= 0) return 0;
-    int n_qg, ns, rps;
-    attend_plan(d, dtype == BKV_BF16 ? 2 : 4, n_seq, count, n_q, &n_qg, &ns, &rps);
-    if (ns <= 1) return 0;
-    return (size_t)n_seq * n_qg * ns * kQT * (d + 2) * sizeof(float);
+static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipStream_t st) {
+    const int64_t inner = (int64_t)p.n_qg * (p.ns[0] + p.ns[1]);
+    const int64_t blocks = inner * (a.by_xcd ? (a.n_seq + 7) / 8 * 8 : a.n_seq);
+    if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
+    const int64_t units = a.n_seq * (a.set[0].count + a.set[1].count);
+    const hipError_t e = p.nqt == 1 ? (p.waves == 4 ? launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, dim3((unsigned)blocks), dim3(256), 0, st, a)
+                                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, dim3((unsigned)blocks), dim3(512), 0, st, a))
+                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, dim3((unsigned)blocks), dim3(512), 0, st, a);
+    if (e != hipSuccess || p.ns[0] + p.ns[1] == 1 || p.fused) return e;
+    return launch_timed(kProfAttendMerge, a.n_seq * a.n_q, attend_merge_kernel<T, D>, dim3(a.n_q, (unsigned)a.n_seq), dim3(kMergeThreads), 0, st,
+                        a, 16 * p.nqt);
 }
 
 // Scratch of the entry point that allocates nothing: the split partials live in this array instead of a caller's
@@ -382,19 +608,24 @@ hipError_t attend_static_scratch(void** ptr) {
     return hipSuccess;
 }
 
-hipError_t launch_attend(int dtype, int d, AttendArgs& a, int64_t n_seq, void* workspace, hipStream_t st) {
-    if (n_seq <= 0 || a.n_q <= 0) return hipSuccess;
-    if (n_seq > 65535) return hipErrorInvalidValue;
-    int n_qg, ns, rps;
-    attend_plan(d, dtype == BKV_BF16 ? 2 : 4, n_seq, a.count, a.n_q, &n_qg, &ns, &rps);
-    if (n_qg > 65535) return hipErrorInvalidValue;
-    a.n_splits = ns;
-    a.rows_per_split = rps;
-    a.partial = reinterpret_cast<float*>(workspace);
-    if (dtype == BKV_BF16 && d == 128) return launch_attend_t<__bf16, 128>(a, n_seq, n_qg, st);
-    if (dtype == BKV_BF16 && d == 64) return launch_attend_t<__bf16, 64>(a, n_seq, n_qg, st);
-    if (dtype == BKV_F32 && d == 128) return launch_attend_t<float, 128>(a, n_seq, n_qg, st);
-    if (dtype == BKV_F32 && d == 64) return launch_attend_t<float, 64>(a, n_seq, n_qg, st);
+hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t max_bytes, hipStream_t st) {
+    if (a.n_seq <= 0 || a.n_q <= 0) return hipSuccess;
+    if (a.n_seq > 65535) return hipErrorInvalidValue;
+    const AttendPlan p = attend_plan(d, dtype == BKV_BF16 ? 2 : 4, a.n_seq, a.set[0].count, a.set[1].count, a.n_q, max_bytes);
+    if (p.ns[0] + p.ns[1] < 1) return hipErrorInvalidValue;
+    a.n_qg = p.n_qg; a.rows = p.rows;
+    for (int k = 0; k < 2; ++k) { a.ns[k] = p.ns[k]; a.set[k].groups_per_split = p.gps[k]; }
+    a.fused = p.fused;
+    a.by_xcd = p.n_qg > 1 && a.n_seq >= 8;
+    a.arrivals = (unsigned long long*)workspace;
+    a.partial = (float*)((char*)workspace + p.arrive_bytes);
+    // every launch's own number, spread over 48 bits (never 0)
+    static std::atomic<unsigned long long> launches{1};
+    a.label = (mix64(launches.fetch_add(1, std::memory_order_relaxed)) | 1ull) << 16;
+    if (dtype == BKV_BF16 && d == 128) return launch_attend_t<__bf16, 128>(a, p, st);
+    if (dtype == BKV_BF16 && d == 64) return launch_attend_t<__bf16, 64>(a, p, st);
+    if (dtype == BKV_F32 && d == 128) return launch_attend_t<float, 128>(a, p, st);
+    if (dtype == BKV_F32 && d == 64) return launch_attend_t<float, 64>(a, p, st);
     return hipErrorInvalidValue;
 }
 

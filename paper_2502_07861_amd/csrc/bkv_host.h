@@ -120,7 +120,6 @@ struct SetsArgs {
 };
 size_t sets_workspace_bytes(int row_bytes, int b, int64_t n_seq, int64_t n);
 hipError_t run_sets(const SetsArgs& q, hipStream_t st);
-hipError_t launch_rescale(int dtype, void* out, const float* lse_num, const float* lse_den, int64_t rows, int d, hipStream_t st);
 
 // Alg. 1 token by token: device state of n_seq sequences.  Every sequence owns `regions` numerator regions of
 // cap_n token places (one per live bucket, handed out on a bucket's first token and taken back when the bucket is
@@ -145,27 +144,38 @@ struct StreamState {
 hipError_t stream_route(const StreamState& s, const void* k, const void* v, int64_t j, hipStream_t st);
 hipError_t stream_fixup(const StreamState& s, int round, hipStream_t st);
 
-struct AttendArgs {
-    const char* K;            // [n_seq, stride_tokens, d]
+// One kept set: keys, values (or null: only its normaliser is wanted), weights.
+struct AttendSet {
+    const char* K;            // [n_seq, stride, d]
     const char* V;
-    const float* w;           // [n_seq, stride_tokens]
+    const float* w;           // [n_seq, stride]
+    int64_t stride, count;    // tokens between sequences; tokens read per sequence
+    int32_t groups_per_split; // set by the launcher
+};
+struct AttendArgs {
+    AttendSet set[2];         // [0] numerator (and denominator if set[1].count is 0), [1] denominator
     const char* Q;            // [n_seq, n_q, d]   (n_q = g * nq query vectors per sequence)
     char* out;                // [n_seq, n_q, d]
     float* lse_out;           // [n_seq, n_q] or null
-    float* partial;           // workspace: [n_seq, n_qgroups, n_splits, QT, d + 2]
-    int64_t stride_tokens;
-    int64_t count;
+    int64_t n_seq;
     int32_t n_q;
-    int32_t n_splits;
-    int32_t rows_per_split;
     float scale_log2;         // log2(e)/sqrt(d)
+    // set by the launcher
+    float* partial;           // workspace: [n_seq, n_qg, splits, rows, d + pad]
+    unsigned long long* arrivals;      // workspace: two words per (sequence, query group)
+    unsigned long long label; // this launch's number
+    int32_t n_qg, rows, ns[2], fused, by_xcd;
 };
-size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q);
-hipError_t launch_attend(int dtype, int d, AttendArgs& a, int64_t n_seq, void* workspace, hipStream_t st);
-// the entry point without allocations: what a launch of this shape writes into the partial buffer, and the
+// Workspace bound for any count; `sets`: 1, or 2 when numerator and denominator run over sets of their own.
+size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q, int sets = 1);
+// max_bytes: what the partial rows may take (fewer splits where they would take more)
+hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t max_bytes, hipStream_t st);
+// the entry point without allocations: what a launch of this shape writes into the scratch buffer, and the
 // library's own buffer for it (a file-scope device array; address of the current device's copy)
 constexpr size_t kAttendStaticScratchBytes = 2304 * 1024;
-size_t attend_partial_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q);
+constexpr size_t kAttendStaticPartialBytes = kAttendStaticScratchBytes - 64 * 1024;    // the rest: arrival words
+constexpr size_t kAttendPartialBytes = (size_t)1 << 40;                                // no limit of its own
+size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q, size_t max_bytes);
 hipError_t attend_static_scratch(void** ptr);
 
 }  // namespace bkv

@@ -293,19 +293,6 @@ __global__ __launch_bounds__(64) void collect_kernel(const int32_t* cnt, const i
     }
 }
 
-// out[seq, q, :] *= exp(lse_num - lse_den): the numerator sum over one set divided by the denominator sum over another
-template <typename T>
-__global__ __launch_bounds__(256) void rescale_kernel(char* out, const float* lse_num, const float* lse_den, int64_t rows, int d) {
-    const int64_t total = rows * d;
-    T* o = reinterpret_cast<T*>(out);
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-        const int64_t row = t / d;
-        const float ln = lse_num[row], ld = lse_den[row];
-        const float f = (ln == -__builtin_inff()) ? 0.f : __expf(ln - ld);
-        o[t] = (T)((float)o[t] * f);
-    }
-}
-
 inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 inline unsigned grid_for(int64_t items, int per_block) {
     int64_t blocks = (items + per_block - 1) / per_block;
@@ -446,15 +433,6 @@ hipError_t run_sets(const SetsArgs& q, hipStream_t st) {
     }
     return hipSuccess;
 }
-
-hipError_t launch_rescale(int dtype, void* out, const float* lse_num, const float* lse_den, int64_t rows, int d, hipStream_t st) {
-    if (rows <= 0) return hipSuccess;
-    const unsigned gg = grid_for(rows * d, 256);
-    if (dtype == BKV_BF16) hipLaunchKernelGGL(rescale_kernel<__bf16>, dim3(gg), dim3(256), 0, st, (char*)out, lse_num, lse_den, rows, d);
-    else hipLaunchKernelGGL(rescale_kernel<float>, dim3(gg), dim3(256), 0, st, (char*)out, lse_num, lse_den, rows, d);
-    return hipGetLastError();
-}
-
 
 // ------------------------------------------------------------------------------------------ Alg. 1 token by token
 namespace {

@@ -7,6 +7,8 @@ the oracle's estimator on the GPU's cache within 1e-4 (fp32) / 2e-2 (bf16) relat
 """
 import math
 
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -661,6 +663,49 @@ def test_attend_bf16_weight_rounding_is_bounded(bk, synth):
     print("bf16-weight path vs fp32-weight path: rel-L2 %.3e, lse difference mean %.2e max %.2e" % (err, dl.mean(), np.abs(dl).max()))
     assert err <= 4e-3
     assert np.abs(dl).max() <= 1e-3 and abs(dl.mean()) <= 3e-4
+
+
+def _two_set_reference(K, V, w, Kd, wd, Q):
+    """Float64: sum over (K, V, w) divided by the normaliser of (Kd, wd); returns (out, ln of the normaliser)."""
+    d = K.shape[-1]
+    Qf = Q.double().cpu().flatten(1, 2)
+    num = w.double().cpu()[:, None] * torch.exp(Qf @ K.double().cpu().transpose(1, 2).contiguous() / d ** 0.5)
+    den = (wd.double().cpu()[:, None] * torch.exp(Qf @ Kd.double().cpu().transpose(1, 2).contiguous() / d ** 0.5)).sum(-1)
+    return ((num @ V.double().cpu()) / den[..., None]).view(*Q.shape), torch.log(den).view(*Q.shape[:-1])
+
+
+@pytest.mark.parametrize("dtype,d,n_seq,count,g,nq", [
+    (torch.bfloat16, 128, 1, 31, 1, 1), (torch.bfloat16, 128, 2, 32, 1, 15), (torch.bfloat16, 64, 3, 33, 4, 4),      # around one key group
+    (torch.bfloat16, 128, 2, 8 * 32 * 3 + 1, 17, 1), (torch.bfloat16, 64, 9, 8 * 32, 33, 1),                         # two query tiles; by XCD
+    (torch.bfloat16, 128, 40, 2048 + 16, 4, 1),                                                                      # several steps, four wavefronts
+    (torch.bfloat16, 128, 1, 40000, 16, 1),                                                                          # splits merged by a second launch
+    (torch.float32, 128, 2, 15, 1, 2), (torch.float32, 64, 3, 17, 16, 1), (torch.float32, 128, 9, 700, 33, 1)])
+def test_attend_edges(bk, dtype, d, n_seq, count, g, nq):
+    """Edges of the attend pass: key groups (32 / 16 keys), query tiles of 16, ranges split or not, runs of absent tokens, a
+    set without a value sum; the workspace arrives with arbitrary content and is used again as the call left it.
+    Bounds: fp32 sums of at most 40000 terms, relative 1e-5; bf16 weights and outputs round to nearest (2^-9 each)."""
+    gen = torch.Generator().manual_seed(count + g)
+    K, V = torch.randn(n_seq, count, d, generator=gen).to(dtype).cuda(), torch.randn(n_seq, count, d, generator=gen).to(dtype).cuda()
+    Q = torch.randn(n_seq, g, nq, d, generator=gen).to(dtype).cuda()
+    w = (2.0 ** torch.randint(0, 4, (n_seq, count), generator=gen)).float()
+    w[:, count // 3:count // 3 + count // 2] = 0.0                      # absent: whole groups where the range is long enough
+    w[0, 0] = 0.0
+    w[:, -1] = 2.0
+    w = w.cuda()
+    m = max(1, count // 2)
+    p = bk.make_params(d, 64, 1, dtype, log_c=0.0)
+    tol = 1e-5 if dtype == torch.float32 else 4e-3
+    ws = torch.full((int(bk.lib().bkv_attend_sets_workspace_bytes(C.byref(p), n_seq, g, nq)),), 0xAB, dtype=torch.uint8, device="cuda")
+    ref, ref_lse = _two_set_reference(K, V, w, K, w, Q)
+    ref2, ref2_lse = _two_set_reference(K, V, w, K[:, :m], torch.ones(n_seq, m), Q)
+    ones = torch.ones(n_seq, m, device="cuda")
+    for _ in range(3):
+        out, lse = bk.attend_kv(p, K, V, w, Q, workspace=ws)
+        assert rel_l2(to_f64(out), ref.numpy()) <= tol
+        np.testing.assert_allclose(lse.cpu().numpy(), ref_lse.numpy(), atol=1e-3 if dtype == torch.bfloat16 else 1e-5, rtol=1e-5)
+        out, lse = bk.attend_sets(p, (K, V, w), (K[:, :m].contiguous(), ones), Q, workspace=ws)
+        assert rel_l2(to_f64(out), ref2.numpy()) <= tol
+        np.testing.assert_allclose(lse.cpu().numpy(), ref2_lse.numpy(), atol=1e-3 if dtype == torch.bfloat16 else 1e-5, rtol=1e-5)
 
 
 def test_attend_empty_cache(bk, synth):
