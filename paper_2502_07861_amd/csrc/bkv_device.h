@@ -126,45 +126,54 @@ __device__ __forceinline__ unsigned int f32_to_bf16_bits(float x) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+// Cross-lane steps without LDS: DPP inside a row of 16 lanes, v_permlane16_swap / v_permlane32_swap between rows
+// (__shfl_xor goes through LDS: about 130 clocks a step, and a reduction is a chain of six).
+template <int CTRL> __device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-    return v;
+struct LanePair { float a, b; };
+// the values of lanes l and l ^ O as an unordered pair, the same pair in both lanes (for commutative reductions)
+template <int O> __device__ __forceinline__ LanePair lane_pair(float x) {
+    if constexpr (O == 32) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return {__uint_as_float(sw[0]), __uint_as_float(sw[1])};
+    } else if constexpr (O == 16) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return {__uint_as_float(sw[0]), __uint_as_float(sw[1])};
+    } else if constexpr (O == 8) return {x, dpp<0x128>(x)};                    // row_ror:8
+    else if constexpr (O == 4) return {x, dpp<0x1B>(dpp<0x141>(x))};           // row_half_mirror (^ 7), quad_perm [3,2,1,0] (^ 3)
+    else if constexpr (O == 2) return {x, dpp<0x4E>(x)};                       // quad_perm [2,3,0,1]
+    else return {x, dpp<0xB1>(x)};                                             // quad_perm [1,0,3,2]
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
+template <int O> __device__ __forceinline__ float xor_max(float x) { const LanePair p = lane_pair<O>(x); return fmaxf(p.a, p.b); }
+template <int O> __device__ __forceinline__ float xor_min(float x) { const LanePair p = lane_pair<O>(x); return fminf(p.a, p.b); }
+template <int O> __device__ __forceinline__ float xor_sum(float x) { const LanePair p = lane_pair<O>(x); return p.a + p.b; }
+__device__ __forceinline__ float wave_max(float v) { return xor_max<1>(xor_max<2>(xor_max<4>(xor_max<8>(xor_max<16>(xor_max<32>(v)))))); }
+__device__ __forceinline__ float wave_min(float v) { return xor_min<1>(xor_min<2>(xor_min<4>(xor_min<8>(xor_min<16>(xor_min<32>(v)))))); }
+__device__ __forceinline__ float wave_sum(float v) { return xor_sum<1>(xor_sum<2>(xor_sum<4>(xor_sum<8>(xor_sum<16>(xor_sum<32>(v)))))); }
 
-// all-reduce (sum) over SL consecutive lanes, SL in {8,16,32}: DPP adds inside a row of 16 lanes
+// all-reduce (sum) over SL consecutive lanes, SL in {8,16,32}
 template <int SL> __device__ __forceinline__ float group_sum(float x) {
-    // all-reduce over SL consecutive lanes (SL in {8,16,32}) with DPP adds
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, true));   // quad_perm [2,3,0,1]
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xF, 0xF, true));  // row_half_mirror
-    if (SL >= 16)
-        x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xF, 0xF, true));  // row_mirror
-    if (SL >= 32) x += __shfl_xor(x, 16);
+    x += dpp<0xB1>(x);
+    x += dpp<0x4E>(x);
+    x += dpp<0x141>(x);                          // row_half_mirror
+    if (SL >= 16) x += dpp<0x140>(x);            // row_mirror
+    if (SL >= 32) x = xor_sum<16>(x);
     return x;
 }
 
 // Sixteen values per lane, summed over the 16 lanes of a row: lane s of the row returns the total of x[s].  Each step
 // halves the values a lane carries (it keeps the half its own lane bit selects and hands the other half to its
-// partner), so the sixteen sums take 15 exchanges instead of 64.
-__device__ __forceinline__ float row16_transpose_sum(const float (&x)[16], int s) {
-    const bool b3 = (s & 8) != 0, b2 = (s & 4) != 0, b1 = (s & 2) != 0, b0 = (s & 1) != 0;
-    float y[8], z[4], u[2];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float mine = b3 ? x[j + 8] : x[j], send = b3 ? x[j] : x[j + 8];
-        y[j] = mine + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0x140, 0xF, 0xF, true));   // row_mirror
-    }
+// partner), so the sixteen sums take 15 exchanges instead of 64.  The first step takes the values two at a time, x[j]
+// and x[j + 8] (where they are formed one after the other, eight sums are held instead of sixteen values).
+__device__ __forceinline__ float row16_pair(float xj, float xj8, int s) {
+    const bool b3 = (s & 8) != 0;
+    const float mine = b3 ? xj8 : xj, send = b3 ? xj : xj8;
+    return mine + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0x140, 0xF, 0xF, true));       // row_mirror
+}
+__device__ __forceinline__ float row16_rest(const float (&y)[8], int s) {
+    const bool b2 = (s & 4) != 0, b1 = (s & 2) != 0, b0 = (s & 1) != 0;
+    float z[4], u[2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float mine = b2 ? y[j + 4] : y[j], send = b2 ? y[j] : y[j + 4];
@@ -177,6 +186,12 @@ __device__ __forceinline__ float row16_transpose_sum(const float (&x)[16], int s
     }
     const float mine = b0 ? u[1] : u[0], send = b0 ? u[0] : u[1];
     return mine + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));        // quad_perm [1,0,3,2]
+}
+__device__ __forceinline__ float row16_transpose_sum(const float (&x)[16], int s) {
+    float y[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) y[j] = row16_pair(x[j], x[j + 8], s);
+    return row16_rest(y, s);
 }
 
 }  // namespace bkv

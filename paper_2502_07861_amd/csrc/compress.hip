@@ -784,9 +784,11 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     }
     if (center) {                        // column sums of every wavefront -> LDS
 #pragma unroll
-        for (int o = SL; o < 64; o <<= 1)
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) part[e] += __shfl_xor(part[e], o);
+        for (int e = 0; e < EPL; ++e) {
+            if (SL == 8) part[e] = xor_sum<8>(part[e]);
+            if (SL <= 16) part[e] = xor_sum<16>(part[e]);
+            part[e] = xor_sum<32>(part[e]);
+        }
         if (lane < SL)
 #pragma unroll
             for (int q = 0; q < EPL / 4; ++q) {
