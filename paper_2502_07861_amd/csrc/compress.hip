@@ -32,23 +32,10 @@
 
 #include "bkv_device.h"
 #include "bkv_host.h"
+#include "compress_device.h"
 
 namespace bkv {
 
-template <typename T, int D> struct Geo {
-    static constexpr int kRowBytes = D * (int)sizeof(T);
-    static constexpr int kLdsRow = kRowBytes;               // rows are packed; 16-byte slices are permuted per row instead
-    static constexpr int kGroups = kRowBytes / 32;          // k-groups of 32 bytes per row
-    static constexpr int kSlices = kRowBytes / 16;          // 16-byte slices per row
-    // Slice s of LDS row r is stored at slice position s ^ key(r).  Sixteen consecutive rows reading the same
-    // logical slice (an MFMA operand fetch) then touch sixteen different groups of four banks, and so do the
-    // slices of one row (staging, gathers): no padding bytes, no bank conflicts.  key(r) = key(r + 16).
-    static __device__ __forceinline__ int key(int row) { return kRowBytes >= 256 ? (row & 15) : ((row >> 1) & (kSlices - 1)); }
-    static __device__ __forceinline__ int slice_off(int row, int slice) { return (slice ^ key(row)) << 4; }
-};
-
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * 64;
 constexpr int kDiagStride = 68;                             // floats per column of the transposed diagonal tile (16-byte rows, conflict-free)
 constexpr int kDiagFloats = 64 * kDiagStride;
 constexpr int kLdsLimit = 160 * 1024;
@@ -117,12 +104,6 @@ struct TileOps {
             const int bit = 8 * ((k & 15) >> 2) + (k & 3);
             sg[k] = __uint_as_float(((w[k >> 4] << (31 - bit)) & 0x80000000u) | 0x3f800000u);   // +1 or -1
         }
-    }
-    // cs0 / cs1: per-lane partial sums for columns n / 32+n over this lane half's rows.  Returns, in lane (n, h), the
-    // full sum of column 32*h + n: one half-wave swap (lanes 32..63 of cs0 <-> lanes 0..31 of cs1) and one add.
-    static __device__ __forceinline__ float halves_sum(float cs0, float cs1) {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(cs0), __float_as_uint(cs1), false, false);
-        return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
     // ... or as +-1 floats from LDS: this lane's 32 entries start at sgn_h = base + 32*h
     static __device__ __forceinline__ void signs_from_lds(float (&sg)[32], const float* sgn_h) {
@@ -477,81 +458,6 @@ struct TileOps {
         }
     }
 };
-
-// One decision of the walk (Alg. 2 lines 6-9 for token j of the panel).  Every lane tests the sign of its sigma
-// (which carries the threshold, see the kernel); the compare mask is then read back as data by the vector unit:
-// bit j of it, sign-extended, becomes the -1/+1 that multiplies row j of the diagonal tile.  No scalar-unit hop
-// on the chain: four dependent vector instructions per step.  A vector instruction that reads a scalar register
-// written by the vector instruction just before it needs two wait states on this hardware, hence the s_nop.
-// Lanes <= j hold g[j] = 0, so their sigma stays at its decision-time value.
-// Eight consecutive steps per asm statement, so that nothing is scheduled into the chain.
-template <int B>
-__device__ __forceinline__ void walk_steps8(float& sv, const float (&g)[64], unsigned int sign_bit) {
-    int t;
-    if constexpr (B < 32)
-        asm volatile("v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %11, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %3\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %12, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %4\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %13, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %5\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %14, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %6\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %15, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %7\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %16, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %8\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %17, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %9\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_lo, %18, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %10"
-                     : "+v"(sv), "=&v"(t)
-                     : "s"(sign_bit), "v"(g[B]), "v"(g[B + 1]), "v"(g[B + 2]), "v"(g[B + 3]), "v"(g[B + 4]), "v"(g[B + 5]), "v"(g[B + 6]), "v"(g[B + 7]),
-                       "n"(B), "n"(B + 1), "n"(B + 2), "n"(B + 3), "n"(B + 4), "n"(B + 5), "n"(B + 6), "n"(B + 7)
-                     : "vcc");
-    else
-        asm volatile("v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %11, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %3\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %12, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %4\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %13, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %5\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %14, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %6\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %15, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %7\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %16, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %8\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %17, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %9\n\t"
-                     "v_cmp_le_f32 vcc, 0, %0\n\ts_nop 1\n\tv_bfe_i32 %1, vcc_hi, %18, 1\n\tv_and_or_b32 %1, %1, %2, 1.0\n\tv_fmac_f32 %0, %1, %10"
-                     : "+v"(sv), "=&v"(t)
-                     : "s"(sign_bit), "v"(g[B]), "v"(g[B + 1]), "v"(g[B + 2]), "v"(g[B + 3]), "v"(g[B + 4]), "v"(g[B + 5]), "v"(g[B + 6]), "v"(g[B + 7]),
-                       "n"(B - 32), "n"(B - 31), "n"(B - 30), "n"(B - 29), "n"(B - 28), "n"(B - 27), "n"(B - 26), "n"(B - 25)
-                     : "vcc");
-    // per step: sigma >= 0 -> bit set, factor -1 (eta = -1); sigma < 0 -> factor +1
-}
-__device__ __forceinline__ void walk_panel(float& sv, const float (&g)[64], unsigned int sign_bit) {
-    walk_steps8<0>(sv, g, sign_bit);  walk_steps8<8>(sv, g, sign_bit);  walk_steps8<16>(sv, g, sign_bit); walk_steps8<24>(sv, g, sign_bit);
-    walk_steps8<32>(sv, g, sign_bit); walk_steps8<40>(sv, g, sign_bit); walk_steps8<48>(sv, g, sign_bit); walk_steps8<56>(sv, g, sign_bit);
-}
-
-// Progress counters in LDS (one writer each, values only grow): a wavefront publishes with a release store and
-// waits with a bounded poll.  Every wait is for an event that only depends on earlier events of the same block, and
-// all eight wavefronts are resident, so the polls end; the bound turns a logic error into a status bit instead of
-// a hang.
-constexpr int kSpinLimit = 1 << 16;
-// The fences name LDS only: a wavefront with global loads or stores in flight (look-ahead touches, dumps) must
-// not wait for them here.
-__device__ __forceinline__ void publish(int* counter, int value) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// The same for a hand-over on the walk's critical path, where counter and data are both in LDS and were written by
-// this wavefront just before: LDS serves a wavefront's requests in order, so the counter cannot become visible before
-// the data, and the wavefront need not wait for its own stores to finish first.  (The fence only keeps the compiler
-// from moving the stores.)
-__device__ __forceinline__ void publish_in_order(int* counter, int value) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <bool EAGER = false>
-__device__ __forceinline__ void await(int* counter, int value, int* err) {
-    for (int it = 0; it < kSpinLimit; ++it) {
-        const int seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-        if (seen >= value) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            return;
-        }
-        if (!EAGER) __builtin_amdgcn_s_sleep(1);          // waits on the walk's critical path poll back to back
-    }
-    __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
 // The walker's hand-overs: a counter and the data it guards are requested in one batch, counter first.  LDS serves a
 // wavefront's requests in order, so data that arrives with a counter value >= the awaited one is current; this saves
@@ -1322,39 +1228,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     // Every wavefront handles the panels p = wave, wave + 8, ...: minority sign ('+' on ties), then exactly
     // b/2 survivors = the minority class plus the lowest-index majority tokens, ascending.
     {
-        // lane q < nP (nP <= 16) carries the counts of panel q; prefix sums run over the first row of 16 lanes
-        auto row_scan = [](int x) -> int {                                // inclusive prefix sum inside a row of 16 lanes
-            x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr:1, zero fill
-            x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);   // row_shr:2
-            x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);   // row_shr:4
-            x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);   // row_shr:8
-            return x;
-        };
-        int plus_q = 0;
-        if (lane < nP) plus_q = __popcll(etaMask[lane]);
-        const int n_plus = __builtin_amdgcn_readlane(row_scan(plus_q), 15);
-        const bool plus_is_minority = n_plus <= b - n_plus;               // tie -> '+'
-        const int n_min = plus_is_minority ? n_plus : b - n_plus;
-        const int need = b / 2 - n_min;                                   // majority tokens to add, lowest index first
-        const int min_q = (lane < nP) ? (plus_is_minority ? plus_q : 64 - plus_q) : 0;
-        const int maj_q = (lane < nP) ? 64 - min_q : 0;
-        const int maj_before_q = row_scan(maj_q) - maj_q;
-        const int kept_q = min_q + max(0, min(maj_q, need - maj_before_q));
-        const int kept_before_q = row_scan(kept_q) - kept_q;
-        const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-        for (int p = wave; p < nP; p += kWaves) {
-            const int maj_before = __builtin_amdgcn_readlane(maj_before_q, p);
-            const int kept_before = __builtin_amdgcn_readlane(kept_before_q, p);
-            const unsigned long long mv = etaMask[p];
-            const unsigned long long m = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned int)(mv >> 32)) << 32) |
-                                         (unsigned int)__builtin_amdgcn_readfirstlane((unsigned int)mv);
-            const unsigned long long minm = plus_is_minority ? m : ~m;
-            const unsigned long long majm = ~minm;
-            const int my_rank = maj_before + __popcll(majm & lt);
-            const bool keep = ((minm >> lane) & 1ull) || (my_rank < need);
-            const unsigned long long km = __ballot(keep);
-            if (keep) keptIdx[kept_before + __popcll(km & lt)] = (p << 6) + lane;
-        }
+        select_survivors(etaMask, b, wave, lane, keptIdx);
     }
     __syncthreads();
     if (wave == 0) {      // side outputs: issued after the barrier so that nobody waits for these stores
@@ -1380,26 +1254,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             const int sync_failed = prog[3];
             const int word = (any_fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (n_margin << 8);
             if (a.status_out) {
-                if (a.tree_mode) {
-                    int* dst = a.status_out + seq * a.status_stride + a.round;
-                    if (any_fail) atomicOr(dst, BKV_STATUS_FAIL);
-                    if (sync_failed) atomicOr(dst, BKV_STATUS_INTERNAL);
-                    if (n_margin) {
-                        // the count lives in bits 8..30 and saturates there: bit 31 is never set.  Margin decisions
-                        // are rare, so the compare-and-swap loop (it ends when no other block updates the word in
-                        // between) is next to never entered twice.
-                        int seen = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        for (;;) {
-                            const int cnt = min((seen >> 8) + n_margin, 0x7fffff);
-                            const int want = (seen & 0xff) | (cnt << 8);
-                            const int prev = atomicCAS(dst, seen, want);
-                            if (prev == seen) break;
-                            seen = prev;
-                        }
-                    }
-                } else {
-                    a.status_out[inst] = word;
-                }
+                if (a.tree_mode) add_status(a.status_out + seq * a.status_stride + a.round, any_fail, sync_failed, n_margin);
+                else a.status_out[inst] = word;
             }
             if (a.stats_out) {
                 a.stats_out[2 * inst] = min_margin;
@@ -1504,8 +1360,8 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     const bool v_lds = vgram && compress_value_gram_fits(row_bytes, a.b);
     a.chunk_rows = chunk_rows_for(row_bytes, a.b, v_lds);
     if (n_inst <= 0) return hipSuccess;
+    a.stagger_blocks = 0; a.stagger_step = 0; a.prefetch_ahead = 0;
     {
-        // one workgroup per compute unit is resident (LDS); with at least two rounds of workgroups, spread the first
         static thread_local int n_cu = 0;
         if (n_cu == 0) {
             int dev = 0;
@@ -1513,7 +1369,17 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
             if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
             n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
         }
-        a.stagger_blocks = 0; a.stagger_step = 0; a.prefetch_ahead = 0;
+        // More blocks than compute units: two of them on each (compress_pair.hip).  Up to one per compute unit a launch takes
+        // as long as one block, and a block that has the compute unit to itself is done sooner (256 blocks of 512 bf16 rows:
+        // 28 us against 33).  Measured over 300 to 3000 blocks of 64 to 1024 rows the pair is 4 to 60 % faster, with two
+        // exceptions: larger blocks in a launch whose last, thinly filled round is most of the difference (513 to 640
+        // blocks of more than 256 rows: 0 to 9 % slower), and single precision beyond one chunk (b > 512: between 20 %
+        // slower and 10 % faster; there a wavefront's tile takes long enough for the walk to wait for it).
+        const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 5 * (int64_t)n_cu / 2 && a.b > 256;
+        if (row_bytes == 256 && !emit_g && !vgram && !a.desc && !a.k_by_idx && n_inst > n_cu && !thin_tail &&
+            (dtype == BKV_BF16 || a.b <= 512) && n_inst <= (1ll << 30))
+            return launch_compress_pair(dtype, d, a, n_inst, st);
+        // one workgroup per compute unit is resident (LDS); with at least two rounds of workgroups, spread the first
         if (n_inst >= 2 * (int64_t)n_cu && !a.desc) {   // (a ragged grid has unused slots: neighbours in the grid are not neighbours in memory)
             // The first workgroups start spread over about two thirds of one block's duration: 100k clock ticks for 1024
             // bf16 tokens, whose blocks take about 145k (a spread over the whole duration keeps the compute units idle

@@ -146,6 +146,35 @@ def test_compress_block_teacher_forced(bk, synth, oracle, dtype, d, b, n_inst, c
             assert abs(u[t, first] - free["p"][t, first]) < MARGIN
 
 
+@pytest.mark.parametrize("dtype,d,b,center,r_key", [
+    (torch.bfloat16, 128, 64, True, 0.0), (torch.bfloat16, 128, 256, False, 0.0), (torch.bfloat16, 128, 320, True, 0.0),     # one chunk: 1, 4, 5
+    (torch.bfloat16, 128, 512, True, 9.0), (torch.float32, 64, 64, True, 0.0), (torch.float32, 64, 512, False, 9.0),         # ... and 8 panels
+    (torch.bfloat16, 128, 576, True, 0.0), (torch.bfloat16, 128, 768, False, 0.0), (torch.bfloat16, 128, 832, True, 0.0),    # second chunk: 1, 4, 5
+    (torch.bfloat16, 128, 1024, True, 0.0), (torch.bfloat16, 128, 1024, False, 9.0)])                                        # ... and 8 panels
+def test_many_blocks_equal_few_blocks(bk, synth, dtype, d, b, center, r_key):
+    """A launch with more blocks than compute units runs two blocks on each (another kernel); the same blocks in launches of
+    at most one per compute unit are the reference (they are held against the oracle above).  Both form every sum in the
+    same order, so nothing may differ: signs, survivors, rows, status and statistics bit for bit."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_inst = n_cu + 9
+    base_K, base_V = _blocks(synth, dtype, d, b, 8, seed=31 + b)
+    perm = torch.randperm(8 * b, generator=torch.Generator().manual_seed(b)).cuda()
+    K = torch.cat([base_K.view(-1, d)[(perm + 97 * k) % (8 * b)].view(8, b, d) for k in range((n_inst + 7) // 8)])[:n_inst].contiguous()
+    V = torch.cat([base_V] * ((n_inst + 7) // 8))[:n_inst].contiguous()
+    from oracle.tuning import tune_log_c
+    lc = f32(tune_log_c(to_f64(K[:1]), target=0.25, center=center))
+    p = bk.make_params(d, b, 1, dtype, log_c=lc, seed=77, center=center, r_key=r_key)
+    ids = (torch.arange(n_inst, dtype=torch.int64) * 5 + 3).cuda()
+    many = bk.compress_block(p, K, V, inst_ids=ids)
+    torch.cuda.synchronize()
+    for lo in range(0, n_inst, n_cu):
+        few = bk.compress_block(p, K[lo:lo + n_cu].contiguous(), V[lo:lo + n_cu].contiguous(), inst_ids=ids[lo:lo + n_cu].contiguous())
+        torch.cuda.synchronize()
+        for name, x in few.items():
+            assert torch.equal(many[name][lo:lo + n_cu], x), name
+    assert (many["status"] & 2 == 0).all()
+
+
 @pytest.mark.parametrize("dtype,d,b", [(torch.bfloat16, 128, 512), (torch.bfloat16, 128, 1024), (torch.float32, 64, 256),
                                        (torch.float32, 128, 320)])
 def test_large_common_key_mean(bk, synth, oracle, dtype, d, b):
