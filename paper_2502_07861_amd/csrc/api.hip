@@ -159,7 +159,8 @@ size_t bkv_merge_reduce_workspace_bytes(const bkv_params* p, int64_t n_seq, int6
 // The n tokens halved may be a window of longer sequences: K points at the window's first row, rows of consecutive
 // sequences are k_stride tokens apart (0: n); V points at token 0 of the first sequence, v_stride tokens apart (0: n),
 // and the window starts at token idx_base; idx_out rows are idx_out_stride apart (0: n >> T).
-struct TreeWindow { int64_t k_stride, v_stride, idx_base, idx_out_stride; };
+// status_clear: the status words are 0 already.
+struct TreeWindow { int64_t k_stride, v_stride, idx_base, idx_out_stride; bool status_clear; };
 static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, int64_t n_seq, int64_t n,
                              int64_t seq_base, void* K_out, void* V_out, float* w_out, int64_t out_stride,
                              int32_t* idx_out, int8_t* signs_out, int32_t* status_out, void* workspace,
@@ -207,7 +208,7 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
             idx_final = (int32_t*)workspace;
         }
     }
-    if (status_out && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
+    if (status_out && !(win && win->status_clear) && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
 
     const char* k_in = (const char*)K;
     const int32_t* i_in = nullptr;
@@ -270,24 +271,20 @@ int bkv_merge_reduce_protected(const bkv_params* p, const void* K, const void* V
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e;
     // the two windows: copies of the original rows, weight 1, their own indices
-    const int64_t from[2] = {0, n - n_recent}, to[2] = {0, count - n_recent}, rows[2] = {n_sink, n_recent};
-    for (int k = 0; k < 2; ++k) {
-        const char* Ks = (const char*)K + (size_t)from[k] * rb;
-        const char* Vs = (const char*)V + (size_t)from[k] * rb;
-        if ((e = bkv::launch_copy_rows(Ks, (char*)K_out + (size_t)to[k] * rb, n_seq, n, count, rows[k], (int)rb, st)) != hipSuccess) return hip_fail(e);
-        if ((e = bkv::launch_copy_rows(Vs, (char*)V_out + (size_t)to[k] * rb, n_seq, n, count, rows[k], (int)rb, st)) != hipSuccess) return hip_fail(e);
-        if (w_out && (e = bkv::launch_fill_w(w_out, n_seq, count, to[k], rows[k], 1.f, st)) != hipSuccess) return hip_fail(e);
-        if (idx_out && (e = bkv::launch_fill_iota(idx_out, n_seq, count, to[k], rows[k], (int32_t)from[k], st)) != hipSuccess) return hip_fail(e);
-    }
-    if (n_mid == 0) {   // nothing to halve: no events to report
-        if (status_out && T > 0 && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
-        return BKV_OK;
-    }
+    bkv::WindowArgs wa;
+    memset(&wa, 0, sizeof(wa));
+    wa.K = (const char*)K; wa.V = (const char*)V; wa.K_out = (char*)K_out; wa.V_out = (char*)V_out;
+    wa.w_out = w_out; wa.idx_out = idx_out; wa.n_seq = n_seq; wa.src_stride = n; wa.dst_stride = count; wa.row_bytes = (int32_t)rb;
+    wa.from[0] = 0; wa.from[1] = n - n_recent; wa.to[0] = 0; wa.to[1] = count - n_recent;
+    wa.rows[0] = n_sink; wa.rows[1] = n_recent; wa.w[0] = wa.w[1] = 1.f;
+    if (status_out && T > 0) { wa.clear = status_out; wa.clear_n = n_seq * T; }
+    if ((e = bkv::launch_copy_windows(wa, st)) != hipSuccess) return hip_fail(e);
+    if (n_mid == 0) return BKV_OK;       // nothing to halve: no events to report
     if (T == 0) {       // the rows in between are kept as they are too
         if (idx_out && (e = bkv::launch_fill_iota(idx_out, n_seq, count, n_sink, n_mid, (int32_t)n_sink, st)) != hipSuccess) return hip_fail(e);
         idx_out = nullptr;
     }
-    const TreeWindow win = {n, n, n_sink, count};
+    const TreeWindow win = {n, n, n_sink, count, true};
     return merge_reduce_impl(p, (const char*)K + (size_t)n_sink * rb, V, n_seq, n_mid, seq_base, (char*)K_out + (size_t)n_sink * rb,
                              (char*)V_out + (size_t)n_sink * rb, w_out ? w_out + n_sink : nullptr, count,
                              idx_out ? idx_out + n_sink : nullptr, nullptr, status_out, workspace, ws_bytes, hip_stream, &win);
@@ -610,10 +607,13 @@ int bkv_append_token(bkv_cache* c, const void* k, const void* v, int32_t* status
         a.w_out_val = (float)(1u << (i + 1));
         e = bkv::launch_compress(c->p.dtype, c->p.d, false, a, c->n_seq, st);
         if (e != hipSuccess) return hip_fail(e);
-        if ((e = bkv::launch_copy_rows(tmpK, c->K + (size_t)first * rb, c->n_seq, b / 2, c->cap, b / 2, rb, st)) != hipSuccess) return hip_fail(e);
-        if ((e = bkv::launch_copy_rows(tmpV, c->V + (size_t)first * rb, c->n_seq, b / 2, c->cap, b / 2, rb, st)) != hipSuccess) return hip_fail(e);
-        if ((e = bkv::launch_fill_w(c->w, c->n_seq, c->cap, first, b / 2, a.w_out_val, st)) != hipSuccess) return hip_fail(e);
-        if ((e = bkv::launch_fill_w(c->w, c->n_seq, c->cap, first + b / 2, b / 2, 0.f, st)) != hipSuccess) return hip_fail(e);
+        bkv::WindowArgs wa;              // survivors to the front of the block, no token behind them
+        memset(&wa, 0, sizeof(wa));
+        wa.K = tmpK; wa.V = tmpV; wa.K_out = c->K; wa.V_out = c->V; wa.w_out = c->w;
+        wa.n_seq = c->n_seq; wa.src_stride = b / 2; wa.dst_stride = c->cap; wa.row_bytes = rb;
+        wa.from[0] = 0; wa.from[1] = -1; wa.to[0] = first; wa.to[1] = first + b / 2; wa.rows[0] = wa.rows[1] = b / 2;
+        wa.w[0] = a.w_out_val; wa.w[1] = 0.f;
+        if ((e = bkv::launch_copy_windows(wa, st)) != hipSuccess) return hip_fail(e);
         c->count -= b / 2;
     }
     return halvings;

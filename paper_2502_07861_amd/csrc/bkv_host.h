@@ -72,6 +72,22 @@ hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t
 hipError_t launch_fill_u32(void* p, uint32_t v, int64_t n, hipStream_t st);
 hipError_t launch_copy_rows(const void* src, void* dst, int64_t n_seq, int64_t src_seq_stride,
                             int64_t dst_seq_stride, int64_t rows, int row_bytes, hipStream_t st);
+// Two ranges of tokens per sequence in one launch: rows `from` .. of K and V to `to` .. (from < 0: no rows are copied), their
+// weights and their own indices; and `clear_n` words set to 0.
+struct WindowArgs {
+    const char* K;            // [n_seq, src_stride, d], V likewise
+    const char* V;
+    char* K_out;              // [n_seq, dst_stride, d], V_out likewise
+    char* V_out;
+    float* w_out;             // [n_seq, dst_stride] or null
+    int32_t* idx_out;         // [n_seq, dst_stride] or null: the rows' places in the source
+    int32_t* clear;           // or null
+    int64_t n_seq, src_stride, dst_stride, clear_n;
+    int64_t from[2], to[2], rows[2];
+    float w[2];
+    int32_t row_bytes;
+};
+hipError_t launch_copy_windows(const WindowArgs& a, hipStream_t st);
 hipError_t launch_append(const void* k, const void* v, void* K, void* V, float* w, int64_t n_seq, int64_t seq_stride,
                          int64_t pos, int row_bytes, hipStream_t st);
 hipError_t launch_copy_f32(const float* src, float* dst, int64_t n_seq, int64_t src_seq_stride,

@@ -1452,6 +1452,44 @@ hipError_t launch_copy_rows(const void* src, void* dst, int64_t n_seq, int64_t s
     return hipGetLastError();
 }
 
+// What is kept beside a halving (the protected windows of a prefill; the survivors of a carry and the places it frees) in one
+// launch: each of the small kernels it stands for takes its launch and little else.  8 sequences, 256 + 256 tokens kept of 8704, whole call:
+// 73.1 us of ten launches beside the two halvings, 59.0 us with one.
+__global__ __launch_bounds__(256) void copy_windows_kernel(const WindowArgs a) {
+    const int slices = a.row_bytes >> 4;
+    const int64_t both = a.rows[0] + a.rows[1], total = a.n_seq * both * slices;
+    const int64_t step = (int64_t)gridDim.x * 256, t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t t = t0; t < total; t += step) {
+        const int64_t row = t / slices;
+        const int s = (int)(t - row * slices);
+        const int64_t seq = row / both;
+        int64_t r = row - seq * both;
+        const int k = r >= a.rows[0] ? 1 : 0;
+        r -= k ? a.rows[0] : 0;
+        const int64_t from = k ? a.from[1] : a.from[0], at = seq * a.dst_stride + (k ? a.to[1] : a.to[0]) + r;
+        if (from >= 0) {
+            const size_t src = (size_t)(seq * a.src_stride + from + r) * a.row_bytes + s * 16, dst = (size_t)at * a.row_bytes + s * 16;
+            const uintx4 x = *reinterpret_cast<const uintx4*>(a.K + src), y = *reinterpret_cast<const uintx4*>(a.V + src);
+            *reinterpret_cast<uintx4*>(a.K_out + dst) = x;
+            *reinterpret_cast<uintx4*>(a.V_out + dst) = y;
+        }
+        if (s == 0) {
+            if (a.w_out) a.w_out[at] = k ? a.w[1] : a.w[0];
+            if (a.idx_out) a.idx_out[at] = (int32_t)(from + r);
+        }
+    }
+    for (int64_t t = t0; t < a.clear_n; t += step) a.clear[t] = 0;
+}
+hipError_t launch_copy_windows(const WindowArgs& a, hipStream_t st) {
+    const int64_t total = a.n_seq * (a.rows[0] + a.rows[1]) * (a.row_bytes >> 4);
+    const int64_t items = total > a.clear_n ? total : a.clear_n;
+    if (items <= 0) return hipSuccess;
+    int64_t blocks = (items + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    hipLaunchKernelGGL(copy_windows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 // dst[seq, r] = src[seq, r] for r < rows (fp32, strided per sequence)
 __global__ void copy_f32_kernel(const float* src, float* dst, int64_t src_seq_stride, int64_t dst_seq_stride,
                                 int64_t rows, int64_t total) {

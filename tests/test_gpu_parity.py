@@ -573,6 +573,27 @@ def test_merge_reduce_protected_windows(bk, synth, oracle, dtype, d, b, T, n_sin
                 np.testing.assert_array_equal(off["w"], w[s])
 
 
+@pytest.mark.parametrize("dtype,d,n_sink,n_recent", [(torch.bfloat16, 64, 1, 0), (torch.float32, 128, 0, 1), (torch.bfloat16, 128, 0, 0),
+                                                     (torch.bfloat16, 128, 257, 3)])
+def test_protected_windows_of_single_rows(bk, synth, dtype, d, n_sink, n_recent):
+    """One launch copies both windows and clears the status words: an empty window, windows of one row, an odd length."""
+    n_seq, mid = 5, 256
+    t = synth.gqa_layer_bf16(n_seq=n_seq, n=n_sink + mid + n_recent, d=d, g=1, nq=1, seed=77, device="cpu", dtype=dtype)
+    K, V = t["K"].cuda(), t["V"].cuda()
+    p = bk.make_params(d, 128, 1, dtype, log_c=-8.0, seed=3, center=True)
+    res = bk.merge_reduce_protected(p, K, V, n_sink, n_recent)
+    alone = bk.merge_reduce(p, K[:, n_sink:n_sink + mid].contiguous(), V[:, n_sink:n_sink + mid].contiguous())
+    ends = list(range(n_sink)), list(range(n_sink + mid, n_sink + mid + n_recent))
+    want = torch.cat([torch.tensor(ends[0], dtype=torch.int32).cuda().expand(n_seq, -1), alone["idx"] + n_sink,
+                      torch.tensor(ends[1], dtype=torch.int32).cuda().expand(n_seq, -1)], dim=1)
+    assert torch.equal(res["idx"], want) and torch.equal(res["status"], alone["status"])
+    gi = want.long()[..., None].expand(-1, -1, d)
+    assert torch.equal(res["K"], torch.gather(K, 1, gi)) and torch.equal(res["V"], torch.gather(V, 1, gi))
+    w = torch.ones_like(res["w"])
+    w[:, n_sink:n_sink + mid // 2] = 2.0
+    assert torch.equal(res["w"], w)
+
+
 def test_merge_reduce_rounds_zero_and_empty(bk, synth):
     t = synth.gqa_layer_bf16(n_seq=2, n=128, d=64, g=1, nq=1, seed=3, device="cpu")
     K, V = t["K"].cuda(), t["V"].cuda()
