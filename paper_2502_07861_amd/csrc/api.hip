@@ -412,7 +412,6 @@ int bkv_balancekv_sets(const bkv_params* p_in, int32_t which, const void* K, con
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e;
     const int T = p.rounds;
-    if (status_out && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * (T > 0 ? T : 1), st)) != hipSuccess) return hip_fail(e);
     bkv::SetsArgs q;
     memset(&q, 0, sizeof(q));
     fill_common(q.common, &p);

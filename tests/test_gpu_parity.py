@@ -1376,6 +1376,37 @@ def test_balancekv_sets_equal_the_oracle_stream(bk, synth, oracle):
     assert compared >= 2
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float32, 64)])
+@pytest.mark.parametrize("n,eps", [(1, 0.0), (255, 0.0), (257, 1e-4), (513, 0.0), (33001, 0.0), (70000, 1e-4)])
+def test_balancekv_sets_keep_every_token_in_slot_order(bk, dtype, d, n, eps):
+    """Without rounds the kept set is the stable partition itself: chunks of one token, of a remainder, of more than 256 tokens, more
+    tokens than 128 chunks of 256.  Slots against the norms in fp64 (rows near a power of two may go either way)."""
+    n_seq = 2
+    gen = torch.Generator().manual_seed(n)
+    scale = torch.exp2(torch.rand(n_seq, n, 1, generator=gen) * 6 - 3)
+    V = (torch.randn(n_seq, n, d, generator=gen) * scale)
+    V[:, n // 2] = 0.0                                                       # a row of no bucket
+    V, K = V.to(dtype).cuda(), torch.randn(n_seq, n, d, generator=gen).to(dtype).cuda()
+    p = bk.make_params(d, 64, 0, dtype, log_c=0.0, seed=1, center=True)
+    num = bk.balancekv_sets(p, bk.BKV_SET_NUMERATOR, K, V, capacity=n, eps=eps, r=0.0)
+    norm = V.double().norm(dim=-1)
+    want = torch.where(norm > 0, 256 + torch.ceil(torch.log2(norm.clamp_min(1e-30))).int(), 511)
+    if eps > 0:
+        gone = torch.exp2(2.0 * (want - 256)) <= (eps / (2 * n)) ** 2 * norm.max(dim=1, keepdim=True).values ** 2
+        want = torch.where(gone, 511, want)
+    near = (torch.log2(norm.clamp_min(1e-30)) - torch.round(torch.log2(norm.clamp_min(1e-30)))).abs() < 1e-5
+    assert torch.all((num["slot"] == want) | near)
+    for s in range(n_seq):
+        order = torch.argsort(num["slot"][s], stable=True)
+        order = order[: int((num["slot"][s] != 511).sum())]
+        c = int(num["count"][s])
+        assert c == order.numel() and torch.equal(num["idx"][s, :c].long(), order)
+        assert torch.equal(num["K"][s, :c], K[s, order]) and torch.equal(num["V"][s, :c], V[s, order])
+        assert torch.all(num["w"][s, :c] == 1.0) and torch.all(num["w"][s, c:] == 0.0) and torch.all(num["K"][s, c:] == 0)
+    den = bk.balancekv_sets(p, bk.BKV_SET_DENOMINATOR, K, V, capacity=n)
+    assert torch.equal(den["idx"], torch.arange(n, dtype=torch.int32, device="cuda").expand(n_seq, -1)) and torch.equal(den["K"], K)
+
+
 def test_balancekv_sets_degenerate_cases(bk, synth, oracle):
     """No rounds (everything kept with weight 1: the two-set output line is exact attention, Eq. 1), a capacity below
     the count (the surplus is not written, the count is still reported), all value rows zero (empty numerator set:
