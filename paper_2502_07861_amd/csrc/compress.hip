@@ -72,6 +72,11 @@ template <typename T, int D>
 struct TileOps {
     typedef Geo<T, D> G;
     typedef typename Elem<T>::Frag Frag;
+    // Rows of 512 bytes: a panel's fragments are 128 registers, more than a wavefront has beside its accumulators, and a k-group
+    // is eight matrix instructions of 64 clocks, against which three LDS reads are nothing: operands are requested a few
+    // k-groups ahead of their use, every time, and none is kept (held, they went to scratch memory and back).  96 blocks of
+    // 384 fp32 rows, d = 128: 134 -> 81 us (256 rows 54 -> 45, 1024 rows 509 -> 374, with the value factor, 256 rows, 142 -> 91).
+    static constexpr bool kStream = G::kGroups > 8;
 
     // 64 rows starting at `base` (row stride in bytes) -> operand fragments of this lane.
     static __device__ __forceinline__ void load_frags(Frag (&F)[G::kGroups][2], const char* base,
@@ -131,7 +136,7 @@ struct TileOps {
     // per column with the row signs; then the same for the second half.  Per MFMA (32 cycles in the matrix pipe)
     // the vector unit gets two elements: 2 FMA + 2 exp2 (+ 2 FMA); the order is written out and fenced, B fragments
     // are requested one k-group ahead.  A fragments come from registers (AREG: the caller's A, reused over several
-    // tiles) or from LDS rows ldsA[0..63], one half at a time; signs come from registers (sg) or, if sg is null,
+    // tiles; AREG = 1) or from LDS rows ldsA[0..63], one half at a time (0), or from memory (2; ldsA: THIS LANE's row n); signs come from registers (sg) or, if sg is null,
     // from LDS (sgn_h: this lane half's 32 floats).  naA / naB: -a_i of the tile's 64 rows / -a_j of its 64 columns.
     // Returns this lane's column 32*h + n of the signed column sums.
     // With BREG the column panel's fragments come from the caller's registers too (Bq), e.g. a panel that a
@@ -142,7 +147,7 @@ struct TileOps {
     // in LDS in the layout of the keys (vA: the 64 rows that match the tile's rows, vB: those that match its columns).
     // VG = 2: they are read from global memory; vA / vA1 are THIS LANE's rows n and n + 32 of the row panel, vB / vB1 of
     // the column panel.
-    template <bool SUM, bool AREG, bool BREG = false, bool DIAG = false, int VG = 0>
+    template <bool SUM, int AREG, bool BREG = false, bool DIAG = false, int VG = 0>
     static __device__ __forceinline__ float tile(floatx16 (&acc)[2][2], const Frag (*A)[2], const char* ldsA, const char* ldsB,
                                                  const float* naA, const float* naB, float alpha, float rc, const float* sg, const float* sgn_h,
                                                  const int (&foff)[G::kGroups], int n, int h, const Frag (*Bq)[2] = nullptr,
@@ -183,7 +188,7 @@ struct TileOps {
         }
         const char* bp0 = BREG ? nullptr : ldsB + (size_t)n * G::kLdsRow;
         const char* bp1 = BREG ? nullptr : bp0 + (size_t)32 * G::kLdsRow;
-        const char* ap = AREG ? nullptr : ldsA + (size_t)n * G::kLdsRow;
+        const char* ap = AREG == 1 ? nullptr : AREG == 2 ? ldsA + 16 * h : ldsA + (size_t)n * G::kLdsRow;
         Frag Ah[2][KG], B0[KG], B1[KG];
         floatx4 sq[2][4];
         // -a_i of this lane's 16 rows of each half, in accumulator order: where the Gram's accumulators start from
@@ -198,7 +203,7 @@ struct TileOps {
         // the column term of this lane's two columns: rc - alpha a_j
         const float cc0 = fmaf(alpha, naB[n], rc), cc1 = fmaf(alpha, naB[32 + n], rc);
         auto load_a = [&](int rb, int g) {
-            Ah[rb][g] = AREG ? A[g][rb] : *reinterpret_cast<const Frag*>(ap + (size_t)(32 * rb) * G::kLdsRow + foff[g]);
+            Ah[rb][g] = AREG == 1 ? A[g][rb] : *reinterpret_cast<const Frag*>(ap + (size_t)(32 * rb) * G::kLdsRow + (AREG == 2 ? 32 * g : foff[g]));
         };
         auto load_b = [&](int g) {
             if (BREG) { B0[g] = Bq[g][0]; B1[g] = Bq[g][1]; return; }
@@ -242,8 +247,9 @@ struct TileOps {
             __builtin_amdgcn_sched_barrier(0);
         };
         // rows 0..31 on the matrix pipe; requests for what the next stage needs ride along
+        constexpr bool kRollA = AREG == 2 || (AREG == 0 && kStream);
 #pragma unroll
-        for (int g = 0; g < KG; ++g) load_a(0, g);
+        for (int g = 0; g < (kRollA ? kAhead : KG); ++g) load_a(0, g);
 #pragma unroll
         for (int g = 0; g < kAhead; ++g) load_b(g);
         load_rinit(0);
@@ -253,7 +259,8 @@ struct TileOps {
             if (g + kAhead < KG) load_b(g + kAhead);
             if (g < 4) load_rowterm(0, g);
             if (g == 0) load_rinit(1);
-            if (!AREG) load_a(1, g);
+            if (kRollA) { if (g + kAhead < KG) load_a(0, g + kAhead); }
+            else if (AREG == 0) load_a(1, g);
             if (g == 0) {                                  // both accumulators start from -a_i of their rows
                 acc[0][0] = Elem<T>::mma_from(Ah[0][0], B0[0], rinit[0]);
                 acc[0][1] = Elem<T>::mma_from(Ah[0][0], B1[0], rinit[0]);
@@ -264,9 +271,9 @@ struct TileOps {
             __builtin_amdgcn_sched_barrier(0);
         }
         // rows 32..63 on the matrix pipe, rows 0..31 on the vector unit
-        if (AREG)
+        if (AREG == 1 || kRollA)
 #pragma unroll
-            for (int g = 0; g < KG; ++g) load_a(1, g);
+            for (int g = 0; g < (kRollA ? kAhead : KG); ++g) load_a(1, g);
         constexpr bool kKeepB = BREG || KG <= 8;           // up to 64 registers: the B fragments of the first half stay
         if (!kKeepB)
 #pragma unroll
@@ -275,6 +282,7 @@ struct TileOps {
 #pragma unroll
         for (int g = 0; g < KG; ++g) {
             if (!kKeepB && g + kAhead < KG) load_b(g + kAhead);
+            if (kRollA && g + kAhead < KG) load_a(1, g + kAhead);
             if (g >= KG - 4) load_rowterm(1, g - (KG - 4));
             if (g == 0) { if (!DIAG) acc[1][0] = Elem<T>::mma_from(Ah[1][0], B0[0], rinit[1]); }
             else if (!DIAG) Elem<T>::mma(acc[1][0], Ah[1][g], B0[g]);
@@ -294,8 +302,9 @@ struct TileOps {
     // software-pipelined over half tiles: while the matrix pipe forms rows 0..31 of the next tile the vector unit
     // finishes rows 32..63 of the current one, and vice versa, so that neither unit waits for the other even when
     // two wavefronts share a SIMD.  emit(jj, cs) receives this lane's column 32*h + n of tile jj's signed column sums.
+    // With kStream the row panel's fragments come from memory (L2) as they are needed: Arow is this lane's row n of the panel.
     template <typename Emit>
-    static __device__ __forceinline__ void row_sweep(const Frag (&A)[G::kGroups][2], const char* ldsB, int nJ,
+    static __device__ __forceinline__ void row_sweep(const Frag (*A)[2], const char* Arow, const char* ldsB, int nJ,
                                                      const float* naA, const float* naB, float alpha, float rc, unsigned long long eta_mask,
                                                      const int (&foff)[G::kGroups], int n, int h, Emit emit) {
         constexpr int KG = G::kGroups;
@@ -312,7 +321,12 @@ struct TileOps {
             return __uint_as_float(((nbw[rb] << (31 - (8 * (r >> 2) + (r & 3)))) & 0x80000000u) | 0x3f800000u);
         };
         const char* bp0 = ldsB + (size_t)n * G::kLdsRow;
-        Frag B0[KG], B1[KG];
+        Frag B0[KG], B1[KG], At[KG];
+        constexpr int kAheadA = 4;
+        auto load_at = [&](int rb, int g) {
+            if constexpr (kStream) At[g] = *reinterpret_cast<const Frag*>(Arow + (size_t)(32 * rb) * G::kRowBytes + 32 * g);
+            else At[g] = A[g][rb];
+        };
         // -a_i of the row panel is where the accumulators start from (fetched anew for every half tile: 16 registers in
         // flight instead of 32 held), -a_j of the column panel at hand makes the FMA's addend (naB moves with bp0)
         float cc0 = 0.f, cc1 = 0.f;                      // rc - alpha a_j of this lane's two columns of the tile being finished
@@ -357,17 +371,20 @@ struct TileOps {
             constexpr int RBM = decltype(rbm_c)::value;
             constexpr bool FIN = decltype(fin_c)::value;
 #pragma unroll
+            for (int g = 0; g < (kStream ? kAheadA : KG); ++g) load_at(RBM, g);
+#pragma unroll
             for (int g = 0; g < kAhead; ++g) load_b(g);
             load_rinit(RBM);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int g = 0; g < KG; ++g) {
+                if (kStream && g + kAheadA < KG) load_at(RBM, g + kAheadA);
                 if (g + kAhead < KG) load_b(g + kAhead);
-                if (g == 0) acc[RBM][0] = Elem<T>::mma_from(A[0][RBM], B0[0], rinit);
-                else Elem<T>::mma(acc[RBM][0], A[g][RBM], B0[g]);
+                if (g == 0) acc[RBM][0] = Elem<T>::mma_from(At[0], B0[0], rinit);
+                else Elem<T>::mma(acc[RBM][0], At[g], B0[g]);
                 if (FIN) finish_group(1 - RBM, g * RPI, 0);
-                if (g == 0) acc[RBM][1] = Elem<T>::mma_from(A[0][RBM], B1[0], rinit);
-                else Elem<T>::mma(acc[RBM][1], A[g][RBM], B1[g]);
+                if (g == 0) acc[RBM][1] = Elem<T>::mma_from(At[0], B1[0], rinit);
+                else Elem<T>::mma(acc[RBM][1], At[g], B1[g]);
                 if (FIN) { finish_group(1 - RBM, g * RPI, 1); finish_group(1 - RBM, g * RPI, 2); }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -964,10 +981,11 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             bool first = true;
             for (int I = wave; I < p0; I += kWaves) {
                 Frag A[G::kGroups][2];
-                Ops::load_frags(A, Kin + (size_t)(I << 6) * G::kRowBytes, G::kRowBytes, n, h);
+                const char* Arow = Kin + (size_t)((I << 6) + n) * G::kRowBytes;
+                if (!Ops::kStream) Ops::load_frags(A, Kin + (size_t)(I << 6) * G::kRowBytes, G::kRowBytes, n, h);
                 if constexpr (!EMIT_G && VG == 0) {
                     const bool first_panel = first;
-                    Ops::row_sweep(A, ldsK, nJ, narow + (I << 6), narow + (p0 << 6), alpha, row_const, etaMask[I], foff, n, h, [&](int jj, float cs) {
+                    Ops::row_sweep(A, Arow + 16 * h, ldsK, nJ, narow + (I << 6), narow + (p0 << 6), alpha, row_const, etaMask[I], foff, n, h, [&](int jj, float cs) {
                         float* slot = partial + (wave * 8 + jj) * 64 + lane;          // this wavefront's own slot
                         *slot = first_panel ? cs : *slot + cs;
                     });
@@ -979,8 +997,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     const int J = p0 + jj;
                     const char* ldsB = lds_rows(jj << 6);
                     floatx16 acc[2][2];
-                    const float cs = Ops::template tile<true, true, false, false, VG>(
-                        acc, A, nullptr, ldsB, narow + (I << 6), narow + (J << 6), alpha, row_const, sg, nullptr, foff, n, h, nullptr,
+                    const float cs = Ops::template tile<true, Ops::kStream ? 2 : 1, false, false, VG>(
+                        acc, A, Ops::kStream ? Arow : nullptr, ldsB, narow + (I << 6), narow + (J << 6), alpha, row_const, sg, nullptr, foff, n, h, nullptr,
                         VG == 2 ? vrow((I << 6) + n) : nullptr, VG == 2 ? vrow((J << 6) + n) : nullptr, inv_rv2,
                         VG == 2 ? vrow((I << 6) + 32 + n) : nullptr, VG == 2 ? vrow((J << 6) + 32 + n) : nullptr, vg_bias);
                     if constexpr (EMIT_G) {
@@ -1099,7 +1117,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 floatx16 dv[2][2];
                 const char* vrows = VG == 1 ? ldsV + (size_t)(l << 6) * G::kLdsRow : VG == 2 ? vrow((I << 6) + n) : nullptr;
                 const char* vrows1 = VG == 2 ? vrow((I << 6) + 32 + n) : nullptr;
-                Ops::template tile<false, true, true, !EMIT_G, VG>(dv, P, nullptr, nullptr, narow + (I << 6), narow + (I << 6), alpha, row_const,
+                const char* krows = Ops::kStream ? lds_rows(l << 6) : nullptr;
+                Ops::template tile<false, !Ops::kStream, !Ops::kStream, !EMIT_G, VG>(dv, P, krows, krows, narow + (I << 6), narow + (I << 6), alpha, row_const,
                                                                    nullptr, nullptr, foff, n, h, P, vrows, vrows, inv_rv2, vrows1, vrows1, vg_bias);
                 if (EMIT_G) {
 #pragma unroll
@@ -1118,7 +1137,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 Ops::store_diag(diag, dv, n, h);
                 publish(diag_ready, l + 1);
             };
-            Frag Bq[G::kGroups][2];
+            Frag Bq[G::kGroups][2];                        // (not with Ops::kStream)
             // Start-up: the diagonal tile of panel 1 (and, where it is not split, that of panel 0) comes from the
             // wavefronts whose own columns are needed last.
             if (kSplitFirst && w <= 3) {
@@ -1134,18 +1153,18 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             }
             if (w >= kWaves - 2 && kWaves - 1 - w < nPc && !(kSplitFirst && w == kWaves - 1)) {
                 if (w == kWaves - 1) __builtin_amdgcn_s_setprio(2);       // the walk cannot start without the first tile
-                Ops::load_panel(Bq, lds_rows((kWaves - 1 - w) << 6), foff, n);
+                if (!Ops::kStream) Ops::load_panel(Bq, lds_rows((kWaves - 1 - w) << 6), foff, n);
                 diagonal(Bq, kWaves - 1 - w);
                 __builtin_amdgcn_s_setprio(0);
             }
             if (owner) {
                 const int J = p0 + w;
-                Ops::load_panel(Bq, lds_rows(w << 6), foff, n);
+                if (!Ops::kStream) Ops::load_panel(Bq, lds_rows(w << 6), foff, n);
                 float sig = sigma[(J << 6) + lane];           // minus the threshold, plus what earlier chunks added
                 for (int i = 0; i < w; ++i) {
                     const int Ii = p0 + i;
                     floatx16 acc[2][2];
-                    Ops::template tile<false, false, true, false, VG>(acc, nullptr, lds_rows(i << 6), nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
+                    Ops::template tile<false, false, !Ops::kStream, false, VG>(acc, nullptr, lds_rows(i << 6), Ops::kStream ? lds_rows(w << 6) : nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
                                                                       nullptr, nullptr, foff, n, h, Bq,
                                                                       VG == 1 ? ldsV + (size_t)(i << 6) * G::kLdsRow : VG == 2 ? vrow((Ii << 6) + n) : nullptr,
                                                                       VG == 1 ? ldsV + (size_t)(w << 6) * G::kLdsRow : VG == 2 ? vrow((J << 6) + n) : nullptr, inv_rv2,
@@ -1183,7 +1202,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 // This column is complete (the walk of panel w is starting): form the diagonal tile that is due two
                 // walks from now.  Wavefront 1, which has no predecessor, also supplies the tile of panel 2.
                 for (int l = (w == 1 ? 2 : w + 2); l <= w + 2 && l < nPc; ++l) {     // wavefront 1 also supplies panel 2's
-                    Ops::load_panel(Bq, lds_rows(l << 6), foff, n);
+                    if (!Ops::kStream) Ops::load_panel(Bq, lds_rows(l << 6), foff, n);
                     diagonal(Bq, l);
                 }
             }
@@ -1625,7 +1644,7 @@ __global__ __launch_bounds__(kThreads) void peak_tile_kernel(float* out, int ite
     Ops::load_panel(A, ldsK + (size_t)(wave << 6) * G::kLdsRow, foff, n);
     float total = 0.f;
     for (int it = 0; it < iters; ++it)
-        Ops::row_sweep(A, ldsK, 8, narow + (wave << 6), narow, 0.1275f, -20.f, 0x5a5a5a5a5a5a5a5aull + it, foff, n, h,
+        Ops::row_sweep(A, nullptr, ldsK, 8, narow + (wave << 6), narow, 0.1275f, -20.f, 0x5a5a5a5a5a5a5a5aull + it, foff, n, h,
                        [&](int, float cs) { total += cs; });
     out[(size_t)blockIdx.x * kThreads + tid] = total;
 }
