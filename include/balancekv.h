@@ -305,8 +305,8 @@ int bkv_attend(const bkv_cache* c, const void* Q, int32_t g, int32_t nq, void* o
  * sequence the instance MR-Denominator and one instance MR-Numerator_i per live value-norm bucket i, each holding the
  * levels Alg. 3 keeps.  Which numerator instance a token feeds, when it carries and which buckets are erased depend
  * on the values, so every counter lives on the device and no call reads anything back: bkv_stream_append is a fixed
- * sequence of launches (route the token; per round r < T: halve the numerator blocks that carry, halve the
- * denominator blocks -- launched only at the tokens where the host knows they carry --, move the survivors back).
+ * sequence of launches (route the token; per round r < T that the stream is long enough to reach: halve the numerator
+ * blocks that carry, in place, and the denominator blocks -- launched only at the tokens where the host knows they carry).
  *   regions     numerator instances a sequence can hold at a time (1..64); a bucket takes a free one on its first
  *               token and gives it back when line 8 erases it
  *   cap_num     token places per numerator region, cap_den places of the denominator region (>= block each); an

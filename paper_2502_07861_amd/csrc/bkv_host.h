@@ -17,7 +17,7 @@ struct InstDesc {
     uint64_t stream, ctr0;
     int32_t seq, valid;
     float rvalue2;
-    int32_t pad;
+    int32_t region;           // of the sequence's counters (CompressArgs::carry_cnt)
 };
 
 struct CompressArgs {
@@ -35,6 +35,12 @@ struct CompressArgs {
     const uint64_t* inst_ids;
     const float* uniforms;
     const InstDesc* desc;     // ragged launches: per-instance coordinates (then blocks_per_seq, strides and bases are not read)
+    // In-place carries (ragged launches): not null, then K_out = K, V_out = V and out_tok = in_tok, the survivors go to the front of
+    // their own block with weight w_out_val and their entries of carry_idx, the rest of the block gets weight 0, and the counter
+    // carry_cnt[seq * carry_cnt_stride + region] shrinks by b / 2
+    float* carry_w;
+    int32_t* carry_idx;
+    int32_t* carry_cnt;
     float* G_out;             // kernel-weight dump (EMIT_G variant only)
     int64_t in_seq_stride;    // tokens between consecutive sequences in K / V / idx_in
     int64_t out_seq_stride;   // tokens between consecutive sequences in K_out / V_out / w_out
@@ -49,6 +55,7 @@ struct CompressArgs {
     int32_t chunk_rows;
     int32_t round;            // level of the tree this launch halves
     int32_t tree_mode;        // 1: stream = 64*(seq_base+seq)+round, ctr = (blk_base+blk)*b + j ; 0: stream = inst, ctr = j
+    int32_t carry_cnt_stride;
     int32_t status_stride;    // tree mode: status_out[seq*status_stride + round] accumulated atomically
     float w_out_val;
     float alpha;              // log2(e)/sqrt(d)
@@ -153,14 +160,11 @@ struct StreamState {
     unsigned int* vmax2;      // [n_seq]: largest |v|^2 so far (bits of a non-negative float)
     int32_t* err;             // one word: BKV_STATUS_INTERNAL of any halving | BKV_STREAM_* overflow bits
     InstDesc* desc;           // [T, 2, n_seq]: the carries of the current token (0: numerator, 1: denominator)
-    char* tmpK; char* tmpV;   // [2, n_seq, b/2, d]: survivors of the halving in flight
-    int32_t* tmpIdx;          // [2, n_seq, b/2]: their places
     int64_t n_seq, seq_base, cap_n, cap_d;
     int32_t regions, b, T, row_bytes, dtype, d;
     float erase2;             // (eps / (2n) * exp(-r^2 / sqrt d))^2, 0: nothing is erased
 };
 hipError_t stream_route(const StreamState& s, const void* k, const void* v, int64_t j, hipStream_t st);
-hipError_t stream_fixup(const StreamState& s, int round, hipStream_t st);
 
 // One kept set: keys, values (or null: only its normaliser is wanted), weights.
 struct AttendSet {

@@ -524,7 +524,8 @@ __device__ __forceinline__ float await_and_read(int* counter, int value, const f
 // VG != 0: the kernel weights carry the value factor <v_i,v_j> / r_value^2 of Alg. 2 line 6.  VG = 1 (resident blocks
 // whose values fit LDS too): the block's value rows are staged in LDS behind the key rows.  VG = 2 (any block): the
 // value panels of every tile are read from global memory (L2) as they are needed.
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0>
+// CARRY: survivors go to the front of their own block (CompressArgs::carry_w).
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false>
 __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a) {
     static_assert(VG == 0 || !EMIT_G, "the weight dump has no values");
     static_assert(VG != 1 || !MULTI, "values in LDS: resident blocks only");
@@ -1300,7 +1301,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         char* Vo = do_v ? a.V_out + out_tok0 * G::kRowBytes : nullptr;
         const bool k_global = Ko && !single_chunk;
         constexpr int U = 16;
-        for (int r0 = rg; r0 < half; r0 += RG * U) {
+        for (int base = CARRY ? 0 : rg; base < half; base += RG * U) {      // (carries: as many passes for every thread)
+            const int r0 = CARRY ? base + rg : base;
             uintx4 kraw[U], vraw[U];
             if (do_v) {
 #pragma unroll
@@ -1332,6 +1334,12 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     }
                 }
             }
+            // In place: survivor r comes from row keptIdx[r] >= r, so a pass may overwrite rows that it reads itself, never rows
+            // of a later one; its loads have arrived, in all wavefronts, before its first store.
+            if constexpr (CARRY) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+            }
             if (Ko) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -1353,13 +1361,29 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         if (a.w_out) a.w_out[out_tok0 + r] = a.w_out_val;
         if (a.idx_out) a.idx_out[idx_out0 + r] = (int32_t)src_token(r);
     }
+    // A carry leaves the stream's state complete: as a launch of its own behind every round (survivors back from a buffer) the
+    // same cost a launch per round and token whether or not anything carried.  An instance of its own: as a run-time choice these
+    // barriers cost every other halving 3 % (8 x 16384 tokens, blocks of 512, two rounds: 63.3 -> 66.2 us).
+    if constexpr (CARRY) {
+        static_assert(kThreads >= 512, "one survivor per thread: blocks of up to 1024 rows");
+        int32_t* o = a.carry_idx + in_tok0;
+        const int32_t mine = tid < half ? o[keptIdx[tid]] : 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid < half) {
+            o[tid] = mine;
+            a.carry_w[in_tok0 + tid] = a.w_out_val;
+            a.carry_w[in_tok0 + half + tid] = 0.f;
+        }
+        if (tid == 0) a.carry_cnt[seq * a.carry_cnt_stride + a.desc[inst].region] -= half;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0>
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false>
 static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t st) {
     const size_t lds = compress_lds_bytes(Geo<T, D>::kRowBytes, a.b, VG == 1);
-    auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG>;
+    auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG, CARRY>;
     static thread_local size_t configured = 0;
     if (lds > configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1376,6 +1400,7 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     // value factor: no Gram dump, value rows required; the values are staged in LDS when they fit next to the keys
     if (vgram && (emit_g || !a.V)) return hipErrorInvalidValue;
     if (a.k_by_idx && (!a.idx_in || emit_g)) return hipErrorInvalidValue;
+    if (a.carry_w && (!a.desc || !a.carry_idx || !a.carry_cnt || emit_g)) return hipErrorInvalidValue;
     const bool v_lds = vgram && compress_value_gram_fits(row_bytes, a.b);
     a.chunk_rows = chunk_rows_for(row_bytes, a.b, v_lds);
     if (n_inst <= 0) return hipSuccess;
@@ -1419,7 +1444,12 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     const bool multi = a.b > a.chunk_rows;       // the Gram-emitting (test) variant always takes the general code
     if (a.k_by_idx && multi) return hipErrorInvalidValue;      // scattered key rows: resident blocks only
 #define BKV_DISPATCH(TT, DD)                                                                \
-    return v_lds ? launch_one<TT, DD, false, false, 1>(a, n_inst, st)                       \
+    return v_lds ? (a.carry_w ? launch_one<TT, DD, false, false, 1, true>(a, n_inst, st)    \
+                              : launch_one<TT, DD, false, false, 1>(a, n_inst, st))         \
+         : a.carry_w ? (vgram ? (multi ? launch_one<TT, DD, false, true, 2, true>(a, n_inst, st)     \
+                                       : launch_one<TT, DD, false, false, 2, true>(a, n_inst, st))   \
+                              : (multi ? launch_one<TT, DD, false, true, 0, true>(a, n_inst, st)     \
+                                       : launch_one<TT, DD, false, false, 0, true>(a, n_inst, st)))  \
          : vgram ? (multi ? launch_one<TT, DD, false, true, 2>(a, n_inst, st)               \
                           : launch_one<TT, DD, false, false, 2>(a, n_inst, st))             \
          : emit_g ? launch_one<TT, DD, true, true>(a, n_inst, st)                           \

@@ -171,7 +171,7 @@ __device__ __forceinline__ InstDesc make_desc(const SegGeo& g, int64_t seq, int 
     d.out_tok = seq * (g.n >> (r + 1)) + (start >> (r + 1)) + (int64_t)j * (g.b / 2);
     d.stream = 64ull * ((uint64_t)(g.seq_base + seq) * kSlots + (uint64_t)slot) + (uint64_t)r;
     d.ctr0 = (uint64_t)j * (uint64_t)g.b;
-    d.seq = (int32_t)seq; d.valid = 1; d.rvalue2 = slot >= kNumSlot0 ? ldexpf(1.f, 2 * (slot - kNumSlot0)) : 0.f; d.pad = 0;
+    d.seq = (int32_t)seq; d.valid = 1; d.rvalue2 = slot >= kNumSlot0 ? ldexpf(1.f, 2 * (slot - kNumSlot0)) : 0.f; d.region = 0;
     return d;
 }
 
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kPartThreads) void segments_kernel(const int32_t* s
             for (int j = tid; j < lnb[e]; j += kPartThreads)
                 if (lbase[e] + j < max_inst) desc[lbase[e] + j] = make_desc(g, seq, lslot[e], lstart[e], r, j);
         InstDesc none;
-        none.in_tok = none.out_tok = 0; none.stream = none.ctr0 = 0; none.seq = 0; none.valid = 0; none.rvalue2 = 0.f; none.pad = 0;
+        none.in_tok = none.out_tok = 0; none.stream = none.ctr0 = 0; none.seq = 0; none.valid = 0; none.rvalue2 = 0.f; none.region = 0;
         for (int64_t j = n_desc + tid; j < max_inst; j += kPartThreads) desc[j] = none;
         return;
     }
@@ -634,55 +634,22 @@ __global__ __launch_bounds__(64) void stream_route_kernel(StreamState s, const c
     const int r = lane & 31, kind = lane >> 5;
     if (r < Tn) {
         InstDesc ds;
-        ds.in_tok = ds.out_tok = 0; ds.stream = ds.ctr0 = 0; ds.seq = (int32_t)seq; ds.valid = 0; ds.rvalue2 = 0.f; ds.pad = 0;
+        ds.in_tok = ds.out_tok = 0; ds.stream = ds.ctr0 = 0; ds.seq = (int32_t)seq; ds.valid = 0; ds.rvalue2 = 0.f; ds.region = 0;
         const int carries = kind ? carries_d : carries_n;
         if (r < carries) {
             const int64_t region0 = kind ? seq * s.cap_d : (seq * R + reg) * s.cap_n;
             const int64_t first = (kind ? pos_d : pos_n) - (int64_t)r * half - b;
             const uint64_t slot = kind ? (uint64_t)kDenSlot : (uint64_t)(kNumSlot0 + i);
             ds.in_tok = region0 + first;
-            ds.out_tok = seq * half;
+            ds.out_tok = ds.in_tok;                              // in place (CompressArgs::carry_w)
             ds.stream = 64ull * ((uint64_t)(s.seq_base + seq) * kSlots + slot) + (uint64_t)r;
             ds.ctr0 = (uint64_t)(((kind ? blocks_d : blocks_n) >> r) - 1) * (uint64_t)b;
             ds.valid = 1;
             ds.rvalue2 = kind ? 0.f : ldexpf(1.f, 2 * i);
-            ds.pad = kind ? R : reg;
+            ds.region = kind ? R : reg;
         }
         s.desc[((int64_t)r * 2 + kind) * s.n_seq + seq] = ds;
     }
-}
-
-// After the halvings of round r: the survivors (rows, original indices) go back to the front of the block they came
-// from with weight 2^(r+1), the rest of the block is marked absent and the region shrinks by half a block.
-__global__ __launch_bounds__(256) void stream_fixup_kernel(StreamState s, int r) {
-    __shared__ int32_t so[512];
-    const int64_t seq = blockIdx.x;
-    const int kind = blockIdx.y, tid = threadIdx.x;
-    const InstDesc ds = s.desc[((int64_t)r * 2 + kind) * s.n_seq + seq];
-    if (!ds.valid) return;
-    const int half = s.b / 2, rb = s.row_bytes, slices = rb >> 4;
-    char* K = kind ? s.Kd : s.Kn;
-    float* w = kind ? s.wd : s.wn;
-    int32_t* o = kind ? s.od : s.on;
-    const int64_t frame = kind ? seq * s.cap_d : seq * (int64_t)s.regions * s.cap_n;      // first place of the sequence
-    const int64_t first = ds.in_tok;
-    const size_t t0 = (size_t)(kind * s.n_seq + seq) * half;
-    const int32_t* ti = s.tmpIdx + t0;
-    for (int t = tid; t < half; t += 256) so[t] = o[frame + ti[t]];
-    __syncthreads();
-    const float wnew = ldexpf(1.f, r + 1);
-    for (int t = tid; t < half; t += 256) {
-        o[first + t] = so[t];
-        w[first + t] = wnew;
-        w[first + half + t] = 0.f;
-    }
-    for (int t = tid; t < half * slices; t += 256) {
-        const int row = t / slices, sl = t - row * slices;
-        const size_t src = (t0 + row) * rb + sl * 16, dst = (size_t)(first + row) * rb + sl * 16;
-        *reinterpret_cast<uintx4*>(K + dst) = *reinterpret_cast<const uintx4*>(s.tmpK + src);
-        if (!kind) *reinterpret_cast<uintx4*>(s.Vn + dst) = *reinterpret_cast<const uintx4*>(s.tmpV + src);
-    }
-    if (tid == 0) s.cnt[seq * (s.regions + 1) + ds.pad] -= half;
 }
 
 }  // namespace
@@ -696,11 +663,6 @@ hipError_t stream_route(const StreamState& s, const void* k, const void* v, int6
     else if (s.dtype == BKV_F32 && s.d == 128) hipLaunchKernelGGL((stream_route_kernel<float, 128>), grid, block, 0, st, s, kp, vp, (int32_t)j);
     else if (s.dtype == BKV_F32 && s.d == 64) hipLaunchKernelGGL((stream_route_kernel<float, 64>), grid, block, 0, st, s, kp, vp, (int32_t)j);
     else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t stream_fixup(const StreamState& s, int round, hipStream_t st) {
-    hipLaunchKernelGGL(stream_fixup_kernel, dim3((unsigned)s.n_seq, 2u), dim3(256), 0, st, s, round);
     return hipGetLastError();
 }
 

@@ -137,6 +137,19 @@ def test_stream_state_equals_the_offline_sets(bk, synth, dtype, d, b, T, n, n_se
     print("launches per token: %.2f" % (launches / n))
 
 
+@pytest.mark.parametrize("dtype,d,b,T,n,n_seq", [
+    (torch.bfloat16, 64, 64, 1, 700, 3),          # fewer survivors than rows in flight
+    (torch.bfloat16, 128, 1024, 1, 6000, 1),      # several chunks: survivors from LDS and from the block itself
+    (torch.float32, 128, 1024, 1, 6000, 1),       # ... in two passes of the gather
+    (torch.float32, 128, 192, 2, 1500, 2),
+    (torch.bfloat16, 128, 64, 3, 767, 2),         # the last round is reached once or twice
+])
+def test_stream_carries_in_place(bk, synth, dtype, d, b, T, n, n_seq):
+    """Survivors are moved to the front of the block they come from while it is being read: the same state as offline,
+    where they go to buffers of their own."""
+    test_stream_state_equals_the_offline_sets(bk, synth, dtype, d, b, T, n, n_seq)
+
+
 def test_stream_equals_the_oracle_stream_with_erasures(bk, synth, oracle):
     """Free-running against the oracle's Alg. 1, token by token, with value norms that grow along the stream and an erase
     rule that drops the early buckets: the same live buckets, per bucket the same tokens and weights, the same
