@@ -314,15 +314,15 @@ def main():
     att_step_ms = sum(r[1] for r in att) / args.steps
     if att_step_ms > comp_step_ms + sum(r[1] for r in carry) / args.steps:
         # the streaming decode spends its time in the attend pass
-        traffic, source = _traffic(args.workload, "attend_partial_bytes_per_launch")
-        roofline = {"bound": "hbm", "kernel": "attend_partial_kernel (weighted softmax estimator over the compressed cache)",
+        traffic, source = _traffic(args.workload, "attend_kernel_bytes_per_launch")
+        roofline = {"bound": "hbm", "kernel": "attend_kernel (weighted softmax estimator over the compressed cache)",
                     "achieved": att_bytes / (att_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": att_bytes / (att_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
                     "avg_launch_ms": att_ms, "launches_per_step": len(att) / args.steps,
                     "algorithmic_bytes_per_launch": att_bytes}
     else:
         traffic, source = _traffic(args.workload, "compress_kernel_bytes_per_launch")
-        roofline = {"bound": "hbm", "kernel": "compress_kernel (Gram + kernel weights + walk + gather)",
+        roofline = {"bound": "hbm", "kernel": "compress_kernel or compress_pair_kernel, by the number of blocks (Gram + kernel weights + walk + gather)",
                     "achieved": comp_bytes / (comp_ms * 1e-3) / 1e9 if comp_ms > 0 else None, "peak": HBM_PEAK_GBS,
                     "unit": "GB/s",
                     "frac": comp_bytes / (comp_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if comp_ms > 0 else None,
