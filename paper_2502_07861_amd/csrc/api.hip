@@ -454,7 +454,7 @@ int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const
     const size_t need = bkv_attend_sets_workspace_bytes(p, n_seq, g, nq);
     if (!workspace || ws_bytes < need || !aligned16(workspace)) return BKV_EWORKSPACE;
     if (n_seq > 65535 || (int64_t)g * nq > 4 * 65535) return BKV_ESHAPE;
-    if (stride_n < count_n || stride_d < count_d || !Q || !out || !aligned16(Q) || !aligned16(out)) return BKV_EINVAL;
+    if (stride_n < count_n || (count_d > 0 && stride_d < count_d) || !Q || !out || !aligned16(Q) || !aligned16(out)) return BKV_EINVAL;
     if (count_d == 0)                                                            // both sets empty: zeros, lse = -inf
         return bkv_attend_kv(p, K_n, V_n, w_n, n_seq, 0, stride_n, Q, g, nq, out, lse_out, workspace, ws_bytes, hip_stream);
     if (count_n > 0 && (!K_n || !V_n || !w_n || !aligned16(K_n) || !aligned16(V_n))) return BKV_EINVAL;
@@ -642,6 +642,10 @@ size_t bkv_stream_bytes(const bkv_params* p, int64_t n_seq, int32_t regions, int
     s += 2 * align_up((size_t)n_seq * (R + 1) * 4, 256) + align_up((size_t)n_seq * R * 4, 256) + align_up((size_t)n_seq * 4, 256);
     s += 256;
     s += align_up(T * 2 * (size_t)n_seq * sizeof(bkv::InstDesc), 256);
+    // (room for the survivors of one halving per instance, two instances per sequence: the carries work in place and leave it
+    // unused; the size that callers plan with is part of the interface and stays)
+    const size_t half = (size_t)p->block / 2;
+    s += 2 * align_up(2 * (size_t)n_seq * half * rb, 256) + align_up(2 * (size_t)n_seq * half * 4, 256);
     return s;
 }
 
