@@ -174,9 +174,9 @@ int bkv_merge_reduce_protected(const bkv_params* p, const void* K, const void* V
  *               log of the estimator's denominator, so partial results over disjoint token ranges
  *               can be merged.  out = sum_i w_i e^{<k_i,q>/sqrt d} v_i / sum_i w_i e^{<k_i,q>/sqrt d}.
  * count == 0 writes zeros and lse = -inf.
- * Precision: logits, running maximum, numerator and denominator sums are fp32.  With BKV_BF16 every softmax weight
- * 2^(logit - max) is rounded to bf16 (to nearest even) before it multiplies its value row, and the denominator adds
- * the same rounded weights (relative error of a weight <= 2^-9, unbiased); with BKV_F32 the weights stay fp32.
+ * Precision: logits, softmax weights, running reference, numerator and denominator sums are fp32.  With BKV_BF16 a weight
+ * multiplies its bf16 value row as the sum of two bf16 numbers (17 bits: relative error <= 2^-17); the denominator adds the
+ * fp32 weights.
  * Limits: n_seq <= 65535 and g * nq <= 262140 (else BKV_ESHAPE).                                    */
 size_t bkv_attend_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t count, int32_t g,
                                   int32_t nq);   /* an upper bound valid for any smaller count too */

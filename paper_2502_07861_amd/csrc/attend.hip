@@ -277,32 +277,54 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     }
     floatx4 s[NQT][NT];
     auto qk = [&]() {
+        if constexpr (B16) {
 #pragma unroll
-        for (int t = 0; t < NQT; ++t)
+            for (int t = 0; t < NQT; ++t)
 #pragma unroll
-            for (int kt = 0; kt < NT; ++kt) s[t][kt] = zero4;
+                for (int kt = 0; kt < NT; ++kt) s[t][kt] = zero4;
 #pragma unroll
-        for (int c = 0; c < KC; ++c)
+            for (int c = 0; c < KC; ++c)
 #pragma unroll
-            for (int kt = 0; kt < NT; ++kt)
+                for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-                for (int t = 0; t < NQT; ++t) {
-                    if constexpr (B16) {
+                    for (int t = 0; t < NQT; ++t)
                         s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[kt][c]), __builtin_bit_cast(bf16x8_t, qf[t][c]),
                                                                            s[t][kt], 0, 0, 0);
-                    } else {
+        } else {
+            // Four columns per matrix instruction, each from zero, added in a tree: one chain over the row rounds d times at
+            // the size of the whole sum, 1.3e-6 off the 64-bit output (d = 128, 8321 tokens), the tree 5.0e-7.
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const unsigned int ka = kf[kt][c][i], qa = qf[t][c][i];
-                            s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka), __uint_as_float(qa), s[t][kt], 0, 0, 0);
-                        }
+            for (int t = 0; t < NQT; ++t) {
+                floatx4 level[4];
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    floatx4 y[4];
+                    asm volatile("" : "+v"(qf[t][c]));        // (registers: a piece starts when the one before it is summed)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const unsigned int ka = kf[0][c][i], qa = qf[t][c][i];
+                        y[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka), __uint_as_float(qa), zero4, 0, 0, 0);
                     }
+                    floatx4 x = (y[0] + y[1]) + (y[2] + y[3]);
+                    int l = 0;
+#pragma unroll
+                    for (int k = c; k & 1; k >>= 1) x = level[l++] + x;
+                    asm volatile("" : "+v"(x));
+                    level[l] = x;
                 }
+                s[t][0] = level[KC == 8 ? 3 : 2];
+            }
+        }
     };
-    // logits -> weights 2^(logit - m), rounded to bf16 (to nearest even) on the bf16 path; the denominator adds the same
-    // rounded weights.  The reference m moves only when a logit passes it by more than kSlack (then to the largest one, for
-    // all lanes of the query): the weights are floating-point numbers, so a reference that is 2^6 too small costs nothing.
-    bf16x8_t pb[NQT];
+    // logits -> weights 2^(logit - m), the difference rounded once (a logit rounded for itself is off by 2^-24 of its size,
+    // which is what the weight is off by).  The denominator adds the fp32 weights.  On the bf16 path the values meet them as
+    // two bf16 numbers each, the upper bits and what they leave (17 bits; one number each is off by up to 2^-9, and a peaked
+    // softmax shows it: 1.96e-3 instead of 1.66e-3 off the 64-bit result over 8321 tokens, where rounding the output makes
+    // 1.65e-3; the second product costs 716 -> 718 us with 1024 sequences, 27.8 -> 28.7 with 256 queries).  The second
+    // number of a weight that has one is never 0: an infinite value stays infinite.
+    // The reference m moves only when a logit passes it by more than kSlack (then to the largest one, for all lanes of the
+    // query): the weights are floating-point numbers, so a reference that is 2^6 too small costs nothing.
+    bf16x8_t pb[NQT], pl[NQT];
     auto softmax = [&](const float (&w)[VR]) {
         float bias[VR];
         bool dead = false;
@@ -326,7 +348,6 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
             for (int x = 0; x < VR; ++x) {
                 const float lg = fmaf(s[t][x >> 2][x & 3], a.scale_log2, bias[x]);
-                s[t][x >> 2][x & 3] = lg;
                 mx[t] = fmaxf(mx[t], lg);
             }
             grew |= mx[t] > m[t] + kSlack;
@@ -344,21 +365,23 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
                 for (int e = 0; e < EPN; ++e) o[t][e] *= sc;
             }
         }
-        const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
         for (int t = 0; t < NQT; ++t) {
 #pragma unroll
-            for (int x = 0; x < VR; ++x) s[t][x >> 2][x & 3] = fast_exp2(s[t][x >> 2][x & 3] - m[t]);
+            for (int x = 0; x < VR; ++x) s[t][x >> 2][x & 3] = fast_exp2(fmaf(s[t][x >> 2][x & 3], a.scale_log2, bias[x] - m[t]));
             if constexpr (B16) {
-                uintx4 pk;
+                uintx4 hi, lo;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const floatx2 pf = {s[t][i >> 1][2 * (i & 1)], s[t][i >> 1][2 * (i & 1) + 1]};
-                    const bf16x2_t pp = __builtin_convertvector(pf, bf16x2_t);
-                    l[t] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l[t], false);
-                    pk[i] = __builtin_bit_cast(unsigned int, pp);
+                    const unsigned int b0 = __float_as_uint(pf[0]), b1 = __float_as_uint(pf[1]);
+                    hi[i] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    const floatx2 rest = {fmaf(pf[0], 0x1p-40f, pf[0] - __uint_as_float(b0 & 0xffff0000u)),
+                                          fmaf(pf[1], 0x1p-40f, pf[1] - __uint_as_float(b1 & 0xffff0000u))};
+                    lo[i] = __builtin_bit_cast(unsigned int, __builtin_convertvector(rest, bf16x2_t));
+                    l[t] += pf[0] + pf[1];
                 }
-                pb[t] = __builtin_bit_cast(bf16x8_t, pk);
+                pb[t] = __builtin_bit_cast(bf16x8_t, hi); pl[t] = __builtin_bit_cast(bf16x8_t, lo);
             } else {
 #pragma unroll
                 for (int x = 0; x < VR; ++x) l[t] += s[t][x >> 2][x & 3];
@@ -374,8 +397,10 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
                 for (int i = 0; i < 4; ++i)       // element e of the rows of keys 2i, 2i + 1 of this lane
                     f[i] = __builtin_amdgcn_perm(vf[2 * i + 1][e >> 1], vf[2 * i][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
 #pragma unroll
-                for (int t = 0; t < NQT; ++t)
+                for (int t = 0; t < NQT; ++t) {
                     o[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f), pb[t], o[t][e], 0, 0, 0);
+                    o[t][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f), pl[t], o[t][e], 0, 0, 0);
+                }
             } else {
 #pragma unroll
                 for (int t = 0; t < NQT; ++t)

@@ -715,6 +715,45 @@ def test_attend_bf16_weight_rounding_is_bounded(bk, synth):
     assert np.abs(dl).max() <= 1e-3 and abs(dl.mean()) <= 3e-4
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("d,n_seq,count,g,nq", [(128, 8, 4357, 4, 4), (128, 4, 4096, 4, 16), (128, 1, 65536, 8, 2), (64, 8, 4357, 4, 4),
+                                                (64, 2, 30000, 8, 5)])
+def test_attend_error_against_64_bits(bk, synth, dtype, d, n_seq, count, g, nq):
+    """What the attend may lose against a 64-bit evaluation of the same inputs.
+
+    fp32: a dot product of d terms whose partial sums stay small (chains of four, then a tree), one rounding of the exponent's
+    argument, one unit of exp2, the sums over the tokens: a few units of 2^-23 together, 7 allowed.  (One chain over the row
+    rounds d times at the size of the whole sum; that alone is 8 to 19 units here.)
+    bf16: weights carried to 2^-17, fp32 sums, and one rounding of the output to bf16.  So the output is the 64-bit result
+    rounded to bf16, except where that lies within 2^-17 times a few of the middle between two bf16 numbers (spacing 2^-7 to 2^-8): at most
+    2 % of the elements.  (Weights rounded to bf16 change a third of them.)  The logarithm of the denominator is fp32 all the way:
+    a few units of 2^-24 of a logit of up to 64."""
+    t = synth.gqa_layer_bf16(n_seq=n_seq, n=count, d=d, g=g, nq=nq, seed=811, device="cuda", dtype=dtype)
+    K, V, Q = t["K"], t["V"], t["Q"]
+    w = torch.full((n_seq, count), 4.0, device="cuda")
+    w[:, int(0.95 * count):] = 2.0
+    w[:, int(0.98 * count):] = 1.0
+    out, lse = bk.attend_kv(bk.make_params(d, 128, 2, dtype, log_c=0.0), K, V, w, Q)
+    q = Q.double().reshape(n_seq, g * nq, d)
+    ref = torch.empty_like(q)
+    ref_lse = torch.empty(n_seq, g * nq, device="cuda", dtype=torch.float64)
+    for s in range(n_seq):
+        logit = torch.matmul(q[s], K[s].double().t().contiguous()) / math.sqrt(d) + torch.log(w[s].double())
+        ref_lse[s] = torch.logsumexp(logit, -1)
+        ref[s] = torch.matmul(torch.exp(logit - ref_lse[s][:, None]), V[s].double())
+    out, lse = out.reshape(n_seq, g * nq, d), lse.reshape(n_seq, g * nq).double()
+    lse_err = float((lse - ref_lse).abs().max())
+    if dtype == torch.float32:
+        err = float((out.double() - ref).norm() / ref.norm())
+        print("rel-L2 %.2e = %.1f units, lse off by %.1e" % (err, err * 2 ** 23, lse_err))
+        assert err <= 7 * 2.0 ** -23
+    else:
+        off = float((out != ref.to(torch.bfloat16)).double().mean())
+        print("differs from the rounded result in %.2f %% of the elements, lse off by %.1e" % (100 * off, lse_err))
+        assert off <= 0.02
+    assert lse_err <= 8 * 2.0 ** -24 * 64
+
+
 def _two_set_reference(K, V, w, Kd, wd, Q):
     """Float64: sum over (K, V, w) divided by the normaliser of (Kd, wd); returns (out, ln of the normaliser)."""
     d = K.shape[-1]
