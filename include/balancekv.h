@@ -177,6 +177,8 @@ int bkv_merge_reduce_protected(const bkv_params* p, const void* K, const void* V
  * Precision: logits, softmax weights, running reference, numerator and denominator sums are fp32.  With BKV_BF16 a weight
  * multiplies its bf16 value row as the sum of two bf16 numbers (17 bits: relative error <= 2^-17); the denominator adds the
  * fp32 weights.
+ * The workspace may hold anything and nothing of it is kept for a later call.  Calls that overlap in time must not share one;
+ * if they do, only their own results suffer.
  * Limits: n_seq <= 65535 and g * nq <= 262140 (else BKV_ESHAPE).                                    */
 size_t bkv_attend_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t count, int32_t g,
                                   int32_t nq);   /* an upper bound valid for any smaller count too */
@@ -193,7 +195,8 @@ int bkv_attend_kv(const bkv_params* p, const void* K_c, const void* V_c, const f
  * BKV_EWORKSPACE (with today's launch plan, which cuts a range into fewer splits where their partials would not fit, every
  * shape that bkv_attend_kv accepts fits).  All calls on one GPU share the array: calls that
  * overlap in time on the same GPU (different streams, different threads) race; calls on one stream do not.  The
- * array keeps the last call's partials; every launch writes all partials it later reads, nothing needs clearing.  */
+ * array keeps the last call's partials; every launch writes all partials it later reads, nothing needs clearing, and a
+ * race leaves nothing behind that a later call could trip over.  */
 size_t bkv_attend_kv_static_max_bytes(void);
 int bkv_attend_kv_static(const bkv_params* p, const void* K_c, const void* V_c, const float* w,
                          int64_t n_seq, int64_t count, int64_t stride_tokens, const void* Q, int32_t g,

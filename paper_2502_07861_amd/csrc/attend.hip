@@ -16,7 +16,10 @@
 // 704 us = 6.25 TB/s); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
 // tokens x 256 queries: 23 us; 113 us on the vector units, four queries per pass); short ranges the sum of two memory
 // round trips and the hand-over between workgroups (8 x 4357 tokens: 11 us in one launch; 14 us as pass + merge launches).
+#include <unistd.h>
+
 #include <atomic>
+#include <chrono>
 
 #include "bkv_device.h"
 #include "bkv_host.h"
@@ -33,30 +36,22 @@ typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------------------------------------------------
-// "Am I the last of `total` workgroups to get here?", without anybody having cleared the counter before: the workspace is
-// the caller's and arrives with any content.  word[0] is (48-bit mark | 16-bit count); while the mark is there one
-// fetch-add per workgroup decides.  A word without it (first use of this memory) sends all workgroups of the launch to
-// word[1], a counter labelled with the launch's own number by compare-and-swap (at most `total` failed attempts each,
-// because every failure is another workgroup's success).  The last one leaves word[0] marked and zero for the next
-// launch.  Calls that share a workspace must not overlap, as before; replays of a captured launch find word[0] as the
-// previous replay left it.
-constexpr unsigned long long kMark = 0x5bd1e995a7c3ull << 16;
-__device__ __forceinline__ bool arrive_last(unsigned long long* word, unsigned int total, unsigned long long label) {
-    const unsigned long long old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned int before;
-    if ((old & ~0xffffull) == kMark) before = (unsigned int)(old & 0xffffull);
-    else {
-        unsigned long long cur = __hip_atomic_load(word + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (;;) {
-            before = (cur & ~0xffffull) == label ? (unsigned int)(cur & 0xffffull) : 0u;
-            if (__hip_atomic_compare_exchange_strong(word + 1, &cur, label | (before + 1u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) break;
-        }
-    }
-    if (before + 1u != total) return false;
-    __hip_atomic_store(word + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(word, kMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+// "Is everybody's partial there?", without anybody having cleared anything before: the workspace is the caller's, arrives with
+// any content, and nothing that a call leaves in it means anything to a later one.  Every workgroup stores the launch's number,
+// which no other launch of the process has, into a word of its own behind its partial, waits until that has arrived, and then
+// reads the words of its group.  The workgroup whose word arrives last finds them all and merges.  (Workgroups that arrive
+// together may all find them: they merge the same partials in the same order and store the same bytes.)  A call that overlaps
+// another one on the same memory may find its words overwritten; the next call does not look at them.  Replays of a captured
+// launch would repeat its number, so a captured call merges in a launch of its own.
+// Called by one wavefront after the workgroup's partial has arrived.
+__device__ __forceinline__ bool all_arrived(unsigned long long* words, unsigned int mine, unsigned int total, unsigned long long label) {
+    const unsigned int lane = threadIdx.x & 63u;
+    if (lane == 0) __hip_atomic_store(words + mine, label, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool there = true;
+    for (unsigned int w = lane; w < total; w += 64u)
+        there &= __hip_atomic_load(words + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == label;
+    return __ballot(!there) == 0ull;
 }
 
 // Partial rows travel between workgroups (other XCDs, other L2s) past the caches, two floats at a time: device-scope
@@ -513,7 +508,10 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     if (ns == 1 || !a.fused) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wavefront's share of the partial has reached memory ...
     __syncthreads();                                            // ... and so has everybody else's
-    if (tid == 0) last_flag = arrive_last(a.arrivals + 2 * grp, ns, a.label) ? 1 : 0;
+    if (wave == 0) {
+        const bool last = all_arrived(a.arrivals + grp * ns, (unsigned int)split, ns, a.label);
+        if (lane == 0) last_flag = last ? 1 : 0;
+    }
     __syncthreads();
     if (!last_flag) return;
     merge_rows<T, D, W * 64>(part, sstride, nqv, a.ns[0], a.ns[1], a.out, a.lse_out, row0, lds);
@@ -536,7 +534,7 @@ __global__ __launch_bounds__(kMergeThreads) void attend_merge_kernel(const Atten
 struct AttendPlan {
     int nqt, waves, n_qg, rows;   // query tiles and wavefronts per workgroup, query groups, rows of a partial
     int ns[2], gps[2];            // splits and key groups per split of each set
-    bool fused;                   // the last workgroup of a query group merges
+    bool fused;                   // the last workgroup of a query group merges (never in a captured launch)
     size_t arrive_bytes, partial_bytes;
 };
 
@@ -572,7 +570,7 @@ static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, in
     }
     const int ns = p.ns[0] + p.ns[1];
     p.partial_bytes = ns > 1 ? (size_t)wgs * ns * row_bytes : 0;
-    p.arrive_bytes = ns > 1 ? ((size_t)wgs * 16 + 255) / 256 * 256 : 0;
+    p.arrive_bytes = ns > 1 ? ((size_t)wgs * ns * 8 + 255) / 256 * 256 : 0;
     // one workgroup reads ns * rows partial rows at the end: up to 128 KB of them that is faster than one more launch (by
     // 2 us with 18 splits of 4 rows, equal with 4 splits of 32)
     p.fused = ns > 1 && (size_t)ns * row_bytes <= (size_t)128 * 1024;
@@ -586,7 +584,7 @@ size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q, int sets) {
     const int64_t wg_target = kTargetWaves / (n_q > 16 ? 8 : 4);
     const int64_t per = wgs > 0 ? (wg_target + wgs - 1) / wgs + sets : 1;
     const size_t row_bytes = (size_t)(n_q < rq ? n_q : rq) * (d + kRowPad) * sizeof(float);
-    return (size_t)(wgs * per) * row_bytes + (size_t)wgs * 16 + 512;
+    return (size_t)(wgs * per) * (row_bytes + 8) + 512;
 }
 
 size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q, size_t max_bytes) {
@@ -633,20 +631,34 @@ hipError_t attend_static_scratch(void** ptr) {
     return hipSuccess;
 }
 
+// A number that no other launch of this process has (mix64 is one to one), and other processes' launches next to never: memory
+// that another one has left must not look arrived.
+static unsigned long long launch_number() {
+    static const unsigned long long first = mix64((unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()) ^
+                                            mix64((unsigned long long)getpid());
+    static std::atomic<unsigned long long> launches{0};
+    return mix64(first + launches.fetch_add(1, std::memory_order_relaxed));
+}
+
 hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t max_bytes, hipStream_t st) {
     if (a.n_seq <= 0 || a.n_q <= 0) return hipSuccess;
     if (a.n_seq > 65535) return hipErrorInvalidValue;
-    const AttendPlan p = attend_plan(d, dtype == BKV_BF16 ? 2 : 4, a.n_seq, a.set[0].count, a.set[1].count, a.n_q, max_bytes);
+    AttendPlan p = attend_plan(d, dtype == BKV_BF16 ? 2 : 4, a.n_seq, a.set[0].count, a.set[1].count, a.n_q, max_bytes);
     if (p.ns[0] + p.ns[1] < 1) return hipErrorInvalidValue;
     a.n_qg = p.n_qg; a.rows = p.rows;
     for (int k = 0; k < 2; ++k) { a.ns[k] = p.ns[k]; a.set[k].groups_per_split = p.gps[k]; }
+    if (p.fused) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+            (void)hipGetLastError();              // (a launch says for itself what is wrong with the stream)
+            p.fused = false;
+        } else if (capture != hipStreamCaptureStatusNone) p.fused = false;
+    }
     a.fused = p.fused;
     a.by_xcd = p.n_qg > 1 && a.n_seq >= 8;
     a.arrivals = (unsigned long long*)workspace;
     a.partial = (float*)((char*)workspace + p.arrive_bytes);
-    // every launch's own number, spread over 48 bits (never 0)
-    static std::atomic<unsigned long long> launches{1};
-    a.label = (mix64(launches.fetch_add(1, std::memory_order_relaxed)) | 1ull) << 16;
+    a.label = launch_number();
     if (dtype == BKV_BF16 && d == 128) return launch_attend_t<__bf16, 128>(a, p, st);
     if (dtype == BKV_BF16 && d == 64) return launch_attend_t<__bf16, 64>(a, p, st);
     if (dtype == BKV_F32 && d == 128) return launch_attend_t<float, 128>(a, p, st);

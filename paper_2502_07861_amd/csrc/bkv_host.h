@@ -184,7 +184,7 @@ struct AttendArgs {
     float scale_log2;         // log2(e)/sqrt(d)
     // set by the launcher
     float* partial;           // workspace: [n_seq, n_qg, splits, rows, d + pad]
-    unsigned long long* arrivals;      // workspace: two words per (sequence, query group)
+    unsigned long long* arrivals;      // workspace: a word per partial
     unsigned long long label; // this launch's number
     int32_t n_qg, rows, ns[2], fused, by_xcd;
 };

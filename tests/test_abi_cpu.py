@@ -178,3 +178,48 @@ def test_ablation_yardstick_is_eq1_and_recipe_norms(oracle):
     assert 14.5 < np.linalg.norm(kc, axis=2).mean() < 16.5
     assert 3.1 < np.linalg.norm(Vd, axis=2).mean() < 3.6 and 14.5 < np.linalg.norm(Qd, axis=3).mean() < 15.1
     assert int(t["member"].max()) == 31
+
+
+def test_attend_hand_over_model():
+    """The attend pass hands its partials to the workgroup that finds the launch's number in every word of its group: a model of
+    the protocol over all interleavings of three workgroups and a second launch that overlaps on the same words.  Whatever the
+    words hold at first, and whatever a launch before left there (an overlap included), a launch that runs alone merges at
+    least once, and only after all partials are stored."""
+    def explore(words, launches):
+        """All outcomes of these launches (number, workgroups) running together: (final words, merges by launch)."""
+        start = (tuple(words), tuple((0, 0, True) for _, n in launches for _ in range(n)), frozenset())
+        who = [(num, w, n) for num, n in launches for w in range(n)]
+        seen, todo, done = set(), [start], set()
+        while todo:
+            state = todo.pop()
+            if state in seen:
+                continue
+            seen.add(state)
+            mem, procs, early = state
+            if all(pc == 2 for pc, _, _ in procs):
+                done.add((mem, tuple(ok for _, _, ok in procs), early))
+                continue
+            for i, (pc, at, ok) in enumerate(procs):
+                num, w, n = who[i]
+                if pc == 0:                                   # the partial is in memory: store the number
+                    nxt, m = (1, 0, True), mem[:w] + (num,) + mem[w + 1:]
+                elif pc == 1:                                 # read the words of the group, one at a time
+                    ok2 = ok and mem[at] == num
+                    nxt, m = ((2, 0, ok2) if at + 1 == n else (1, at + 1, ok2)), mem
+                else:
+                    continue
+                e = early
+                if nxt[0] == 2 and nxt[2] and any(procs[k][0] == 0 for k in range(len(procs)) if who[k][0] == num):
+                    e = early | {num}                         # a merge while one of its own partials is missing
+                todo.append((m, procs[:i] + (nxt,) + procs[i + 1:], e))
+        return done
+
+    alone = lambda words, num: explore(words, [(num, 3)])
+    for words in ((0, 0, 0), (7, 7, 7), (7, 8, 9)):
+        for mem, merged, early in alone(words, 1):
+            assert any(merged) and not early and mem == (1, 1, 1)
+    left = {mem for mem, _, early in explore((0, 0, 0), [(1, 3), (2, 2)])}
+    assert len(left) > 1                                      # overlapped launches leave several kinds of leftovers
+    for words in left:
+        for mem, merged, early in alone(words, 3):
+            assert any(merged) and not early

@@ -797,6 +797,53 @@ def test_attend_edges(bk, dtype, d, n_seq, count, g, nq):
         np.testing.assert_allclose(lse.cpu().numpy(), ref2_lse.numpy(), atol=1e-3 if dtype == torch.bfloat16 else 1e-5, rtol=1e-5)
 
 
+@pytest.mark.parametrize("n_seq,count,g,nq", [(8, 4357, 4, 1), (3, 2000, 1, 1), (8, 4096, 4, 16)])
+def test_attend_does_not_depend_on_what_the_workspace_holds(bk, n_seq, count, g, nq):
+    """A call gives the same bytes on a fresh workspace and on one that holds what an earlier call left there, shifted by anything
+    (what two overlapping calls can leave), and on one that replays of a captured call share with eager calls."""
+    d = 128
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(torch.bfloat16)
+    p = bk.make_params(d, 64, 1, torch.bfloat16, log_c=0.0)
+    sets = [(rand(n_seq, count, d), rand(n_seq, count, d), rand(n_seq, g, nq, d)) for _ in range(2)]
+    w = torch.ones(n_seq, count, device="cuda")
+    need = int(bk.lib().bkv_attend_workspace_bytes(C.byref(p), n_seq, count, g, nq))
+    fresh = lambda: torch.zeros(need, dtype=torch.uint8, device="cuda")
+    want = [bk.attend_kv(p, K, V, w, Q, workspace=fresh()) for K, V, Q in sets]
+    ws = fresh()
+    K, V, Q = sets[0]
+    bk.attend_kv(p, K, V, w, Q, workspace=ws)
+    left = ws.clone()
+    words = left.view(torch.int64)[: min(left.numel() // 8, 8192)]           # (counters or labels in front of the partials)
+    for shift in (0, 1, 2, 3, 5, 16, 17, 33, -1):
+        ws.copy_(left)
+        ws.view(torch.int64)[: words.numel()] = words + shift
+        for k in (1, 0, 1):                                                   # other inputs than the partials there are of
+            K, V, Q = sets[k]
+            out, lse = bk.attend_kv(p, K, V, w, Q, workspace=ws)
+            assert torch.equal(out, want[k][0]) and torch.equal(lse, want[k][1]), "shift %d" % shift
+    # a captured call on the same workspace: its replays repeat whatever the launch was given
+    K1 = sets[0][0].clone()
+    out, lse = torch.empty_like(want[0][0]), torch.empty_like(want[0][1])
+    bk.attend_kv(p, K1, sets[0][1], w, sets[0][2], workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out, lse = bk.attend_kv(p, K1, sets[0][1], w, sets[0][2], workspace=ws)
+    ref1 = bk.attend_kv(p, sets[1][0], sets[0][1], w, sets[0][2], workspace=fresh())
+    for k, shift in ((0, 0), (1, 1), (0, 2), (1, 5), (0, 0)):
+        K1.copy_(sets[k][0])
+        ws.view(torch.int64)[: words.numel()] += shift
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = ref1 if k else want[0]
+        tol = dict(rtol=0, atol=0.01 * float(ref[0].float().abs().max()))     # (other order of the splits' sums: a bf16 unit, 2^-8, here and there)
+        torch.testing.assert_close(out.float(), ref[0].float(), **tol)
+        torch.testing.assert_close(lse, ref[1], rtol=0, atol=1e-4)
+        K, V, Q = sets[1]
+        got = bk.attend_kv(p, K, V, w, Q, workspace=ws)
+        assert torch.equal(got[0], want[1][0])
+
+
 def test_attend_empty_cache(bk, synth):
     t = synth.gqa_layer_bf16(n_seq=2, n=64, d=64, g=2, nq=1, seed=1, device="cpu")
     K, V, Q = t["K"].cuda(), t["V"].cuda(), t["Q"].cuda()
