@@ -143,7 +143,8 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
         if (c < C) {
             float f = L > 0.f ? 1.f / L : 0.f;
             if (ns1 > 0) {
-                f = L > 0.f && Ld > 0.f ? fast_exp2(M - Md) / Ld : 0.f;
+                // a denominator of 0 or NaN (no mass, a broken row) gives infinities, not zeros that look like a result
+                f = L > 0.f ? (Ld > 0.f ? fast_exp2(M - Md) / Ld : INFINITY) : 0.f;
                 M = Md; L = Ld;
             }
             store4<T>(out, (row0 + q) * D + col, acc * f);

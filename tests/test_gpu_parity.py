@@ -844,6 +844,49 @@ def test_attend_does_not_depend_on_what_the_workspace_holds(bk, n_seq, count, g,
         assert torch.equal(got[0], want[1][0])
 
 
+@pytest.mark.parametrize("count", [40, 4000])                                     # one split and several
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float32, 64)])
+def test_attend_shows_what_is_not_finite(bk, dtype, d, count):
+    """A NaN in a key, an infinite value and a denominator set without mass are visible in the outputs of their sequence and in no
+    other; rows of absent tokens may hold any key."""
+    n_seq, g = 3, 2
+    gen = torch.Generator(device="cuda").manual_seed(count)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(dtype)
+    p = bk.make_params(d, 64, 1, dtype, log_c=0.0)
+    K, V, Kd, Q = rand(n_seq, count, d), rand(n_seq, count, d), rand(n_seq, count, d), 0.1 * rand(n_seq, g, 1, d)
+    w, wd = torch.ones(n_seq, count, device="cuda"), torch.ones(n_seq, count, device="cuda")
+    at = count - 3
+    bad = lambda x, i, v: x.clone().index_put_((torch.tensor(1), torch.tensor(at), torch.tensor(i)), torch.tensor(v, dtype=dtype, device="cuda"))
+    ok = [0, 2]
+    base, _ = bk.attend_kv(p, K, V, w, Q)
+    base2, _ = bk.attend_sets(p, (K, V, w), (Kd, wd), Q)
+    assert torch.isfinite(base.float()).all() and torch.isfinite(base2.float()).all()
+    # a NaN in a key of the only set, of the numerator set, of the denominator set
+    out, _ = bk.attend_kv(p, bad(K, 5, float("nan")), V, w, Q)
+    assert torch.equal(out[ok], base[ok]) and torch.isnan(out[1].float()).all()
+    out, _ = bk.attend_sets(p, (bad(K, 5, float("nan")), V, w), (Kd, wd), Q)
+    assert torch.equal(out[ok], base2[ok]) and torch.isnan(out[1].float()).all()
+    out, lse = bk.attend_sets(p, (K, V, w), (bad(Kd, 5, float("nan")), wd), Q)
+    assert torch.equal(out[ok], base2[ok]) and not torch.isfinite(out[1].float()).any() and not torch.isfinite(lse[1]).any()
+    # a denominator set without mass
+    none = wd.clone()
+    none[1] = 0.0
+    out, lse = bk.attend_sets(p, (K, V, w), (Kd, none), Q)
+    assert torch.equal(out[ok], base2[ok]) and not torch.isfinite(out[1].float()).any() and (lse[1] == -math.inf).all()
+    # an infinite value: its column is infinite, the others are what they were
+    for sign in (1.0, -1.0):
+        for call, ref in ((lambda v: bk.attend_kv(p, K, v, w, Q)[0], base), (lambda v: bk.attend_sets(p, (K, v, w), (Kd, wd), Q)[0], base2)):
+            out = call(bad(V, 7, sign * math.inf))
+            assert (out[1, ..., 7].float() == sign * math.inf).all()
+            keep = torch.arange(d, device="cuda") != 7
+            assert torch.equal(out[..., keep], ref[..., keep]) and torch.equal(out[ok], ref[ok])
+    # an absent token's key may hold anything
+    gone = w.clone()
+    gone[1, at] = 0.0
+    ref, _ = bk.attend_kv(p, K, V, gone, Q)
+    assert torch.equal(bk.attend_kv(p, bad(K, 5, float("nan")), V, gone, Q)[0], ref)
+
+
 def test_attend_empty_cache(bk, synth):
     t = synth.gqa_layer_bf16(n_seq=2, n=64, d=64, g=2, nq=1, seed=1, device="cpu")
     K, V, Q = t["K"].cuda(), t["V"].cuda(), t["Q"].cuda()
