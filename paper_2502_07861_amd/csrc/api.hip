@@ -342,7 +342,7 @@ static int attend_kv_impl(const bkv_params* p, const void* K_c, const void* V_c,
     a.set[0].stride = stride_tokens; a.set[0].count = count;
     a.Q = (const char*)Q; a.out = (char*)out; a.lse_out = lse_out; a.n_seq = n_seq; a.n_q = n_q;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
-    e = bkv::launch_attend(p->dtype, p->d, a, workspace, limit, st);
+    e = bkv::launch_attend(p->dtype, p->d, a, workspace, ws_bytes, limit, st);
     return e == hipSuccess ? BKV_OK : hip_fail(e);
 }
 
@@ -466,7 +466,7 @@ int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const
     a.set[1].K = (const char*)K_d; a.set[1].w = w_d; a.set[1].stride = stride_d; a.set[1].count = count_d;
     a.Q = (const char*)Q; a.out = (char*)out; a.lse_out = lse_out; a.n_seq = n_seq; a.n_q = g * nq;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
-    const hipError_t e = bkv::launch_attend(p->dtype, p->d, a, workspace, bkv::kAttendPartialBytes, (hipStream_t)hip_stream);
+    const hipError_t e = bkv::launch_attend(p->dtype, p->d, a, workspace, ws_bytes, bkv::kAttendPartialBytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? BKV_OK : hip_fail(e);
 }
 

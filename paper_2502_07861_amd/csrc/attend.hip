@@ -578,14 +578,16 @@ static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, in
     return p;
 }
 
-// Upper bounds for any token count: a set is cut into at most ceil(kTargetWaves / (wavefronts per workgroup * wgs)) splits.
+// Upper bounds for any token count.  One set is cut into at most S = ceil(kTargetWaves / (wavefronts per workgroup * wgs))
+// splits, two sets together into at most S + 1 (each rounds up once); one split in all needs no memory.
 size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q, int sets) {
     const int rq = n_q > 16 ? 32 : 16;
     const int64_t wgs = n_seq * ((n_q + rq - 1) / rq);
     const int64_t wg_target = kTargetWaves / (n_q > 16 ? 8 : 4);
-    const int64_t per = wgs > 0 ? (wg_target + wgs - 1) / wgs + sets : 1;
+    int64_t splits = wgs > 0 ? (wg_target + wgs - 1) / wgs + sets - 1 : 0;
+    if (splits == 1) splits = 0;
     const size_t row_bytes = (size_t)(n_q < rq ? n_q : rq) * (d + kRowPad) * sizeof(float);
-    return (size_t)(wgs * per) * (row_bytes + 8) + 512;
+    return (size_t)(wgs * splits) * (row_bytes + 8) + 512;
 }
 
 size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int n_q, size_t max_bytes) {
@@ -641,11 +643,11 @@ static unsigned long long launch_number() {
     return mix64(first + launches.fetch_add(1, std::memory_order_relaxed));
 }
 
-hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t max_bytes, hipStream_t st) {
+hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t ws_bytes, size_t max_bytes, hipStream_t st) {
     if (a.n_seq <= 0 || a.n_q <= 0) return hipSuccess;
     if (a.n_seq > 65535) return hipErrorInvalidValue;
     AttendPlan p = attend_plan(d, dtype == BKV_BF16 ? 2 : 4, a.n_seq, a.set[0].count, a.set[1].count, a.n_q, max_bytes);
-    if (p.ns[0] + p.ns[1] < 1) return hipErrorInvalidValue;
+    if (p.ns[0] + p.ns[1] < 1 || p.partial_bytes + p.arrive_bytes > ws_bytes) return hipErrorInvalidValue;
     a.n_qg = p.n_qg; a.rows = p.rows;
     for (int k = 0; k < 2; ++k) { a.ns[k] = p.ns[k]; a.set[k].groups_per_split = p.gps[k]; }
     if (p.fused) {

@@ -191,7 +191,7 @@ struct AttendArgs {
 // Workspace bound for any count; `sets`: 1, or 2 when numerator and denominator run over sets of their own.
 size_t attend_workspace_bytes(int d, int64_t n_seq, int n_q, int sets = 1);
 // max_bytes: what the partial rows may take (fewer splits where they would take more)
-hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t max_bytes, hipStream_t st);
+hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t ws_bytes, size_t max_bytes, hipStream_t st);
 // the entry point without allocations: what a launch of this shape writes into the scratch buffer, and the
 // library's own buffer for it (a file-scope device array; address of the current device's copy)
 constexpr size_t kAttendStaticScratchBytes = 2304 * 1024;

@@ -223,3 +223,17 @@ def test_attend_hand_over_model():
     for words in left:
         for mem, merged, early in alone(words, 3):
             assert any(merged) and not early
+
+
+def test_attend_workspace_holds_partials_only_where_a_range_is_split(bk):
+    """From 512 query groups on (16 queries each, 256 of 32 queries) one set is never split and needs no partials; two sets need one
+    row of d + 4 floats and a word per set and query."""
+    L = bk.lib()
+    p = bk.make_params(128, 64, 1, bk.BKV_BF16, log_c=0.0)
+    one = lambda n_seq, nq, count=8321: L.bkv_attend_workspace_bytes(C.byref(p), n_seq, count, 4, nq)
+    for n_seq, nq in ((512, 1), (1024, 1), (65535, 4), (256, 8), (128, 16), (65535, 1024)):
+        assert 0 < one(n_seq, nq) <= 1024
+    assert one(8, 1) > 64 * 4 * 128 * 4                                       # (and is, below)
+    two = lambda n_seq, nq: L.bkv_attend_sets_workspace_bytes(C.byref(p), n_seq, 4, nq)
+    for n_seq, nq in ((512, 1), (1024, 1), (256, 8)):
+        assert two(n_seq, nq) <= 2 * n_seq * (4 * nq * (132 * 4) + 8) + 1024

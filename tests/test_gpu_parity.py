@@ -887,6 +887,28 @@ def test_attend_shows_what_is_not_finite(bk, dtype, d, count):
     assert torch.equal(bk.attend_kv(p, bad(K, 5, float("nan")), V, gone, Q)[0], ref)
 
 
+@pytest.mark.parametrize("n_seq,count,g,nq", [(511, 40, 1, 1), (512, 700, 2, 1), (513, 700, 1, 16), (128, 1000, 8, 8), (127, 1000, 8, 8), (85, 3000, 1, 5),
+                                              (1, 40000, 1, 1), (3, 9000, 17, 1), (2, 31, 1, 1)])
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.float32, 128)])
+def test_attend_stays_within_the_published_workspace(bk, dtype, d, n_seq, count, g, nq):
+    """Around the sizes at which ranges are no longer split: the call works with exactly the published bytes and writes nothing behind."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(dtype)
+    K, V, Q = rand(n_seq, count, d), rand(n_seq, count, d), rand(n_seq, g, nq, d)
+    w = torch.ones(n_seq, count, device="cuda")
+    p = bk.make_params(d, 64, 1, dtype, log_c=0.0)
+    want, _ = bk.attend_kv(p, K.float(), V.float(), w, Q.float()) if dtype == torch.float32 else bk.attend_kv(
+        bk.make_params(d, 64, 1, torch.float32, log_c=0.0), K.float(), V.float(), w, Q.float())
+    tol = 1e-5 if dtype == torch.float32 else 4e-3
+    for need, call in ((int(bk.lib().bkv_attend_workspace_bytes(C.byref(p), n_seq, count, g, nq)), lambda ws: bk.attend_kv(p, K, V, w, Q, workspace=ws)[0]),
+                       (int(bk.lib().bkv_attend_sets_workspace_bytes(C.byref(p), n_seq, g, nq)),
+                        lambda ws: bk.attend_sets(p, (K, V, w), (K, w), Q, workspace=ws)[0])):
+        ws = torch.full((need + 65536,), 0xAB, dtype=torch.uint8, device="cuda")
+        out = call(ws[:need])
+        assert bool((ws[need:] == 0xAB).all())
+        assert rel_l2(to_f64(out), to_f64(want)) <= tol
+
+
 def test_attend_empty_cache(bk, synth):
     t = synth.gqa_layer_bf16(n_seq=2, n=64, d=64, g=2, nq=1, seed=1, device="cpu")
     K, V, Q = t["K"].cuda(), t["V"].cuda(), t["Q"].cuda()
