@@ -179,18 +179,12 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     const int n = lane & 15, kg = lane >> 4;
 
     // workgroup -> (sequence, query group, split).  Where several query groups read the same rows, the workgroups of a
-    // sequence go to one XCD (blocks are dealt to the eight XCDs in turn), whose L2 then serves all but the first read.
-    const unsigned int ns = (unsigned int)(a.ns[0] + a.ns[1]), inner = ns * (unsigned int)a.n_qg;
-    unsigned int seq_u, rest;
-    if (a.by_xcd) {
-        const unsigned int k = blockIdx.x >> 3;
-        seq_u = (k / inner) * 8u + (blockIdx.x & 7u);
-        rest = k % inner;
-        if (seq_u >= (unsigned int)a.n_seq) return;
-    } else {
-        seq_u = blockIdx.x / inner;
-        rest = blockIdx.x % inner;
-    }
+    // sequence go to one XCD (blocks are dealt to the eight XCDs in turn, x fastest), whose L2 then serves all but the first
+    // read: a row of the grid holds the workgroups of eight sequences, else those of one.
+    const unsigned int ns = (unsigned int)(a.ns[0] + a.ns[1]);
+    const unsigned int seq_u = a.by_xcd ? blockIdx.y * 8u + (blockIdx.x & 7u) : blockIdx.y;
+    const unsigned int rest = a.by_xcd ? blockIdx.x >> 3 : blockIdx.x;
+    if (seq_u >= (unsigned int)a.n_seq) return;
     const int qg = (int)(rest % (unsigned int)a.n_qg);
     const int split = (int)(rest / (unsigned int)a.n_qg);
     const int64_t seq = seq_u;
@@ -598,13 +592,13 @@ size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int 
 
 template <typename T, int D>
 static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipStream_t st) {
-    const int64_t inner = (int64_t)p.n_qg * (p.ns[0] + p.ns[1]);
-    const int64_t blocks = inner * (a.by_xcd ? (a.n_seq + 7) / 8 * 8 : a.n_seq);
-    if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
+    // (two dimensions: a grid may not exceed 2^32 threads in one of them)
+    const unsigned int inner = (unsigned int)p.n_qg * (unsigned int)(p.ns[0] + p.ns[1]);
+    const dim3 grid = a.by_xcd ? dim3(8u * inner, (unsigned)((a.n_seq + 7) / 8)) : dim3(inner, (unsigned)a.n_seq);
     const int64_t units = a.n_seq * (a.set[0].count + a.set[1].count);
-    const hipError_t e = p.nqt == 1 ? (p.waves == 4 ? launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, dim3((unsigned)blocks), dim3(256), 0, st, a)
-                                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, dim3((unsigned)blocks), dim3(512), 0, st, a))
-                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, dim3((unsigned)blocks), dim3(512), 0, st, a);
+    const hipError_t e = p.nqt == 1 ? (p.waves == 4 ? launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, grid, dim3(256), 0, st, a)
+                                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, grid, dim3(512), 0, st, a))
+                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, grid, dim3(512), 0, st, a);
     if (e != hipSuccess || p.ns[0] + p.ns[1] == 1 || p.fused) return e;
     return launch_timed(kProfAttendMerge, a.n_seq * a.n_q, attend_merge_kernel<T, D>, dim3(a.n_q, (unsigned)a.n_seq), dim3(kMergeThreads), 0, st,
                         a, 16 * p.nqt);

@@ -909,6 +909,32 @@ def test_attend_stays_within_the_published_workspace(bk, dtype, d, n_seq, count,
         assert rel_l2(to_f64(out), to_f64(want)) <= tol
 
 
+def test_attend_with_as_many_query_groups_as_the_limits_allow(bk):
+    """n_seq = 65535 sequences and 129 groups of 32 queries each: 2^23 workgroups of 512 threads and more, which one dimension of a
+    grid does not hold.  Queries of zero: the output is the weighted mean of the values, 34 GB of it."""
+    n_seq, nq, d, count = 65535, 4097, 64, 3
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 90 GB of device memory")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    K = torch.randn(n_seq, count, d, generator=gen, device="cuda").to(torch.bfloat16)
+    V = torch.randn(n_seq, count, d, generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.tensor([1.0, 2.0, 4.0], device="cuda").repeat(n_seq, 1)
+    Q = torch.zeros(n_seq, 1, nq, d, dtype=torch.bfloat16, device="cuda")
+    out = torch.full_like(Q, 7.0)
+    ws = torch.empty(int(bk.lib().bkv_attend_workspace_bytes(C.byref(bk.make_params(d, 64, 1, torch.bfloat16, log_c=0.0)), n_seq, count, 1, nq)),
+                     dtype=torch.uint8, device="cuda")
+    bk.attend_kv(bk.make_params(d, 64, 1, torch.bfloat16, log_c=0.0), K, V, w, Q, workspace=ws, out=out, lse=False)
+    want = ((V.double() * w.double()[..., None]).sum(1) / 7.0).to(torch.bfloat16)
+    first = out[:, 0, 0]
+    off = (first.float() - want.float()).abs().max()
+    assert float(off) <= 2.0 ** -7 * float(want.float().abs().max())           # a bf16 unit at a tie
+    for s in range(0, n_seq, 4096):                                            # all queries of a sequence alike
+        part = out[s:s + 4096, 0]
+        assert torch.equal(part.amax(1), first[s:s + 4096]) and torch.equal(part.amin(1), first[s:s + 4096])
+    del Q, out, ws
+    torch.cuda.empty_cache()
+
+
 def test_attend_empty_cache(bk, synth):
     t = synth.gqa_layer_bf16(n_seq=2, n=64, d=64, g=2, nq=1, seed=1, device="cpu")
     K, V, Q = t["K"].cuda(), t["V"].cuda(), t["Q"].cuda()
