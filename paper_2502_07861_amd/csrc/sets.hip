@@ -175,15 +175,38 @@ __device__ __forceinline__ InstDesc make_desc(const SegGeo& g, int64_t seq, int 
     return d;
 }
 
+// Counts per chunk and slot -> those of the chunks before (in place), and the sequence's counts.  Workgroups of one wavefront, 64
+// slots of a sequence each.
+__global__ __launch_bounds__(64) void chunk_prefix_kernel(int32_t* chunk_cnt, int chunks, int32_t* cnt) {
+    constexpr int U = 32;
+    const int64_t seq = blockIdx.y;
+    const int slot = (int)blockIdx.x * 64 + (int)threadIdx.x;
+    int32_t* c = chunk_cnt + seq * chunks * kSlots + slot;
+    int run = 0;
+    for (int k0 = 0; k0 < chunks; k0 += U) {
+        int x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = k0 + u < chunks ? c[(int64_t)(k0 + u) * kSlots] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + u < chunks) { c[(int64_t)(k0 + u) * kSlots] = run; run += x[u]; }
+    }
+    cnt[seq * kSlots + slot] = run;
+}
+
 // The numerator's instances, from the counts per chunk and slot, in one launch.  Workgroups (seq, chunk): stable partition of the
 // chunk's tokens, perm[seq][start[slot] + rank among the slot's tokens] = token; a token's place is its slot's start + the
 // counts of the chunks before + the wavefronts before its own + its rank in its wavefront.  Workgroups (seq, chunks + r):
 // instance table of round r, for every segment its (full blocks >> r) blocks; unused entries of the grid are marked.  Every
-// workgroup sums the counts for itself (a few KB from L2; what it saves is launches of one wavefront per sequence that nothing
-// else can run beside: 8 sequences x 8192 tokens, two rounds, starts, tables and partition 29 us in four launches, one
-// workgroup per sequence, now 7 us in one).
+// workgroup sums the counts of all chunks for itself, 2 KB each from L2 (what it saves is a launch: 8 sequences x 8192 tokens, two
+// rounds, starts, tables and partition 29 us in four launches, one workgroup per sequence, 7 us in one).  That is quadratic in the
+// chunks: 32 MB a sequence from 32768 tokens on.  So from kPrefixFrom sums on chunk_prefix_kernel forms them once (SUMMED).
+// Whole numerator call with / without it: 4 x 32768 tokens 132 / 129 us, 64 x 8192 456 / 455, 16 x 32768 453 / 459, 64 x 32768
+// 1634 / 1678, 256 x 32768 6400 / 7440 (66e3, 70e3, 266e3, 1.06e6, 4.3e6 sums).
+constexpr int64_t kPrefixFrom = 160 * 1024;
 constexpr int kPartThreads = 512, kPartWaves = kPartThreads / 64, kPartIds = 128;   // at most 123 slots are ever in use
 static_assert(kPartThreads == kSlots, "a thread per slot");
+template <bool SUMMED>
 __global__ __launch_bounds__(kPartThreads) void segments_kernel(const int32_t* slot, const int32_t* chunk_cnt, int chunks, int64_t chunk,
                                                                 SegGeo g, int32_t* cnt, int32_t* start, int32_t* perm) {
     __shared__ int cid[kSlots];                   // slot -> dense id of the non-empty slots
@@ -198,7 +221,10 @@ __global__ __launch_bounds__(kPartThreads) void segments_kernel(const int32_t* s
     for (int i = tid; i < kPartWaves * kPartIds; i += kPartThreads) (&wcnt[0][0])[i] = 0;
     // thread = slot: its tokens, those of the chunks before this one, where its segment starts, its number among the occupied
     int total = 0, before = 0;
-    {
+    if constexpr (SUMMED) {
+        total = cnt[seq * kSlots + tid];
+        if (part < chunks) before = chunk_cnt[(seq * chunks + part) * kSlots + tid];
+    } else {
         const int32_t* c = chunk_cnt + seq * chunks * kSlots + tid;
 #pragma unroll 8
         for (int k = 0; k < chunks; ++k) {
@@ -218,7 +244,10 @@ __global__ __launch_bounds__(kPartThreads) void segments_kernel(const int32_t* s
         n_ids += wtot[1][w]; n_desc += wtot[2][w];
     }
     if (n_ids > kPartIds) n_ids = kPartIds;
-    if (part == 0) { cnt[seq * kSlots + tid] = total; start[seq * kSlots + tid] = at; }
+    if (part == 0) {
+        if (!SUMMED) cnt[seq * kSlots + tid] = total;
+        start[seq * kSlots + tid] = at;
+    }
     if (r >= 0) {
         if (total > 0 && id < kPartIds) { lslot[id] = tid; lstart[id] = at; lnb[id] = nb; lbase[id] = bat; }
         __syncthreads();
@@ -454,8 +483,13 @@ hipError_t run_sets(const SetsArgs& q, hipStream_t st) {
             hipLaunchKernelGGL(slot_kernel, g1, dim3(256), 0, st, norm2, vmax2, n, ch.tokens, q.erase2, slot, chunk_cnt);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(segments_kernel, dim3((unsigned)n_seq, (unsigned)(ch.n + rounds)), dim3(kPartThreads), 0, st, slot, chunk_cnt,
-                           (int)ch.n, ch.tokens, g, cnt, start, perm);
+        const dim3 g2((unsigned)n_seq, (unsigned)(ch.n + rounds));
+        if (n_seq * ch.n * (ch.n + rounds) >= kPrefixFrom) {
+            hipLaunchKernelGGL(chunk_prefix_kernel, dim3(kSlots / 64, (unsigned)n_seq), dim3(64), 0, st, chunk_cnt, (int)ch.n, cnt);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            hipLaunchKernelGGL(segments_kernel<true>, g2, dim3(kPartThreads), 0, st, slot, chunk_cnt, (int)ch.n, ch.tokens, g, cnt, start, perm);
+        } else
+            hipLaunchKernelGGL(segments_kernel<false>, g2, dim3(kPartThreads), 0, st, slot, chunk_cnt, (int)ch.n, ch.tokens, g, cnt, start, perm);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // blocks resident as one chunk read their key rows through perm (no copy in slot order); larger blocks need the copy
         if (!compress_block_resident(rb, b, true)) {

@@ -1467,6 +1467,26 @@ def test_balancekv_sets_against_oracle(bk, synth, oracle, dtype, d, b, T, n, n_s
     np.testing.assert_allclose(lse.cpu().numpy(), ref_lse, atol=1e-3 if dtype == torch.float32 else 2e-2)
 
 
+@pytest.mark.parametrize("n_seq,group,n,eps", [(40, 4, 32768, 0.0), (11, 1, 32767, 0.0), (72, 9, 12000, 3e3)])
+def test_balancekv_sets_many_sequences_equal_few(bk, n_seq, group, n, eps):
+    """Many sequences of many chunks have the counts of the chunks summed by a launch of its own; the same sequences in small groups
+    (seq_base) do not: the same sets, bit for bit."""
+    d, b, T = 64, 64, 2
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    K = torch.randn(n_seq, n, d, generator=gen, device="cuda").to(torch.bfloat16)
+    V = (torch.randn(n_seq, n, d, generator=gen, device="cuda") *
+         torch.exp2(torch.rand(n_seq, n, 1, generator=gen, device="cuda") * 5 - 2.5)).to(torch.bfloat16)
+    V[:, 17] = 0.0                                                            # a row of no bucket
+    p = bk.make_params(d, b, T, torch.bfloat16, log_c=-57.0, seed=11, center=True, value_gram=True)
+    call = lambda lo, hi: bk.balancekv_sets(p, bk.BKV_SET_NUMERATOR, K[lo:hi].contiguous(), V[lo:hi].contiguous(), seq_base=lo, eps=eps,
+                                            max_buckets=12)
+    whole = call(0, n_seq)
+    for lo in range(0, n_seq, group):
+        part = call(lo, min(n_seq, lo + group))
+        for name in ("K", "V", "w", "idx", "count", "slot", "status"):
+            assert torch.equal(whole[name][lo:lo + group], part[name]), (name, lo)
+
+
 def test_balancekv_sets_replay_from_a_captured_graph(bk, synth):
     """Both set builds and the two-set output line are plain kernel launches without host round trips (grids are upper
     bounds, counts stay on the device): captured once, every replay reproduces the eager result bit for bit."""
