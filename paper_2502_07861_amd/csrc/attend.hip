@@ -281,24 +281,30 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
                         s[t][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[kt][c]), __builtin_bit_cast(bf16x8_t, qf[t][c]),
                                                                            s[t][kt], 0, 0, 0);
         } else {
-            // Four columns per matrix instruction, each from zero, added in a tree: one chain over the row rounds d times at
-            // the size of the whole sum, 1.3e-6 off the 64-bit output (d = 128, 8321 tokens), the tree 5.0e-7.
+            // Chains of two matrix instructions (eight columns), their results added in a tree: one chain over the row rounds d
+            // times at the size of the whole sum, 1.3e-6 off the 64-bit output (d = 128, 8321 tokens), this 5.3e-7.  With 16
+            // queries a piece is added while the next one is in the matrix cores; with 32 there are no registers for that.
 #pragma unroll
             for (int t = 0; t < NQT; ++t) {
-                floatx4 level[4];
+                constexpr int LAG = NQT == 1 ? 1 : 0;
+                floatx4 level[4], y[LAG + 1][2];
 #pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    floatx4 y[4];
-                    asm volatile("" : "+v"(qf[t][c]));        // (registers: a piece starts when the one before it is summed)
+                for (int c = 0; c < KC + LAG; ++c) {
+                    if (c < KC) {
+                        asm volatile("" : "+v"(qf[t][c < KC ? c : 0]));       // (registers: pieces start one after the other)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const unsigned int ka = kf[0][c][i], qa = qf[t][c][i];
-                        y[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka), __uint_as_float(qa), zero4, 0, 0, 0);
+                        for (int i = 0; i < 4; ++i) {
+                            const int j = 2 * (i & 1) + (i >> 1);
+                            const unsigned int ka = kf[0][c < KC ? c : 0][j], qa = qf[t][c < KC ? c : 0][j];
+                            y[c & LAG][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka), __uint_as_float(qa), i < 2 ? zero4 : y[c & LAG][i & 1], 0, 0, 0);
+                        }
                     }
-                    floatx4 x = (y[0] + y[1]) + (y[2] + y[3]);
+                    const int p = c - LAG;
+                    if (p < 0) continue;
+                    floatx4 x = y[p & LAG][0] + y[p & LAG][1];
                     int l = 0;
 #pragma unroll
-                    for (int k = c; k & 1; k >>= 1) x = level[l++] + x;
+                    for (int k = p; k & 1; k >>= 1) x = level[l++] + x;
                     asm volatile("" : "+v"(x));
                     level[l] = x;
                 }
@@ -546,9 +552,11 @@ static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, in
     const int64_t wgs = n_seq * p.n_qg;
     const int64_t cnt[2] = {count0, count1};
     const int64_t all = (count0 + keys - 1) / keys + (count1 + keys - 1) / keys;
-    // four wavefronts per workgroup let three workgroups share a compute unit (registers); eight mean half the splits where
-    // a wavefront has a single group anyway, and are what 32 queries take (one workgroup per compute unit, LDS)
-    p.waves = p.nqt == 1 && all * wgs > kTargetWaves ? 4 : 8;
+    // bf16: four wavefronts per workgroup let three workgroups share a compute unit (registers); eight mean half the splits
+    // where a wavefront has a single group anyway.  fp32: eight, four take more registers and fewer of them are resident
+    // (1024 x 2000 tokens, d = 64: 184 us against 196; 256 x 1000, d = 128: 43 against 47; one sequence of 65536, d = 64: 16.7
+    // against 15.9).  32 queries take eight (one workgroup per compute unit, LDS).
+    p.waves = elem == 2 && p.nqt == 1 && all * wgs > kTargetWaves ? 4 : 8;
     const size_t row_bytes = (size_t)p.rows * (d + kRowPad) * sizeof(float);
     int64_t most = (int64_t)(max_bytes / ((size_t)wgs * row_bytes));          // splits whose partials fit the buffer
     int64_t steps = (all * wgs + kTargetWaves - 1) / kTargetWaves;             // per wavefront
@@ -596,9 +604,10 @@ static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipS
     const unsigned int inner = (unsigned int)p.n_qg * (unsigned int)(p.ns[0] + p.ns[1]);
     const dim3 grid = a.by_xcd ? dim3(8u * inner, (unsigned)((a.n_seq + 7) / 8)) : dim3(inner, (unsigned)a.n_seq);
     const int64_t units = a.n_seq * (a.set[0].count + a.set[1].count);
-    const hipError_t e = p.nqt == 1 ? (p.waves == 4 ? launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, grid, dim3(256), 0, st, a)
-                                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, grid, dim3(512), 0, st, a))
-                                    : launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, grid, dim3(512), 0, st, a);
+    hipError_t e = hipSuccess;
+    if (p.nqt == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, grid, dim3(512), 0, st, a);
+    else if (p.waves == 8) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, grid, dim3(512), 0, st, a);
+    else if constexpr (sizeof(T) == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, grid, dim3(256), 0, st, a);
     if (e != hipSuccess || p.ns[0] + p.ns[1] == 1 || p.fused) return e;
     return launch_timed(kProfAttendMerge, a.n_seq * a.n_q, attend_merge_kernel<T, D>, dim3(a.n_q, (unsigned)a.n_seq), dim3(kMergeThreads), 0, st,
                         a, 16 * p.nqt);
