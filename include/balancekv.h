@@ -321,7 +321,9 @@ int bkv_attend(const bkv_cache* c, const void* Q, int32_t g, int32_t nq, void* o
  *               instances use the value factor with r_value = 2^i whether or not BKV_VALUE_GRAM is set
  * Buckets, bucket clamp, rows without a bucket, instance numbers and draws exactly as in bkv_balancekv_sets: with
  * eps <= 0 the state after n tokens holds the same tokens with the same weights as the offline call on those n tokens.
- * device_storage: bkv_stream_bytes() bytes, 256-byte aligned, caller-owned, must outlive the handle; cleared by init.
+ * device_storage: bkv_stream_bytes() bytes, 256-byte aligned, caller-owned, must outlive the handle; init clears what it uses.
+ *             The end of it (the size of block survivors per sequence: 2 n_seq (block / 2) rows twice and as many int32) is reserved
+ *             and not touched.
  * Overflow never writes out of bounds: the token is dropped for that instance and a bit is set in the error word. */
 #define BKV_STREAM_NUM_FULL  4   /* error word: a numerator region was full, a token was not stored           */
 #define BKV_STREAM_DEN_FULL  8   /* error word: the denominator region was full                               */

@@ -688,7 +688,7 @@ int bkv_stream_init(bkv_stream** out, const bkv_params* p, int64_t n_seq, int64_
     }
     // weights 0 (no token), counters 0, rows finite; every region free
     hipStream_t st = (hipStream_t)hip_stream;
-    hipError_t e = bkv::launch_fill_u32(device_storage, 0u, (int64_t)(need / 4), st);
+    hipError_t e = bkv::launch_fill_u32(device_storage, 0u, (at - (char*)device_storage) / 4, st);
     if (e == hipSuccess) e = bkv::launch_fill_u32(s.bucket, 0x80000000u, n_seq * (int64_t)R, st);
     if (e != hipSuccess) { delete h; return hip_fail(e); }
     *out = h;

@@ -218,3 +218,25 @@ def test_stream_overflow_is_flagged_not_written(bk, synth):
         bk.Stream(p, n_seq, 65, b, b)
     with pytest.raises(bk.BkvError):
         bk.Stream(p, n_seq, 4, b - 1, b)
+
+
+def test_stream_init_touches_only_what_it_uses(bk):
+    """The published size has a reserved end (room for the survivors of two halvings per sequence): init neither clears it nor needs
+    the rest to be clear."""
+    import ctypes as C
+    n_seq, regions, cap, b, d = 3, 2, 128, 64, 128
+    p = bk.make_params(d, b, 2, torch.bfloat16, log_c=-10.0)
+    need = int(bk.lib().bkv_stream_bytes(C.byref(p), n_seq, regions, cap, cap))
+    up = lambda x: (x + 255) // 256 * 256
+    reserved = 2 * up(2 * n_seq * (b // 2) * d * 2) + up(2 * n_seq * (b // 2) * 4)
+    store = torch.full((need + 256,), 0xAB, dtype=torch.uint8, device="cuda")
+    off = (-store.data_ptr()) % 256
+    h = C.c_void_p()
+    assert bk.lib().bkv_stream_init(C.byref(h), C.byref(p), n_seq, 0, regions, cap, cap, 0, 0.0, 0.0, C.c_void_p(store.data_ptr() + off), need,
+                                    C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    used = store[off:off + need - reserved]
+    assert bool((store[off + need - reserved:] == 0xAB).all())
+    bucket = torch.tensor([0, 0, 0, 0x80], dtype=torch.uint8, device="cuda").repeat(n_seq * regions)     # every region free
+    assert int((used != 0).sum()) == int((bucket != 0).sum())
+    bk.lib().bkv_stream_free(h)
