@@ -175,6 +175,88 @@ def test_many_blocks_equal_few_blocks(bk, synth, dtype, d, b, center, r_key):
     assert (many["status"] & 2 == 0).all()
 
 
+def _tuned(synth, dtype, d, b):
+    from oracle.tuning import tune_log_c
+    K, _ = _blocks(synth, dtype, d, b, 2, seed=5 + b)
+    return f32(tune_log_c(to_f64(K), target=0.25, center=True))
+
+
+@pytest.mark.parametrize("dtype,d,b,over", [(torch.bfloat16, 128, 512, 1), (torch.bfloat16, 128, 1024, 65), (torch.bfloat16, 128, 320, 128)])
+def test_two_to_two_and_a_half_blocks_per_compute_unit(bk, synth, dtype, d, b, over):
+    """Launches whose last round would be thin stay with one block per compute unit, the first of them started spread out
+    (compress_kernel): the blocks of small launches, bit for bit."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_inst = 2 * n_cu + over
+    K, V = _blocks(synth, dtype, d, b, 16, seed=b)
+    K = torch.cat([K.roll(k, 0).roll(7 * k, 1) for k in range((n_inst + 15) // 16)])[:n_inst].contiguous()
+    V = torch.cat([V.roll(k, 0) for k in range((n_inst + 15) // 16)])[:n_inst].contiguous()
+    p = bk.make_params(d, b, 1, dtype, log_c=_tuned(synth, dtype, d, b), seed=9, center=True)
+    ids = torch.arange(n_inst, dtype=torch.int64).cuda()
+    many = bk.compress_block(p, K, V, inst_ids=ids)
+    for lo in range(0, n_inst, n_cu):
+        few = bk.compress_block(p, K[lo:lo + n_cu].contiguous(), V[lo:lo + n_cu].contiguous(), inst_ids=ids[lo:lo + n_cu].contiguous())
+        for name, x in few.items():
+            assert torch.equal(many[name][lo:lo + n_cu], x), name
+    assert (many["status"] & 2 == 0).all()
+
+
+@pytest.mark.parametrize("n_sink,n_recent", [(0, 0), (37, 101)])
+@pytest.mark.parametrize("dtype,d,b,per_seq", [(torch.bfloat16, 128, 64, 4), (torch.bfloat16, 128, 128, 8), (torch.bfloat16, 128, 512, 8),
+                                               (torch.bfloat16, 128, 1024, 4), (torch.float32, 64, 256, 8), (torch.float32, 64, 448, 4)])
+def test_many_sequences_equal_few_in_a_tree(bk, synth, dtype, d, b, per_seq, n_sink, n_recent):
+    """Two rounds over more blocks than compute units in each (two blocks per compute unit): survivors' indices, strided windows,
+    draws by sequence and block, status words that several blocks share, against the same sequences in groups that
+    stay below (seq_base), bit for bit."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_seq = 3 * n_cu // per_seq + 5 if b <= 256 else 6 * n_cu // per_seq + 5           # (clear of two to two and a half per unit)
+    group = n_cu // per_seq
+    n = b * per_seq + n_sink + n_recent
+    base = _blocks(synth, dtype, d, n, 8, seed=b + n_sink)
+    K, V = (torch.cat([x.roll(k, 0).roll(11 * k, 1) for k in range((n_seq + 7) // 8)])[:n_seq].contiguous() for x in base)
+    p = bk.make_params(d, b, 2, dtype, log_c=_tuned(synth, dtype, d, b), seed=21, center=True)
+
+    def call(lo, hi):
+        if n_sink + n_recent:
+            return bk.merge_reduce_protected(p, K[lo:hi].contiguous(), V[lo:hi].contiguous(), n_sink, n_recent, seq_base=40 + lo)
+        return bk.merge_reduce(p, K[lo:hi].contiguous(), V[lo:hi].contiguous(), seq_base=40 + lo)
+
+    many = call(0, n_seq)
+    for lo in range(0, n_seq, group):
+        for name, x in call(lo, min(n_seq, lo + group)).items():
+            assert torch.equal(many[name][lo:lo + group], x), (name, lo)
+    assert (many["status"] & 2 == 0).all()
+
+
+@pytest.mark.parametrize("dtype,d,b", [(torch.bfloat16, 128, 64), (torch.bfloat16, 128, 128), (torch.float32, 64, 64)])
+def test_many_sequences_equal_few_in_carries(bk, synth, dtype, d, b):
+    """Carries of more sequences than compute units, with draws given: the same caches in two halves, bit for bit."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_seq, T = n_cu + 24, 2
+    half = n_seq // 2
+    p = bk.make_params(d, b, T, dtype, log_c=_tuned(synth, dtype, d, b), seed=3, center=True)
+    steps = 2 * b + 1
+    K, V = _blocks(synth, dtype, d, steps, 8, seed=b + 1)
+    K, V = (torch.cat([x.roll(k, 0).roll(5 * k, 1) for k in range((n_seq + 7) // 8)])[:n_seq].transpose(0, 1).contiguous() for x in (K, V))
+    u = torch.rand(T, n_seq, b, generator=torch.Generator().manual_seed(8)).cuda()
+    parts = [(0, n_seq), (0, half), (half, n_seq)]
+    caches = [bk.Cache(p, hi - lo, 4 * b) for lo, hi in parts]
+    status = [torch.zeros(hi - lo, T, dtype=torch.int32, device="cuda") for lo, hi in parts]
+    signs = [torch.zeros(T, hi - lo, b, dtype=torch.int8, device="cuda") for lo, hi in parts]
+    us = [u[:, lo:hi].contiguous() for lo, hi in parts]
+    for j in range(steps):
+        done = [c.append_token(K[j, lo:hi].contiguous(), V[j, lo:hi].contiguous(), status=st, uniforms=x, signs=sg)
+                for c, (lo, hi), st, x, sg in zip(caches, parts, status, us, signs)]
+        assert done[0] == done[1] == done[2] == {b: 1, 2 * b: 2}.get(j + 1, 0)
+    n = caches[0].count
+    whole = [x[:, :n] for x in caches[0].views()]
+    for c, (lo, hi), st, sg in list(zip(caches, parts, status, signs))[1:]:
+        assert c.count == n
+        for x, y in zip(whole, c.views()):
+            assert torch.equal(x[lo:hi], y[:, :n])
+        assert torch.equal(status[0][lo:hi], st) and torch.equal(signs[0][:, lo:hi], sg)
+    assert caches[0].error_word() == 0
+
+
 @pytest.mark.parametrize("dtype,d,b", [(torch.bfloat16, 128, 512), (torch.bfloat16, 128, 1024), (torch.float32, 64, 256),
                                        (torch.float32, 128, 320)])
 def test_large_common_key_mean(bk, synth, oracle, dtype, d, b):
@@ -635,7 +717,7 @@ def test_merge_reduce_workload3_sampled(bk, synth, oracle):
 
 def test_merge_reduce_workload4_sampled(bk, synth, oracle):
     """64 layers x 8 KV heads, n=131072, d=128 bf16, b=1024, T=3 (the benchmark's default workload, in its launch
-    configuration: grids of 65536 / 32768 / 16384 blocks, staggered start): 64 sampled instances per round are
+    configuration: grids of 65536 / 32768 / 16384 blocks, two on each compute unit): 64 sampled instances per round are
     teacher-forced against the oracle, the survivor bookkeeping is checked on every block."""
     cfg = dict(synth.WORKLOADS["cfg4"])
     t = synth.gqa_layer_bf16(cfg["n_seq"], cfg["n"], cfg["d"], cfg["g"], 1, seed=cfg["seed"], device="cuda")
@@ -696,10 +778,10 @@ def test_attend_matches_oracle(bk, synth, oracle, dtype, d, n_seq, count, stride
 
 
 def test_attend_bf16_weight_rounding_is_bounded(bk, synth):
-    """The bf16 path rounds every softmax weight to bf16 (to nearest even) before the value accumulation and the
-    denominator; the fp32 path keeps them in fp32.  The same bf16 values through both paths: the outputs differ by
-    the rounding of the output itself (2^-9 relative per element) plus an unbiased 2^-9 per weight, and the
-    log-denominator shows no bias (a truncation would shift it by about -2^-9 = -0.002)."""
+    """The bf16 path multiplies its value rows by weights of 17 bits (two bf16 numbers) and adds fp32 weights to the denominator;
+    the fp32 path keeps fp32 throughout.  The same bf16 values through both paths: the outputs differ by the rounding of the
+    output itself (2^-9 relative per element), and the log-denominator shows no bias (weights rounded to bf16 once were cut,
+    which shifted it by about -2^-9 = -0.002)."""
     n_seq, count, d, g = 3, 8192, 128, 4
     t = synth.gqa_layer_bf16(n_seq=n_seq, n=count, d=d, g=g, nq=1, seed=404, device="cpu")
     K, V, Q = t["K"].cuda(), t["V"].cuda(), t["Q"].cuda()
@@ -772,7 +854,7 @@ def _two_set_reference(K, V, w, Kd, wd, Q):
 def test_attend_edges(bk, dtype, d, n_seq, count, g, nq):
     """Edges of the attend pass: key groups (32 / 16 keys), query tiles of 16, ranges split or not, runs of absent tokens, a
     set without a value sum; the workspace arrives with arbitrary content and is used again as the call left it.
-    Bounds: fp32 sums of at most 40000 terms, relative 1e-5; bf16 weights and outputs round to nearest (2^-9 each)."""
+    Bounds: fp32 sums of at most 40000 terms, relative 1e-5; bf16 outputs round to nearest (2^-9)."""
     gen = torch.Generator().manual_seed(count + g)
     K, V = torch.randn(n_seq, count, d, generator=gen).to(dtype).cuda(), torch.randn(n_seq, count, d, generator=gen).to(dtype).cuda()
     Q = torch.randn(n_seq, g, nq, d, generator=gen).to(dtype).cuda()

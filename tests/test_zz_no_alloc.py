@@ -51,3 +51,22 @@ def test_static_scratch_attend_equals_workspace_attend(oracle):
     one = C.c_void_p(0x1000)
     assert L.bkv_attend_kv_static(C.byref(p), one, one, one, 70000, 8, 8, one, 4, 1, one, None, None) == bkm.binding.BKV_ESHAPE
     assert L.bkv_attend_kv_static(C.byref(p), one, one, one, 2, 8, 4, one, 4, 1, one, None, None) == bkm.binding.BKV_EINVAL
+
+
+@pytest.mark.parametrize("dtype,d,count,g", [(torch.bfloat16, 128, 200000, 16), (torch.float32, 128, 100000, 32)])
+def test_static_scratch_limits_the_splits(dtype, d, count, g):
+    """One long sequence with a full tile of queries: unlimited, the splits' partials would take more than the static array
+    (391 splits of 16 x 132 floats: 3.3 MB), so the call makes fewer splits.  The sums then differ in their order only."""
+    import paper_2502_07861_amd as bkm
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(dtype)
+    K, V, Q = rand(1, count, d), rand(1, count, d), rand(1, g, 1, d)
+    w = torch.ones(1, count, device="cuda")
+    p = bkm.make_params(d, 128, 2, dtype, log_c=0.0)
+    need = int(bkm.lib().bkv_attend_workspace_bytes(C.byref(p), 1, count, g, 1))
+    assert need > int(bkm.lib().bkv_attend_kv_static_max_bytes())
+    ref, ref_lse = bkm.attend_kv(p, K, V, w, Q)
+    out, lse = torch.full_like(ref, float("nan")), torch.full_like(ref_lse, float("nan"))
+    bkm.binding.attend_kv_static(p, K, V, w, Q, out, lse)
+    assert rel_l2(to_f64(out), to_f64(ref)) <= (1e-5 if dtype == torch.float32 else 4e-3)
+    torch.testing.assert_close(lse, ref_lse, rtol=0, atol=1e-5)
