@@ -1414,12 +1414,13 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
             n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
         }
         // More blocks than compute units: two of them on each (compress_pair.hip).  Up to one per compute unit a launch takes
-        // as long as one block, and a block that has the compute unit to itself is done sooner (256 blocks of 512 bf16 rows:
-        // 28 us against 33).  Measured over 300 to 3000 blocks of 64 to 1024 rows the pair is 4 to 60 % faster, with two
-        // exceptions: larger blocks in a launch whose last, thinly filled round is most of the difference (513 to 640
-        // blocks of more than 256 rows: 0 to 9 % slower), and single precision beyond one chunk (b > 512: between 20 %
+        // as long as one block, and a block that has the compute unit to itself is done sooner (192 and 256 blocks of 512 bf16
+        // rows 11 % sooner, of 1024 rows 15 %).  With more the pair is faster (time of the other kernel over its own, 256
+        // compute units): b = 64 1.25 (257 blocks) to 2.0 (1024), 256 1.15 to 1.5, 512 1.08 to 1.24, 1024 1.02 to 1.25, where
+        // the last round is thin least.  Two exceptions: two blocks everywhere and a few more of more than 768 rows (514 and
+        // 528 blocks: 0.97 to 1.00; 560 on: 1.01 to 1.04), and single precision beyond one chunk (b > 512: between 20 %
         // slower and 10 % faster; there a wavefront's tile takes long enough for the walk to wait for it).
-        const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 5 * (int64_t)n_cu / 2 && a.b > 256;
+        const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 2 * (int64_t)n_cu + n_cu / 8 && a.b > 768;
         if (row_bytes == 256 && !emit_g && !vgram && !a.desc && !a.k_by_idx && n_inst > n_cu && !thin_tail &&
             (dtype == BKV_BF16 || a.b <= 512) && n_inst <= (1ll << 30))
             return launch_compress_pair(dtype, d, a, n_inst, st);

@@ -181,10 +181,11 @@ def _tuned(synth, dtype, d, b):
     return f32(tune_log_c(to_f64(K), target=0.25, center=True))
 
 
-@pytest.mark.parametrize("dtype,d,b,over", [(torch.bfloat16, 128, 512, 1), (torch.bfloat16, 128, 1024, 65), (torch.bfloat16, 128, 320, 128)])
-def test_two_to_two_and_a_half_blocks_per_compute_unit(bk, synth, dtype, d, b, over):
-    """Launches whose last round would be thin stay with one block per compute unit, the first of them started spread out
-    (compress_kernel): the blocks of small launches, bit for bit."""
+@pytest.mark.parametrize("dtype,d,b,over", [(torch.bfloat16, 128, 1024, 1), (torch.bfloat16, 128, 896, 32), (torch.bfloat16, 128, 896, 33),
+                                            (torch.bfloat16, 128, 512, 1), (torch.float32, 64, 320, 128)])
+def test_a_few_more_than_two_blocks_per_compute_unit(bk, synth, dtype, d, b, over):
+    """A few more large blocks than two on every compute unit (up to an eighth of them) stay with one at a time, the first of them
+    started spread out (compress_kernel); others run two at a time: the blocks of small launches, bit for bit."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     n_inst = 2 * n_cu + over
     K, V = _blocks(synth, dtype, d, b, 16, seed=b)
@@ -208,7 +209,7 @@ def test_many_sequences_equal_few_in_a_tree(bk, synth, dtype, d, b, per_seq, n_s
     draws by sequence and block, status words that several blocks share, against the same sequences in groups that
     stay below (seq_base), bit for bit."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    n_seq = 3 * n_cu // per_seq + 5 if b <= 256 else 6 * n_cu // per_seq + 5           # (clear of two to two and a half per unit)
+    n_seq = 3 * n_cu // per_seq + 5 if b <= 256 else 6 * n_cu // per_seq + 5           # (clear of a few more than two per unit)
     group = n_cu // per_seq
     n = b * per_seq + n_sink + n_recent
     base = _blocks(synth, dtype, d, n, 8, seed=b + n_sink)
