@@ -53,6 +53,12 @@ template <> struct Elem<__bf16> {
     static __device__ __forceinline__ floatx16 mma_from(Frag a, Frag b, const floatx16& c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
+    // several products with one b, their accumulators in turn
+    template <int N>
+    static __device__ __forceinline__ void mma_turns(floatx16 (&acc)[N], const Frag (&a)[N], Frag b) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b, acc[i], 0, 0, 0);
+    }
     static __device__ __forceinline__ void unpack(const uintx4& raw, float (&f)[8]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -100,6 +106,13 @@ template <> struct Elem<float> {
 #pragma unroll
         for (int e = 1; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
         return acc;
+    }
+    template <int N>
+    static __device__ __forceinline__ void mma_turns(floatx16 (&acc)[N], const Frag (&a)[N], Frag b) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[e], acc[i], 0, 0, 0);
     }
     static __device__ __forceinline__ void unpack(const uintx4& raw, float (&f)[4]) {
 #pragma unroll

@@ -4,18 +4,18 @@
 // One workgroup (8 wavefronts) owns one block of b tokens; its keys are staged in LDS in chunks of as many 64-row
 // panels as fit.  The walk is organised over 64-token panels.  sigma[l] (LDS) starts at minus the decision threshold
 // of token l and accumulates sum_{i signed so far} eta_i g_il.  Wavefront 0 is the walker: for panel I it holds the
-// strictly-upper part of the 64x64 diagonal tile of kernel weights as "one column per lane" registers and takes the 64
-// sequential decisions of Alg. 2 (lane j tests the sign of its sigma; bit j of the compare mask becomes the +-1 that
-// every later lane multiplies g_jl with).  Wavefronts 1..7 form tiles on MFMA while the walker walks.  There are no
+// strictly-upper part of the 64x64 diagonal tile of kernel weights in registers, column by column, and takes the 64
+// sequential decisions of Alg. 2 (walk_quarters.h).  Wavefronts 1..7 form tiles on MFMA while the walker walks.  There are no
 // workgroup barriers inside the pipeline: the wavefronts hand data over through progress counters in LDS.
 //
-//   walker, panel I     take diagonal tile D(I) (registers), mark the buffer free, wait until column I is complete,
-//                       take sigma of the panel, walk 64 steps, publish the signs of panel I
+//   walker, panel I     wait for diagonal tile D(I) and until column I is complete, take sigma of the panel, walk 64 steps
+//                       (the tile comes in on the way), mark the tile's buffer free, publish the signs of panel I
 //   wave w = 1..7       owns column panel w (its keys stay in registers as the B operand): tiles (i, w), i = 0..w-1, in
 //                       row order: weights first, then wait for the signs of panel i, signed column sum in a register;
 //                       after tile (w-1, w) the sum goes into sigma[panel w] and column w is published.  Then the
 //                       diagonal tile of panel w+2 (start-up tiles come from the wavefronts whose columns are due last),
-//                       stored once the walker has taken the previous one.
+//                       stored once the walker has taken the tile before the previous one.  Where a tile takes long and there are
+//                       at most four panels the wavefronts own half columns instead (HALF).
 //
 // so the only work between two walks is one signed column sum and two hand-overs.  Rows of earlier chunks (b larger
 // than one chunk) come back from global memory (L2) as the A operand against the resident chunk before its own panels
@@ -33,18 +33,26 @@
 #include "bkv_device.h"
 #include "bkv_host.h"
 #include "compress_device.h"
+#include "walk_quarters.h"
 
 namespace bkv {
 
-constexpr int kDiagStride = 68;                             // floats per column of the transposed diagonal tile (16-byte rows, conflict-free)
-constexpr int kDiagFloats = 64 * kDiagStride;
+// A diagonal tile in LDS, transposed, only what the walk reads: of column c, in quarter k = c / 16, the rows of quarters 0..k.
+// Columns of quarters 1..3 are 16 k + 20 floats apart, so that the sixteen columns of a quarter meet all banks with 16 bytes each;
+// those of quarter 0 are 16 apart, their pieces of 16 bytes permuted to the same end (piece p at p ^ (c / 4)).
+__host__ __device__ constexpr int diag_quarter(int k) { return k == 0 ? 0 : 128 * k * k + 192 * k - 64; }
+__host__ __device__ constexpr int diag_stride(int k) { return k == 0 ? 16 : 16 * k + 20; }
+constexpr int kDiagFloats = diag_quarter(4);                // 11 KB
+// Two tiles, so that the next one is there when the walk over the panel before ends (with one it could only be stored once
+// that walk had read its own: up to 1k clocks a panel).
+constexpr int kDiagArea = 2 * kDiagFloats;                  // floats; also: mean partials, earlier-chunk sums, survivor list
 constexpr int kLdsLimit = 160 * 1024;
 
 static inline size_t lds_fixed_bytes(int b) {
     return (size_t)b * 4 * 2             // sigma, -a_i of every row
            + 16 * 8                      // eta of each panel as a 64-bit mask (bit j = 1 iff eta_j = +1)
            + 8 * 64 * 4                  // eta of the resident chunk's panels as +-1 floats, accumulator order
-           + kDiagFloats * 4             // diagonal tile (also: mean partials, survivor list)
+           + (size_t)kDiagArea * 4
            + 64                          // scalars
            + 128;                        // progress counters of the panel pipeline
 }
@@ -67,6 +75,9 @@ bool compress_block_resident(int row_bytes, int b, bool value_gram) {
     const bool v_lds = value_gram && compress_value_gram_fits(row_bytes, b);
     return b <= chunk_rows_for(row_bytes, b, v_lds);
 }
+
+// rows of a full chunk of a block that does not fit LDS
+template <typename T, int D> constexpr int G_rows() { return Geo<T, D>::kRowBytes <= 256 ? 512 : 256; }
 
 template <typename T, int D>
 struct TileOps {
@@ -408,34 +419,37 @@ struct TileOps {
     // Diagonal tile: zero everything that is not strictly above the diagonal
     // (the walk only ever adds eta_j * g_jl for l > j) ...
     // Quadrant by quadrant: rows 0..31 x columns 32..63 lie above the diagonal as a whole, rows 32..63 x columns
-    // 0..31 below it as a whole; only the two diagonal quadrants need the per-entry test (local row < n in both).
+    // 0..31 below it as a whole and are not stored; only the two diagonal quadrants need the per-entry test (local row < n in both).
     static __device__ __forceinline__ void mask_diag(floatx16 (&v)[2][2], int n, int h) {
-        const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int lrow = 8 * (r >> 2) + 4 * h + (r & 3);                  // row inside its half
             v[0][0][r] = (n > lrow) ? v[0][0][r] : 0.f;
             v[1][1][r] = (n > lrow) ? v[1][1][r] : 0.f;
         }
-        v[1][0] = zero;
     }
-    // ... and store it transposed, diag[col * kDiagStride + row]: four consecutive rows per 16-byte store.
+    // ... and store one 32x32 quadrant of it (rows 32 QR.., columns 32 QC..), four consecutive rows per 16-byte store, as far as the
+    // walk reads it.
+    template <int QR, int QC>
+    static __device__ __forceinline__ void store_quadrant(float* diag, const floatx16& v, int n, int h) {
+        asm volatile("" : "+v"(n), "+v"(h));            // the addresses are formed here, not kept across the panels
+        const int k = 2 * QC + (n >> 4);
+        float* at = diag + ((k & 1) ? diag_quarter(2 * QC + 1) + (n & 15) * diag_stride(2 * QC + 1) : diag_quarter(2 * QC) + (n & 15) * diag_stride(2 * QC));
+        const int permuted = QC == 0 && n < 16 ? n & 12 : 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (QR < QC || q < 2 || (k & 1))
+                *reinterpret_cast<floatx4*>(at + ((32 * QR + 8 * q + 4 * h) ^ permuted)) = floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    }
     static __device__ __forceinline__ void store_diag(float* diag, const floatx16 (&v)[2][2], int n, int h) {
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    floatx4 t = {v[rb][cb][4 * q], v[rb][cb][4 * q + 1], v[rb][cb][4 * q + 2], v[rb][cb][4 * q + 3]};
-                    *reinterpret_cast<floatx4*>(diag + (32 * cb + n) * kDiagStride + 32 * rb + 8 * q + 4 * h) = t;
-                }
+        store_quadrant<0, 0>(diag, v[0][0], n, h);
+        store_quadrant<0, 1>(diag, v[0][1], n, h);
+        store_quadrant<1, 1>(diag, v[1][1], n, h);
     }
     // One 32x32 quadrant (rows 32 QR.., columns 32 QC..) of a diagonal tile, from the panel's rows in LDS straight to
     // the transposed tile buffer: the same arithmetic, in the same order, as tile<DIAG> + mask_diag + store_diag give
     // that quadrant.  Three wavefronts on three SIMDs form the first tile of a chunk this way, so that the walk starts
-    // after a third of the time one wavefront needs for the whole tile.  QR = QC = 0 also clears the quadrant below
-    // the diagonal.
+    // after a third of the time one wavefront needs for the whole tile.
     template <int QR, int QC>
     static __device__ __forceinline__ void diag_quadrant(float* diag, const char* lds_panel, const float* naP, float alpha,
                                                          float rc, const int (&foff)[G::kGroups], int n, int h) {
@@ -464,15 +478,92 @@ struct TileOps {
             const float w = fast_exp2(fmaf(acc[r], alpha, cc));
             acc[r] = (QR != QC || n > lrow) ? w : 0.f;
         }
+        store_quadrant<QR, QC>(diag, acc, n, h);
+    }
+    // ------------------------------------------------------------------------------------------------ half columns
+    // NRB x 32 rows (this lane's first at a) times 32 columns (this lane's at b) on top of acc; operands are requested kQuadAhead
+    // k-groups before their use.  The accumulators take turns: a chain of dependent matrix instructions leaves the pipe to
+    // the other wavefront of the SIMD between any two, and one that the walk waits for then takes twice as long.  fill(g) is
+    // work for the vector unit beside the matrix instructions of k-group g.
+    static constexpr int kQuadAhead = G::kGroups < 4 ? G::kGroups : 4;
+    template <int NRB, typename Fill>
+    static __device__ __forceinline__ void quads(floatx16 (&acc)[NRB], const char* a, const char* b, const int (&foff)[G::kGroups], Fill fill) {
+        constexpr int KG = G::kGroups;
+        Frag A[KG][NRB], B[KG];
+        auto load = [&](int g) {
+            B[g] = *reinterpret_cast<const Frag*>(b + foff[g]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const floatx4 t = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-            *reinterpret_cast<floatx4*>(diag + (32 * QC + n) * kDiagStride + 32 * QR + 8 * q + 4 * h) = t;
-            if (QR == 0 && QC == 0) {
-                const floatx4 z = {0.f, 0.f, 0.f, 0.f};
-                *reinterpret_cast<floatx4*>(diag + n * kDiagStride + 32 + 8 * q + 4 * h) = z;
-            }
+            for (int rb = 0; rb < NRB; ++rb) A[g][rb] = *reinterpret_cast<const Frag*>(a + (size_t)(32 * rb) * G::kLdsRow + foff[g]);
+        };
+#pragma unroll
+        for (int g = 0; g < kQuadAhead; ++g) load(g);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            if (g + kQuadAhead < KG) load(g + kQuadAhead);
+            Elem<T>::template mma_turns<NRB>(acc, A[g], B[g]);
+            fill(g);
+            __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    // Kernel weights of the 64 (NRB = 2) or first 32 (NRB = 1) rows of the panel at `rows` against the 32 columns whose rows start
+    // at `cols`, both in LDS; naR / naC: their -a_i.  With VG the value rows of both are at vrows / vcols.  The same
+    // arithmetic as tile(), entry by entry.
+    template <int NRB, bool VG>
+    static __device__ __forceinline__ void half_tile(floatx16 (&w)[NRB], const char* rows, const char* cols, const float* naR, const float* naC, float alpha, float rc,
+                                                     const int (&foff)[G::kGroups], int n, int h, const char* vrows, const char* vcols, float inv_rv2, float vg_bias) {
+        constexpr int KG = G::kGroups, RPI = 16 / KG;
+        const float cc = fmaf(alpha, naC[n], rc);
+        const size_t lane_row = (size_t)n * G::kLdsRow;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const floatx4 t = *reinterpret_cast<const floatx4*>(naR + 32 * rb + 8 * q + 4 * h);
+                w[rb][4 * q] = t[0]; w[rb][4 * q + 1] = t[1]; w[rb][4 * q + 2] = t[2]; w[rb][4 * q + 3] = t[3];
+            }
+        quads<NRB>(w, rows + lane_row, cols + lane_row, foff, [](int) {});
+        auto finish = [&](int g) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+                for (int r = g * RPI; r < (g + 1) * RPI; ++r) w[rb][r] = fast_exp2(fmaf(w[rb][r], alpha, cc));
+        };
+        if constexpr (!VG) {
+#pragma unroll
+            for (int g = 0; g < KG; ++g) finish(g);
+        } else {
+            floatx16 vg[NRB];
+            const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) vg[rb] = zero;
+            quads<NRB>(vg, vrows + lane_row, vcols + lane_row, foff, finish);
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) w[rb][r] *= fmaf(vg[rb][r], inv_rv2, vg_bias);
+        }
+    }
+    // Column half QC of a diagonal tile (rows 0 .. 32 QC + 31 of its panel at `panel`), zero where the row is not before the
+    // column.  QR >= 0: only the quadrant of row half QR.  free() waits for the buffer.
+    template <int QC, int QR, bool VG, typename Free>
+    static __device__ __forceinline__ void half_diag(float* diag, const char* panel, const float* naP, float alpha, float rc, const int (&foff)[G::kGroups], int n, int h,
+                                                     const char* vpanel, float inv_rv2, float vg_bias, Free free) {
+        constexpr int first = QR >= 0 ? QR : 0, NRB = QR >= 0 ? 1 : QC + 1;
+        floatx16 w[NRB];
+        half_tile<NRB, VG>(w, panel + first * 32 * G::kLdsRow, panel + QC * 32 * G::kLdsRow, naP + 32 * first, naP + 32 * QC, alpha, rc, foff, n, h,
+                           VG ? vpanel + first * 32 * G::kLdsRow : nullptr, VG ? vpanel + QC * 32 * G::kLdsRow : nullptr, inv_rv2, vg_bias);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (first + NRB - 1 == QC) {
+                const int lrow = 8 * (r >> 2) + 4 * h + (r & 3);
+                w[NRB - 1][r] = n > lrow ? w[NRB - 1][r] : 0.f;
+            }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) asm volatile("" : "+v"(w[rb]));        // complete before the wait
+        free();
+        if constexpr (first == 0) store_quadrant<0, QC>(diag, w[0], n, h);
+        if constexpr (first + NRB - 1 == 1) store_quadrant<1, QC>(diag, w[NRB - 1], n, h);
     }
 };
 
@@ -482,41 +573,17 @@ struct TileOps {
 __device__ __forceinline__ unsigned int lds_offset(const void* p) {
     return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
-// the walker's column of the diagonal tile (16 x 16 bytes) once `counter` >= value
-__device__ __forceinline__ void await_and_read_tile(int* counter, int value, const float* tile_col, float (&g)[64], int* err) {
-    const unsigned int a0 = lds_offset(counter), a2 = lds_offset(tile_col);
-    floatx4 q0, q1, q2, q3, q4, q5, q6, q7, q8, q9, q10, q11, q12, q13, q14, q15;
-    bool ok = false;
-    for (int it = 0; it < kSpinLimit && !ok; ++it) {
-        int s0;
-        asm volatile("ds_read_b32 %0, %17\n\t"
-                     "ds_read_b128 %1, %18\n\tds_read_b128 %2, %18 offset:16\n\tds_read_b128 %3, %18 offset:32\n\tds_read_b128 %4, %18 offset:48\n\t"
-                     "ds_read_b128 %5, %18 offset:64\n\tds_read_b128 %6, %18 offset:80\n\tds_read_b128 %7, %18 offset:96\n\tds_read_b128 %8, %18 offset:112\n\t"
-                     "ds_read_b128 %9, %18 offset:128\n\tds_read_b128 %10, %18 offset:144\n\tds_read_b128 %11, %18 offset:160\n\tds_read_b128 %12, %18 offset:176\n\t"
-                     "ds_read_b128 %13, %18 offset:192\n\tds_read_b128 %14, %18 offset:208\n\tds_read_b128 %15, %18 offset:224\n\tds_read_b128 %16, %18 offset:240\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(s0), "=&v"(q0), "=&v"(q1), "=&v"(q2), "=&v"(q3), "=&v"(q4), "=&v"(q5), "=&v"(q6), "=&v"(q7),
-                       "=&v"(q8), "=&v"(q9), "=&v"(q10), "=&v"(q11), "=&v"(q12), "=&v"(q13), "=&v"(q14), "=&v"(q15)
-                     : "v"(a0), "v"(a2) : "memory");
-        ok = __builtin_amdgcn_readfirstlane(s0) >= value;
-    }
-    if (!ok) __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const floatx4 q[16] = {q0, q1, q2, q3, q4, q5, q6, q7, q8, q9, q10, q11, q12, q13, q14, q15};
-#pragma unroll
-    for (int t = 0; t < 16; ++t) { g[4 * t] = q[t][0]; g[4 * t + 1] = q[t][1]; g[4 * t + 2] = q[t][2]; g[4 * t + 3] = q[t][3]; }
-}
-// one float once `counter` >= value
-__device__ __forceinline__ float await_and_read(int* counter, int value, const float* data, int* err) {
+// sigma of tokens 16 k + lane % 16, k = 0..3, once `counter` >= value (data: this lane's first one)
+__device__ __forceinline__ void await_and_read4(int* counter, int value, const float* data, float (&x)[4], int* err) {
     const unsigned int ca = lds_offset(counter), da = lds_offset(data);
-    float x = 0.f;
     for (int it = 0; it < kSpinLimit; ++it) {
         int seen;
-        asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(seen), "=&v"(x) : "v"(ca), "v"(da) : "memory");
-        if (__builtin_amdgcn_readfirstlane(seen) >= value) return x;
+        asm volatile("ds_read_b32 %0, %5\n\tds_read_b32 %1, %6\n\tds_read_b32 %2, %6 offset:64\n\tds_read_b32 %3, %6 offset:128\n\t"
+                     "ds_read_b32 %4, %6 offset:192\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(seen), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]) : "v"(ca), "v"(da) : "memory");
+        if (__builtin_amdgcn_readfirstlane(seen) >= value) return;
     }
     __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    return x;
 }
 
 // MULTI = false: the launcher guarantees b <= chunk_rows (the block is resident in LDS as one chunk), and the
@@ -525,10 +592,12 @@ __device__ __forceinline__ float await_and_read(int* counter, int value, const f
 // whose values fit LDS too): the block's value rows are staged in LDS behind the key rows.  VG = 2 (any block): the
 // value panels of every tile are read from global memory (L2) as they are needed.
 // CARRY: survivors go to the front of their own block (CompressArgs::carry_w).
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false>
+// HALF: blocks (or chunks) of at most four panels, dealt out to the wavefronts as half columns.
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false>
 __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a) {
     static_assert(VG == 0 || !EMIT_G, "the weight dump has no values");
     static_assert(VG != 1 || !MULTI, "values in LDS: resident blocks only");
+    static_assert(!HALF || (!EMIT_G && VG != 2 && (!MULTI || G_rows<T, D>() <= 256)), "at most four panels at a time");
     typedef Geo<T, D> G;
     typedef TileOps<T, D> Ops;
     typedef typename Elem<T>::Frag Frag;
@@ -545,13 +614,13 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     float* narow = sigma + b;                                      // -a_i of every row (a_i = <k_i, mu>)
     unsigned long long* etaMask = reinterpret_cast<unsigned long long*>(narow + b);   // bit j of entry I: eta of token 64 I + j is +1
     float* etaF = reinterpret_cast<float*>(etaMask + 16);          // [8][2][32]: +-1 of the chunk's panel l, entry h*32 + 16*rb + r
-    float* diag = etaF + 512;                                      // [64 columns][kDiagStride], transposed
-    float* scal = diag + kDiagFloats;                              // [0] |mu|^2, [1] A, [2..2+kWaves) partial maxima
+    float* diag = etaF + 512;                                      // two diagonal tiles
+    float* scal = diag + kDiagArea;                              // [0] |mu|^2, [1] A, [2..2+kWaves) partial maxima
     int* prog = reinterpret_cast<int*>(scal + 16);                 // progress counters, see the panel pipeline below
     float* wpart = diag;                                           // [kWaves][D] column sums (statistics phase only)
     int* keptIdx = reinterpret_cast<int*>(diag);                   // [b/2]        (output phase only)
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: roles branch on scalars
     const int n = lane & 31, h = lane >> 5;
     const int64_t inst = blockIdx.x;
@@ -577,7 +646,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     // without idx_in a token's index within its sequence is its place in the input: by block number, or (ragged
     // launches, keys and values stored side by side) the instance's first token less the start of its sequence
     const int64_t tok_base = a.desc ? in_tok0 - seq * a.v_seq_stride : a.idx_base + (int64_t)blk * b;
-    const int sl = tid % SL, rg = tid / SL;
+    int sl = tid % SL, rg = tid / SL;
     const bool center = (a.flags & BKV_CENTER_KEYS) != 0;
     const bool need_norm = !(a.rkey2 > 0.f);
     const bool single_chunk = MULTI ? (CH == b) : true;
@@ -611,9 +680,16 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         return ldsK + (size_t)r * G::kLdsRow;
     };
 
-    // sigma starts at minus the threshold: the walk tests (sum of signed weights - threshold) < 0.  Integer work,
-    // done first so that it overlaps the latency of the loads below.
-    for (int i = tid; i < b; i += kThreads) sigma[i] = 0.f - threshold(i);      // never -0: the sign bit alone decides
+    // sigma starts at minus the threshold: the walk tests (sum of signed weights - threshold) < 0.  Integer work of about 1k clocks,
+    // done while the first rows are on their way.  (Every thread takes part in every step, the last token's again behind the
+    // end: a loop that lanes leave one by one ends with none of them active, and a register spilled there is lost.)
+    auto thresholds = [&]() {
+#pragma unroll 1
+        for (int i0 = 0; i0 < b; i0 += kThreads) {
+            const int i = min(i0 + tid, b - 1);
+            sigma[i] = 0.f - threshold(i);                                       // never -0: the sign bit alone decides
+        }
+    };
 
     // column sums for the block mean, accumulated while rows pass through the registers
     float part[EPL];
@@ -623,7 +699,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     const int n_chunks = MULTI ? (b + CH - 1) / CH : 1;
     // Rows [row0, row0 + rows_here) of the block -> LDS, many rows in flight per thread; the first rows_sum rows
     // from row0 (possibly more than are staged) also enter the column sums of the mean.
-    auto stage_chunk = [&](int row0, int rows_here, int rows_sum) {
+    auto stage_chunk = [&](int row0, int rows_here, int rows_sum, auto meanwhile) {
         constexpr int U = 16;
         const int rows_all = max(rows_here, rows_sum);
         for (int i0 = rg; i0 < rows_all; i0 += RG * U) {
@@ -638,6 +714,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     raw[u] = *reinterpret_cast<const uintx4*>(src + sl * 16);
                 }
             }
+            if (i0 == rg) meanwhile();                              // (b and RG are such that all threads are in the first round)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = i0 + u * RG;
@@ -666,6 +743,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (i < b) raw[u] = *reinterpret_cast<const uintx4*>(Kin + (size_t)i * G::kRowBytes + sl * 16);
             else raw[u] = uintx4{0u, 0u, 0u, 0u};                // (rows past the block's end: defined, never counted)
         }
+        thresholds();
 #pragma unroll
         for (int u = 0; u < kU2; ++u) {
             const int i = rg + u * RG;
@@ -674,7 +752,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (center && i < b) Elem<T>::accumulate(part, raw[u]);
         }
     } else {
-        stage_chunk(0, min(CH, b), center ? b : 0);
+        stage_chunk(0, min(CH, b), center ? b : 0, thresholds);
     }
     // Value factor: the value row of every token of the block -> LDS (the row of token i is the ORIGINAL row of that
     // token, as in the gather at the end); |v_i|^2 on the way when r_value has to be measured.
@@ -704,7 +782,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             }
         }
         vmax = wave_max(vmax);
-        if (lane == 0) diag[kDiagFloats - 64 + wave] = vmax;   // the tail of the buffer: beyond the mean partials
+        if (lane == 0) diag[kDiagArea - 64 + wave] = vmax;   // the tail of the buffer: beyond the mean partials
     }
     if (center) {                        // column sums of every wavefront -> LDS
 #pragma unroll
@@ -921,9 +999,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         if constexpr (VG != 0) {                                // 1 / r_value^2: given, or the largest |v_i|^2 of the block
             float r2 = rvalue2;
             if (!(r2 > 0.f)) {
-                r2 = diag[kDiagFloats - 64];
+                r2 = diag[kDiagArea - 64];
 #pragma unroll
-                for (int w = 1; w < kWaves; ++w) r2 = fmaxf(r2, diag[kDiagFloats - 64 + w]);
+                for (int w = 1; w < kWaves; ++w) r2 = fmaxf(r2, diag[kDiagArea - 64 + w]);
             }
             inv_rv2 = r2 > 0.f ? 1.f / r2 : 0.f;               // all values zero: every weight is zero
             if (a.flags & BKV_VALUE_AUGMENT) {                  // value [v / r ; 1], radius^2 = 2 (or 1 when all values are zero)
@@ -965,7 +1043,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         const int p0 = row0 >> 6, p1 = (row0 + rows_here) >> 6;
         if (c > 0) {
             __syncthreads();                           // previous users of ldsK are done
-            if (!pre_on) stage_chunk(row0, rows_here, 0);      // (else the previous pipeline has brought the rows in already)
+            if (!pre_on) stage_chunk(row0, rows_here, 0, []() {});      // (else the previous pipeline has brought the rows in already)
             if (tid < 32 && tid != 3) prog[tid] = 0;   // progress counters of this chunk's pipeline (the error flag is sticky)
             __syncthreads();
         }
@@ -1035,7 +1113,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         // ---------------------------------------------------------- panels of this chunk: a dataflow pipeline
         // No barriers in here.  Counters (all start at 0, local panel index l = I - p0):
         //   eta_done      panels walked so far (the walker publishes after writing the signs of panel l)
-        //   diag_ready    diagonal tiles stored so far        diag_taken   diagonal tiles the walker has loaded so far
+        //   tile_parts[l] parts of diagonal tile l stored so far (three quadrants from three wavefronts, or the tile in one)
+        //   diag_taken    diagonal tiles the walker has loaded so far
         //   col[l]        set to l by the owner of column panel l once sigma of that panel holds every earlier row panel
         //   rowp[w]       row panels whose LDS rows column owner w has read for the last time (only where the next chunk is
         //                 brought in during this pipeline, see kPre)
@@ -1049,32 +1128,39 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         // its contributions in the same order on every run.  At most one tile per wavefront and walked panel is due,
         // so the walk (wavefront 0) only ever waits for the tile (l-1, l) that depends on its last signs.
         int* eta_done = prog;
-        int* diag_ready = prog + 1;
         int* diag_taken = prog + 2;
         int* sync_err = prog + 3;
-        int* first_parts = prog + 4;                  // quadrants of the chunk's first diagonal tile stored so far (three writers)
         int* col = prog + 8;
         int* rowp = prog + 16;                        // rowp[w]: row panels whose LDS rows column owner w needs no more
+        int* tile_parts = prog + 24;
+        constexpr bool kHalf = HALF;
         constexpr bool kSplitFirst = !EMIT_G && VG == 0;   // the first tile comes in three quadrants from three wavefronts
+        constexpr bool kJoin = !EMIT_G && VG == 0 && sizeof(T) == 2 && !MULTI;
         const int nPc = p1 - p0;
         const int next0 = row0 + rows_here;                                           // first row of the next chunk
         const int nN = pre_on && c + 1 < n_chunks ? (min(CH, b - next0) >> 6) : 0;    // its panels (0: nothing to bring in)
         if (wave == 0) {
-            unsigned int sign_bit = 0x80000000u;
-            asm volatile("" : "+s"(sign_bit));             // stays in a scalar register
             __builtin_amdgcn_s_setprio(3);                    // the serial chain goes first on its SIMD
             for (int l = 0; l < nPc; ++l) {
                 const int I = p0 + l;
                 // ------------------------------------------------ the walk over panel I (Alg. 2 lines 4-11)
-                // this lane's column of the diagonal tile: g[j] = g_{j,lane} for j < lane, else 0
                 // sigma holds (sum of signed weights so far) - (1 - 2 u): eta = +1 <=> u < 1/2 - s/2 <=> sigma < 0; it is
                 // complete when the owner of this column panel says so (col[l] == l)
-                float g[64];
-                if (kSplitFirst && l == 0) await_and_read_tile(first_parts, 3, diag + lane * kDiagStride, g, sync_err);
-                else await_and_read_tile(diag_ready, l + 1, diag + lane * kDiagStride, g, sync_err);
-                publish(diag_taken, l + 1);                   // the tile is in registers: the buffer may be overwritten
-                float sv = await_and_read(col + l, l, sigma + (I << 6) + lane, sync_err);
-                walk_panel(sv, g, sign_bit);
+                WalkStart start;
+                float s[4];
+                const float* column = diag + (l & 1) * kDiagFloats;
+                int c16 = lane & 15;
+                asm volatile("" : "+v"(c16));              // (the addresses are formed here)
+                const float* quarter[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) quarter[k] = column + diag_quarter(k) + c16 * diag_stride(k);
+                const auto tile = [&](int m, int k, int q) -> floatx4 { return *reinterpret_cast<const floatx4*>(quarter[k] + (k == 0 ? (4 * q) ^ (c16 & 12) : 16 * m + 4 * q)); };
+                if constexpr (kHalf) await<true>(tile_parts + l, l != 1 || nPc == 2 ? 3 : 2, sync_err);
+                else await<true>(tile_parts + l, kSplitFirst && l == 0 ? 3 : 1, sync_err);
+                walk_begin(start, tile);
+                await_and_read4(col + l, kHalf && l > 0 ? 2 : l, sigma + (I << 6) + (lane & 15), s, sync_err);
+                // (once the tile is in registers the buffer may be overwritten)
+                const float sv = walk_quarters(s, lane, start, tile, [&]() { publish(diag_taken, l + 1); });
                 const unsigned long long m = __ballot(sv < 0.f);
                 if (lane == 0) etaMask[I] = m;
                 {
@@ -1112,6 +1198,87 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     for (int j = 0; j < PF; ++j) pfv0[j] = *reinterpret_cast<const int*>(Kpf + (size_t)(p0 << 6) * G::kRowBytes + j * 1024);
                 }
             }
+            if constexpr (kHalf) {
+                // A half column (w, cb): columns 32 cb .. 32 cb + 31 of column panel w, w = 1 .. 3 (four panels at most).  Its owner forms
+                // the 64x32 tiles (i, w), i < w, in row order and adds up the signed sums, which are those of the whole column
+                // panel in the same order.  In quadrants of 32x32 the column (w, cb) is 2 w, the diagonal tile of a panel three.
+                // A wavefront for each half column, spread so that the SIMDs get 7 (the walker's) to 11 quadrants of four panels.  The
+                // diagonal tile of panel 1 comes from its owners, that of panel 2 from wavefront 1, that of panel 3 from the owners
+                // of column 1, who are done by then.
+                const bool two_panels = nPc == 2;                 // then nobody is short of time: the second diagonal tile has three makers too
+                // wavefronts of half columns 0, 1, ..: 6 7 | 6 7 5 4 | 6 7 3 2 5 4
+                const int item = w >= 6 ? w - 6 : w >= 4 ? (nPc == 3 ? 7 - w : 9 - w) : w >= 2 && nPc == 4 ? 5 - w : -1;
+                const int wc = item >= 0 ? 1 + (item >> 1) : nPc, cb = item & 1;                                 // (nPc: no column)
+                auto v_lds = [&](int r) -> const char* { asm volatile("" : "+s"(r)); return VG == 1 ? ldsV + (size_t)r * G::kLdsRow : nullptr; };
+                auto part_done = [&](int l) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    if (lane == 0) __hip_atomic_fetch_add(tile_parts + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                };
+                // a quadrant (qr, qc) of the diagonal tile of panel l, stored once its buffer's previous tile is in the walker's registers
+                auto one_quadrant = [&](auto qr, auto qc, int l) {
+                    Ops::template half_diag<decltype(qc)::value, decltype(qr)::value, VG == 1>(diag + (l & 1) * kDiagFloats, lds_rows(l << 6), narow + ((p0 + l) << 6), alpha,
+                                                                                               row_const, foff, n, h, v_lds(l << 6), inv_rv2, vg_bias,
+                                                                                               [&]() { await(diag_taken, l - 1, sync_err); });
+                    part_done(l);
+                };
+                constexpr std::integral_constant<int, 0> c0{};
+                constexpr std::integral_constant<int, 1> c1{};
+                // the walk cannot start without the first tile: three wavefronts take a quadrant each
+                if (w == 1) one_quadrant(c0, c0, 0);
+                else if (w == 4) one_quadrant(c0, c1, 0);
+                else if (w == 5) one_quadrant(c1, c1, 0);
+                if (two_panels) {
+                    if (w == 1) one_quadrant(c0, c0, 1);
+                    else if (w == 2) one_quadrant(c0, c1, 1);
+                    else if (w == 3) one_quadrant(c1, c1, 1);
+                }
+                if (wc < nPc) {
+                    float sig = sigma[((p0 + wc) << 6) + 32 * cb + n];
+                    for (int i = 0; i < wc; ++i) {
+                        const bool urgent = i == wc - 1;           // the walker is waiting for this one
+                        floatx16 acc[2];
+                        Ops::template half_tile<2, VG == 1>(acc, lds_rows(i << 6), lds_rows((wc << 6) + 32 * cb), narow + ((p0 + i) << 6), narow + ((p0 + wc) << 6) + 32 * cb, alpha,
+                                                            row_const, foff, n, h, v_lds(i << 6), v_lds((wc << 6) + 32 * cb), inv_rv2, vg_bias);
+                        // the weights are complete here: the compiler must not sink their arithmetic below the wait
+                        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
+                        if (wc == 1 && !two_panels) {
+                            float* dt = diag + kDiagFloats;
+                            auto free = [&]() { await(diag_taken, 0, sync_err); };
+                            if (cb == 0) Ops::template half_diag<0, -1, VG == 1>(dt, lds_rows(64), narow + ((p0 + 1) << 6), alpha, row_const, foff, n, h, v_lds(64), inv_rv2, vg_bias, free);
+                            else Ops::template half_diag<1, -1, VG == 1>(dt, lds_rows(64), narow + ((p0 + 1) << 6), alpha, row_const, foff, n, h, v_lds(64), inv_rv2, vg_bias, free);
+                            part_done(1);
+                        }
+                        if (urgent) { __builtin_amdgcn_s_setprio(3); await<true>(eta_done, i + 1, sync_err); }
+                        else await(eta_done, i + 1, sync_err);
+                        const float* sgn = etaF + (i << 6) + 32 * h;
+                        float cs = 0.f;
+#pragma unroll
+                        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const floatx4 t = *reinterpret_cast<const floatx4*>(sgn + 16 * rb + 4 * q);
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) cs = fmaf(t[r], acc[rb][4 * q + r], cs);
+                            }
+                        sig += xor_sum<32>(cs);
+                        if (urgent) {
+                            sigma[((p0 + wc) << 6) + 32 * cb + n] = sig;                          // (both lane halves: the same value)
+                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");      // (in order, see publish_in_order)
+                            if (lane == 0) __hip_atomic_fetch_add(col + wc, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            __builtin_amdgcn_s_setprio(0);
+                        }
+                    }
+                }
+                if (w == 1 && nPc > 2) {
+                    one_quadrant(c0, c0, 2);
+                    one_quadrant(c0, c1, 2);
+                    one_quadrant(c1, c1, 2);
+                }
+                if (nPc > 3) {
+                    if (w == 6) { one_quadrant(c0, c0, 3); one_quadrant(c0, c1, 3); }
+                    else if (w == 7) one_quadrant(c1, c1, 3);
+                }
+            } else {
             // diagonal tile of local panel l from the panel's fragments P (both operands), stored in turn
             auto diagonal = [&](const Frag (&P)[G::kGroups][2], int l) {
                 const int I = p0 + l;
@@ -1134,9 +1301,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 Ops::mask_diag(dv, n, h);
                 // the tile is complete here: the compiler must not sink its arithmetic below the wait
                 asm volatile("" : "+v"(dv[0][0]), "+v"(dv[0][1]), "+v"(dv[1][0]), "+v"(dv[1][1]));
-                await(diag_taken, l, sync_err);               // the walker holds the previous tile in registers
-                Ops::store_diag(diag, dv, n, h);
-                publish(diag_ready, l + 1);
+                await(diag_taken, l - 1, sync_err);   // the walker holds the buffer's previous tile in registers
+                Ops::store_diag(diag + (l & 1) * kDiagFloats, dv, n, h);
+                publish(tile_parts + l, 1);
             };
             Frag Bq[G::kGroups][2];                        // (not with Ops::kStream)
             // Start-up: the diagonal tile of panel 1 (and, where it is not split, that of panel 0) comes from the
@@ -1149,7 +1316,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 else if (w == 2) Ops::template diag_quadrant<0, 1>(diag, lds_rows(0), ap0, alpha, row_const, foff, n, h);
                 else Ops::template diag_quadrant<1, 1>(diag, lds_rows(0), ap0, alpha, row_const, foff, n, h);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                if (lane == 0) __hip_atomic_fetch_add(first_parts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (lane == 0) __hip_atomic_fetch_add(tile_parts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 __builtin_amdgcn_s_setprio(0);
             }
             if (w >= kWaves - 2 && kWaves - 1 - w < nPc && !(kSplitFirst && w == kWaves - 1)) {
@@ -1165,6 +1332,20 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 for (int i = 0; i < w; ++i) {
                     const int Ii = p0 + i;
                     floatx16 acc[2][2];
+                    // The later columns run behind the walk: where the signs of row panel i are there already, they join the
+                    // tile's exponentials and nothing is waited for (a look at the counter, the signs and the sums by themselves
+                    // take 0.9k clocks of 2.7k a tile).
+                    if (kJoin && __builtin_amdgcn_readfirstlane(__hip_atomic_load(eta_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > i) {
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                        sig += Ops::template tile<true, false, !Ops::kStream, false, VG>(acc, nullptr, lds_rows(i << 6), Ops::kStream ? lds_rows(w << 6) : nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
+                                                                      nullptr, etaF + (i << 6) + 32 * h, foff, n, h, Bq);
+                        if (kPre && nN > 0) publish_in_order(rowp + w, i + 1);
+                        if (i == w - 1) {
+                            sigma[(J << 6) + lane] = sig;
+                            publish_in_order(col + w, w);
+                        }
+                        continue;
+                    }
                     Ops::template tile<false, false, !Ops::kStream, false, VG>(acc, nullptr, lds_rows(i << 6), Ops::kStream ? lds_rows(w << 6) : nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
                                                                       nullptr, nullptr, foff, n, h, Bq,
                                                                       VG == 1 ? ldsV + (size_t)(i << 6) * G::kLdsRow : VG == 2 ? vrow((Ii << 6) + n) : nullptr,
@@ -1207,6 +1388,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     diagonal(Bq, l);
                 }
             }
+            }
 #pragma unroll
             for (int j = 0; j < PF; ++j) pfacc ^= pfv[j] ^ pfv0[j];
             asm volatile("" :: "v"(pfacc));                   // the touches must not be optimised away
@@ -1226,8 +1408,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                         for (int v = (q == 7 ? 7 : q + 1); v < 8; ++v)
                             if (v != w) await(rowp + v, need, sync_err);
                         if (q >= 1 && q != 7) await(rowp + q, 1, sync_err);
-                        if (q == 0) await(first_parts, 3, sync_err);
-                        else if (q != 7) await(diag_ready, q + 1, sync_err);
+                        if (q == 0) await(tile_parts, 3, sync_err);
+                        else if (q != 7) await(tile_parts + q, 1, sync_err);
                         uintx4 t[16];
                         const char* src = Kin + (size_t)(next0 + (q << 6) + r_w) * G::kRowBytes + s_w * 16;
 #pragma unroll
@@ -1244,6 +1426,15 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         __syncthreads();                                   // the chunk is done: LDS rows, counters and tile buffer are free
     }
 
+    // The thread's coordinates, formed anew: kept in registers (and what the compiler derives from them) through the pipeline they
+    // went to scratch memory in the instances that have none to spare.
+    {
+        unsigned int ones = ~0u;
+        asm volatile("" : "+s"(ones));
+        lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
+        tid = (wave << 6) + lane;
+        sl = tid % SL; rg = tid / SL;
+    }
     // ------------------------------------------------------------------ output step (Alg. 2 lines 12-16 + strict n/2)
     // Every wavefront handles the panels p = wave, wave + 8, ...: minority sign ('+' on ties), then exactly
     // b/2 survivors = the minority class plus the lowest-index majority tokens, ascending.
@@ -1380,18 +1571,29 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false>
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false>
 static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t st) {
-    const size_t lds = compress_lds_bytes(Geo<T, D>::kRowBytes, a.b, VG == 1);
-    auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG, CARRY>;
-    static thread_local size_t configured = 0;
-    if (lds > configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        configured = lds;
+    // Half columns where a tile takes long (single precision, the value factor with the values in LDS) and a chunk has at most four
+    // panels: whole call, 4 blocks of 256 fp32 rows, d = 64: 29.3 -> 24.0 us; 256 of 256 bf16 rows with the value factor 25.4 -> 21.2
+    // (2048 of them 185 -> 155); 96 of 384 fp32 rows, d = 128: 81 -> 66.  With eight panels there are two half columns to a wavefront and twice the operand reads of whole ones: 128 blocks
+    // of 512 rows, d = 64, value factor, 27.4 -> 31.4 us, 64 of 1024 fp32 rows 180 -> 190: whole columns.
+    constexpr bool may = !EMIT_G && (VG == 1 || (VG == 0 && sizeof(T) == 4)) && (!MULTI || G_rows<T, D>() <= 256);
+    constexpr bool always = may && Geo<T, D>::kRowBytes * (VG == 1 ? 2 : 1) >= 512;         // more than 256 such rows never are in LDS
+    if constexpr (may && !HALF) {
+        if (always || a.chunk_rows <= 256) return launch_one<T, D, EMIT_G, MULTI, VG, CARRY, true>(a, n_inst, st);
     }
-    return launch_timed(kProfCompress, n_inst * a.b, kern, dim3((unsigned)n_inst), dim3(kThreads), lds, st, a);
+    if constexpr (HALF || !always) {
+        const size_t lds = compress_lds_bytes(Geo<T, D>::kRowBytes, a.b, VG == 1);
+        auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG, CARRY, HALF>;
+        static thread_local size_t configured = 0;
+        if (lds > configured) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            configured = lds;
+        }
+        return launch_timed(kProfCompress, n_inst * a.b, kern, dim3((unsigned)n_inst), dim3(kThreads), lds, st, a);
+    }
 }
 
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st) {

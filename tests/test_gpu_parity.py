@@ -146,6 +146,27 @@ def test_compress_block_teacher_forced(bk, synth, oracle, dtype, d, b, n_inst, c
             assert abs(u[t, first] - free["p"][t, first]) < MARGIN
 
 
+# panels dealt out as half columns (one to four at a time): single precision, and the value factor with the values in LDS
+@pytest.mark.parametrize("dtype,d,b,value", [(torch.float32, d, b, False) for d in (64, 128) for b in (64, 128, 192, 256)] +
+                         [(torch.float32, 128, 448, False), (torch.float32, 64, 192, True), (torch.float32, 128, 128, True),
+                          (torch.bfloat16, 128, 128, True), (torch.bfloat16, 128, 192, True), (torch.bfloat16, 64, 256, True)])
+def test_half_columns(bk, synth, oracle, dtype, d, b, value):
+    n_inst = 3
+    K, V = _blocks(synth, dtype, d, b, n_inst, seed=11 + b + d)
+    Kd, Vd = to_f64(K), to_f64(V)
+    _, log_c = _log_c_setting(oracle, "tuned", Kd, b, True)
+    seed = 0x5EED + b
+    p = bk.make_params(d, b, 1, dtype, log_c=log_c, seed=seed, center=True, value_gram=value)
+    out = bk.compress_block(p, K, V)
+    u = np.stack([oracle.uniform_fill(seed, t, 0, b) for t in range(n_inst)])
+    signs = out["signs"].cpu().numpy()
+    chk = oracle.softmax_balance_batch(Kd, Vd if value else None, u=u, log_c=log_c, center=True, forced=signs)
+    hard = (chk["dec"] != signs) & (np.abs(u - chk["p"]) >= 1e-4)
+    assert not hard.any()
+    assert not (out["status"].cpu().numpy() & 2).any()         # BKV_STATUS_INTERNAL: a wait inside the block ran out
+    np.testing.assert_array_equal(out["idx"].cpu().numpy(), expected_survivors(oracle, signs))
+
+
 @pytest.mark.parametrize("dtype,d,b,center,r_key", [
     (torch.bfloat16, 128, 64, True, 0.0), (torch.bfloat16, 128, 256, False, 0.0), (torch.bfloat16, 128, 320, True, 0.0),     # one chunk: 1, 4, 5
     (torch.bfloat16, 128, 512, True, 9.0), (torch.float32, 64, 64, True, 0.0), (torch.float32, 64, 512, False, 9.0),         # ... and 8 panels
