@@ -20,6 +20,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <utility>
 
 #include "bkv_device.h"
 #include "bkv_host.h"
@@ -93,35 +94,51 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
         const int q = c / CG, col = 4 * (c - q * CG);
         const float* row = part + (size_t)q * P;
         if (sg < SR && c < C) {
-// (twelve splits requested before the first is used: device-scope loads are not reordered by the compiler)
-            constexpr int U = 12;
-            for (int s = sg; s < ns0; s += U * SR) {
-                floatx2 ml[U], x[U], y[U];
+// All of a thread's splits are requested before the first is used (device-scope loads are not reordered by the
+            // compiler), up to twelve at a time, and no more of them than there are: each is a trip past the caches for the whole
+            // wavefront.
+            auto numerator = [&](auto u_c) {
+                constexpr int U = decltype(u_c)::value;
+                for (int s = sg; s < ns0; s += U * SR) {
+                    floatx2 ml[U], x[U], y[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const float* r = row + (size_t)min(s + u * SR, ns0 - 1) * sstride;
-                    ml[u] = get2(r + D); x[u] = get2(r + col); y[u] = get2(r + col + 2);
+                    for (int u = 0; u < U; ++u) {
+                        const float* r = row + (size_t)min(s + u * SR, ns0 - 1) * sstride;
+                        ml[u] = get2(r + D); x[u] = get2(r + col); y[u] = get2(r + col + 2);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (s + u * SR >= ns0) break;
+                        const float mn = fmaxf(M, ml[u][0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(ml[u][0] - mn);
+                        M = mn; L = L * f0 + ml[u][1] * f1;
+                        acc[0] = acc[0] * f0 + x[u][0] * f1; acc[1] = acc[1] * f0 + x[u][1] * f1;
+                        acc[2] = acc[2] * f0 + y[u][0] * f1; acc[3] = acc[3] * f0 + y[u][1] * f1;
+                    }
                 }
+            };
+            auto denominator = [&](auto u_c) {
+                constexpr int U = decltype(u_c)::value;
+                for (int s = ns0 + sg; s < ns0 + ns1; s += U * SR) {
+                    floatx2 ml[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (s + u * SR >= ns0) break;
-                    const float mn = fmaxf(M, ml[u][0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(ml[u][0] - mn);
-                    M = mn; L = L * f0 + ml[u][1] * f1;
-                    acc[0] = acc[0] * f0 + x[u][0] * f1; acc[1] = acc[1] * f0 + x[u][1] * f1;
-                    acc[2] = acc[2] * f0 + y[u][0] * f1; acc[3] = acc[3] * f0 + y[u][1] * f1;
+                    for (int u = 0; u < U; ++u) ml[u] = get2(row + (size_t)min(s + u * SR, ns0 + ns1 - 1) * sstride + D);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (s + u * SR >= ns0 + ns1) break;
+                        const float mn = fmaxf(Md, ml[u][0]);
+                        Ld = Ld * fast_exp2(Md - mn) + ml[u][1] * fast_exp2(ml[u][0] - mn);
+                        Md = mn;
+                    }
                 }
-            }
-            for (int s = ns0 + sg; s < ns0 + ns1; s += U * SR) {
-                floatx2 ml[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) ml[u] = get2(row + (size_t)min(s + u * SR, ns0 + ns1 - 1) * sstride + D);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (s + u * SR >= ns0 + ns1) break;
-                    const float mn = fmaxf(Md, ml[u][0]);
-                    Ld = Ld * fast_exp2(Md - mn) + ml[u][1] * fast_exp2(ml[u][0] - mn);
-                    Md = mn;
-                }
+            };
+            const int per = (ns0 + SR - 1) / SR;                      // splits of a thread
+            if (per <= 2) numerator(std::integral_constant<int, 2>{});
+            else if (per <= 4) numerator(std::integral_constant<int, 4>{});
+            else if (per <= 6) numerator(std::integral_constant<int, 6>{});
+            else numerator(std::integral_constant<int, 12>{});
+            if (ns1 > 0) {
+                if (ns1 <= 4 * SR) denominator(std::integral_constant<int, 4>{});
+                else denominator(std::integral_constant<int, 12>{});
             }
         }
         if (SR > 1) {
