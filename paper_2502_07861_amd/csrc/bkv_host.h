@@ -74,7 +74,7 @@ size_t compress_lds_bytes(int row_bytes, int b, bool value_gram = false);
 bool compress_value_gram_fits(int row_bytes, int b);   // keys and values of one block resident in LDS together
 bool compress_block_resident(int row_bytes, int b, bool value_gram);   // the block runs as one resident chunk
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st);
-// two blocks per compute unit (compress_pair.hip): rows of 256 bytes, no weight dump, value factor, table or scattered rows
+// two blocks per compute unit (compress_pair.hip): rows of 256 bytes, no weight dump, value factor, in-place carry or scattered rows
 hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t n_inst, hipStream_t st);
 hipError_t launch_fill_u32(void* p, uint32_t v, int64_t n, hipStream_t st);
 hipError_t launch_copy_rows(const void* src, void* dst, int64_t n_seq, int64_t src_seq_stride,

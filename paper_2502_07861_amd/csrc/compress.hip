@@ -1623,7 +1623,7 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
         // 528 blocks: 0.97 to 1.00; 560 on: 1.01 to 1.04), and single precision beyond one chunk (b > 512: between 20 %
         // slower and 10 % faster; there a wavefront's tile takes long enough for the walk to wait for it).
         const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 2 * (int64_t)n_cu + n_cu / 8 && a.b > 768;
-        if (row_bytes == 256 && !emit_g && !vgram && !a.desc && !a.k_by_idx && n_inst > n_cu && !thin_tail &&
+        if (row_bytes == 256 && !emit_g && !vgram && !a.carry_w && !a.k_by_idx && n_inst > n_cu && !thin_tail &&
             (dtype == BKV_BF16 || a.b <= 512) && n_inst <= (1ll << 30))
             return launch_compress_pair(dtype, d, a, n_inst, st);
         // one workgroup per compute unit is resident (LDS); with at least two rounds of workgroups, spread the first

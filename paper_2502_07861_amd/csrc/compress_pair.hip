@@ -61,7 +61,13 @@ __device__ __forceinline__ const CompressArgs* args_here() {
     return (const CompressArgs*)(const __attribute__((address_space(4))) CompressArgs*)p;
 }
 
-template <typename T, int D, bool TWO>
+// An entry of an instance table, by scalar loads.
+__device__ __forceinline__ const InstDesc* table_entry(const InstDesc* table, int64_t inst) {
+    return (const InstDesc*)(const __attribute__((address_space(4))) InstDesc*)(unsigned long long)(table + inst);
+}
+
+// TABLE: ragged launches, the instances' coordinates come from CompressArgs::desc.
+template <typename T, int D, bool TWO, bool TABLE>
 __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const CompressArgs a0) {
     const CompressArgs& a = *args_here();
     typedef Geo<T, D> G;
@@ -92,8 +98,14 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
         uint64_t stream = a.tree_mode ? (uint64_t)(64 * (a.seq_base + seq) + a.round) : (uint64_t)inst;
         if (a.inst_ids) stream = a.inst_ids[inst];
         ctr0 = a.tree_mode ? (uint64_t)(a.blk_base + blk) * (uint64_t)b : 0ull;
+        int64_t in_tok0 = seq * a.in_seq_stride + (int64_t)blk * b;
+        if constexpr (TABLE) {
+            const InstDesc& ds = *table_entry(a.desc, inst);
+            if (!ds.valid) return;                                  // the grid is an upper bound; uniform for the workgroup, before any barrier
+            in_tok0 = ds.in_tok; stream = ds.stream; ctr0 = ds.ctr0;
+        }
         key = stream_key(a.seed, stream);
-        Kin = a.K + (seq * a.in_seq_stride + (int64_t)blk * b) * G::kRowBytes;
+        Kin = a.K + in_tok0 * G::kRowBytes;
     }
     const bool center = (a.flags & BKV_CENTER_KEYS) != 0;
     const bool need_norm = !(a.rkey2 > 0.f);
@@ -685,17 +697,23 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
 
     // ------------------------------------------------------------------ output
     const CompressArgs& o = *args_here();
-    const int64_t seq = inst / o.blocks_per_seq;
+    int64_t seq = inst / o.blocks_per_seq;
     const int blk = (int)(inst - seq * o.blocks_per_seq);
-    const int64_t in_tok0 = seq * o.in_seq_stride + (int64_t)blk * b;
-    const int64_t out_tok0 = seq * o.out_seq_stride + (int64_t)blk * (b / 2);
-    const int64_t idx_out0 = seq * o.idx_out_seq_stride + (int64_t)blk * (b / 2);
-    const int64_t tok_base = o.idx_base + (int64_t)blk * b;
+    int64_t in_tok0 = seq * o.in_seq_stride + (int64_t)blk * b;
+    int64_t out_tok0 = seq * o.out_seq_stride + (int64_t)blk * (b / 2);
+    int64_t idx_out0 = seq * o.idx_out_seq_stride + (int64_t)blk * (b / 2);
+    int64_t tok_base = o.idx_base + (int64_t)blk * b;
+    int64_t signs0 = inst * b;
+    if constexpr (TABLE) {
+        const InstDesc& ds = *table_entry(o.desc, inst);
+        seq = ds.seq; in_tok0 = ds.in_tok; out_tok0 = ds.out_tok; idx_out0 = ds.out_tok; signs0 = ds.in_tok;
+        tok_base = in_tok0 - seq * o.v_seq_stride;
+    }
     select_survivors(etaMask, b, wave, lane, keptIdx);
     __syncthreads();
     if (wave == 0) {
         if (o.signs_out)
-            for (int p = 0; p < nP; ++p) o.signs_out[(size_t)(inst * b) + (p << 6) + lane] = ((etaMask[p] >> lane) & 1ull) ? 1 : -1;
+            for (int p = 0; p < nP; ++p) o.signs_out[(size_t)signs0 + (p << 6) + lane] = ((etaMask[p] >> lane) & 1ull) ? 1 : -1;
     } else if (wave == 2 && lane == 0 && (o.status_out || o.stats_out)) {
         const float min_margin = __builtin_bit_cast(float, events[0]), max_sigma = __builtin_bit_cast(float, events[1]);
         const int n_margin = (int)events[2], any_fail = (int)events[3];
@@ -758,10 +776,10 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
     }
 }
 
-template <typename T, int D, bool TWO>
+template <typename T, int D, bool TWO, bool TABLE>
 hipError_t launch_pair_t(const CompressArgs& a, int64_t n_inst, hipStream_t st) {
     const size_t lds = (size_t)kOffNa + (size_t)a.b * 4;
-    auto kern = compress_pair_kernel<T, D, TWO>;
+    auto kern = compress_pair_kernel<T, D, TWO, TABLE>;
     static thread_local size_t configured = 0;
     if (lds > configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -774,9 +792,11 @@ hipError_t launch_pair_t(const CompressArgs& a, int64_t n_inst, hipStream_t st) 
 }  // namespace
 
 hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t n_inst, hipStream_t st) {
-    const bool two = a.b > 512;
-    if (dtype == BKV_BF16 && d == 128) return two ? launch_pair_t<__bf16, 128, true>(a, n_inst, st) : launch_pair_t<__bf16, 128, false>(a, n_inst, st);
-    if (dtype == BKV_F32 && d == 64) return two ? hipErrorInvalidValue : launch_pair_t<float, 64, false>(a, n_inst, st);
+    const bool two = a.b > 512, table = a.desc != nullptr;
+#define BKV_PAIR(TT, DD, TWO) return table ? launch_pair_t<TT, DD, TWO, true>(a, n_inst, st) : launch_pair_t<TT, DD, TWO, false>(a, n_inst, st)
+    if (dtype == BKV_BF16 && d == 128) { if (two) { BKV_PAIR(__bf16, 128, true); } else { BKV_PAIR(__bf16, 128, false); } }
+    if (dtype == BKV_F32 && d == 64 && !two) { BKV_PAIR(float, 64, false); }
+#undef BKV_PAIR
     return hipErrorInvalidValue;
 }
 
