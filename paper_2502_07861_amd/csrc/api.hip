@@ -710,10 +710,15 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e;
     int launches = 0;
-    if ((e = bkv::stream_route(s, k, v, h->seen, st)) != hipSuccess) return hip_fail(e);
-    ++launches;
-    const int64_t j = ++h->seen;
     const int b = s.b;
+    // From the token on that can carry, the first round's halving launch takes the token in itself (one launch of 2 to 6 a token less:
+    // 32 sequences, T = 2, append and attend over 288 tokens: 21.8 -> 19.7 us a token).
+    const bool in_front = s.T == 0 || h->seen + 1 < b;
+    if (in_front) {
+        if ((e = bkv::stream_route(s, k, v, h->seen, st)) != hipSuccess) return hip_fail(e);
+        ++launches;
+    }
+    const int64_t j = ++h->seen;
     for (int r = 0; r < s.T; ++r) {
         // Round r takes a block when its instance has seen a multiple of block * 2^r tokens; before the stream has that many none
         // can.  The halvings leave the state complete (in-place carries): one launch per round where there were a halving and a
@@ -730,6 +735,7 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
         a.v_seq_stride = (int64_t)s.regions * s.cap_n;
         a.status_out = status_num; a.status_stride = s.T; a.sticky_err = s.err;
         a.tree_mode = 1; a.round = r; a.blocks_per_seq = 1;
+        if (r == 0) { a.tok_k = (const char*)k; a.tok_v = (const char*)v; a.tok_no = (int32_t)(j - 1); a.stream = s; }
         if ((e = bkv::launch_compress(s.dtype, s.d, false, a, s.n_seq, st)) != hipSuccess) return hip_fail(e);
         ++launches;
         // MR-Denominator sees every token: it carries at round r exactly when block * 2^r divides j

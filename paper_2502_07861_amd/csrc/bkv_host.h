@@ -20,6 +20,25 @@ struct InstDesc {
     int32_t region;           // of the sequence's counters (CompressArgs::carry_cnt)
 };
 
+// Alg. 1 token by token: device state of n_seq sequences.  Every sequence owns `regions` numerator regions of
+// cap_n token places (one per live bucket, handed out on a bucket's first token and taken back when the bucket is
+// erased) and one denominator region of cap_d places.  A region holds the levels of its MergeAndReduce instance as
+// the streaming cache does: level-T survivors first, then levels T-1..1, then the tail; places beyond `cnt` have
+// weight 0.  All counters live on the device: which instance carries at a token depends on the values.
+struct StreamState {
+    char* Kn; char* Vn; float* wn; int32_t* on;   // [n_seq, regions, cap_n(, d)]: keys, values, weights, original token index
+    char* Kd; float* wd; int32_t* od;             // [n_seq, cap_d(, d)]
+    int32_t* cnt;             // [n_seq, regions + 1]: stored tokens; entry `regions` is the denominator instance
+    int32_t* jj;              // [n_seq, regions + 1]: tokens the instance has seen since it was created
+    int32_t* bucket;          // [n_seq, regions]: bucket index of the region, INT32_MIN: free
+    unsigned int* vmax2;      // [n_seq]: largest |v|^2 so far (bits of a non-negative float)
+    int32_t* err;             // one word: BKV_STATUS_INTERNAL of any halving | BKV_STREAM_* overflow bits
+    InstDesc* desc;           // [T, 2, n_seq]: the carries of the current token (0: numerator, 1: denominator)
+    int64_t n_seq, seq_base, cap_n, cap_d;
+    int32_t regions, b, T, row_bytes, dtype, d;
+    float erase2;             // (eps / (2n) * exp(-r^2 / sqrt d))^2, 0: nothing is erased
+};
+
 struct CompressArgs {
     const char* K;            // input keys, dtype T
     const char* V;            // input values or null
@@ -41,6 +60,10 @@ struct CompressArgs {
     float* carry_w;
     int32_t* carry_idx;
     int32_t* carry_cnt;
+    // Not null (in-place carries of round 0): the launch takes token `tok_no` of every sequence in first; its carry then comes from
+    // the routing and not from the table (the other rounds' and kinds' entries are written there).
+    const char* tok_k;
+    const char* tok_v;
     float* G_out;             // kernel-weight dump (EMIT_G variant only)
     int64_t in_seq_stride;    // tokens between consecutive sequences in K / V / idx_in
     int64_t out_seq_stride;   // tokens between consecutive sequences in K_out / V_out / w_out
@@ -67,7 +90,9 @@ struct CompressArgs {
     int32_t stagger_step;     // ticks apart, so that the memory-bound phases of successive blocks do not coincide chip-wide
     int32_t k_by_idx;         // 1 (resident blocks only): the key rows of the block are read at their ORIGINAL index (idx_in), like
                               // the value rows, from K [n_seq, v_seq_stride, d]: no copy of the keys in block order is needed
+    int32_t tok_no;
     int32_t prefetch_ahead;   // > 0: while walking, touch the keys of block (this + prefetch_ahead) so that they sit in L2 / MALL
+    StreamState stream;       // with tok_k
 };
 
 size_t compress_lds_bytes(int row_bytes, int b, bool value_gram = false);
@@ -146,24 +171,6 @@ struct SetsArgs {
 size_t sets_workspace_bytes(int row_bytes, int b, int64_t n_seq, int64_t n);
 hipError_t run_sets(const SetsArgs& q, hipStream_t st);
 
-// Alg. 1 token by token: device state of n_seq sequences.  Every sequence owns `regions` numerator regions of
-// cap_n token places (one per live bucket, handed out on a bucket's first token and taken back when the bucket is
-// erased) and one denominator region of cap_d places.  A region holds the levels of its MergeAndReduce instance as
-// the streaming cache does: level-T survivors first, then levels T-1..1, then the tail; places beyond `cnt` have
-// weight 0.  All counters live on the device: which instance carries at a token depends on the values.
-struct StreamState {
-    char* Kn; char* Vn; float* wn; int32_t* on;   // [n_seq, regions, cap_n(, d)]: keys, values, weights, original token index
-    char* Kd; float* wd; int32_t* od;             // [n_seq, cap_d(, d)]
-    int32_t* cnt;             // [n_seq, regions + 1]: stored tokens; entry `regions` is the denominator instance
-    int32_t* jj;              // [n_seq, regions + 1]: tokens the instance has seen since it was created
-    int32_t* bucket;          // [n_seq, regions]: bucket index of the region, INT32_MIN: free
-    unsigned int* vmax2;      // [n_seq]: largest |v|^2 so far (bits of a non-negative float)
-    int32_t* err;             // one word: BKV_STATUS_INTERNAL of any halving | BKV_STREAM_* overflow bits
-    InstDesc* desc;           // [T, 2, n_seq]: the carries of the current token (0: numerator, 1: denominator)
-    int64_t n_seq, seq_base, cap_n, cap_d;
-    int32_t regions, b, T, row_bytes, dtype, d;
-    float erase2;             // (eps / (2n) * exp(-r^2 / sqrt d))^2, 0: nothing is erased
-};
 hipError_t stream_route(const StreamState& s, const void* k, const void* v, int64_t j, hipStream_t st);
 
 // One kept set: keys, values (or null: only its normaliser is wanted), weights.

@@ -33,6 +33,7 @@
 #include "bkv_device.h"
 #include "bkv_host.h"
 #include "compress_device.h"
+#include "stream_route.h"
 #include "walk_quarters.h"
 
 namespace bkv {
@@ -567,6 +568,11 @@ struct TileOps {
     }
 };
 
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+    const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)x), hi = __builtin_amdgcn_readfirstlane((unsigned int)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // The walker's hand-overs: a counter and the data it guards are requested in one batch, counter first.  LDS serves a
 // wavefront's requests in order, so data that arrives with a counter value >= the awaited one is current; this saves
 // one LDS round trip per hand-over compared to "poll, then read".
@@ -635,8 +641,24 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     if (a.inst_ids) stream = a.inst_ids[inst];
     uint64_t ctr0 = a.tree_mode ? (uint64_t)(a.blk_base + blk) * (uint64_t)b : 0ull;
     float rvalue2 = a.rvalue2;
+    int region = 0;
     if (a.desc) {                               // ragged launches: every coordinate of the instance comes from a table
-        const InstDesc ds = a.desc[inst];
+        InstDesc ds;
+        if (CARRY && VG != 0 && a.tok_k) {      // one wavefront takes the sequence's token in; its carry, if any, is this workgroup's
+            InstDesc* carry = reinterpret_cast<InstDesc*>(scal);
+            if (wave == 0) {
+                const InstDesc mine = stream_route_token<T, D>(a.stream, a.tok_k, a.tok_v, a.tok_no, inst, lane);
+                if (lane == 0) *carry = mine;
+            }
+            __syncthreads();                    // the state's new entries and the row are in memory too
+            ds.in_tok = uniform64(carry->in_tok); ds.out_tok = uniform64(carry->out_tok);
+            ds.stream = (uint64_t)uniform64((int64_t)carry->stream); ds.ctr0 = (uint64_t)uniform64((int64_t)carry->ctr0);
+            ds.seq = __builtin_amdgcn_readfirstlane(carry->seq); ds.valid = __builtin_amdgcn_readfirstlane(carry->valid);
+            ds.region = __builtin_amdgcn_readfirstlane(carry->region);
+            ds.rvalue2 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(carry->rvalue2)));
+            __syncthreads();                    // (the scalars' place is used again)
+        } else ds = a.desc[inst];
+        region = ds.region;
         if (!ds.valid) return;                  // the grid is an upper bound; uniform for the workgroup, before any barrier
         seq = ds.seq; in_tok0 = ds.in_tok; out_tok0 = ds.out_tok; idx_out0 = ds.out_tok; signs0 = ds.in_tok;
         stream = ds.stream; ctr0 = ds.ctr0;
@@ -1566,7 +1588,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             a.carry_w[in_tok0 + tid] = a.w_out_val;
             a.carry_w[in_tok0 + half + tid] = 0.f;
         }
-        if (tid == 0) a.carry_cnt[seq * a.carry_cnt_stride + a.desc[inst].region] -= half;
+        if (tid == 0) a.carry_cnt[seq * a.carry_cnt_stride + region] -= half;
     }
 }
 
