@@ -840,8 +840,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 mumu = fmaf(mcol[hh], mcol[hh], mumu);
             }
             mumu = wave_sum(mumu);
-            // mu goes back to LDS, one copy per wavefront (no barrier needed): the row pass below reads it at uniform
-            // addresses (broadcast reads), which costs the vector unit nothing, unlike a cross-lane read per column
+            // mu goes back to LDS, one copy per wavefront (no barrier needed)
             float* mu_w = wpart + kWaves * D + wave * D;
 #pragma unroll
             for (int hh = 0; hh < MH; ++hh) mu_w[64 * hh + lane] = mcol[hh];
@@ -889,30 +888,31 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         float pa_row = 0.f;
         if (center || need_norm) {
             float amax = -3.0e38f;
-            // One row per thread: mu comes through scalar registers, MC columns at a time, so the dot products need
-            // no cross-lane step; |k|^2 from exact bf16 products (v_dot2c_f32_bf16).
+            // One row per thread.  Lane l holds column 16 c + l % 16 of mu in mu16[c]; the multiply-add of column e takes it by DPP
+            // (row_newbcast), so the dot product needs no cross-lane step and LDS only serves the rows (read back at uniform addresses
+            // mu was two thirds of this pass's LDS time).  |k|^2 from exact bf16 products (v_dot2c_f32_bf16).
             if constexpr (!MULTI) {
-                constexpr int MC = 16;                          // columns of mu held in scalar registers at a time
-                constexpr int SLQ = MC * (int)sizeof(T) / 16;   // 16-byte slices per MC columns
+                constexpr int SLQ = (int)sizeof(T);             // 16-byte slices per 16 columns
+                float mu16[D / 16];
+                const float* mu_w = wpart + kWaves * D + wave * D + (lane & 15);
+#pragma unroll
+                for (int c = 0; c < D / 16; ++c) mu16[c] = mu_w[16 * c];
                 float pn = 0.f;
+                if (has_row) {                                  // (whole wavefronts: blocks are multiples of 64)
 #pragma unroll
-                for (int qc = 0; qc < D / MC; ++qc) {
-                    float sm[MC];
-                    const float* mu_w = wpart + kWaves * D + wave * D;
-#pragma unroll
-                    for (int jj = 0; jj < MC / 4; ++jj) {
-                        const floatx4 t = *reinterpret_cast<const floatx4*>(mu_w + qc * MC + 4 * jj);
-                        sm[4 * jj] = t[0]; sm[4 * jj + 1] = t[1]; sm[4 * jj + 2] = t[2]; sm[4 * jj + 3] = t[3];
-                    }
-                    if (has_row) {
-#pragma unroll
-                        for (int ss = 0; ss < SLQ; ++ss) {
-                            const uintx4 raw = *reinterpret_cast<const uintx4*>(ldsK + (size_t)tid * G::kLdsRow + G::slice_off(tid, qc * SLQ + ss));
+                    for (int c = 0; c < D / 16; ++c) {
+                        auto slice = [&](auto ss) {
+                            const uintx4 raw = *reinterpret_cast<const uintx4*>(ldsK + (size_t)tid * G::kLdsRow + G::slice_off(tid, c * SLQ + ss));
                             float f[EPL];
                             Elem<T>::unpack(raw, f);
-#pragma unroll
-                            for (int e = 0; e < EPL; ++e) pa_row = fmaf(f[e], sm[ss * EPL + e], pa_row);
+                            dpp_dot<decltype(ss)::value * EPL>(pa_row, mu16[c], f);
                             pn += Elem<T>::dot(raw, raw);
+                        };
+                        slice(std::integral_constant<int, 0>{});
+                        slice(std::integral_constant<int, 1>{});
+                        if constexpr (SLQ == 4) {
+                            slice(std::integral_constant<int, 2>{});
+                            slice(std::integral_constant<int, 3>{});
                         }
                     }
                 }
