@@ -717,8 +717,9 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
     if (in_front) {
         if ((e = bkv::stream_route(s, k, v, h->seen, st)) != hipSuccess) return hip_fail(e);
         ++launches;
+        ++h->seen;
     }
-    const int64_t j = ++h->seen;
+    const int64_t j = in_front ? h->seen : h->seen + 1;
     for (int r = 0; r < s.T; ++r) {
         // Round r takes a block when its instance has seen a multiple of block * 2^r tokens; before the stream has that many none
         // can.  The halvings leave the state complete (in-place carries): one launch per round where there were a halving and a
@@ -738,6 +739,7 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
         if (r == 0) { a.tok_k = (const char*)k; a.tok_v = (const char*)v; a.tok_no = (int32_t)(j - 1); a.stream = s; }
         if ((e = bkv::launch_compress(s.dtype, s.d, false, a, s.n_seq, st)) != hipSuccess) return hip_fail(e);
         ++launches;
+        h->seen = j;                     // (a launch that failed has not taken the token)
         // MR-Denominator sees every token: it carries at round r exactly when block * 2^r divides j
         if (j % ((int64_t)b << r) == 0) {
             bkv_params pd = h->p;
