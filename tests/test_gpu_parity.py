@@ -1591,6 +1591,30 @@ def test_balancekv_sets_many_sequences_equal_few(bk, n_seq, group, n, eps):
             assert torch.equal(whole[name][lo:lo + group], part[name]), (name, lo)
 
 
+@pytest.mark.parametrize("dtype,d,b,n_seq,group,n", [
+    (torch.bfloat16, 128, 64, 7, 5, 3001), (torch.bfloat16, 128, 512, 20, 15, 8200), (torch.bfloat16, 128, 576, 20, 11, 10003),
+    (torch.bfloat16, 128, 1024, 44, 10, 8300), (torch.float32, 64, 64, 7, 5, 2999), (torch.float32, 64, 512, 20, 15, 8200)])
+def test_balancekv_sets_denominator_many_sequences_equal_few(bk, synth, dtype, d, b, n_seq, group, n):
+    """An instance table of more blocks than compute units runs two blocks on each (another kernel); the same sequences in groups
+    whose tables have at most one block per compute unit: the same bits."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert n_seq * (n // b) > n_cu >= group * (n // b)
+    K, _ = _blocks(synth, dtype, d, 64, 32, seed=b + d)
+    base = K.view(-1, d)
+    at = torch.arange(n_seq * n, dtype=torch.int64)
+    K = base[((at * 1009 + at // n * 37 + at // 2048) % base.shape[0]).cuda()].view(n_seq, n, d).contiguous()
+    V = K.roll(1, 2).contiguous()
+    p = bk.make_params(d, b, 2, dtype, log_c=_tuned(synth, dtype, d, b), seed=41, center=True)
+    call = lambda lo, hi: bk.balancekv_sets(p, bk.BKV_SET_DENOMINATOR, K[lo:hi].contiguous(), V[lo:hi].contiguous(), seq_base=lo)
+    whole = call(0, n_seq)
+    assert not (whole["status"] & 2).any()
+    for lo in range(0, n_seq, group):
+        part = call(lo, min(n_seq, lo + group))
+        torch.cuda.synchronize()
+        for name in ("K", "w", "idx", "count", "status"):
+            assert torch.equal(whole[name][lo:lo + group], part[name]), (name, lo)
+
+
 def test_balancekv_sets_replay_from_a_captured_graph(bk, synth):
     """Both set builds and the two-set output line are plain kernel launches without host round trips (grids are upper
     bounds, counts stay on the device): captured once, every replay reproduces the eager result bit for bit."""
