@@ -94,7 +94,7 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
         const int q = c / CG, col = 4 * (c - q * CG);
         const float* row = part + (size_t)q * P;
         if (sg < SR && c < C) {
-// All of a thread's splits are requested before the first is used (device-scope loads are not reordered by the
+            // All of a thread's splits are requested before the first is used (device-scope loads are not reordered by the
             // compiler), up to twelve at a time, and no more of them than there are: each is a trip past the caches for the whole
             // wavefront.
             auto numerator = [&](auto u_c) {
