@@ -1157,7 +1157,10 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         int* tile_parts = prog + 24;
         constexpr bool kHalf = HALF;
         constexpr bool kSplitFirst = !EMIT_G && VG == 0;   // the first tile comes in three quadrants from three wavefronts
-        constexpr bool kJoin = !EMIT_G && VG == 0 && sizeof(T) == 2 && !MULTI;
+        // (Rows of 256 bytes only.  With those of 128 the joined tile took the kernel from 165 registers to 178: 168 let three wavefronts
+        // on a SIMD, so that a block starts while the one before still stores its rows.  3000 blocks, d = 64, whole call: b = 64
+        // 101 -> 82 us, 128: 118 -> 111, 256: 154 -> 144, 384: 201 -> 189; 512 and more the same.)
+        constexpr bool kJoin = !EMIT_G && VG == 0 && sizeof(T) == 2 && !MULTI && G::kRowBytes == 256;
         const int nPc = p1 - p0;
         const int next0 = row0 + rows_here;                                           // first row of the next chunk
         const int nN = pre_on && c + 1 < n_chunks ? (min(CH, b - next0) >> 6) : 0;    // its panels (0: nothing to bring in)
