@@ -703,15 +703,16 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
 
     // sigma starts at minus the threshold: the walk tests (sum of signed weights - threshold) < 0.  Integer work of about 1k clocks,
-    // done while the first rows are on their way.  (Every thread takes part in every step, the last token's again behind the
-    // end: a loop that lanes leave one by one ends with none of them active, and a register spilled there is lost.)
+    // done while the first rows are on their way.  (As many steps for every thread: a loop that lanes leave one by one ends with none
+    // of them active, and a register spilled there is lost.)
     auto thresholds = [&]() {
 #pragma unroll 1
-        for (int i0 = 0; i0 < b; i0 += kThreads) {
-            const int i = min(i0 + tid, b - 1);
-            sigma[i] = 0.f - threshold(i);                                       // never -0: the sign bit alone decides
-        }
+        for (int i0 = 0; i0 < b; i0 += kThreads)
+            if (i0 + tid < b) sigma[i0 + tid] = 0.f - threshold(i0 + tid);       // never -0: the sign bit alone decides
     };
+    // With the values in memory they come before the loads: across them they cost those kernels registers that the tiles' operands
+    // went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024 318 -> 276 us, of 640 157 -> 135).
+    constexpr bool kThresholdsFirst = VG == 2;
 
     // column sums for the block mean, accumulated while rows pass through the registers
     float part[EPL];
@@ -757,6 +758,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     if constexpr (MULTI) {
         kept = CH == kCHm && b > CH && b <= RG * kU2 && b - CH <= RG * kUK && kU2 > kU0 && (center || need_norm);
     }
+    if (kThresholdsFirst) thresholds();
     if (MULTI && kept) {
         uintx4 raw[kU2];
 #pragma unroll
@@ -765,7 +767,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (i < b) raw[u] = *reinterpret_cast<const uintx4*>(Kin + (size_t)i * G::kRowBytes + sl * 16);
             else raw[u] = uintx4{0u, 0u, 0u, 0u};                // (rows past the block's end: defined, never counted)
         }
-        thresholds();
+        if (!kThresholdsFirst) thresholds();
 #pragma unroll
         for (int u = 0; u < kU2; ++u) {
             const int i = rg + u * RG;
@@ -774,7 +776,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (center && i < b) Elem<T>::accumulate(part, raw[u]);
         }
     } else {
-        stage_chunk(0, min(CH, b), center ? b : 0, thresholds);
+        stage_chunk(0, min(CH, b), center ? b : 0, [&]() { if (!kThresholdsFirst) thresholds(); });
     }
     // Value factor: the value row of every token of the block -> LDS (the row of token i is the ORIGINAL row of that
     // token, as in the gather at the end); |v_i|^2 on the way when r_value has to be measured.
