@@ -711,9 +711,16 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
     hipError_t e;
     int launches = 0;
     const int b = s.b;
-    // From the token on that can carry, the first round's halving launch takes the token in itself (one launch of 2 to 6 a token less:
-    // 32 sequences, T = 2, append and attend over 288 tokens: 21.8 -> 19.7 us a token).
-    const bool in_front = s.T == 0 || h->seen + 1 < b;
+    // From the token on that can carry, the first round's halving launch takes the token in itself, as long as its workgroups (one
+    // per sequence and compute unit) run side by side.  Above that they follow one another, each with a trip to memory first, and a
+    // launch of single wavefronts in front is sooner done.  A token in us, with the launch in front in brackets; first while no sequence
+    // carries, then while some do at every token (bf16, d = 128, T = 2):
+    //   blocks of  64    32 sequences 11.4 (13.3), 12.6 (13.0);  256: 11.0 (13.1), 14.9 (15.5);  320: 11.7 (13.1), 16.6 (16.2);
+    //                    512: 13.3 (13.5), 21.5 (17.6);  1024: 20.8 (17.3), 36.1 (28.7);  4096: 71 (46), 120 (96)
+    //   blocks of 512    256: 11.1 (13.5), 38.1 (39.5);  320: 11.4 (13.8), 39.2 (39.2);  512: 11.7 (14.0), 41.9 (39.6);  1024: 18.2 (17.2), 77 (72)
+    const int n_cu = bkv::compute_units();
+    if (n_cu == 0) return hip_fail(hipErrorUnknown);
+    const bool in_front = s.T == 0 || h->seen + 1 < b || s.n_seq > n_cu;
     if (in_front) {
         if ((e = bkv::stream_route(s, k, v, h->seen, st)) != hipSuccess) return hip_fail(e);
         ++launches;
@@ -736,7 +743,7 @@ int bkv_stream_append(bkv_stream* h, const void* k, const void* v, int32_t* stat
         a.v_seq_stride = (int64_t)s.regions * s.cap_n;
         a.status_out = status_num; a.status_stride = s.T; a.sticky_err = s.err;
         a.tree_mode = 1; a.round = r; a.blocks_per_seq = 1;
-        if (r == 0) { a.tok_k = (const char*)k; a.tok_v = (const char*)v; a.tok_no = (int32_t)(j - 1); a.stream = s; }
+        if (r == 0 && !in_front) { a.tok_k = (const char*)k; a.tok_v = (const char*)v; a.tok_no = (int32_t)(j - 1); a.stream = s; }
         if ((e = bkv::launch_compress(s.dtype, s.d, false, a, s.n_seq, st)) != hipSuccess) return hip_fail(e);
         ++launches;
         h->seen = j;                     // (a launch that failed has not taken the token)

@@ -95,6 +95,7 @@ struct CompressArgs {
     StreamState stream;       // with tok_k
 };
 
+int compute_units();                                  // of this thread's first device, 0: not to be had
 size_t compress_lds_bytes(int row_bytes, int b, bool value_gram = false);
 bool compress_value_gram_fits(int row_bytes, int b);   // keys and values of one block resident in LDS together
 bool compress_block_resident(int row_bytes, int b, bool value_gram);   // the block runs as one resident chunk

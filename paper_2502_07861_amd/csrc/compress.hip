@@ -599,10 +599,13 @@ __device__ __forceinline__ void await_and_read4(int* counter, int value, const f
 // value panels of every tile are read from global memory (L2) as they are needed.
 // CARRY: survivors go to the front of their own block (CompressArgs::carry_w).
 // HALF: blocks (or chunks) of at most four panels, dealt out to the wavefronts as half columns.
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false>
+// TOKEN: the workgroup takes a streamed token in first (CompressArgs::tok_k).  An instance of its own: as a run-time choice it cost the
+// other carries up to 18 spilled registers and a launch in which no sequence carries 3 % (4096 sequences, blocks of 128).
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false, bool TOKEN = false>
 __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a) {
     static_assert(VG == 0 || !EMIT_G, "the weight dump has no values");
     static_assert(VG != 1 || !MULTI, "values in LDS: resident blocks only");
+    static_assert(!TOKEN || (CARRY && VG != 0), "the carries of a numerator");
     static_assert(!HALF || (!EMIT_G && VG != 2 && (!MULTI || G_rows<T, D>() <= 256)), "at most four panels at a time");
     typedef Geo<T, D> G;
     typedef TileOps<T, D> Ops;
@@ -644,7 +647,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     int region = 0;
     if (a.desc) {                               // ragged launches: every coordinate of the instance comes from a table
         InstDesc ds;
-        if (CARRY && VG != 0 && a.tok_k) {      // one wavefront takes the sequence's token in; its carry, if any, is this workgroup's
+        if constexpr (TOKEN) {                  // one wavefront takes the sequence's token in; its carry, if any, is this workgroup's
             InstDesc* carry = reinterpret_cast<InstDesc*>(scal);
             if (wave == 0) {
                 const InstDesc mine = stream_route_token<T, D>(a.stream, a.tok_k, a.tok_v, a.tok_no, inst, lane);
@@ -1601,8 +1604,11 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false>
+template <typename T, int D, bool EMIT_G, bool MULTI, int VG = 0, bool CARRY = false, bool HALF = false, bool TOKEN = false>
 static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t st) {
+    if constexpr (CARRY && VG != 0 && !TOKEN) {
+        if (a.tok_k) return launch_one<T, D, EMIT_G, MULTI, VG, CARRY, HALF, true>(a, n_inst, st);
+    }
     // Half columns where a tile takes long (single precision, the value factor with the values in LDS) and a chunk has at most four
     // panels: whole call, 4 blocks of 256 fp32 rows, d = 64: 29.3 -> 24.0 us; 256 of 256 bf16 rows with the value factor 25.4 -> 21.2
     // (2048 of them 185 -> 155); 96 of 384 fp32 rows, d = 128: 81 -> 66.  With eight panels there are two half columns to a wavefront and twice the operand reads of whole ones: 128 blocks
@@ -1610,11 +1616,11 @@ static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t 
     constexpr bool may = !EMIT_G && (VG == 1 || (VG == 0 && sizeof(T) == 4)) && (!MULTI || G_rows<T, D>() <= 256);
     constexpr bool always = may && Geo<T, D>::kRowBytes * (VG == 1 ? 2 : 1) >= 512;         // more than 256 such rows never are in LDS
     if constexpr (may && !HALF) {
-        if (always || a.chunk_rows <= 256) return launch_one<T, D, EMIT_G, MULTI, VG, CARRY, true>(a, n_inst, st);
+        if (always || a.chunk_rows <= 256) return launch_one<T, D, EMIT_G, MULTI, VG, CARRY, true, TOKEN>(a, n_inst, st);
     }
     if constexpr (HALF || !always) {
         const size_t lds = compress_lds_bytes(Geo<T, D>::kRowBytes, a.b, VG == 1);
-        auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG, CARRY, HALF>;
+        auto kern = compress_kernel<T, D, EMIT_G, MULTI, VG, CARRY, HALF, TOKEN>;
         static thread_local size_t configured = 0;
         if (lds > configured) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1624,6 +1630,17 @@ static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t 
         }
         return launch_timed(kProfCompress, n_inst * a.b, kern, dim3((unsigned)n_inst), dim3(kThreads), lds, st, a);
     }
+}
+
+int compute_units() {
+    static thread_local int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+        n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
+    }
+    return n_cu;
 }
 
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st) {
@@ -1638,13 +1655,8 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     if (n_inst <= 0) return hipSuccess;
     a.stagger_blocks = 0; a.stagger_step = 0; a.prefetch_ahead = 0;
     {
-        static thread_local int n_cu = 0;
-        if (n_cu == 0) {
-            int dev = 0;
-            hipDeviceProp_t prop;
-            if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
-            n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
-        }
+        const int n_cu = compute_units();
+        if (n_cu == 0) return hipErrorUnknown;
         // More blocks than compute units: two of them on each (compress_pair.hip).  Up to one per compute unit a launch takes
         // as long as one block, and a block that has the compute unit to itself is done sooner (192 and 256 blocks of 512 bf16
         // rows 11 % sooner, of 1024 rows 15 %).  With more the pair is faster (time of the other kernel over its own, 256

@@ -240,3 +240,31 @@ def test_stream_init_touches_only_what_it_uses(bk):
     bucket = torch.tensor([0, 0, 0, 0x80], dtype=torch.uint8, device="cuda").repeat(n_seq * regions)     # every region free
     assert int((used != 0).sum()) == int((bucket != 0).sum())
     bk.lib().bkv_stream_free(h)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float32, 64)])
+def test_more_sequences_than_compute_units_equal_few(bk, synth, dtype, d):
+    """Up to one sequence per compute unit the first round's halving launch takes the token in, above a launch in front does: the same
+    state, bit for bit."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    b, n, n_seq = 64, 3 * 64 + 5, n_cu + 3
+    t = synth.clustered_layer_bf16(n_seq=8, n=n, d=d, g=1, nq=1, seed=77, device="cpu", dtype=dtype)
+    at = (torch.arange(n_seq)[:, None] * 5 + torch.arange(n)[None] * 11) % (8 * n)       # sequences that differ
+    K = t["K"].reshape(-1, d)[at].cuda().contiguous()
+    V = _scaled_values(t["V"].reshape(-1, d)[at], seed=3, lo=-0.9, hi=0.9).cuda().contiguous()
+    p = bk.make_params(d, b, 2, dtype, log_c=-4.6749, seed=91, center=True)
+    call = lambda lo, hi: _feed(bk, p, K[lo:hi].contiguous(), V[lo:hi].contiguous(), regions=6, cap_num=n, cap_den=n, seq_base=lo)
+    st, num, den, launches = call(0, n_seq)
+    whole = st.views()
+    assert int(whole["error_word"][0]) == 0 and not np.any((num | den) & 2)
+    assert float(whole["w_n"].max()) >= 2.0 and float(whole["w_d"].max()) == 4.0
+    for lo, hi in ((0, n_cu), (n_cu, n_seq)):
+        part_st, num_p, den_p, launches_p = call(lo, hi)
+        assert launches == launches_p + (n - b + 1)                                      # a launch more for every token that can carry
+        part = part_st.views()
+        for name in ("count", "bucket", "w_n", "orig_n", "K_n", "V_n", "w_d", "orig_d", "K_d"):
+            assert torch.equal(whole[name][lo:hi], part[name]), (name, lo)
+        np.testing.assert_array_equal(num[lo:hi], num_p)
+        np.testing.assert_array_equal(den[lo:hi], den_p)
+        part_st.close()
+    st.close()

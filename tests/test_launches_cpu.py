@@ -1,0 +1,44 @@
+"""What the library launches and when, on the host alone (launch_host.cpp stands in for the GPU runtime)."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def lines(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no compiler")
+    from paper_2502_07861_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2502_07861_amd.build import build
+        build()
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_host")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-rdynamic", os.path.join(HERE, "launch_host.cpp"), "-x", "none",
+                    binding.LIB_PATH, "-Wl,-rpath," + os.path.dirname(binding.LIB_PATH), "-o", exe], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0, run.stderr
+    return run.stdout.splitlines()
+
+
+def test_the_launch_that_takes_a_token_in(lines):
+    """Up to one sequence per compute unit (256 here) the first round's halving launch takes the token in, above a launch in front does."""
+    got = dict(l[len("append "):].split(": ") for l in lines if l.startswith("append "))
+    assert len(got) == 12
+    for n_seq in (1, 256, 257, 4096):
+        one = int(n_seq > 256)                                      # the launch in front
+        assert got["T=0 n_seq=%d" % n_seq] == "1 1 1 1, seen 128"
+        # no block yet | a block of either kind | the numerator alone | again, and with T = 2 the second round of both
+        assert got["T=1 n_seq=%d" % n_seq] == "1 %d %d %d, seen 128" % (2 + one, 1 + one, 2 + one)
+        assert got["T=2 n_seq=%d" % n_seq] == "1 %d %d %d, seen 128" % (2 + one, 1 + one, 4 + one)
+
+
+def test_a_token_whose_launch_failed_is_not_taken(lines):
+    got = dict(l[len("failed "):].split(": ") for l in lines if l.startswith("failed "))
+    assert len(got) == 4
+    for key, line in got.items():
+        at = int(key.split("at=")[1])
+        assert line == "EHIP, seen %d, again 1, seen %d" % (at - 1, at), (key, line)
