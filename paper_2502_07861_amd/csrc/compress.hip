@@ -1650,6 +1650,8 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     if (vgram && (emit_g || !a.V)) return hipErrorInvalidValue;
     if (a.k_by_idx && (!a.idx_in || emit_g)) return hipErrorInvalidValue;
     if (a.carry_w && (!a.desc || !a.carry_idx || !a.carry_cnt || emit_g)) return hipErrorInvalidValue;
+    // a streamed token: the workgroup of sequence i takes it in before its numerator's carry, other kernels would leave it out
+    if (a.tok_k && (!a.tok_v || !a.carry_w || !vgram || n_inst != a.stream.n_seq)) return hipErrorInvalidValue;
     const bool v_lds = vgram && compress_value_gram_fits(row_bytes, a.b);
     a.chunk_rows = chunk_rows_for(row_bytes, a.b, v_lds);
     if (n_inst <= 0) return hipSuccess;

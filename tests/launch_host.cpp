@@ -63,5 +63,17 @@ int main() {
                    (int)bkv_stream_tokens_seen(h));
             bkv_stream_free(h);
         }
+    // a halving launch that is to take a token in, with one of the things it needs left out: refused, nothing launched
+    for (int without = 0; without < 5; ++without) {
+        bkv::CompressArgs a;
+        memset(&a, 0, sizeof(a));
+        a.b = 64; a.flags = without == 3 ? 0 : BKV_VALUE_GRAM; a.blocks_per_seq = 1; a.desc = (bkv::InstDesc*)some;
+        a.K = a.V = (const char*)some; a.tok_k = (const char*)some; a.tok_v = without == 1 ? nullptr : (const char*)some;
+        a.carry_w = without == 2 ? nullptr : (float*)some; a.carry_idx = a.carry_cnt = (int32_t*)some;
+        a.stream.n_seq = without == 4 ? 7 : 8;
+        launches = 0;
+        const hipError_t e = bkv::launch_compress(BKV_BF16, 128, false, a, 8, nullptr);
+        printf("token without=%d: %s, %d launches\n", without, e == hipSuccess ? "ok" : e == hipErrorInvalidValue ? "invalid" : "?", launches);
+    }
     return 0;
 }

@@ -42,3 +42,9 @@ def test_a_token_whose_launch_failed_is_not_taken(lines):
     for key, line in got.items():
         at = int(key.split("at=")[1])
         assert line == "EHIP, seen %d, again 1, seen %d" % (at - 1, at), (key, line)
+
+
+def test_a_launch_that_would_leave_the_token_out_is_refused(lines):
+    """0: everything is there; without the token's value, the carry's arrays, the value factor, or a workgroup per sequence."""
+    got = [l.split(": ")[1] for l in lines if l.startswith("token ")]
+    assert got == ["ok, 1 launches"] + ["invalid, 0 launches"] * 4
