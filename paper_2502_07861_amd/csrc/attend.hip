@@ -95,8 +95,9 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
         const float* row = part + (size_t)q * P;
         if (sg < SR && c < C) {
             // All of a thread's splits are requested before the first is used (device-scope loads are not reordered by the
-            // compiler), up to twelve at a time, and no more of them than there are: each is a trip past the caches for the whole
-            // wavefront.
+            // compiler), up to twelve at a time: each is a trip past the caches for the whole wavefront, so batches are of 2, 4, 6 or 12
+            // (denominator 4 or 12), the places behind the last split taken by that split again.  The products that are rounded and those
+            // that are fused are written out: left to the compiler they differed between the batches.
             auto numerator = [&](auto u_c) {
                 constexpr int U = decltype(u_c)::value;
                 for (int s = sg; s < ns0; s += U * SR) {
@@ -110,9 +111,9 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
                     for (int u = 0; u < U; ++u) {
                         if (s + u * SR >= ns0) break;
                         const float mn = fmaxf(M, ml[u][0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(ml[u][0] - mn);
-                        M = mn; L = L * f0 + ml[u][1] * f1;
-                        acc[0] = acc[0] * f0 + x[u][0] * f1; acc[1] = acc[1] * f0 + x[u][1] * f1;
-                        acc[2] = acc[2] * f0 + y[u][0] * f1; acc[3] = acc[3] * f0 + y[u][1] * f1;
+                        M = mn; L = fmaf(L, f0, ml[u][1] * f1);
+                        acc[0] = fmaf(acc[0], f0, x[u][0] * f1); acc[1] = fmaf(acc[1], f0, x[u][1] * f1);
+                        acc[2] = fmaf(acc[2], f0, y[u][0] * f1); acc[3] = fmaf(acc[3], f0, y[u][1] * f1);
                     }
                 }
             };
@@ -126,7 +127,7 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
                     for (int u = 0; u < U; ++u) {
                         if (s + u * SR >= ns0 + ns1) break;
                         const float mn = fmaxf(Md, ml[u][0]);
-                        Ld = Ld * fast_exp2(Md - mn) + ml[u][1] * fast_exp2(ml[u][0] - mn);
+                        Ld = fmaf(ml[u][1], fast_exp2(ml[u][0] - mn), Ld * fast_exp2(Md - mn));
                         Md = mn;
                     }
                 }
@@ -150,10 +151,11 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
             for (int r = 1; r < SR; ++r) {
                 const floatx4 x = *reinterpret_cast<const floatx4*>(red + (r * C + tid) * 8), k = *reinterpret_cast<const floatx4*>(red + (r * C + tid) * 8 + 4);
                 const float mn = fmaxf(M, k[0]), f0 = fast_exp2(M - mn), f1 = fast_exp2(k[0] - mn);
-                M = mn; L = L * f0 + k[1] * f1;
-                acc = acc * f0 + x * f1;
+                M = mn; L = fmaf(L, f0, k[1] * f1);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = fmaf(acc[e], f0, x[e] * f1);
                 const float dn = fmaxf(Md, k[2]);
-                Ld = Ld * fast_exp2(Md - dn) + k[3] * fast_exp2(k[2] - dn);
+                Ld = fmaf(Ld, fast_exp2(Md - dn), k[3] * fast_exp2(k[2] - dn));
                 Md = dn;
             }
         }
