@@ -149,14 +149,14 @@ template <int CTRL> __device__ __forceinline__ float dpp(float x) {
 template <int FIRST> __device__ __forceinline__ void dpp_dot(float& acc, float x, const float (&f)[4]) {
     asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc) : "v"(x), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "n"(FIRST), "n"(FIRST + 1), "n"(FIRST + 2), "n"(FIRST + 3));
+        : "+&v"(acc) : "v"(x), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "n"(FIRST), "n"(FIRST + 1), "n"(FIRST + 2), "n"(FIRST + 3));
 }
 template <int FIRST> __device__ __forceinline__ void dpp_dot(float& acc, float x, const float (&f)[8]) {
     asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %5 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %0, %1, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %0, %1, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %0, %1, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc) : "v"(x), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(f[4]), "v"(f[5]), "v"(f[6]), "v"(f[7]), "n"(FIRST), "n"(FIRST + 1),
+        : "+&v"(acc) : "v"(x), "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(f[4]), "v"(f[5]), "v"(f[6]), "v"(f[7]), "n"(FIRST), "n"(FIRST + 1),
           "n"(FIRST + 2), "n"(FIRST + 3), "n"(FIRST + 4), "n"(FIRST + 5), "n"(FIRST + 6), "n"(FIRST + 7));
 }
 struct LanePair { float a, b; };

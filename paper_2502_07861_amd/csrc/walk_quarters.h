@@ -54,10 +54,10 @@ __device__ __forceinline__ float walk_both(float& s, float& p, float& q, const f
     float x, y;
     if constexpr (H == 0)
         asm volatile(BKV_EIGHT_BOTH(BKV_ADD("s", "y", "c7", 7), 0, 1, 2, 3, 4, 5, 6, 7)
-                     : [s] "+v"(s), [p] "+v"(p), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, b));
+                     : [s] "+&v"(s), [p] "+&v"(p), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, b));
     else
         asm volatile(BKV_EIGHT_BOTH("", 8, 9, 10, 11, 12, 13, 14, 15)
-                     : [s] "+v"(s), [p] "+v"(p), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a + 8), BKV_IN8(b, b + 8));
+                     : [s] "+&v"(s), [p] "+&v"(p), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a + 8), BKV_IN8(b, b + 8));
     return y;
 }
 template <int H>
@@ -65,10 +65,10 @@ __device__ __forceinline__ float walk_mix(float& s, float& p, float& q, float z,
     float x, y;
     if constexpr (H == 0)
         asm volatile(BKV_EIGHT_MIX(BKV_ADD("s", "y", "c7", 7), 0, 1, 2, 3, 4, 5, 6, 7)
-                     : [s] "+v"(s), [p] "+v"(p), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, b));
+                     : [s] "+&v"(s), [p] "+&v"(p), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, b));
     else
         asm volatile(BKV_EIGHT_MIX("", 8, 9, 10, 11, 12, 13, 14, 15)
-                     : [s] "+v"(s), [p] "+v"(p), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a + 8), BKV_IN8(b, b + 8));
+                     : [s] "+&v"(s), [p] "+&v"(p), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a + 8), BKV_IN8(b, b + 8));
     return y;
 }
 // quarter 2: its first half takes the signs of quarter 1 (z) to the last quarter, its second half its own
@@ -79,22 +79,22 @@ __device__ __forceinline__ void walk_late(float& s, float& q, float z, const flo
         asm volatile(BKV_EIGHT(BKV_WAIT1 BKV_ADD("q", "z", "a0", 0), BKV_TWO("z", "a1", 1, "a2", 2), BKV_TWO("z", "a3", 3, "a4", 4), BKV_TWO("z", "a5", 5, "a6", 6),
                                BKV_TWO("z", "a7", 7, "b0", 8), BKV_TWO("z", "b1", 9, "b2", 10), BKV_TWO("z", "b3", 11, "b4", 12), BKV_TWO("z", "b5", 13, "b6", 14),
                                BKV_ADD("s", "y", "c7", 7), BKV_ADD("q", "z", "b7", 15), 0, 1, 2, 3, 4, 5, 6)
-                     : [s] "+v"(s), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, a + 8));
+                     : [s] "+&v"(s), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [z] "v"(z), [m] "s"(m), BKV_IN8(c, c), BKV_IN8(a, a), BKV_IN8(b, a + 8));
     else
         asm volatile(BKV_EIGHT(BKV_WAIT2, BKV_TWO("x", "a0", 0, "a1", 1), BKV_TWO("y", "a2", 2, "a3", 3), BKV_TWO("x", "a4", 4, "a5", 5),
                                BKV_TWO("y", "a6", 6, "a7", 7), BKV_TWO("x", "b0", 8, "b1", 9), BKV_TWO("y", "b2", 10, "b3", 11), BKV_TWO("x", "b4", 12, "b5", 13),
                                "", BKV_TWO("y", "b6", 14, "b7", 15), 8, 9, 10, 11, 12, 13, 14)
-                     : [s] "+v"(s), [q] "+v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a), BKV_IN8(b, a + 8));
+                     : [s] "+&v"(s), [q] "+&v"(q), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8), BKV_IN8(a, a), BKV_IN8(b, a + 8));
 }
 template <int H>
 __device__ __forceinline__ void walk_plain(float& s, const float* c, unsigned int m) {
     float x, y;
     if constexpr (H == 0)
         asm volatile(BKV_EIGHT(BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_ADD("s", "y", "c7", 7), "", 0, 1, 2, 3, 4, 5, 6)
-                     : [s] "+v"(s), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c));
+                     : [s] "+&v"(s), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c));
     else
         asm volatile(BKV_EIGHT(BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, BKV_WAIT2, "", "", "", 8, 9, 10, 11, 12, 13, 14)
-                     : [s] "+v"(s), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8));
+                     : [s] "+&v"(s), [x] "=&v"(x), [y] "=&v"(y) : [m] "s"(m), BKV_IN8(c, c + 8));
 }
 #undef BKV_TWO
 #undef BKV_EIGHT_MIX
