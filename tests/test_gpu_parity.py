@@ -196,6 +196,29 @@ def test_many_blocks_equal_few_blocks(bk, synth, dtype, d, b, center, r_key):
     assert (many["status"] & 2 == 0).all()
 
 
+@pytest.mark.parametrize("dtype,d,b", [(torch.bfloat16, 128, 64), (torch.bfloat16, 128, 576), (torch.float32, 64, 256)])
+def test_weights_that_overflow_decide_alike(bk, dtype, d, b):
+    """A given r_key far below the keys' norms lets weights overflow: sums become infinite and then NaN, from which the two kernels
+    (more blocks than compute units or fewer) must not decide differently."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator().manual_seed(b)
+    K = torch.randn(b, d, generator=gen)
+    c = torch.randn(d, generator=gen)
+    c *= math.sqrt(120 * math.sqrt(d)) / c.norm()
+    for i in (3, 10, 20, 30, 37, 50):                                        # six keys a panel whose weights are e^120 among themselves
+        K[i::64] = c * (1 + 1e-4 * i)
+    K, V = K.to(dtype).cuda()[None], torch.randn(1, b, d, generator=gen).to(dtype).cuda()
+    p = bk.make_params(d, b, 1, dtype, log_c=0.0, seed=5, center=False, r_key=1e-3)
+    assert int(torch.isinf(bk.kernel_weights(p, K)).sum()) >= 36 * (b // 64)
+    got = []
+    for n in (2, n_cu + 9):
+        out = bk.compress_block(p, K.repeat(n, 1, 1), V.repeat(n, 1, 1), inst_ids=torch.full((n,), 7, dtype=torch.int64, device="cuda"))
+        assert (out["signs"] == out["signs"][:1]).all() and (out["idx"] == out["idx"][:1]).all()
+        assert not (out["status"] & 2).any()
+        got.append((out["signs"][0], out["idx"][0]))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 def _tuned(synth, dtype, d, b):
     from oracle.tuning import tune_log_c
     K, _ = _blocks(synth, dtype, d, b, 2, seed=5 + b)
@@ -1591,28 +1614,34 @@ def test_balancekv_sets_many_sequences_equal_few(bk, n_seq, group, n, eps):
             assert torch.equal(whole[name][lo:lo + group], part[name]), (name, lo)
 
 
-@pytest.mark.parametrize("dtype,d,b,n_seq,group,n", [
-    (torch.bfloat16, 128, 64, 7, 5, 3001), (torch.bfloat16, 128, 512, 20, 15, 8200), (torch.bfloat16, 128, 576, 20, 11, 10003),
-    (torch.bfloat16, 128, 1024, 44, 10, 8300), (torch.float32, 64, 64, 7, 5, 2999), (torch.float32, 64, 512, 20, 15, 8200)])
-def test_balancekv_sets_denominator_many_sequences_equal_few(bk, synth, dtype, d, b, n_seq, group, n):
-    """An instance table of more blocks than compute units runs two blocks on each (another kernel); the same sequences in groups
-    whose tables have at most one block per compute unit: the same bits."""
+@pytest.mark.parametrize("dtype,d,b,per_seq,T", [
+    (torch.bfloat16, 128, 64, 8, 2), (torch.bfloat16, 128, 512, 4, 2), (torch.bfloat16, 128, 576, 4, 2), (torch.bfloat16, 128, 1024, 4, 2),
+    (torch.bfloat16, 128, 128, 8, 3), (torch.float32, 64, 64, 8, 3), (torch.float32, 64, 512, 4, 2)])
+def test_balancekv_sets_denominator_many_sequences_equal_few(bk, synth, dtype, d, b, per_seq, T):
+    """An instance table of more blocks than compute units runs two blocks on each (another kernel), in the first round and in later
+    ones (rows found through the indices of the round before, no rows stored in the last); the same sequences in groups whose
+    tables have at most one block per compute unit: the same signs and the same bits."""
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    assert n_seq * (n // b) > n_cu >= group * (n // b)
+    n_seq, group, n = n_cu // (per_seq // 2) + 5, n_cu // per_seq, b * per_seq + 37
+    assert n_seq * (per_seq // 2) > n_cu >= group * per_seq
     K, _ = _blocks(synth, dtype, d, 64, 32, seed=b + d)
     base = K.view(-1, d)
     at = torch.arange(n_seq * n, dtype=torch.int64)
     K = base[((at * 1009 + at // n * 37 + at // 2048) % base.shape[0]).cuda()].view(n_seq, n, d).contiguous()
     V = K.roll(1, 2).contiguous()
-    p = bk.make_params(d, b, 2, dtype, log_c=_tuned(synth, dtype, d, b), seed=41, center=True)
-    call = lambda lo, hi: bk.balancekv_sets(p, bk.BKV_SET_DENOMINATOR, K[lo:hi].contiguous(), V[lo:hi].contiguous(), seq_base=lo)
+    p = bk.make_params(d, b, T, dtype, log_c=_tuned(synth, dtype, d, b), seed=41, center=True)
+    call = lambda lo, hi: bk.balancekv_sets(p, bk.BKV_SET_DENOMINATOR, K[lo:hi].contiguous(), V[lo:hi].contiguous(), seq_base=lo, emit_signs=True)
     whole = call(0, n_seq)
     assert not (whole["status"] & 2).any()
     for lo in range(0, n_seq, group):
-        part = call(lo, min(n_seq, lo + group))
+        hi = min(n_seq, lo + group)
+        part = call(lo, hi)
         torch.cuda.synchronize()
         for name in ("K", "w", "idx", "count", "status"):
-            assert torch.equal(whole[name][lo:lo + group], part[name]), (name, lo)
+            assert torch.equal(whole[name][lo:hi], part[name]), (name, lo)
+        for r in range(T):                                                    # the halvings' rows of the level-r buffers
+            rows = (per_seq >> r) * b
+            assert rows and torch.equal(whole["signs"][r][lo:hi, :rows], part["signs"][r][:, :rows]), (r, lo)
 
 
 def test_balancekv_sets_replay_from_a_captured_graph(bk, synth):
