@@ -13,14 +13,15 @@ namespace bkv {
 //     two wait states                         (a DPP operand may not be read sooner after a vector instruction wrote it)
 //     s -= x[lane j of the row] * g           v_fmac_f32 with row_newbcast:j
 // four issue slots of 4 clocks a decision.  The wait states take the multiply-adds for the quarters behind: quarter 0 those of
-// 1 and 2, quarter 1 those of 2 and, with the signs of quarter 0, of 3, quarter 2 the rest of 3.  261 slots a panel,
+// 1 and 2, quarter 1 those of 2 and, with the signs of quarter 0, of 3, quarter 2 the rest of 3.  259 slots a panel,
 // where walk_panel's compare mask takes six a decision; one wavefront alone on its compute unit, the tile's reads from LDS included,
 // 1404 clocks a panel against 1780.  It reads 40 pieces of 16 bytes a lane instead of 16: with two blocks on a compute unit, where LDS is
 // the scarcer thing, that costs what the chain gains (128 x 131072 tokens, blocks of 1024: 6.34 ms, 6.40 this way), and the pair
 // kernel keeps walk_panel.
 // Every s[k] receives eta_j g_jl in the order of j and nothing else.  Lanes l <= j of j's own quarter hold g = 0: s[k] keeps the
 // value it had at decision time.  s never is -0 (it starts as 0 - threshold, and a sum is -0 only if both terms are), so its
-// sign bit says whether s < 0.
+// sign bit says whether s < 0.  Weights that overflow make it a NaN (inf - inf), which this hardware makes with the sign bit set: it
+// decides as +, as walk_panel's compare takes it, and is published as - by both kernels (it is not < 0).
 // Eight decisions per asm statement, so that nothing is scheduled into the chain.  What a statement reads by DPP has been
 // written two wait states before, whatever instruction precedes the statement.
 #define BKV_ADD(ACC, X, G, L) "v_fmac_f32_dpp %[" ACC "], -%[" X "], %[" G "] row_newbcast:" #L " row_mask:0xf bank_mask:0xf\n\t"
