@@ -79,3 +79,50 @@ def test_carries_do_not_pay_for_the_token(kernels, dtype, d, most):
     nothing (as a run-time choice 66, 87 and 62 spilled registers)."""
     plain = [v for k, v in _compress(kernels, dtype, d, 0, 2, 1).items() if "ELb0ELb0EE" in k[k.index("compress_kernel"):]]
     assert len(plain) == 1 and plain[0][1] <= most, plain
+
+
+def _spills_behind_loops(listing):
+    """Places of a disassembly where a register is spilled or brought back (scratch memory, or an accumulator register as the place) between the
+    end of a loop that lanes leave one by one, where none of them is active, and the instruction that makes them active again."""
+    bad, lines = [], [l for l in listing if l.strip()]
+    address = lambda l: int(re.search(r"// ([0-9A-F]{12}):", l).group(1), 16)
+    start = 0
+    for i, line in enumerate(lines):
+        head = re.match(r"([0-9a-f]{16}) <\S+>:", line)
+        if head:
+            start = int(head.group(1), 16)
+            continue
+        jump = re.search(r"s_cbranch_execnz .*<\S+?(?:\+0x([0-9a-f]+))?>\s*$", line)
+        if not jump or start + int(jump.group(1) or "0", 16) > address(line):                # forward: not the end of a loop
+            continue
+        for after in lines[i + 1:]:
+            op = after.split("//")[0]
+            if re.search(r"\bexec\b", op) or re.search(r"s_endpgm|s_branch|s_cbranch|s_setpc", op):
+                break
+            if re.search(r"scratch_(load|store)|v_accvgpr_(write|read)", op):
+                bad.append((address(after), op.strip()))
+    return bad
+
+
+def test_nothing_is_spilled_where_no_lane_is_active(kernels, tmp_path):
+    """The compiler may spill a register right behind a loop that lanes leave one by one, before it makes them active again: nothing is
+    stored then, and what comes back later is something else.  It did so once, around the thresholds' loop."""
+    planted = """0000000000000100 <a>:
+\tv_add_u32 v0, 1, v0                                        // 000000000100: 00000000
+\ts_andn2_b64 exec, exec, s[0:1]                             // 000000000104: 00000000
+\ts_cbranch_execnz 65533                                     // 000000000108: 00000000 <a>
+\tscratch_store_dword off, v1, off                           // 00000000010C: 00000000
+\ts_or_b64 exec, exec, s[2:3]                                // 000000000110: 00000000
+\tscratch_store_dword off, v2, off                           // 000000000114: 00000000"""
+    assert [a for a, _ in _spills_behind_loops(planted.split("\n"))] == [0x10c]
+    from paper_2502_07861_amd import binding
+    loops = 0
+    for i, obj in enumerate(_code_objects(binding.LIB_PATH)):
+        path = tmp_path / ("%d.elf" % i)
+        path.write_bytes(obj)
+        run = subprocess.Popen([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", str(path)], stdout=subprocess.PIPE, text=True)
+        listing = [l for l in run.stdout if any(w in l for w in ("exec", "branch", "scratch", "accvgpr", "endpgm", ">:"))]
+        assert run.wait() == 0
+        loops += sum("s_cbranch_execnz" in l for l in listing)
+        assert _spills_behind_loops(listing) == []
+    assert loops > 100
