@@ -1142,14 +1142,15 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         //   eta_done      panels walked so far (the walker publishes after writing the signs of panel l)
         //   tile_parts[l] parts of diagonal tile l stored so far (three quadrants from three wavefronts, or the tile in one)
         //   diag_taken    diagonal tiles the walker has loaded so far
-        //   col[l]        set to l by the owner of column panel l once sigma of that panel holds every earlier row panel
+        //   col[l]        set to l by the owner of column panel l once sigma of that panel holds every earlier row panel (HALF: counted
+        //                 up by the two owners of its halves, complete at 2)
         //   rowp[w]       row panels whose LDS rows column owner w has read for the last time (only where the next chunk is
         //                 brought in during this pipeline, see kPre)
         // Wavefront w = 1..7 owns column panel w of the chunk: it keeps the panel's fragments in registers as the B
         // operand and forms, in row order, the tiles (i, w), i < w (weights need nothing; the signed column sum needs
         // eta_done > i and goes into a register copy of sigma); then, its column being complete just as the walk of
-        // panel w starts, the diagonal tile of panel w+2, which it stores when the walker has taken the previous one
-        // (at start-up the tile of panel 0 comes as three quadrants from wavefronts 1-3 -- as a whole from wavefront 7 in
+        // panel w starts, the diagonal tile of panel w+2, which it stores when the walker has taken the tile of panel w, whose
+        // buffer it goes to (at start-up the tile of panel 0 comes as three quadrants from wavefronts 1-3 -- as a whole from wavefront 7 in
         // the instances with a weight dump or the value factor --, that of panel 1 from wavefront 6, that of panel 2 from
         // wavefront 1).  Every sigma receives
         // its contributions in the same order on every run.  At most one tile per wavefront and walked panel is due,
@@ -1160,7 +1161,6 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         int* col = prog + 8;
         int* rowp = prog + 16;                        // rowp[w]: row panels whose LDS rows column owner w needs no more
         int* tile_parts = prog + 24;
-        constexpr bool kHalf = HALF;
         constexpr bool kSplitFirst = !EMIT_G && VG == 0;   // the first tile comes in three quadrants from three wavefronts
         // (Rows of 256 bytes only.  With those of 128 the joined tile took the kernel from 165 registers to 178: 168 let three wavefronts
         // on a SIMD, so that a block starts while the one before still stores its rows.  3000 blocks, d = 64, whole call: b = 64
@@ -1185,10 +1185,10 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 #pragma unroll
                 for (int k = 0; k < 4; ++k) quarter[k] = column + diag_quarter(k) + c16 * diag_stride(k);
                 const auto tile = [&](int m, int k, int q) -> floatx4 { return *reinterpret_cast<const floatx4*>(quarter[k] + (k == 0 ? (4 * q) ^ (c16 & 12) : 16 * m + 4 * q)); };
-                if constexpr (kHalf) await<true>(tile_parts + l, l != 1 || nPc == 2 ? 3 : 2, sync_err);
+                if constexpr (HALF) await<true>(tile_parts + l, l != 1 || nPc == 2 ? 3 : 2, sync_err);
                 else await<true>(tile_parts + l, kSplitFirst && l == 0 ? 3 : 1, sync_err);
                 walk_begin(start, tile);
-                await_and_read4(col + l, kHalf && l > 0 ? 2 : l, sigma + (I << 6) + (lane & 15), s, sync_err);
+                await_and_read4(col + l, HALF && l > 0 ? 2 : l, sigma + (I << 6) + (lane & 15), s, sync_err);
                 // (once the tile is in registers the buffer may be overwritten)
                 const float sv = walk_quarters(s, lane, start, tile, [&]() { publish(diag_taken, l + 1); });
                 const unsigned long long m = __ballot(sv < 0.f);
@@ -1228,7 +1228,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     for (int j = 0; j < PF; ++j) pfv0[j] = *reinterpret_cast<const int*>(Kpf + (size_t)(p0 << 6) * G::kRowBytes + j * 1024);
                 }
             }
-            if constexpr (kHalf) {
+            if constexpr (HALF) {
                 // A half column (w, cb): columns 32 cb .. 32 cb + 31 of column panel w, w = 1 .. 3 (four panels at most).  Its owner forms
                 // the 64x32 tiles (i, w), i < w, in row order and adds up the signed sums, which are those of the whole column
                 // panel in the same order.  In quadrants of 32x32 the column (w, cb) is 2 w, the diagonal tile of a panel three.
@@ -1368,16 +1368,17 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     // The later columns run behind the walk: where the signs of row panel i are there already, they join the
                     // tile's exponentials and nothing is waited for (a look at the counter, the signs and the sums by themselves
                     // take 0.9k clocks of 2.7k a tile).
-                    if (kJoin && __builtin_amdgcn_readfirstlane(__hip_atomic_load(eta_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > i) {
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                        sig += Ops::template tile<true, false, !Ops::kStream, false, VG>(acc, nullptr, lds_rows(i << 6), Ops::kStream ? lds_rows(w << 6) : nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
-                                                                      nullptr, etaF + (i << 6) + 32 * h, foff, n, h, Bq);
-                        if (kPre && nN > 0) publish_in_order(rowp + w, i + 1);
-                        if (i == w - 1) {
-                            sigma[(J << 6) + lane] = sig;
-                            publish_in_order(col + w, w);
+                    if constexpr (kJoin) {
+                        if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(eta_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > i) {
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                            sig += Ops::template tile<true, false, true>(acc, nullptr, lds_rows(i << 6), nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
+                                                                         nullptr, etaF + (i << 6) + 32 * h, foff, n, h, Bq);
+                            if (i == w - 1) {
+                                sigma[(J << 6) + lane] = sig;
+                                publish_in_order(col + w, w);
+                            }
+                            continue;
                         }
-                        continue;
                     }
                     Ops::template tile<false, false, !Ops::kStream, false, VG>(acc, nullptr, lds_rows(i << 6), Ops::kStream ? lds_rows(w << 6) : nullptr, narow + (Ii << 6), narow + (J << 6), alpha, row_const,
                                                                       nullptr, nullptr, foff, n, h, Bq,
@@ -1611,8 +1612,10 @@ static hipError_t launch_one(const CompressArgs& a, int64_t n_inst, hipStream_t 
     }
     // Half columns where a tile takes long (single precision, the value factor with the values in LDS) and a chunk has at most four
     // panels: whole call, 4 blocks of 256 fp32 rows, d = 64: 29.3 -> 24.0 us; 256 of 256 bf16 rows with the value factor 25.4 -> 21.2
-    // (2048 of them 185 -> 155); 96 of 384 fp32 rows, d = 128: 81 -> 66.  With eight panels there are two half columns to a wavefront and twice the operand reads of whole ones: 128 blocks
-    // of 512 rows, d = 64, value factor, 27.4 -> 31.4 us, 64 of 1024 fp32 rows 180 -> 190: whole columns.
+    // (2048 of them 185 -> 155); 96 of 384 fp32 rows, d = 128: 81.6 -> 67.5.  With eight panels there are two half columns to a
+    // wavefront and twice the operand reads of whole ones: 128 blocks of 512 rows, d = 64, value factor, 27.4 -> 31.4 us, 64 of 1024
+    // fp32 rows 180 -> 190: whole columns.  Five to seven panels (d = 64 only) take whole columns as well, unmeasured: the half columns'
+    // order of work is written for up to four.
     constexpr bool may = !EMIT_G && (VG == 1 || (VG == 0 && sizeof(T) == 4)) && (!MULTI || G_rows<T, D>() <= 256);
     constexpr bool always = may && Geo<T, D>::kRowBytes * (VG == 1 ? 2 : 1) >= 512;         // more than 256 such rows never are in LDS
     if constexpr (may && !HALF) {
