@@ -706,16 +706,19 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
 
     // sigma starts at minus the threshold: the walk tests (sum of signed weights - threshold) < 0.  Integer work of about 1k clocks,
-    // done while the first rows are on their way.  (As many steps for every thread: a loop that lanes leave one by one ends with none
-    // of them active, and a register spilled there is lost.)
+    // done while the first rows are on their way.  (Every thread takes part in every step, the last token's again behind the
+    // end: a loop that lanes leave one by one ends with none of them active, and a register spilled there is lost.)
     auto thresholds = [&]() {
 #pragma unroll 1
-        for (int i0 = 0; i0 < b; i0 += kThreads)
-            if (i0 + tid < b) sigma[i0 + tid] = 0.f - threshold(i0 + tid);       // never -0: the sign bit alone decides
+        for (int i0 = 0; i0 < b; i0 += kThreads) {
+            const int i = min(i0 + tid, b - 1);
+            sigma[i] = 0.f - threshold(i);                                       // never -0: the sign bit alone decides
+        }
     };
-    // With the values in memory they come before the loads: across them they cost those kernels registers that the tiles' operands
-    // went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024 318 -> 276 us, of 640 157 -> 135).
-    constexpr bool kThresholdsFirst = VG == 2;
+    // In blocks of several chunks with the values in memory they come before the loads: across them they cost those kernels registers
+    // that the tiles' operands went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024
+    // 318 -> 276 us, of 640 157 -> 135).
+    constexpr bool kThresholdsFirst = VG == 2 && MULTI;
 
     // column sums for the block mean, accumulated while rows pass through the registers
     float part[EPL];
