@@ -717,7 +717,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
     // In blocks of several chunks with the values in memory they come before the loads: across them they cost those kernels registers
     // that the tiles' operands went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024
-    // 318 -> 276 us, of 640 157 -> 135).
+    // 318 -> 277 us, of 640 157 -> 134; blocks resident as one chunk gain nothing).
     constexpr bool kThresholdsFirst = VG == 2 && MULTI;
 
     // column sums for the block mean, accumulated while rows pass through the registers
@@ -1167,7 +1167,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         constexpr bool kSplitFirst = !EMIT_G && VG == 0;   // the first tile comes in three quadrants from three wavefronts
         // (Rows of 256 bytes only.  With those of 128 the joined tile took the kernel from 165 registers to 178: 168 let three wavefronts
         // on a SIMD, so that a block starts while the one before still stores its rows.  3000 blocks, d = 64, whole call: b = 64
-        // 101 -> 82 us, 128: 118 -> 111, 256: 154 -> 144, 384: 201 -> 189; 512 and more the same.)
+        // 101 -> 83 us, 128: 118 -> 113, 256: 154 -> 147, 384: 201 -> 190; 512 and more the same.)
         constexpr bool kJoin = !EMIT_G && VG == 0 && sizeof(T) == 2 && !MULTI && G::kRowBytes == 256;
         const int nPc = p1 - p0;
         const int next0 = row0 + rows_here;                                           // first row of the next chunk
