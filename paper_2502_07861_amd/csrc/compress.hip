@@ -1143,7 +1143,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         // ---------------------------------------------------------- panels of this chunk: a dataflow pipeline
         // No barriers in here.  Counters (all start at 0, local panel index l = I - p0):
         //   eta_done      panels walked so far (the walker publishes after writing the signs of panel l)
-        //   tile_parts[l] parts of diagonal tile l stored so far (three quadrants from three wavefronts, or the tile in one)
+        //   tile_parts[l] parts of diagonal tile l stored so far (three quadrants, two column halves, or the tile in one)
         //   diag_taken    diagonal tiles the walker has loaded so far
         //   col[l]        set to l by the owner of column panel l once sigma of that panel holds every earlier row panel (HALF: counted
         //                 up by the two owners of its halves, complete at 2)
@@ -1188,7 +1188,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 #pragma unroll
                 for (int k = 0; k < 4; ++k) quarter[k] = column + diag_quarter(k) + c16 * diag_stride(k);
                 const auto tile = [&](int m, int k, int q) -> floatx4 { return *reinterpret_cast<const floatx4*>(quarter[k] + (k == 0 ? (4 * q) ^ (c16 & 12) : 16 * m + 4 * q)); };
-                if constexpr (HALF) await<true>(tile_parts + l, l != 1 || nPc == 2 ? 3 : 2, sync_err);
+                if constexpr (HALF) await<true>(tile_parts + l, nPc <= 2 ? 3 : 2, sync_err);
                 else await<true>(tile_parts + l, kSplitFirst && l == 0 ? 3 : 1, sync_err);
                 walk_begin(start, tile);
                 await_and_read4(col + l, HALF && l > 0 ? 2 : l, sigma + (I << 6) + (lane & 15), s, sync_err);
@@ -1232,43 +1232,58 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                 }
             }
             if constexpr (HALF) {
-                // A half column (w, cb): columns 32 cb .. 32 cb + 31 of column panel w, w = 1 .. 3 (four panels at most).  Its owner forms
-                // the 64x32 tiles (i, w), i < w, in row order and adds up the signed sums, which are those of the whole column
-                // panel in the same order.  In quadrants of 32x32 the column (w, cb) is 2 w, the diagonal tile of a panel three.
-                // A wavefront for each half column, spread so that the SIMDs get 7 (the walker's) to 11 quadrants of four panels.  The
-                // diagonal tile of panel 1 comes from its owners, that of panel 2 from wavefront 1, that of panel 3 from the owners
-                // of column 1, who are done by then.
-                const bool two_panels = nPc == 2;                 // then nobody is short of time: the second diagonal tile has three makers too
-                // wavefronts of half columns 0, 1, ..: 6 7 | 6 7 5 4 | 6 7 3 2 5 4
-                const int item = w >= 6 ? w - 6 : w >= 4 ? (nPc == 3 ? 7 - w : 9 - w) : w >= 2 && nPc == 4 ? 5 - w : -1;
-                const int wc = item >= 0 ? 1 + (item >> 1) : nPc, cb = item & 1;                                 // (nPc: no column)
-                auto v_lds = [&](int r) -> const char* { asm volatile("" : "+s"(r)); return VG == 1 ? ldsV + (size_t)r * G::kLdsRow : nullptr; };
-                auto part_done = [&](int l) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    if (lane == 0) __hip_atomic_fetch_add(tile_parts + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                // A half column (wc, cb): columns 32 cb .. 32 cb + 31 of column panel wc = 1 .. 3 (four panels at most).  Its owner forms
+                // the 64x32 tiles (i, wc), i < wc, in row order and adds up the signed sums, which are those of the whole column
+                // panel in the same order.  A diagonal tile comes as column half 0 (X: one quadrant) and column half 1 (Y: two).  In
+                // quadrants of 32x32 3, 7, 11 and 15 stand before the walks of four panels.  Wavefronts (SIMD = wavefront modulo 4, the
+                // walker is 0) and what they form, in this order:
+                //    1: X0, X2, Y2    2: X1, column 2    3: Y1, column 2    4: Y0, column 3    5: column 3    6: column 1, Y3    7: column 1, X3
+                // (three panels: column 2 goes to 4 and 5, Y2 and X2 to 2 and 3): 8 to 10 quadrants a SIMD, and what an earlier walk
+                // waits for first, at the higher wave priority.  Two quadrants at a time where the walk waits: a single one is a chain
+                // of dependent matrix instructions, between any two of which the other wavefront of the SIMD gets in.  fp32 matrix
+                // instructions leave the vector unit nothing while they run, so wavefront 5 starts when the first tile is there.
+                // Against quadrants of 32x32 without priorities, 7 to 11 of them a SIMD and the first tile on two (4 sequences, two rounds):
+                // fp32, d = 64, b = 192 39.8 -> 36.1 us, 256 47.3 -> 45.5; d = 128, b = 192 59.5 -> 50.6, 384 133.9 -> 130.5; value factor, fp32,
+                // d = 64, b = 192 62.0 -> 52.9, 256 72.0 -> 69.3; bf16 the same.
+                const bool four = nPc == 4;
+                const int wc = w >= 6 ? 1 : w >= 4 ? (nPc >= 3 ? nPc - 1 : nPc) : w >= 2 && four ? 2 : nPc, cb = w & 1;       // (nPc: no column)
+                auto priority = [&](int panel) {
+                    if (panel <= 1) __builtin_amdgcn_s_setprio(2);
+                    else if (panel < nPc - 1) __builtin_amdgcn_s_setprio(1);
+                    else __builtin_amdgcn_s_setprio(0);
                 };
-                // a quadrant (qr, qc) of the diagonal tile of panel l, stored once its buffer's previous tile is in the walker's registers
-                auto one_quadrant = [&](auto qr, auto qc, int l) {
+                auto v_lds = [&](int r) -> const char* { asm volatile("" : "+s"(r)); return VG == 1 ? ldsV + (size_t)r * G::kLdsRow : nullptr; };
+                // a part of the diagonal tile of panel l, stored once its buffer's previous tile is in the walker's registers: column half
+                // qc, with qr >= 0 only its quadrant of row half qr
+                auto diagonal_part = [&](auto qc, auto qr, int l) {
                     Ops::template half_diag<decltype(qc)::value, decltype(qr)::value, VG == 1>(diag + (l & 1) * kDiagFloats, lds_rows(l << 6), narow + ((p0 + l) << 6), alpha,
                                                                                                row_const, foff, n, h, v_lds(l << 6), inv_rv2, vg_bias,
                                                                                                [&]() { await(diag_taken, l - 1, sync_err); });
-                    part_done(l);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    if (lane == 0) __hip_atomic_fetch_add(tile_parts + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 };
                 constexpr std::integral_constant<int, 0> c0{};
                 constexpr std::integral_constant<int, 1> c1{};
-                // the walk cannot start without the first tile: three wavefronts take a quadrant each.  A block of one panel has
-                // nothing else to form, so they are of three SIMDs there (1, 4 and 5 share two: 3000 blocks of 64 fp32 rows, d = 128,
-                // whole call, 162 -> 139 us, with value factor 224 -> 179).
-                const bool one_panel = nPc == 1;
-                if (w == 1) one_quadrant(c0, c0, 0);
-                else if (w == (one_panel ? 2 : 4)) one_quadrant(c0, c1, 0);
-                else if (w == (one_panel ? 3 : 5)) one_quadrant(c1, c1, 0);
-                if (two_panels) {
-                    if (w == 1) one_quadrant(c0, c0, 1);
-                    else if (w == 2) one_quadrant(c0, c1, 1);
-                    else if (w == 3) one_quadrant(c1, c1, 1);
+                constexpr std::integral_constant<int, -1> whole{};
+                if (nPc <= 2) {
+                    // Nobody is short of time: quadrants, the first tile's from three SIMDs where there is no other work (two share a SIMD:
+                    // 3000 blocks of 64 fp32 rows, d = 128, whole call, 162 -> 139 us, with value factor 224 -> 179).
+                    if (w == 1) diagonal_part(c0, c0, 0);
+                    else if (w == (nPc == 1 ? 2 : 4)) diagonal_part(c1, c0, 0);
+                    else if (w == (nPc == 1 ? 3 : 5)) diagonal_part(c1, c1, 0);
+                    if (nPc == 2) {
+                        if (w == 1) diagonal_part(c0, c0, 1);
+                        else if (w == 2) diagonal_part(c1, c0, 1);
+                        else if (w == 3) diagonal_part(c1, c1, 1);
+                    }
+                } else {
+                    priority(w == 1 || w == 4 || !four ? 0 : 1);
+                    if (w == 1 || w == 2) diagonal_part(c0, whole, w - 1);
+                    else if (w == 3 || w == 4) diagonal_part(c1, whole, 4 - w);
+                    else if (w == 5 && sizeof(T) == 4) await(tile_parts, 2, sync_err);
                 }
                 if (wc < nPc) {
+                    if (nPc > 2) priority(wc);
                     float sig = sigma[((p0 + wc) << 6) + 32 * cb + n];
                     for (int i = 0; i < wc; ++i) {
                         const bool urgent = i == wc - 1;           // the walker is waiting for this one
@@ -1277,13 +1292,6 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                                                             row_const, foff, n, h, v_lds(i << 6), v_lds((wc << 6) + 32 * cb), inv_rv2, vg_bias);
                         // the weights are complete here: the compiler must not sink their arithmetic below the wait
                         asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
-                        if (wc == 1 && !two_panels) {
-                            float* dt = diag + kDiagFloats;
-                            auto free = [&]() { await(diag_taken, 0, sync_err); };
-                            if (cb == 0) Ops::template half_diag<0, -1, VG == 1>(dt, lds_rows(64), narow + ((p0 + 1) << 6), alpha, row_const, foff, n, h, v_lds(64), inv_rv2, vg_bias, free);
-                            else Ops::template half_diag<1, -1, VG == 1>(dt, lds_rows(64), narow + ((p0 + 1) << 6), alpha, row_const, foff, n, h, v_lds(64), inv_rv2, vg_bias, free);
-                            part_done(1);
-                        }
                         if (urgent) { __builtin_amdgcn_s_setprio(3); await<true>(eta_done, i + 1, sync_err); }
                         else await(eta_done, i + 1, sync_err);
                         const float* sgn = etaF + (i << 6) + 32 * h;
@@ -1301,19 +1309,16 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                             sigma[((p0 + wc) << 6) + 32 * cb + n] = sig;                          // (both lane halves: the same value)
                             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");      // (in order, see publish_in_order)
                             if (lane == 0) __hip_atomic_fetch_add(col + wc, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            __builtin_amdgcn_s_setprio(0);
                         }
                     }
                 }
-                if (w == 1 && nPc > 2) {
-                    one_quadrant(c0, c0, 2);
-                    one_quadrant(c0, c1, 2);
-                    one_quadrant(c1, c1, 2);
+                if (nPc > 2) {
+                    priority(nPc - 1);
+                    const int x = four ? (w == 1 ? 2 : w == 7 ? 3 : 0) : w == 3 ? 2 : 0, y = four ? (w == 1 ? 2 : w == 6 ? 3 : 0) : w == 2 ? 2 : 0;
+                    if (x) diagonal_part(c0, whole, x);
+                    if (y) diagonal_part(c1, whole, y);
                 }
-                if (nPc > 3) {
-                    if (w == 6) { one_quadrant(c0, c0, 3); one_quadrant(c0, c1, 3); }
-                    else if (w == 7) one_quadrant(c1, c1, 3);
-                }
+                __builtin_amdgcn_s_setprio(0);
             } else {
             // diagonal tile of local panel l from the panel's fragments P (both operands), stored in turn
             auto diagonal = [&](const Frag (&P)[G::kGroups][2], int l) {
