@@ -625,6 +625,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     float* etaF = reinterpret_cast<float*>(etaMask + 16);          // [8][2][32]: +-1 of the chunk's panel l, entry h*32 + 16*rb + r
     float* diag = etaF + 512;                                      // two diagonal tiles
     float* scal = diag + kDiagArea;                              // [0] |mu|^2, [1] A, [2..2+kWaves) partial maxima
+    unsigned int* events = reinterpret_cast<unsigned int*>(scal + 12);   // smallest margin, largest |sigma|, near ties, FAIL
     int* prog = reinterpret_cast<int*>(scal + 16);                 // progress counters, see the panel pipeline below
     float* wpart = diag;                                           // [kWaves][D] column sums (statistics phase only)
     int* keptIdx = reinterpret_cast<int*>(diag);                   // [b/2]        (output phase only)
@@ -715,7 +716,24 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             sigma[i] = 0.f - threshold(i);                                       // never -0: the sign bit alone decides
         }
     };
-    // In blocks of several chunks with the values in memory they come before the loads: across them they cost those kernels registers
+    // What the walks have met (FAIL events, Alg. 2 line 7; near-tie decisions), from the decision-time values.  Wavefronts whose part in the
+    // pipeline is over look at all panels of a chunk but the last and leave it in the block's record; one wavefront behind the walk, all
+    // panels one after the other and its rows of the gather after that, ended 1.1 us (four panels) to 2.8 us (eight) after the others.
+    struct Events { int fail, near; float least, most; };
+    auto panel_events = [&](int p, Events& ev) {
+        const float tau = threshold((p << 6) + lane);
+        const float sg = sigma[(p << 6) + lane] + tau;                            // y^T eta / (c R^2) at decision time
+        const float margin = 0.5f * fabsf(fminf(fmaxf(sg, -1.f), 1.f) - tau);    // |u - clamp(p)|
+        ev.fail |= (__ballot(fabsf(sg) > 1.f) != 0ull);
+        ev.near += __popcll(__ballot(margin < 1e-4f));
+        ev.least = fminf(ev.least, margin);                                       // (a NaN counts as nothing)
+        ev.most = fmaxf(ev.most, fabsf(sg));
+    };
+    const bool want_events = a.status_out || a.stats_out;
+    // Chunks of up to so many panels leave all of them for the end: fp32 ones of two gain nothing (26.2 us for 4 x 512 tokens, d = 64, b = 128,
+    // two rounds, and 27.7), and with the values in memory the code beside the tiles costs registers that they have not got.
+    constexpr int kLateEvents = VG == 2 ? 16 : sizeof(T) == 4 ? 2 : 0;
+    // In blocks of several chunks with the values in memory the thresholds come before the loads: across them they cost those kernels registers
     // that the tiles' operands went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024
     // 318 -> 277 us, of 640 157 -> 134; blocks resident as one chunk gain nothing).
     constexpr bool kThresholdsFirst = VG == 2 && MULTI;
@@ -1051,6 +1069,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (has_row) narow[tid] = -pa_row;
             if (tid == 0) scal[1] = rc;
             if (tid < 32) prog[tid] = 0;                        // progress counters of the first chunk's pipeline
+            if (tid < 4) events[tid] = tid == 0 ? 0x7f61b1e6u : 0u;   // 3e38: no margin seen yet
         }
         __syncthreads();
     }
@@ -1201,8 +1220,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     const int row = 32 * (k >> 4) + 8 * ((k & 15) >> 2) + 4 * h + (k & 3);
                     etaF[(l << 6) + lane] = ((m >> row) & 1ull) ? 1.f : -1.f;
                 }
+                sigma[(I << 6) + lane] = sv;                  // decision-time values, for the events
                 publish_in_order(eta_done, l + 1);
-                sigma[(I << 6) + lane] = sv;                  // decision-time values, read back for the statistics (nobody waits for it)
             }
             __builtin_amdgcn_s_setprio(0);
         } else {
@@ -1464,6 +1483,20 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     }
                 }
             }
+            if (VG != 2 && want_events && w < nPc && nPc > kLateEvents) {   // (signs of this panel have met the wavefront's own column: no wait to speak of)
+                await(eta_done, w, sync_err);
+                Events ev = {0, 0, 3.0e38f, 0.f};
+                panel_events(p0 + w - 1, ev);
+                if (a.stats_out) { ev.least = wave_min(ev.least); ev.most = wave_max(ev.most); }
+                if (lane == 0) {
+                    if (a.stats_out) {                        // (non-negative floats: ordered as their bits)
+                        atomicMin(events, __float_as_uint(ev.least));
+                        atomicMax(events + 1, __float_as_uint(ev.most));
+                    }
+                    if (ev.near) atomicAdd(events + 2, (unsigned int)ev.near);
+                    if (ev.fail) atomicOr(events + 3, 1u);
+                }
+            }
         }
         __syncthreads();                                   // the chunk is done: LDS rows, counters and tile buffer are free
     }
@@ -1484,35 +1517,25 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         select_survivors(etaMask, b, wave, lane, keptIdx);
     }
     __syncthreads();
-    if (wave == 0) {      // side outputs: issued after the barrier so that nobody waits for these stores
-        if (a.signs_out)
-            for (int p = 0; p < nP; ++p)
-                a.signs_out[(size_t)signs0 + (p << 6) + lane] = ((etaMask[p] >> lane) & 1ull) ? 1 : -1;
-    } else if (wave == 2 && (a.status_out || a.stats_out)) {
-        // walk statistics from the decision-time values: FAIL events (Alg. 2 line 7), near-tie decisions
-        int n_margin = 0, any_fail = 0;
-        float min_margin = 3.0e38f, max_sigma = 0.f;
-        for (int p = 0; p < nP; ++p) {
-            const float tau = threshold((p << 6) + lane);
-            const float sg = sigma[(p << 6) + lane] + tau;                        // y^T eta / (c R^2) at decision time
-            any_fail |= (__ballot(fabsf(sg) > 1.f) != 0ull);
-            const float margin = 0.5f * fabsf(fminf(fmaxf(sg, -1.f), 1.f) - tau);  // |u - clamp(p)|
-            n_margin += __popcll(__ballot(margin < 1e-4f));
-            min_margin = fminf(min_margin, margin);
-            max_sigma = fmaxf(max_sigma, fabsf(sg));
+    // side outputs: behind the barrier, so that nobody waits for these stores
+    if (a.signs_out && wave == 0)
+        for (int p = 0; p < nP; ++p) a.signs_out[(size_t)signs0 + (p << 6) + lane] = ((etaMask[p] >> lane) & 1ull) ? 1 : -1;
+    if (wave == 2 && want_events) {
+        Events ev = {(int)events[3], (int)events[2], __uint_as_float(events[0]), __uint_as_float(events[1])};
+        for (int c = 0; c < n_chunks; ++c) {                       // the last panel of every chunk, or all of a short one
+            const int p1 = min((c + 1) * CH, b) >> 6, short_chunk = p1 - ((c * CH) >> 6) <= kLateEvents;
+            for (int p = short_chunk ? (c * CH) >> 6 : p1 - 1; p < p1; ++p) panel_events(p, ev);
         }
-        min_margin = wave_min(min_margin);
-        max_sigma = wave_max(max_sigma);
+        if (a.stats_out) { ev.least = wave_min(ev.least); ev.most = wave_max(ev.most); }
         if (lane == 0) {
             const int sync_failed = prog[3];
-            const int word = (any_fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (n_margin << 8);
             if (a.status_out) {
-                if (a.tree_mode) add_status(a.status_out + seq * a.status_stride + a.round, any_fail, sync_failed, n_margin);
-                else a.status_out[inst] = word;
+                if (a.tree_mode) add_status(a.status_out + seq * a.status_stride + a.round, ev.fail, sync_failed, ev.near);
+                else a.status_out[inst] = (ev.fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (ev.near << 8);
             }
             if (a.stats_out) {
-                a.stats_out[2 * inst] = min_margin;
-                a.stats_out[2 * inst + 1] = max_sigma;
+                a.stats_out[2 * inst] = ev.least;
+                a.stats_out[2 * inst + 1] = ev.most;
             }
         }
     }
