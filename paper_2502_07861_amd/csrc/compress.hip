@@ -783,7 +783,53 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         kept = CH == kCHm && b > CH && b <= RG * kU2 && b - CH <= RG * kUK && kU2 > kU0 && (center || need_norm);
     }
     if (kThresholdsFirst) thresholds();
-    if (MULTI && kept) {
+    float vmax = 0.f;
+    // this lane's value row of token i of the block (VG = 2: the operand fetches go through these)
+    const char* Vseq = VG != 0 ? a.V + (size_t)seq * a.v_seq_stride * G::kRowBytes : nullptr;
+    auto vrow = [&](int i) -> const char* {
+        const int64_t tok = a.idx_in ? (int64_t)a.idx_in[in_tok0 + i] : tok_base + i;
+        return Vseq + (size_t)tok * G::kRowBytes;
+    };
+    const bool measure_v = VG != 0 && !(rvalue2 > 0.f);
+    if constexpr (VG == 1) {
+        // Keys and values of the whole block in one trip to memory (with survivor indices, which come first, two): the value row of
+        // token i is the ORIGINAL row of that token, as in the gather at the end.  One after the other they were two (three, with keys
+        // by index four) trips of about 1.5 us.
+        constexpr int U = 8;                                        // (a thread's rows: keys and values of a block take 128 KB at most)
+        int32_t tok[U];
+        uintx4 kr[U], vr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)                                 // (b is a multiple of RG)
+            if (u * RG < b) tok[u] = a.idx_in ? a.idx_in[in_tok0 + u * RG + rg] : (int32_t)tok_base + u * RG + rg;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u * RG < b) {
+                const char* src = Kin + (size_t)(u * RG + rg) * G::kRowBytes;
+                if (a.k_by_idx) src = a.K + ((size_t)seq * a.v_seq_stride + (size_t)tok[u]) * G::kRowBytes;   // the block's rows lie scattered in the original tensor
+                kr[u] = *reinterpret_cast<const uintx4*>(src + sl * 16);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u * RG < b) vr[u] = *reinterpret_cast<const uintx4*>(Vseq + (size_t)tok[u] * G::kRowBytes + sl * 16);
+        thresholds();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u * RG < b) {
+                const int i = u * RG + rg;
+                *reinterpret_cast<uintx4*>(ldsK + (size_t)i * G::kLdsRow + G::slice_off(i, sl)) = kr[u];
+                if (center) Elem<T>::accumulate(part, kr[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u * RG < b) {
+                const int i = u * RG + rg;
+                *reinterpret_cast<uintx4*>(ldsV + (size_t)i * G::kLdsRow + G::slice_off(i, sl)) = vr[u];
+            }
+        if (measure_v)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * RG < b) vmax = fmaxf(vmax, group_sum<SL>(Elem<T>::dot(vr[u], vr[u])));
+    } else if (MULTI && kept) {
         uintx4 raw[kU2];
 #pragma unroll
         for (int u = 0; u < kU2; ++u) {
@@ -802,16 +848,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     } else {
         stage_chunk(0, min(CH, b), center ? b : 0, [&]() { if (!kThresholdsFirst) thresholds(); });
     }
-    // Value factor: the value row of every token of the block -> LDS (the row of token i is the ORIGINAL row of that
-    // token, as in the gather at the end); |v_i|^2 on the way when r_value has to be measured.
-    float vmax = 0.f;
-    // this lane's value row of token i of the block (VG = 2: the operand fetches go through these)
-    const char* Vseq = VG != 0 ? a.V + (size_t)seq * a.v_seq_stride * G::kRowBytes : nullptr;
-    auto vrow = [&](int i) -> const char* {
-        const int64_t tok = a.idx_in ? (int64_t)a.idx_in[in_tok0 + i] : tok_base + i;
-        return Vseq + (size_t)tok * G::kRowBytes;
-    };
-    if (VG == 1 || (VG == 2 && !(rvalue2 > 0.f))) {      // VG = 2 with a given radius: nothing to do here
+    if (VG == 2 && measure_v) {                         // r_value from the block's value rows (with a given radius: nothing to do here)
         constexpr int U = 16;
         for (int i0 = rg; i0 < b; i0 += RG * U) {
             uintx4 raw[U];
@@ -823,12 +860,11 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int i = i0 + u * RG;
-                if (i < b) {
-                    if constexpr (VG == 1) *reinterpret_cast<uintx4*>(ldsV + (size_t)i * G::kLdsRow + G::slice_off(i, sl)) = raw[u];
-                    vmax = fmaxf(vmax, group_sum<SL>(Elem<T>::dot(raw[u], raw[u])));
-                }
+                if (i < b) vmax = fmaxf(vmax, group_sum<SL>(Elem<T>::dot(raw[u], raw[u])));
             }
         }
+    }
+    if (measure_v) {
         vmax = wave_max(vmax);
         if (lane == 0) diag[kDiagArea - 64 + wave] = vmax;   // the tail of the buffer: beyond the mean partials
     }
@@ -1564,7 +1600,10 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int r = r0 + u * RG;
-                    if (r < half) vraw[u] = *reinterpret_cast<const uintx4*>(Vseq + (size_t)src_token(r) * G::kRowBytes + sl * 16);
+                    if constexpr (VG == 1) {                        // (resident, like the keys)
+                        const int kr = r < half ? keptIdx[r] : 0;
+                        if (r < half) vraw[u] = *reinterpret_cast<const uintx4*>(ldsV + (size_t)kr * G::kLdsRow + G::slice_off(kr, sl));
+                    } else if (r < half) vraw[u] = *reinterpret_cast<const uintx4*>(Vseq + (size_t)src_token(r) * G::kRowBytes + sl * 16);
                 }
             }
             if (k_global) {
@@ -1688,6 +1727,7 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     if (a.tok_k && (!a.tok_v || !a.carry_w || !vgram || n_inst != a.stream.n_seq)) return hipErrorInvalidValue;
     const bool v_lds = vgram && compress_value_gram_fits(row_bytes, a.b);
     a.chunk_rows = chunk_rows_for(row_bytes, a.b, v_lds);
+    if (v_lds && (a.chunk_rows < a.b || a.b * row_bytes > 8 * 16 * kThreads)) return hipErrorInvalidValue;    // eight rows of keys and of values a thread
     if (n_inst <= 0) return hipSuccess;
     a.stagger_blocks = 0; a.stagger_step = 0; a.prefetch_ahead = 0;
     {
