@@ -55,7 +55,8 @@ static inline size_t lds_fixed_bytes(int b) {
            + 8 * 64 * 4                  // eta of the resident chunk's panels as +-1 floats, accumulator order
            + (size_t)kDiagArea * 4
            + 64                          // scalars
-           + 128;                        // progress counters of the panel pipeline
+           + 128                         // progress counters of the panel pipeline
+           + (b <= kThreads ? (size_t)b * 4 : 0);   // original index of every token (blocks resident as one chunk)
 }
 // rows of the block staged in LDS at a time: as many 64-row panels as fit, at most 8
 // (with the value factor of Alg. 2 line 6 the value rows are staged next to the key rows: twice the bytes per row)
@@ -627,6 +628,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     float* scal = diag + kDiagArea;                              // [0] |mu|^2, [1] A, [2..2+kWaves) partial maxima
     unsigned int* events = reinterpret_cast<unsigned int*>(scal + 12);   // smallest margin, largest |sigma|, near ties, FAIL
     int* prog = reinterpret_cast<int*>(scal + 16);                 // progress counters, see the panel pipeline below
+    int32_t* tokOf = reinterpret_cast<int32_t*>(prog + 32);        // [b] original index of every token (kTokens, with idx_in)
     float* wpart = diag;                                           // [kWaves][D] column sums (statistics phase only)
     int* keptIdx = reinterpret_cast<int*>(diag);                   // [b/2]        (output phase only)
 
@@ -782,6 +784,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     if constexpr (MULTI) {
         kept = CH == kCHm && b > CH && b <= RG * kU2 && b - CH <= RG * kUK && kU2 > kU0 && (center || need_norm);
     }
+    // Resident blocks whose value rows are fetched by the gather: the survivors' indices are in LDS by then, and the rows take one
+    // trip to memory instead of two.
+    constexpr bool kTokens = !MULTI && VG == 0;                        // (b <= kThreads)
     if (kThresholdsFirst) thresholds();
     float vmax = 0.f;
     // this lane's value row of token i of the block (VG = 2: the operand fetches go through these)
@@ -846,7 +851,10 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             if (center && i < b) Elem<T>::accumulate(part, raw[u]);
         }
     } else {
+        int32_t mine = 0;
+        if (kTokens && a.idx_in && tid < b) mine = a.idx_in[in_tok0 + tid];
         stage_chunk(0, min(CH, b), center ? b : 0, [&]() { if (!kThresholdsFirst) thresholds(); });
+        if (kTokens && a.idx_in && tid < b) tokOf[tid] = mine;
     }
     if (VG == 2 && measure_v) {                         // r_value from the block's value rows (with a given radius: nothing to do here)
         constexpr int U = 16;
@@ -1582,6 +1590,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     // survivors: rows of the ORIGINAL keys / values, ascending index (16-byte slices, several rows in flight)
     auto src_token = [&](int r) -> int64_t {      // token of survivor r within its sequence, in the value tensor's frame
         const int kept = keptIdx[r];
+        if constexpr (kTokens) return a.idx_in ? (int64_t)tokOf[kept] : tok_base + kept;
         return a.idx_in ? (int64_t)a.idx_in[in_tok0 + kept] : tok_base + kept;
     };
     {
