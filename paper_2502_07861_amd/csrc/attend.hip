@@ -9,7 +9,8 @@
 //                 query n (B): the same pieces, so the contraction meets every column once.  Result: query n, keys 4 kg + r.
 //   O^T += V^T P  the weights are already where the next product wants them (column = query n, the lane's own keys), if the
 //                 lane loads the value rows of exactly those keys.  It takes columns d = kEpn n + e, e < kEpn, of each (16
-//                 lanes cover a row): element e is operand row n of product e.  bf16 pairs two keys per register by a byte
+//                 lanes cover a row; of fp32 rows of 512 bytes 4 n + e and 64 + 4 n + e, e < 4, so that a load covers 256 bytes
+//                 without gaps): element e is operand row n of product e.  bf16 pairs two keys per register by a byte
 //                 permute; fp32 elements are operands as they are.
 // So the pass needs no transposes, and a query's weights, running reference and sums stay in its own lanes.
 // What bounds it: with few queries per sequence the stream over K, V, w (1024 sequences x 8321 tokens x 4 queries, bf16:
@@ -176,7 +177,8 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
 // key groups of the range in turn.  Registers (NQT = 1, bf16, d = 128): 64 for the K and V rows in flight, 16 queries, 32
 // sums.  The rows of the next group are requested as soon as the registers of the current one are free (keys after S^T,
 // values after O^T), so that about 12 KB per wavefront are under way at any time.
-template <typename T, int D, int NQT, int W>
+// STREAM: K and V are read past the caches (see attend_streams).
+template <typename T, int D, int NQT, int W, bool STREAM = false>
 __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     constexpr bool B16 = sizeof(T) == 2;
     constexpr int ROWB = D * (int)sizeof(T);
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     uintx4 kf[NT][KC];
     unsigned int vf[VR][VD];
     float w0[VR], w1[VR];
-    const int koff = n * ROWB + kg * 16, voff = 4 * kg * ROWB + n * VD * 4;
+    const int koff = n * ROWB + kg * 16, vcol = n * (VD < 4 ? VD : 4) * 4, voff = 4 * kg * ROWB + vcol;
     auto load_w = [&](float (&w)[VR], int64_t g) {
         const float* p = wb + g * KEYS + 4 * kg;
 #pragma unroll
@@ -231,14 +233,15 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
             for (int r = 0; r < 4; ++r) w[4 * t + r] = x[r];
         }
     };
+    auto fetch = [](const auto* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; };
     auto load_v_row = [&](int j, const char* p) {
         if constexpr (VD == 2) {
-            const uintx2 x = *reinterpret_cast<const uintx2*>(p);
+            const uintx2 x = fetch(reinterpret_cast<const uintx2*>(p));
             vf[j][0] = x[0]; vf[j][1] = x[1];
         } else {
 #pragma unroll
             for (int c = 0; c < VD / 4; ++c) {
-                const uintx4 x = *reinterpret_cast<const uintx4*>(p + 16 * c);
+                const uintx4 x = fetch(reinterpret_cast<const uintx4*>(p + 256 * c));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) vf[j][4 * c + i] = x[i];
             }
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int c = 0; c < KC; ++c) kf[t][c] = *reinterpret_cast<const uintx4*>(p + 16 * t * ROWB + 64 * c);
+            for (int c = 0; c < KC; ++c) kf[t][c] = fetch(reinterpret_cast<const uintx4*>(p + 16 * t * ROWB + 64 * c));
     };
     auto load_v = [&](int64_t g) {
         const char* p = Vb + (size_t)g * (KEYS * ROWB) + voff;
@@ -468,7 +471,7 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
             const int row = 4 * kg + (j & 3) + 16 * (j >> 2);
             const float x = wb[full * KEYS + min(row, left)];
             wt[j] = row <= left ? x : 0.f;
-            if (has_v) load_v_row(j, Vb + (size_t)full * (KEYS * ROWB) + min(row, left) * ROWB + n * VD * 4);
+            if (has_v) load_v_row(j, Vb + (size_t)full * (KEYS * ROWB) + min(row, left) * ROWB + vcol);
         }
         qk();
         softmax(wt);
@@ -492,7 +495,7 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
                     for (int e = 0; e < EPN; e += 4) {
                         const floatx4 x = {o[t][e][r], o[t][e + 1][r], o[t][e + 2][r], o[t][e + 3][r]};
-                        *reinterpret_cast<floatx4*>(row + EPN * (4 * kg + r) + e) = x;
+                        *reinterpret_cast<floatx4*>(row + (VD > 4 ? 16 * e + 4 * (4 * kg + r) : EPN * (4 * kg + r) + e)) = x;
                     }
             }
             if (kg == 0) *reinterpret_cast<floatx2*>(row + D) = floatx2{m[t], l[t]};
@@ -576,6 +579,16 @@ static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, in
     // (1024 x 2000 tokens, d = 64: 184 us against 196; 256 x 1000, d = 128: 43 against 47; one sequence of 65536, d = 64: 16.7
     // against 15.9).  32 queries take eight (one workgroup per compute unit, LDS).
     p.waves = elem == 2 && p.nqt == 1 && all * wgs > kTargetWaves ? 4 : 8;
+    if (p.waves == 4) {
+        // Eight as well where such workgroups fill most of the compute units once (one each at a time): all start together and end together,
+        // and half as many partials are merged.  4 queries, 4 wavefronts / 8: 256 x 1000 tokens (256 workgroups) 24.2 / 21.6 us, 64 x 4100
+        // 25.1 / 24.5, caches read in turn 30.1 / 28.5, 256 x 8321 170.7 / 165.5, 32 x 8321 (224) 26.2 / 25.0, 16 x 16000 (208) 27.7 / 24.8, 64 x 2100
+        // (192) 17.1 / 16.2; not so with 300 (100 x 3000 27.7 / 37.3) or four rounds of them (1024 x 1000 81.5 / 85.8).
+        const int64_t steps8 = (all * wgs + kTargetWaves - 1) / kTargetWaves, n_cu = compute_units();
+        int64_t ns8 = 0;
+        for (int k = 0; k < 2; ++k) ns8 += ((cnt[k] + keys - 1) / keys + steps8 * 8 - 1) / (steps8 * 8);
+        if (wgs * ns8 <= n_cu && 4 * wgs * ns8 >= 3 * n_cu) p.waves = 8;
+    }
     const size_t row_bytes = (size_t)p.rows * (d + kRowPad) * sizeof(float);
     int64_t most = (int64_t)(max_bytes / ((size_t)wgs * row_bytes));          // splits whose partials fit the buffer
     int64_t steps = (all * wgs + kTargetWaves - 1) / kTargetWaves;             // per wavefront
@@ -617,6 +630,15 @@ size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int 
     return p.partial_bytes + p.arrive_bytes;
 }
 
+// Rows that are read once (up to 16 queries: one query group) and are more than the 256 MB that the cache in front of the memory
+// holds come back from memory the next time whatever is done, and keeping them costs.  Past the caches (4 queries, d = 128): bf16 1024 x 8321
+// tokens 707 -> 649 us, 1024 x 1000 (0.5 GB) 90.0 -> 81.5; fp32 256 x 8321 366 -> 340, 1024 x 1000 183 -> 175.  Below that they may still be
+// there (bf16 256 x 2000 tokens, 0.26 GB: 42.4 us when they are, 46.3 past the caches), so the line lies a little above what the cache holds.
+static bool attend_streams(int row_bytes, const AttendArgs& a) {
+    const int64_t rows = a.n_seq * (2 * a.set[0].count + a.set[1].count);
+    return rows * row_bytes > ((int64_t)320 << 20);
+}
+
 template <typename T, int D>
 static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipStream_t st) {
     // (two dimensions: a grid may not exceed 2^32 threads in one of them)
@@ -625,7 +647,10 @@ static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipS
     const int64_t units = a.n_seq * (a.set[0].count + a.set[1].count);
     hipError_t e = hipSuccess;
     if (p.nqt == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, grid, dim3(512), 0, st, a);
-    else if (p.waves == 8) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, grid, dim3(512), 0, st, a);
+    else if (attend_streams(D * (int)sizeof(T), a)) {
+        if (p.waves == 8) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8, true>, grid, dim3(512), 0, st, a);
+        else if constexpr (sizeof(T) == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4, true>, grid, dim3(256), 0, st, a);
+    } else if (p.waves == 8) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8>, grid, dim3(512), 0, st, a);
     else if constexpr (sizeof(T) == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 4>, grid, dim3(256), 0, st, a);
     if (e != hipSuccess || p.ns[0] + p.ns[1] == 1 || p.fused) return e;
     return launch_timed(kProfAttendMerge, a.n_seq * a.n_q, attend_merge_kernel<T, D>, dim3(a.n_q, (unsigned)a.n_seq), dim3(kMergeThreads), 0, st,

@@ -924,6 +924,30 @@ def test_attend_edges(bk, dtype, d, n_seq, count, g, nq):
         np.testing.assert_allclose(lse.cpu().numpy(), ref2_lse.numpy(), atol=1e-3 if dtype == torch.bfloat16 else 1e-5, rtol=1e-5)
 
 
+@pytest.mark.parametrize("dtype,d,n_seq,count,stride,g", [
+    (torch.bfloat16, 128, 64, 10301, 10310, 4), (torch.bfloat16, 128, 701, 999, 1000, 16), (torch.bfloat16, 64, 520, 2600, 2601, 5),      # more than the
+    (torch.float32, 128, 41, 8193, 8200, 4), (torch.float32, 64, 90, 8190, 8192, 16),                                                     # caches hold
+    (torch.bfloat16, 128, 256, 97, 100, 1), (torch.bfloat16, 128, 200, 1001, 1001, 4), (torch.bfloat16, 64, 64, 4100, 4111, 2)])          # one round of eight
+def test_attend_of_many_sequences_equals_few(bk, dtype, d, n_seq, count, stride, g):
+    """Rows read past the caches, and workgroups of eight wavefronts where they fill the compute units once, against the same sequences eight
+    at a time (neither rule takes those).  Only the order of the sums differs: outputs to their own rounding (bf16: 2^-9 each) or to that
+    of fp32 sums, lse to that of fp32 sums."""
+    gen = torch.Generator(device="cuda").manual_seed(count)
+    K = torch.randn(n_seq, stride, d, generator=gen, device="cuda", dtype=torch.float32).mul_(2.0).to(dtype)
+    V = torch.randn(n_seq, stride, d, generator=gen, device="cuda", dtype=torch.float32).to(dtype)
+    Q = torch.randn(n_seq, g, 1, d, generator=gen, device="cuda", dtype=torch.float32).to(dtype)
+    w = torch.tensor([0.0, 1.0, 2.0, 4.0], device="cuda")[torch.randint(0, 4, (n_seq, stride), generator=gen, device="cuda")]
+    w[:, 64:96] = 0.0                                                    # a group without a live token
+    p = bk.make_params(d, 128, 2, dtype, log_c=0.0)
+    out, lse = bk.attend_kv(p, K, V, w, Q, count=count)
+    for lo in range(0, n_seq, 8):
+        s = slice(lo, lo + 8)
+        ref, ref_lse = bk.attend_kv(p, K[s].contiguous(), V[s].contiguous(), w[s].contiguous(), Q[s].contiguous(), count=count)
+        x, y = out[s].double(), ref.double()
+        assert float((x - y).norm() / y.norm()) <= (1e-5 if dtype == torch.float32 else 4e-3)
+        torch.testing.assert_close(lse[s], ref_lse, rtol=1e-6, atol=1e-5)
+
+
 @pytest.mark.parametrize("n_seq,count,g,nq", [(8, 4357, 4, 1), (3, 2000, 1, 1), (8, 4096, 4, 16)])
 def test_attend_does_not_depend_on_what_the_workspace_holds(bk, n_seq, count, g, nq):
     """A call gives the same bytes on a fresh workspace and on one that holds what an earlier call left there, shifted by anything
