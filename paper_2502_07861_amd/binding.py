@@ -121,6 +121,10 @@ def _torch_dtype(p):
     return torch.bfloat16 if p.dtype == BKV_BF16 else torch.float32
 
 
+# Short calls are over on the GPU before the next one is issued unless the marshalling is short too: addresses go to ctypes as plain
+# integers, the current stream is asked for its handle without a Stream object around it, nothing is asked of the library that the
+# call does not need, and outputs come from the input (new_empty).  Time to issue a call, us: merge_reduce of one head 19-25 -> 17-18,
+# attend_kv 12-13 -> 9-10, a token appended to a Stream and attended 17-19 -> 12-13.
 def _ptr(t, dtype=None, what="tensor"):
     if t is None:
         return None
@@ -130,11 +134,18 @@ def _ptr(t, dtype=None, what="tensor"):
         raise ValueError("%s must be contiguous" % what)
     if dtype is not None and t.dtype != dtype:
         raise ValueError("%s must be %s, got %s" % (what, dtype, t.dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is None or _current_device is None:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
+else:
+    def _stream():
+        """Handle of the current device's current stream (a tensor is on the GPU, so the runtime is up)."""
+        return _raw_stream(_current_device())
 
 
 def _check(rc, what):
@@ -154,14 +165,14 @@ def compress_block(p, K, V=None, *, inst_ids=None, w_in=1.0, uniforms=None, emit
     dt = _torch_dtype(p)
     n_inst, b, d = K.shape
     assert b == p.block and d == p.d
-    dev = K.device
-    K_out = torch.empty(n_inst, b // 2, d, device=dev, dtype=dt)
-    V_out = torch.empty(n_inst, b // 2, d, device=dev, dtype=dt) if V is not None else None
-    w_out = torch.empty(n_inst, b // 2, device=dev, dtype=torch.float32)
-    idx = torch.empty(n_inst, b // 2, device=dev, dtype=torch.int32)
-    signs = torch.empty(n_inst, b, device=dev, dtype=torch.int8) if emit_signs else None
-    status = torch.empty(n_inst, device=dev, dtype=torch.int32)
-    stats = torch.empty(n_inst, 2, device=dev, dtype=torch.float32) if emit_stats else None
+    new = K.new_empty
+    K_out = new((n_inst, b // 2, d), dtype=dt)
+    V_out = new((n_inst, b // 2, d), dtype=dt) if V is not None else None
+    w_out = new((n_inst, b // 2), dtype=torch.float32)
+    idx = new((n_inst, b // 2), dtype=torch.int32)
+    signs = new((n_inst, b), dtype=torch.int8) if emit_signs else None
+    status = new((n_inst,), dtype=torch.int32)
+    stats = new((n_inst, 2), dtype=torch.float32) if emit_stats else None
     ids = inst_ids.view(torch.int64) if inst_ids is not None else None
     rc = lib().bkv_compress_block(C.byref(p), _ptr(K, dt, "K"), _ptr(V, dt, "V"), n_inst, _ptr(ids, torch.int64),
                                   float(w_in), _ptr(uniforms, torch.float32, "uniforms"), _ptr(K_out), _ptr(V_out),
@@ -192,14 +203,12 @@ def merge_reduce(p, K, V, *, seq_base=0, emit_signs=False, workspace=None, out=N
     dev = K.device
     m = n >> T
     if out is None:
-        out = dict(K=torch.empty(n_seq, m, d, device=dev, dtype=dt), V=torch.empty(n_seq, m, d, device=dev, dtype=dt),
-                   w=torch.empty(n_seq, m, device=dev, dtype=torch.float32),
-                   idx=torch.empty(n_seq, m, device=dev, dtype=torch.int32),
-                   status=torch.empty(n_seq, max(T, 1), device=dev, dtype=torch.int32))
+        new = K.new_empty
+        out = dict(K=new((n_seq, m, d), dtype=dt), V=new((n_seq, m, d), dtype=dt), w=new((n_seq, m), dtype=torch.float32),
+                   idx=new((n_seq, m), dtype=torch.int32), status=new((n_seq, max(T, 1)), dtype=torch.int32))
     signs_flat = torch.empty(n_seq * (2 * n - ((2 * n) >> T)), device=dev, dtype=torch.int8) if emit_signs else None
-    need = merge_reduce_workspace_bytes(p, n_seq, n)
     if workspace is None:
-        workspace = torch.empty(need, device=dev, dtype=torch.uint8)
+        workspace = torch.empty(merge_reduce_workspace_bytes(p, n_seq, n), device=dev, dtype=torch.uint8)
     rc = lib().bkv_merge_reduce(C.byref(p), _ptr(K, dt, "K"), _ptr(V, dt, "V"), n_seq, n, seq_base, _ptr(out["K"]),
                                 _ptr(out["V"]), _ptr(out["w"]), _ptr(out["idx"]) if T > 0 else None, _ptr(signs_flat),
                                 _ptr(out["status"]) if T > 0 else None, _ptr(workspace), workspace.numel(), _stream())
@@ -219,9 +228,9 @@ def merge_reduce_protected(p, K, V, n_sink, n_recent, *, seq_base=0, workspace=N
     dev = K.device
     n_mid = n - n_sink - n_recent
     count = n_sink + (max(n_mid, 0) >> T) + n_recent
-    out = dict(K=torch.empty(n_seq, count, d, device=dev, dtype=dt), V=torch.empty(n_seq, count, d, device=dev, dtype=dt),
-               w=torch.empty(n_seq, count, device=dev, dtype=torch.float32),
-               idx=torch.empty(n_seq, count, device=dev, dtype=torch.int32),
+    new = K.new_empty
+    out = dict(K=new((n_seq, count, d), dtype=dt), V=new((n_seq, count, d), dtype=dt), w=new((n_seq, count), dtype=torch.float32),
+               idx=new((n_seq, count), dtype=torch.int32),
                # the library writes every entry when T > 0 (poisoned here so that a test can tell)
                status=torch.full((n_seq, T), -1, device=dev, dtype=torch.int32) if T > 0
                else torch.zeros(n_seq, 1, device=dev, dtype=torch.int32))
@@ -248,8 +257,8 @@ def attend_kv(p, K_c, V_c, w, Q, *, count=None, workspace=None, out=None, lse=Tr
         count = stride
     dev = Q.device
     if out is None:
-        out = torch.empty(n_seq, g, nq, d, device=dev, dtype=dt)
-    lse_t = torch.empty(n_seq, g, nq, device=dev, dtype=torch.float32) if lse else None
+        out = Q.new_empty((n_seq, g, nq, d), dtype=dt)
+    lse_t = Q.new_empty((n_seq, g, nq), dtype=torch.float32) if lse else None
     if workspace is None:
         workspace = torch.empty(attend_workspace_bytes(p, n_seq, count, g, nq), device=dev, dtype=torch.uint8)
     rc = lib().bkv_attend_kv(C.byref(p), _ptr(K_c, dt, "K_c"), _ptr(V_c, dt, "V_c"), _ptr(w, torch.float32, "w"), n_seq,
@@ -288,16 +297,14 @@ def balancekv_sets(p, which, K, V, *, seq_base=0, eps=0.0, r=0.0, capacity=None,
     T = p.rounds
     if capacity is None:
         capacity = int(lib().bkv_sets_capacity(C.byref(p), n, max_buckets if which == BKV_SET_NUMERATOR else 1))
-    res = dict(K=torch.empty(n_seq, capacity, d, device=dev, dtype=dt), V=torch.empty(n_seq, capacity, d, device=dev, dtype=dt),
-               w=torch.empty(n_seq, capacity, device=dev, dtype=torch.float32),
-               idx=torch.empty(n_seq, capacity, device=dev, dtype=torch.int32),
-               count=torch.empty(n_seq, device=dev, dtype=torch.int32),
-               slot=torch.empty(n_seq, n, device=dev, dtype=torch.int32) if emit_slots else None,
-               status=torch.empty(n_seq, max(T, 1), device=dev, dtype=torch.int32))
+    new = K.new_empty
+    res = dict(K=new((n_seq, capacity, d), dtype=dt), V=new((n_seq, capacity, d), dtype=dt), w=new((n_seq, capacity), dtype=torch.float32),
+               idx=new((n_seq, capacity), dtype=torch.int32), count=new((n_seq,), dtype=torch.int32),
+               slot=new((n_seq, n), dtype=torch.int32) if emit_slots else None, status=new((n_seq, max(T, 1)), dtype=torch.int32))
     sizes = [n_seq * (n >> r_) for r_ in range(T)]
     signs_flat = torch.zeros(max(sum(sizes), 1), device=dev, dtype=torch.int8) if emit_signs else None
-    need = int(lib().bkv_balancekv_sets_workspace_bytes(C.byref(p), n_seq, n, capacity))
     if workspace is None:
+        need = int(lib().bkv_balancekv_sets_workspace_bytes(C.byref(p), n_seq, n, capacity))
         workspace = torch.empty(max(need, 1), device=dev, dtype=torch.uint8)
     rc = lib().bkv_balancekv_sets(C.byref(p), which, _ptr(K, dt, "K"), _ptr(V, dt, "V"), n_seq, n, seq_base, float(eps), float(r),
                                   _ptr(res["K"]), _ptr(res["V"]), _ptr(res["w"]), _ptr(res["idx"]), capacity, _ptr(res["count"]),
@@ -319,8 +326,8 @@ def attend_sets(p, num, den, Q, *, count_n=None, count_d=None, workspace=None):
     Kn, Vn, wn = num
     Kd, wd = den
     n_seq, g, nq, d = Q.shape
-    out = torch.empty(n_seq, g, nq, d, device=Q.device, dtype=dt)
-    lse = torch.empty(n_seq, g, nq, device=Q.device, dtype=torch.float32)
+    out = Q.new_empty((n_seq, g, nq, d), dtype=dt)
+    lse = Q.new_empty((n_seq, g, nq), dtype=torch.float32)
     if workspace is None:
         workspace = torch.empty(int(lib().bkv_attend_sets_workspace_bytes(C.byref(p), n_seq, g, nq)), device=Q.device, dtype=torch.uint8)
     rc = lib().bkv_attend_sets(C.byref(p), _ptr(Kn, dt, "K_n"), _ptr(Vn, dt, "V_n"), _ptr(wn, torch.float32, "w_n"),
@@ -349,6 +356,7 @@ class Cache:
         self.h = h
         self._append_ws = torch.empty(int(lib().bkv_append_workspace_bytes(h)), device=device, dtype=torch.uint8)
         self._attend_ws = {}
+        self._dt = _torch_dtype(p)           # (the library has taken a copy of the parameters)
 
     def close(self):
         if self.h:
@@ -387,25 +395,25 @@ class Cache:
 
     def append_token(self, k, v, status=None, uniforms=None, signs=None):
         """bkv_append_token; uniforms / signs [T, n_seq, block] (fp32 / int8) are the decision-level hooks."""
-        dt = _torch_dtype(self.p)
+        dt, ws = self._dt, self._append_ws
         return _check(lib().bkv_append_token(self.h, _ptr(k, dt, "k"), _ptr(v, dt, "v"), _ptr(status),
                                              _ptr(uniforms, torch.float32, "uniforms"), _ptr(signs, torch.int8, "signs"),
-                                             _ptr(self._append_ws), self._append_ws.numel(), _stream()),
+                                             ws.data_ptr(), ws.numel(), _stream()),
                       "bkv_append_token")
 
     def attend(self, Q, out=None, lse=True):
-        dt = _torch_dtype(self.p)
+        dt = self._dt
         n_seq, g, nq, d = Q.shape
         if out is None:
-            out = torch.empty(n_seq, g, nq, d, device=Q.device, dtype=dt)
-        lse_t = torch.empty(n_seq, g, nq, device=Q.device, dtype=torch.float32) if lse else None
+            out = Q.new_empty((n_seq, g, nq, d), dtype=dt)
+        lse_t = Q.new_empty((n_seq, g, nq), dtype=torch.float32) if lse else None
         ws = self._attend_ws.get((g, nq))
         if ws is None:
             ws = torch.empty(int(lib().bkv_cache_attend_workspace_bytes(self.h, g, nq)), device=Q.device,
                              dtype=torch.uint8)
             self._attend_ws[(g, nq)] = ws
-        _check(lib().bkv_attend(self.h, _ptr(Q, dt, "Q"), g, nq, _ptr(out), _ptr(lse_t), _ptr(ws), ws.numel(),
-                                _stream()), "bkv_attend")
+        _check(lib().bkv_attend(self.h, _ptr(Q, dt, "Q"), g, nq, _ptr(out), None if lse_t is None else lse_t.data_ptr(), ws.data_ptr(),
+                                ws.numel(), _stream()), "bkv_attend")
         return out, lse_t
 
     def error_word(self) -> int:
@@ -454,6 +462,7 @@ class Stream:
                                      C.c_void_p(self.storage.data_ptr() + off), nbytes, _stream()), "bkv_stream_init")
         self.h = h
         self._attend_ws = {}
+        self._dt = _torch_dtype(p)           # (the library has taken a copy of the parameters)
 
     def close(self):
         if self.h:
@@ -472,22 +481,22 @@ class Stream:
 
     def append(self, k, v, status_num=None, status_den=None):
         """bkv_stream_append; returns the number of launches issued."""
-        dt = _torch_dtype(self.p)
+        dt = self._dt
         return _check(lib().bkv_stream_append(self.h, _ptr(k, dt, "k"), _ptr(v, dt, "v"), _ptr(status_num, torch.int32, "status_num"),
                                               _ptr(status_den, torch.int32, "status_den"), _stream()), "bkv_stream_append")
 
     def attend(self, Q, out=None, lse=True):
-        dt = _torch_dtype(self.p)
+        dt = self._dt
         n_seq, g, nq, d = Q.shape
         if out is None:
-            out = torch.empty(n_seq, g, nq, d, device=Q.device, dtype=dt)
-        lse_t = torch.empty(n_seq, g, nq, device=Q.device, dtype=torch.float32) if lse else None
+            out = Q.new_empty((n_seq, g, nq, d), dtype=dt)
+        lse_t = Q.new_empty((n_seq, g, nq), dtype=torch.float32) if lse else None
         ws = self._attend_ws.get((g, nq))
         if ws is None:
             ws = torch.empty(int(lib().bkv_stream_attend_workspace_bytes(self.h, g, nq)), device=Q.device, dtype=torch.uint8)
             self._attend_ws[(g, nq)] = ws
-        _check(lib().bkv_stream_attend(self.h, _ptr(Q, dt, "Q"), g, nq, _ptr(out), _ptr(lse_t), _ptr(ws), ws.numel(),
-                                       _stream()), "bkv_stream_attend")
+        _check(lib().bkv_stream_attend(self.h, _ptr(Q, dt, "Q"), g, nq, _ptr(out), None if lse_t is None else lse_t.data_ptr(), ws.data_ptr(),
+                                       ws.numel(), _stream()), "bkv_stream_attend")
         return out, lse_t
 
     def views(self):
