@@ -208,7 +208,27 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
             idx_final = (int32_t*)workspace;
         }
     }
-    if (status_out && !(win && win->status_clear) && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
+    // The status words.  A round with room for a word per block sums its own up (the first one also clears the others'): the first round has
+    // it in the key buffer of the second, the last one in the buffer it would write if it were not the last, with one round the workspace, if it
+    // is there and does not hold the indices.  Not in a launch that will be replayed: its label would repeat.  Else they are cleared first
+    // and added to.  The sum is one trip to memory at the end of a launch, additions by many blocks wait for each other: the last round
+    // takes it from eight blocks a sequence on (two rounds, additions / sum: b = 512, 16 blocks 54.2 / 52.1 us, b = 128, 8 blocks 24.2 / 23.6, b = 64, 2
+    // blocks 19.8 / 20.2); the first round saves the launch that clears whatever it holds (3.3 us).
+    bool may_sum = false;
+    if (status_out && T <= 64) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();       // (a launch says for itself what is wrong with the stream)
+        else may_sum = capture == hipStreamCaptureStatusNone;
+    }
+    auto words_of = [&](int r) -> unsigned long long* {
+        const int64_t per_seq = (n >> r) / b;
+        if (!may_sum || (r > 0 && (r < T - 1 || per_seq < 8))) return nullptr;
+        if (!bkv::compress_sums_status(p->dtype, p->d, b, (p->flags & BKV_VALUE_GRAM) != 0, n_seq * per_seq)) return nullptr;
+        if (T > 1) return (unsigned long long*)kbuf[r == 0 ? 1 : r & 1];                      // (at least n_seq * n / 4 rows)
+        return idx_out && workspace && aligned16(workspace) && ws_bytes >= (size_t)(n_seq * per_seq) * 8 ? (unsigned long long*)workspace : nullptr;
+    };
+    unsigned long long* words = words_of(0);
+    if (status_out && !words && !(win && win->status_clear) && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
 
     const char* k_in = (const char*)K;
     const int32_t* i_in = nullptr;
@@ -229,6 +249,8 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
         a.idx_out = last ? idx_final : ibuf[r & 1];
         a.signs_out = signs_out ? signs_out + (size_t)n_seq * (size_t)(2 * n - ((2 * n) >> r)) : nullptr;
         a.status_out = status_out; a.status_stride = T; a.sticky_err = sticky_err;
+        if (r > 0) words = words_of(r);
+        if (words) { a.status_words = words; a.status_label = bkv::status_label(); }
         a.in_seq_stride = r == 0 ? k_stride : m; a.out_seq_stride = last ? out_stride : m / 2;
         a.idx_out_seq_stride = (last && idx_out && win && win->idx_out_stride) ? win->idx_out_stride : m / 2;
         a.blocks_per_seq = (int32_t)(m / b);

@@ -683,12 +683,15 @@ hipError_t attend_static_scratch(void** ptr) {
 
 // A number that no other launch of this process has (mix64 is one to one), and other processes' launches next to never: memory
 // that another one has left must not look arrived.
-static unsigned long long launch_number() {
+static unsigned long long launch_count() {
     static const unsigned long long first = mix64((unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()) ^
                                             mix64((unsigned long long)getpid());
     static std::atomic<unsigned long long> launches{0};
-    return mix64(first + launches.fetch_add(1, std::memory_order_relaxed));
+    return first + launches.fetch_add(1, std::memory_order_relaxed);
 }
+static unsigned long long launch_number() { return mix64(launch_count()); }
+// The same in 51 bits, for launches that keep theirs in words with something else: the count itself.
+unsigned long long status_label() { return launch_count() & ((1ull << 51) - 1); }
 
 hipError_t launch_attend(int dtype, int d, AttendArgs& a, void* workspace, size_t ws_bytes, size_t max_bytes, hipStream_t st) {
     if (a.n_seq <= 0 || a.n_q <= 0) return hipSuccess;

@@ -50,6 +50,10 @@ struct CompressArgs {
     int8_t* signs_out;
     int32_t* status_out;
     float* stats_out;
+    // Tree mode, with status_out and no table: a word per block.  The launch then writes status_out instead of adding to it, and clears
+    // the entries of the rounds behind its own (see sum_status_words).
+    unsigned long long* status_words;
+    unsigned long long status_label;   // 51 bits that no other launch has
     int32_t* sticky_err;      // or null: one word that collects BKV_STATUS_INTERNAL of every instance (never cleared by the kernel)
     const uint64_t* inst_ids;
     const float* uniforms;
@@ -99,6 +103,8 @@ int compute_units();                                  // of this thread's first 
 size_t compress_lds_bytes(int row_bytes, int b, bool value_gram = false);
 bool compress_value_gram_fits(int row_bytes, int b);   // keys and values of one block resident in LDS together
 bool compress_block_resident(int row_bytes, int b, bool value_gram);   // the block runs as one resident chunk
+bool compress_sums_status(int dtype, int d, int b, bool value_gram, int64_t n_inst);   // does a launch of this shape take status_words?
+unsigned long long status_label();                                                      // a new one
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st);
 // two blocks per compute unit (compress_pair.hip): rows of 256 bytes, no weight dump, value factor, in-place carry or scattered rows
 hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t n_inst, hipStream_t st);

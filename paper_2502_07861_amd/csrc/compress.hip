@@ -1564,22 +1564,30 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     // side outputs: behind the barrier, so that nobody waits for these stores
     if (a.signs_out && wave == 0)
         for (int p = 0; p < nP; ++p) a.signs_out[(size_t)signs0 + (p << 6) + lane] = ((etaMask[p] >> lane) & 1ull) ? 1 : -1;
+    // (What is only needed here is read here: held, it is spilled to vector registers' lanes and back in the pipeline, 32 to 48 scalar registers
+    // with the values in LDS.  But for bf16 with the values in memory: 300 blocks of 512 128 us held, 134 read here; fp32, numerator sets of
+    // 4 x 4000 tokens, b = 256, 200 and 181.)
+    constexpr bool kArgsHeld = VG == 2 && sizeof(T) == 2;
+    int fails = 0, near_ties = 0;              // of the whole block (wavefront 2)
     if (wave == 2 && want_events) {
+        const CompressArgs& o = kArgsHeld ? a : *args_here();
+        unsigned long long* words = CARRY ? nullptr : o.status_words;
+        int32_t* status = o.tree_mode ? nullptr : o.status_out;
+        float* stats = o.stats_out;
+        const unsigned long long label = o.status_label;
         Events ev = {(int)events[3], (int)events[2], __uint_as_float(events[0]), __uint_as_float(events[1])};
         for (int c = 0; c < n_chunks; ++c) {                       // the last panel of every chunk, or all of a short one
             const int p1 = min((c + 1) * CH, b) >> 6, short_chunk = p1 - ((c * CH) >> 6) <= kLateEvents;
             for (int p = short_chunk ? (c * CH) >> 6 : p1 - 1; p < p1; ++p) panel_events(p, ev);
         }
-        if (a.stats_out) { ev.least = wave_min(ev.least); ev.most = wave_max(ev.most); }
+        if (stats) { ev.least = wave_min(ev.least); ev.most = wave_max(ev.most); }
+        fails = ev.fail; near_ties = ev.near;
         if (lane == 0) {
-            const int sync_failed = prog[3];
-            if (a.status_out) {
-                if (a.tree_mode) add_status(a.status_out + seq * a.status_stride + a.round, ev.fail, sync_failed, ev.near);
-                else a.status_out[inst] = (ev.fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (ev.near << 8);
-            }
-            if (a.stats_out) {
-                a.stats_out[2 * inst] = ev.least;
-                a.stats_out[2 * inst + 1] = ev.most;
+            if (words) put_status_word(words + inst, label, fails, prog[3], near_ties);
+            if (status) status[inst] = (fails ? BKV_STATUS_FAIL : 0) | (prog[3] ? BKV_STATUS_INTERNAL : 0) | (near_ties << 8);
+            if (stats) {
+                stats[2 * inst] = ev.least;
+                stats[2 * inst + 1] = ev.most;
             }
         }
     }
@@ -1665,6 +1673,19 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         if (a.w_out) a.w_out[out_tok0 + r] = a.w_out_val;
         if (a.idx_out) a.idx_out[idx_out0 + r] = (int32_t)src_token(r);
     }
+    // (Behind the rows: an update takes trips to memory, one after the other for blocks that meet there, and rows that wait for it make
+    // the block late.)
+    if (wave == 2 && a.tree_mode && a.status_out) {
+        const CompressArgs& o = kArgsHeld ? a : *args_here();
+        if (!CARRY && o.status_words) {
+            unsigned int i = blockIdx.x;                     // (the block's coordinates anew: kept through the pipeline they cost registers)
+            asm volatile("" : "+s"(i));
+            const unsigned int per = (unsigned int)o.blocks_per_seq, s = i / per;
+            int32_t* status = o.status_out + (int64_t)s * o.status_stride;
+            sum_status_words(o.status_words + (int64_t)s * per, (int)per, o.status_label, lane, status + o.round);
+            if (i == s * per && lane < o.status_stride && lane > o.round) status[lane] = 0;      // the rounds to come add to theirs
+        } else if (lane == 0) add_status(o.status_out + seq * o.status_stride + o.round, fails, prog[3], near_ties);
+    }
     // A carry leaves the stream's state complete: as a launch of its own behind every round (survivors back from a buffer) the
     // same cost a launch per round and token whether or not anything carried.  An instance of its own: as a run-time choice these
     // barriers cost every other halving 3 % (8 x 16384 tokens, blocks of 512, two rounds: 63.3 -> 66.2 us).
@@ -1725,12 +1746,29 @@ int compute_units() {
     return n_cu;
 }
 
+// More blocks than compute units: two of them on each (compress_pair.hip).  Up to one per compute unit a launch takes
+// as long as one block, and a block that has the compute unit to itself is done sooner (192 and 256 blocks of 512 bf16
+// rows 11 % sooner, of 1024 rows 15 %).  With more the pair is faster (time of the other kernel over its own, 256
+// compute units): b = 64 1.25 (257 blocks) to 2.0 (1024), 256 1.15 to 1.5, 512 1.08 to 1.24, 1024 1.02 to 1.25, where
+// the last round is thin least.  Two exceptions: two blocks everywhere and a few more of more than 768 rows (514 and
+// 528 blocks: 0.97 to 1.00; 560 on: 1.01 to 1.04), and single precision beyond one chunk (b > 512: between 20 %
+// slower and 10 % faster; there a wavefront's tile takes long enough for the walk to wait for it).
+static bool pair_is_faster(int dtype, int row_bytes, int b, int64_t n_inst, int n_cu) {
+    const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 2 * (int64_t)n_cu + n_cu / 8 && b > 768;
+    return row_bytes == 256 && n_inst > n_cu && !thin_tail && (dtype == BKV_BF16 || b <= 512) && n_inst <= (1ll << 30);
+}
+bool compress_sums_status(int dtype, int d, int b, bool value_gram, int64_t n_inst) {
+    const int n_cu = compute_units();
+    return n_cu > 0 && (value_gram || !pair_is_faster(dtype, d * (dtype == BKV_BF16 ? 2 : 4), b, n_inst, n_cu));
+}
+
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st) {
     const int row_bytes = d * (dtype == BKV_BF16 ? 2 : 4);
     const bool vgram = (a.flags & BKV_VALUE_GRAM) != 0;
     // value factor: no Gram dump, value rows required; the values are staged in LDS when they fit next to the keys
     if (vgram && (emit_g || !a.V)) return hipErrorInvalidValue;
     if (a.k_by_idx && (!a.idx_in || emit_g)) return hipErrorInvalidValue;
+    if (a.status_words && (!a.tree_mode || !a.status_out || a.desc || a.carry_w || a.status_stride > 64 || a.round >= a.status_stride)) return hipErrorInvalidValue;
     if (a.carry_w && (!a.desc || !a.carry_idx || !a.carry_cnt || emit_g)) return hipErrorInvalidValue;
     // a streamed token: the workgroup of sequence i takes it in before its numerator's carry, other kernels would leave it out
     if (a.tok_k && (!a.tok_v || !a.carry_w || !vgram || n_inst != a.stream.n_seq)) return hipErrorInvalidValue;
@@ -1742,17 +1780,10 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     {
         const int n_cu = compute_units();
         if (n_cu == 0) return hipErrorUnknown;
-        // More blocks than compute units: two of them on each (compress_pair.hip).  Up to one per compute unit a launch takes
-        // as long as one block, and a block that has the compute unit to itself is done sooner (192 and 256 blocks of 512 bf16
-        // rows 11 % sooner, of 1024 rows 15 %).  With more the pair is faster (time of the other kernel over its own, 256
-        // compute units): b = 64 1.25 (257 blocks) to 2.0 (1024), 256 1.15 to 1.5, 512 1.08 to 1.24, 1024 1.02 to 1.25, where
-        // the last round is thin least.  Two exceptions: two blocks everywhere and a few more of more than 768 rows (514 and
-        // 528 blocks: 0.97 to 1.00; 560 on: 1.01 to 1.04), and single precision beyond one chunk (b > 512: between 20 %
-        // slower and 10 % faster; there a wavefront's tile takes long enough for the walk to wait for it).
-        const bool thin_tail = n_inst > 2 * (int64_t)n_cu && n_inst <= 2 * (int64_t)n_cu + n_cu / 8 && a.b > 768;
-        if (row_bytes == 256 && !emit_g && !vgram && !a.carry_w && !a.k_by_idx && n_inst > n_cu && !thin_tail &&
-            (dtype == BKV_BF16 || a.b <= 512) && n_inst <= (1ll << 30))
+        if (!emit_g && !vgram && !a.carry_w && !a.k_by_idx && pair_is_faster(dtype, row_bytes, a.b, n_inst, n_cu)) {
+            if (a.status_words) return hipErrorInvalidValue;
             return launch_compress_pair(dtype, d, a, n_inst, st);
+        }
         // one workgroup per compute unit is resident (LDS); with at least two rounds of workgroups, spread the first
         if (n_inst >= 2 * (int64_t)n_cu && !a.desc) {   // (a ragged grid has unused slots: neighbours in the grid are not neighbours in memory)
             // The first workgroups start spread over about two thirds of one block's duration: 100k clock ticks for 1024

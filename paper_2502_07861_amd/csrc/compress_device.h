@@ -2,6 +2,7 @@
 // 64-token panel, the hand-over counters.
 #pragma once
 #include "bkv_device.h"
+#include "bkv_host.h"
 
 namespace bkv {
 
@@ -101,6 +102,13 @@ __device__ __forceinline__ void await(int* counter, int value, int* err) {
     __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The kernel's arguments, read where they are used: an opaque pointer keeps them out of registers in between.
+__device__ __forceinline__ const CompressArgs* args_here() {
+    unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return (const CompressArgs*)(const __attribute__((address_space(4))) CompressArgs*)p;
+}
+
 // Output step (Alg. 2 lines 12-16 + strict n/2): every wavefront handles the panels p = wave, wave + 8, ...: minority
 // sign ('+' on ties), then exactly b/2 survivors = the minority class plus the lowest-index majority tokens, ascending.
 __device__ __forceinline__ void select_survivors(const unsigned long long* etaMask, int b, int wave, int lane, int* keptIdx) {
@@ -155,6 +163,33 @@ __device__ __forceinline__ void add_status(int* dst, int any_fail, int sync_fail
         if (prev == seen) break;
         seen = prev;
     }
+}
+
+// The same without a status word that is 0 before the launch (clearing it was a launch of its own, 3.3 us in front of trees that take 20 to
+// 60): every block of a sequence leaves its events in a word of its own, under the launch's label, waits until that has arrived
+// and reads all words of the sequence; the one whose word arrives last finds them all and writes the sum.  (Blocks that arrive
+// together may all find them: they write the same.)  Nothing that the memory held before means anything: 51 bits of a word are the
+// label, which no other launch of the process has.
+constexpr int kLabelShift = 13;                            // FAIL, INTERNAL, near ties of a block (at most 1024)
+__device__ __forceinline__ void put_status_word(unsigned long long* word, unsigned long long label, int any_fail, int sync_failed, int n_margin) {
+    const unsigned long long x = label << kLabelShift | (unsigned int)n_margin << 2 | (sync_failed ? 2u : 0u) | (any_fail ? 1u : 0u);
+    __hip_atomic_store(word, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Called by the wavefront that has put its block's word.
+__device__ __forceinline__ void sum_status_words(const unsigned long long* words, int n, unsigned long long label, int lane, int32_t* status) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool there = true;
+    unsigned int events = 0, near = 0;
+    for (int w0 = 0; w0 < n; w0 += 64) {
+        const unsigned long long x = __hip_atomic_load(words + min(w0 + lane, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        there &= x >> kLabelShift == label;
+        if (w0 + lane < n) { events |= (unsigned int)x & 3u; near += ((unsigned int)x & ((1u << kLabelShift) - 1u)) >> 2; }
+    }
+    if (__ballot(!there) != 0ull) return;
+    const int any_fail = __ballot(events & 1u) != 0ull, sync_failed = __ballot(events & 2u) != 0ull;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) near += __shfl_xor(near, o);
+    if (lane == 0) *status = (any_fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (int)(min(near, 0x7fffffu) << 8);
 }
 
 }  // namespace bkv

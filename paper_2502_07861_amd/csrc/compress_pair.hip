@@ -29,6 +29,8 @@
 namespace bkv {
 namespace {
 
+// (128 vector registers hold a panel, 32 to 64 weights and little else: every value that could be kept across the tile loops is formed
+// anew where it is needed, see also args_here and local_copy.)
 constexpr int kPanelBytes = 64 * 256;                       // one panel of 64 key rows
 constexpr int kSlotCount = 3;                               // row panels resident in LDS
 constexpr int kTileStrideA = 36, kTileStrideB = 68;         // floats per column of a diagonal tile: columns 0..31 (rows 0..31), 32..63
@@ -51,15 +53,6 @@ __device__ __forceinline__ void load_lds16(const char* src, char* dst) {       /
 // a value that the compiler forms address arithmetic from here and does not carry around in several registers
 __device__ __forceinline__ int local_copy(int x) { asm volatile("" : "+v"(x)); return x; }
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// The kernel's arguments, read where they are used: an opaque pointer keeps them out of registers in between.  (128 vector
-// registers hold a panel, 32 to 64 weights and little else: every value that could be kept across the tile loops is formed
-// anew where it is needed, see also local_copy.)
-__device__ __forceinline__ const CompressArgs* args_here() {
-    unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return (const CompressArgs*)(const __attribute__((address_space(4))) CompressArgs*)p;
-}
 
 // An entry of an instance table, by scalar loads.
 __device__ __forceinline__ const InstDesc* table_entry(const InstDesc* table, int64_t inst) {

@@ -647,6 +647,39 @@ def test_merge_reduce_with_value_factor(bk, synth, oracle):
     assert torch.equal(prot["V"][:, 32:32 + kept], res["V"]) and torch.equal(prot["K"][:, 32:32 + kept], res["K"])
 
 
+@pytest.mark.parametrize("dtype,d,b,T,n_seq,per_seq,value", [
+    (torch.float32, 64, 64, 1, 3, 1, False), (torch.float32, 64, 64, 1, 2, 65, False), (torch.bfloat16, 128, 64, 1, 1, 200, False),
+    (torch.bfloat16, 128, 128, 2, 5, 16, False), (torch.bfloat16, 64, 64, 3, 4, 64, True), (torch.bfloat16, 128, 1024, 1, 2, 4, False)])
+def test_status_words_without_clearing(bk, synth, dtype, d, b, T, n_seq, per_seq, value):
+    """The first round's blocks sum up their events through words of their own, whatever status and workspace held; a captured call, which
+    clears the status first and adds to it, is the reference."""
+    n = b * (-(-per_seq // (1 << T)) << T)
+    t = synth.clustered_layer_bf16(n_seq=n_seq, n=n, d=d, g=1, nq=1, seed=9, device="cuda", dtype=dtype)
+    K, V = t["K"], t["V"]
+    V[0] = 0.0 if value else V[0]
+    p = bk.make_params(d, b, T, dtype, log_c=-8.0, seed=4, center=True, value_gram=value)        # large weights: FAIL events
+    need = bk.binding.merge_reduce_workspace_bytes(p, n_seq, n)
+    ws = torch.randint(0, 256, (need,), device="cuda", dtype=torch.uint8)
+    out = bk.merge_reduce(p, K, V, workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    ref_ws = torch.zeros_like(ws)
+    with torch.cuda.stream(side):
+        ref = {k: torch.empty_like(v) for k, v in out.items()}
+        with torch.cuda.graph(graph, stream=side):
+            bk.merge_reduce(p, K, V, workspace=ref_ws, out=ref)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert (ref["status"] & 1).any() and not (ref["status"] & 2).any()
+    for k in out:
+        assert torch.equal(out[k], ref[k]), k
+    for _ in range(3):                                                   # on what the call before has left
+        out["status"].fill_(-1)
+        bk.merge_reduce(p, K, V, workspace=ws, out=out)
+        assert torch.equal(out["status"], ref["status"])
+
+
 @pytest.mark.parametrize("dtype,d,b,T,n_sink,n_recent,n_mid", [
     (torch.bfloat16, 128, 512, 2, 256, 256, 4096),      # the paper's windows, workload-2 blocks
     (torch.float32, 64, 128, 1, 40, 7, 512),            # ragged windows
