@@ -465,9 +465,13 @@ size_t bkv_attend_sets_workspace_bytes(const bkv_params* p, int64_t n_seq, int32
     return align_up(bkv::attend_workspace_bytes(p->d, n_seq, g * nq, 2), 256);
 }
 
-int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const float* w_n, int64_t count_n, int64_t stride_n,
+}  // extern "C"
+
+// live: tokens that the numerator set holds at most and the ranges they lie in, 0: not known
+static int attend_sets_impl(const bkv_params* p, const void* K_n, const void* V_n, const float* w_n, int64_t count_n, int64_t stride_n,
                     const void* K_d, const float* w_d, int64_t count_d, int64_t stride_d, int64_t n_seq, const void* Q,
-                    int32_t g, int32_t nq, void* out, float* lse_out, void* workspace, size_t ws_bytes, void* hip_stream) {
+                    int32_t g, int32_t nq, void* out, float* lse_out, void* workspace, size_t ws_bytes, int64_t live_tokens, int64_t live_ranges,
+                            void* hip_stream) {
     int rc = check_params(p);
     if (rc) return rc;
     if (n_seq < 0 || g <= 0 || nq <= 0 || count_n < 0 || count_d < 0) return BKV_EINVAL;
@@ -488,8 +492,18 @@ int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const
     a.set[1].K = (const char*)K_d; a.set[1].w = w_d; a.set[1].stride = stride_d; a.set[1].count = count_d;
     a.Q = (const char*)Q; a.out = (char*)out; a.lse_out = lse_out; a.n_seq = n_seq; a.n_q = g * nq;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)p->d));
+    if (live_tokens > 0) a.live = live_tokens / (p->dtype == BKV_BF16 ? 32 : 16) + live_ranges;
     const hipError_t e = bkv::launch_attend(p->dtype, p->d, a, workspace, ws_bytes, bkv::kAttendPartialBytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? BKV_OK : hip_fail(e);
+}
+
+extern "C" {
+
+int bkv_attend_sets(const bkv_params* p, const void* K_n, const void* V_n, const float* w_n, int64_t count_n, int64_t stride_n,
+                    const void* K_d, const float* w_d, int64_t count_d, int64_t stride_d, int64_t n_seq, const void* Q,
+                    int32_t g, int32_t nq, void* out, float* lse_out, void* workspace, size_t ws_bytes, void* hip_stream) {
+    return attend_sets_impl(p, K_n, V_n, w_n, count_n, stride_n, K_d, w_d, count_d, stride_d, n_seq, Q, g, nq, out, lse_out, workspace,
+                            ws_bytes, 0, 0, hip_stream);
 }
 
 // ------------------------------------------------------------------------------------------ Alg. 3 streaming
@@ -828,8 +842,8 @@ int bkv_stream_attend(const bkv_stream* h, const void* Q, int32_t g, int32_t nq,
         if (s.T == 0) count_d = h->seen;
         if (count_d > s.cap_d) count_d = s.cap_d;
     }
-    return bkv_attend_sets(&h->p, s.Kn, s.Vn, s.wn, places, places, s.Kd, s.wd, count_d, s.cap_d, s.n_seq, Q, g, nq, out, lse_out,
-                           workspace, ws_bytes, hip_stream);
+    return attend_sets_impl(&h->p, s.Kn, s.Vn, s.wn, places, places, s.Kd, s.wd, count_d, s.cap_d, s.n_seq, Q, g, nq, out, lse_out,
+                            workspace, ws_bytes, h->seen, s.regions, hip_stream);
 }
 
 }  // extern "C"

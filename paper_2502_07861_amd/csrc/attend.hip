@@ -28,6 +28,7 @@
 
 namespace bkv {
 
+constexpr int kOneGroups = 128;              // groups of a set that one workgroup looks through (attend_in_one)
 constexpr int kTargetWaves = 2048;           // wavefronts of the pass when token ranges are split (see attend_plan)
 constexpr int kRowPad = 4;                   // floats behind the D sums of a partial row: [0] reference exponent, [1] denominator
 constexpr float kNeg = -1.0e30f;             // "minus infinity" that stays finite under subtraction
@@ -178,7 +179,8 @@ __device__ __forceinline__ void merge_rows(const float* part, size_t sstride, in
 // sums.  The rows of the next group are requested as soon as the registers of the current one are free (keys after S^T,
 // values after O^T), so that about 12 KB per wavefront are under way at any time.
 // STREAM: K and V are read past the caches (see attend_streams).
-template <typename T, int D, int NQT, int W, bool STREAM = false>
+// ONE: a workgroup takes both sets of a sequence as a whole, nothing is merged behind it (see attend_in_one).
+template <typename T, int D, int NQT, int W, bool STREAM = false, bool ONE = false>
 __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     constexpr bool B16 = sizeof(T) == 2;
     constexpr int ROWB = D * (int)sizeof(T);
@@ -202,19 +204,64 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     // workgroup -> (sequence, query group, split).  Where several query groups read the same rows, the workgroups of a
     // sequence go to one XCD (blocks are dealt to the eight XCDs in turn, x fastest), whose L2 then serves all but the first
     // read: a row of the grid holds the workgroups of eight sequences, else those of one.
-    const unsigned int ns = (unsigned int)(a.ns[0] + a.ns[1]);
+    const unsigned int ns = ONE ? 1u : (unsigned int)(a.ns[0] + a.ns[1]);
     const unsigned int seq_u = a.by_xcd ? blockIdx.y * 8u + (blockIdx.x & 7u) : blockIdx.y;
     const unsigned int rest = a.by_xcd ? blockIdx.x >> 3 : blockIdx.x;
     if (seq_u >= (unsigned int)a.n_seq) return;
     const int qg = (int)(rest % (unsigned int)a.n_qg);
     const int split = (int)(rest / (unsigned int)a.n_qg);
     const int64_t seq = seq_u;
-    const int which = split >= a.ns[0] ? 1 : 0;
+    int which = split >= a.ns[0] ? 1 : 0;
+    // ONE: the groups with a live token of each set, dealt out to wavefronts that take one set each (of W as many as their share of the
+    // rows; a numerator's group has two)
+    __shared__ int order[ONE ? 2 : 1][ONE ? kOneGroups : 1];
+    __shared__ int n_live[2];
+    int w0_waves = W, mine = 0, stride = 1, listed = 0;
+    if constexpr (ONE) {
+        constexpr int GPL = 64 / KEYS, U = 8;                 // groups per weight load of a wavefront; loads under way
+        __shared__ int live[2][kOneGroups + 64 / KEYS];
+        const int chunks0 = (int)((a.set[0].count + 63) / 64), chunks = chunks0 + (int)((a.set[1].count + 63) / 64);
+        for (int c0 = wave; c0 < chunks; c0 += W * U) {
+            float x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * W, k = c >= chunks0 ? 1 : 0;
+                const int64_t key = 64ll * (k ? c - chunks0 : c) + lane;
+                const AttendSet& Z = a.set[k];
+                x[u] = c < chunks && key < Z.count ? Z.w[(size_t)seq * Z.stride + key] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = c0 + u * W, k = c >= chunks0 ? 1 : 0;
+                const unsigned long long m = __ballot(x[u] > 0.f);
+                if (c < chunks && lane < GPL)
+                    live[k][(k ? c - chunks0 : c) * GPL + lane] = ((m >> (lane * KEYS)) & ((1ull << KEYS) - 1ull)) != 0ull ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        if (wave < 2) {
+            const int groups = (int)((a.set[wave].count + KEYS - 1) / KEYS);
+            int n_so_far = 0;
+            for (int g = lane; g < (groups + 63) / 64 * 64; g += 64) {
+                const bool is = g < groups && live[wave][g] != 0;
+                const unsigned long long m = __ballot(is);
+                if (is) order[wave][n_so_far + (int)__popcll(m & ((1ull << lane) - 1ull))] = g;
+                n_so_far += (int)__popcll(m);
+            }
+            if (lane == 0) n_live[wave] = n_so_far;
+        }
+        __syncthreads();
+        const int l0 = __builtin_amdgcn_readfirstlane(n_live[0]), l1 = __builtin_amdgcn_readfirstlane(n_live[1]);
+        const int w1 = l1 == 0 ? 0 : l0 == 0 ? W : min(max((W * l1 + l0) / (2 * l0 + l1), 1), W - 1);
+        w0_waves = W - w1;
+        which = wave >= w0_waves ? 1 : 0;
+        mine = which ? wave - w0_waves : wave; stride = which ? w1 : w0_waves; listed = which ? l1 : l0;
+    }
     const AttendSet S = which ? a.set[1] : a.set[0];
     const bool has_v = S.V != nullptr;
     const int64_t groups = (S.count + KEYS - 1) / KEYS, full = S.count / KEYS;
-    const int64_t g0 = (int64_t)(split - (which ? a.ns[0] : 0)) * S.groups_per_split;
-    const int64_t g1 = min(groups, g0 + S.groups_per_split), gf = min(full, g1);
+    const int64_t g0 = ONE ? 0 : (int64_t)(split - (which ? a.ns[0] : 0)) * S.groups_per_split;
+    const int64_t g1 = ONE ? 0 : min(groups, g0 + S.groups_per_split), gf = min(full, g1);
 
     const char* Kb = S.K + (size_t)seq * S.stride * ROWB;
     const char* Vb = has_v ? S.V + (size_t)seq * S.stride * ROWB : nullptr;
@@ -260,12 +307,43 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
         for (int j = 0; j < VR; ++j) load_v_row(j, p + ((j & 3) + 16 * (j >> 2)) * ROWB);
     };
 
+    // the sequence's last group, if it is not full: rows past the end repeat the last row with weight 0
+    const int left = (int)(S.count - full * KEYS) - 1;           // its last valid row
+    auto load_w_end = [&](float (&w)[VR]) {
+#pragma unroll
+        for (int j = 0; j < VR; ++j) {
+            const int row = 4 * kg + (j & 3) + 16 * (j >> 2);
+            const float x = wb[full * KEYS + min(row, left)];
+            w[j] = row <= left ? x : 0.f;
+        }
+    };
+    auto load_k_end = [&]() {
+        const char* kp = Kb + (size_t)full * (KEYS * ROWB) + kg * 16;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int c = 0; c < KC; ++c) kf[t][c] = *reinterpret_cast<const uintx4*>(kp + min(16 * t + n, left) * ROWB + 64 * c);
+    };
+    auto load_v_end = [&]() {
+#pragma unroll
+        for (int j = 0; j < VR; ++j) {
+            const int row = 4 * kg + (j & 3) + 16 * (j >> 2);
+            load_v_row(j, Vb + (size_t)full * (KEYS * ROWB) + min(row, left) * ROWB + vcol);
+        }
+    };
     int64_t g = g0 + wave;
-    const bool any_full = g < gf;
+    const bool any_full = !ONE && g < gf;
     if (any_full) {
         load_w(w0, g);
         load_k(g);
         if (has_v) load_v(g);
+    }
+    if constexpr (ONE) {
+        if (mine < listed) {
+            const int x = __builtin_amdgcn_readfirstlane(order[which][mine]);
+            if (x < full) { load_w(w0, x); load_k(x); if (has_v) load_v(x); }
+            else { load_w_end(w0); load_k_end(); if (has_v) load_v_end(); }
+        }
     }
     // queries: lane (n, kg) holds its quarter of query n of each tile (queries past the end repeat the last one)
     uintx4 qf[NQT][KC];
@@ -457,22 +535,29 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
             g = gn;
         }
     }
-    // the sequence's last group, if it is not full: one wavefront, rows past the end repeat the last row with weight 0
-    if (g1 > full && (int)((full - g0) % W) == wave) {
-        const int left = (int)(S.count - full * KEYS) - 1;           // last valid row of the group
-        const char* kp = Kb + (size_t)full * (KEYS * ROWB) + kg * 16;
+    if constexpr (ONE) {
+        for (int i = mine; i < listed; i += stride) {
+            const bool more = i + stride < listed;
+            const int x = more ? __builtin_amdgcn_readfirstlane(order[which][i + stride]) : 0;
+            float wc[VR];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int c = 0; c < KC; ++c) kf[t][c] = *reinterpret_cast<const uintx4*>(kp + min(16 * t + n, left) * ROWB + 64 * c);
-        float wt[VR];
-#pragma unroll
-        for (int j = 0; j < VR; ++j) {
-            const int row = 4 * kg + (j & 3) + 16 * (j >> 2);
-            const float x = wb[full * KEYS + min(row, left)];
-            wt[j] = row <= left ? x : 0.f;
-            if (has_v) load_v_row(j, Vb + (size_t)full * (KEYS * ROWB) + min(row, left) * ROWB + vcol);
+            for (int y = 0; y < VR; ++y) wc[y] = w0[y];
+            if (more) { if (x < full) load_w(w0, x); else load_w_end(w0); }
+            qk();
+            if (more) { if (x < full) load_k(x); else load_k_end(); }
+            softmax(wc);
+            if (has_v) {
+                pv();
+                if (more) { if (x < full) load_v(x); else load_v_end(); }
+            }
         }
+    }
+    // (the last group: one wavefront)
+    if (!ONE && g1 > full && (int)((full - g0) % W) == wave) {
+        float wt[VR];
+        load_k_end();
+        load_w_end(wt);
+        if (has_v) load_v_end();
         qk();
         softmax(wt);
         if (has_v) pv();
@@ -508,6 +593,27 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
     for (int c = tid; c < nqv * (D / 4); c += W * 64) {
         const int q = c / (D / 4), col = 4 * (c - q * (D / 4));
         const float* row = lds + q * P;
+        if constexpr (ONE) {
+            float M = kNeg, L = 0.f, Md = kNeg, Ld = 0.f;
+            for (int w = 0; w < W; ++w) {
+                const float x = row[w * RQ * P + D];
+                if (w < w0_waves) M = fmaxf(M, x); else Md = fmaxf(Md, x);
+            }
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int w = 0; w < W; ++w) {
+                const floatx2 x = *reinterpret_cast<const floatx2*>(row + w * RQ * P + D);
+                if (w < w0_waves) {
+                    const float f = fast_exp2(x[0] - M);
+                    L = fmaf(x[1], f, L);
+                    acc += *reinterpret_cast<const floatx4*>(row + w * RQ * P + col) * f;
+                } else Ld = fmaf(x[1], fast_exp2(x[0] - Md), Ld);
+            }
+            // (as in merge_rows: a denominator of 0 or NaN shows)
+            const float f = L > 0.f ? (Ld > 0.f ? fast_exp2(M - Md) / Ld : INFINITY) : 0.f;
+            store4<T>(a.out, (row0 + q) * D + col, acc * f);
+            if (col == 0 && a.lse_out) a.lse_out[row0 + q] = Ld > 0.f ? log2_or(Ld, Md) * 0.6931471805599453f : -INFINITY;
+            continue;
+        }
         floatx2 ml[W];
         float M = kNeg, L = 0.f;
 #pragma unroll
@@ -528,7 +634,7 @@ __global__ __launch_bounds__(W * 64) void attend_kernel(const AttendArgs a) {
             if (col == 0) put2(dst + D, M, L);
         }
     }
-    if (ns == 1 || !a.fused) return;
+    if (ONE || ns == 1 || !a.fused) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wavefront's share of the partial has reached memory ...
     __syncthreads();                                            // ... and so has everybody else's
     if (wave == 0) {
@@ -639,6 +745,17 @@ static bool attend_streams(int row_bytes, const AttendArgs& a) {
     return rows * row_bytes > ((int64_t)320 << 20);
 }
 
+// Two sets in one workgroup per sequence: sets whose places are mostly empty, of which the caller knows about how many tokens they hold
+// (AttendArgs::live: a stream's), on a chip that is not full.  Splits, hand-over and merge cost about 4 us, more than such a workgroup's
+// few steps (8 regions x 256 places, bf16, d = 128, over 288 tokens, append and attend: 32 streams 18.2 -> 16.6 us a token, 200 over 200
+// tokens 35 -> 17.8).  The line: four steps a wavefront, a numerator's group counted as one, a denominator's as half; one workgroup a compute unit.
+static bool attend_in_one(const AttendArgs& a, const AttendPlan& p, int keys) {
+    const int64_t g0 = (a.set[0].count + keys - 1) / keys, g1 = (a.set[1].count + keys - 1) / keys;
+    if (p.nqt != 1 || a.set[0].count <= 0 || a.set[1].count <= 0 || !a.set[0].V || a.live <= 0 || g0 > kOneGroups || g1 > kOneGroups) return false;
+    const int64_t live0 = min(g0, a.live);
+    return a.n_seq <= compute_units() && 2 * live0 + g1 <= 2 * 4 * 8;
+}
+
 template <typename T, int D>
 static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipStream_t st) {
     // (two dimensions: a grid may not exceed 2^32 threads in one of them)
@@ -646,6 +763,11 @@ static hipError_t launch_attend_t(const AttendArgs& a, const AttendPlan& p, hipS
     const dim3 grid = a.by_xcd ? dim3(8u * inner, (unsigned)((a.n_seq + 7) / 8)) : dim3(inner, (unsigned)a.n_seq);
     const int64_t units = a.n_seq * (a.set[0].count + a.set[1].count);
     hipError_t e = hipSuccess;
+    if (attend_in_one(a, p, sizeof(T) == 2 ? 32 : 16)) {
+        AttendArgs one = a;
+        one.n_qg = 1; one.by_xcd = 0; one.ns[0] = 1; one.ns[1] = 0;
+        return launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8, false, true>, dim3(1, (unsigned)a.n_seq), dim3(512), 0, st, one);
+    }
     if (p.nqt == 2) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 2, 8>, grid, dim3(512), 0, st, a);
     else if (attend_streams(D * (int)sizeof(T), a)) {
         if (p.waves == 8) e = launch_timed(kProfAttend, units, attend_kernel<T, D, 1, 8, true>, grid, dim3(512), 0, st, a);

@@ -268,3 +268,32 @@ def test_more_sequences_than_compute_units_equal_few(bk, synth, dtype, d):
         np.testing.assert_array_equal(den[lo:hi], den_p)
         part_st.close()
     st.close()
+
+
+@pytest.mark.parametrize("dtype,d,n_seq,regions,cap_num,tokens,g,zero", [
+    (torch.bfloat16, 128, 1, 6, 200, 1, 1, False), (torch.bfloat16, 128, 5, 8, 131, 97, 16, False), (torch.bfloat16, 64, 256, 6, 256, 70, 4, False),
+    (torch.float32, 128, 3, 8, 256, 161, 5, False), (torch.float32, 64, 7, 6, 130, 129, 4, False), (torch.bfloat16, 128, 4, 8, 512, 40, 4, True),
+    (torch.bfloat16, 128, 257, 6, 200, 33, 4, False), (torch.bfloat16, 128, 2, 8, 520, 60, 17, False)])
+def test_attend_of_a_short_stream_equals_attend_of_its_sets(bk, dtype, d, n_seq, regions, cap_num, tokens, g, zero):
+    """A stream's mostly empty sets are taken by one workgroup a sequence; attend_sets on the same sets (which knows nothing of how many tokens
+    they hold) cuts them into splits.  Only the order of the sums differs.  (The last two take the splits as well: more sequences than compute
+    units, places or queries beyond the rule.)"""
+    gen = torch.Generator(device="cuda").manual_seed(tokens)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
+    k, v, Q = rand(tokens, n_seq, d).to(dtype), rand(tokens, n_seq, d) * 2.0 ** torch.randint(-1, 2, (tokens, n_seq, 1), generator=gen, device="cuda"), rand(n_seq, g, 1, d)
+    v, Q = (torch.zeros_like(v) if zero else v).to(dtype), Q.to(dtype)
+    p = bk.make_params(d, 64, 2, dtype, log_c=-4.7, seed=3, center=True)
+    s = bk.Stream(p, n_seq, regions, cap_num, tokens + 64)
+    for j in range(tokens):
+        s.append(k[j], v[j])
+    out, lse = s.attend(Q)
+    view = s.views()
+    assert int(view["error_word"].item()) == 0
+    flat = lambda x: x.reshape(n_seq, regions * cap_num, *x.shape[3:])
+    ref, ref_lse = bk.attend_sets(p, (flat(view["K_n"]), flat(view["V_n"]), flat(view["w_n"])), (view["K_d"], view["w_d"]), Q)
+    if zero:                                                # no numerator holds a token
+        assert not out.any() and not ref.any()
+    else:
+        x, y = out.double(), ref.double()
+        assert float((x - y).norm() / y.norm()) <= (1e-5 if dtype == torch.float32 else 4e-3)
+    torch.testing.assert_close(lse, ref_lse, rtol=1e-6, atol=1e-5)
