@@ -173,6 +173,12 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
     if (tid < 4) reinterpret_cast<unsigned int*>(scal + 16)[tid] = tid == 0 ? 0x7f61b1e6u : 0u;          // 3e38: no margin seen yet
     const int flip = (blockIdx.x >> 8) & 1;
     int l = flip ? 7 - wave : wave;                                 // this wavefront's column panel of the chunk
+    // Blocks of two chunks fetch rows and form their statistics for a third of their time, beside a block that walks at raised priority and leaves
+    // them the vector unit's gaps: 40 of 125 us, where the statistics take 2.3 by themselves.  One step up they are sooner done and the two
+    // blocks' phases lie better (256 x 32768 tokens, b = 1024, one round 2.04 -> 1.97 ms, 64 x 32768, two rounds 764 -> 740 us, b = 640 305 -> 296,
+    // 768 364 -> 362, 896 471 -> 458).  Three steps give less, raised for the output or the second chunk's rows as well nothing; blocks of one
+    // chunk lose (b = 384 340 -> 352 us, 256 488 -> 495).
+    if constexpr (TWO) __builtin_amdgcn_s_setprio(1);
     // Two batches at a time are on their way: one straight into LDS, one into registers.
     fetch(0);
     uintx4 rows1[8], keep[TWO ? 8 : 1];
@@ -321,6 +327,7 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
     }
 
     // ------------------------------------------------------------------ the chunks
+    if constexpr (TWO) __builtin_amdgcn_s_setprio(0);
     unsigned int* events = reinterpret_cast<unsigned int*>(scal + 16);   // smallest margin, largest |sigma|, near ties, FAIL
     int* eta_done = prog;
     int* diag_taken = prog + 1;
