@@ -139,10 +139,11 @@ int bkv_kernel_weights(const bkv_params* p, const void* K, int64_t n_inst, float
 }
 
 // ------------------------------------------------------------------------------------------ Alg. 3 offline
-// workspace: K ping [n_seq, n/2, d] | K pong [n_seq, n/4, d] | idx ping [n_seq, n/2] | idx pong [n_seq, n/4]
+// workspace: K ping [n_seq, n/2, d] | K pong [n_seq, n/4, d] | idx ping [n_seq, n/2] | idx pong [n_seq, n/4]; first in K pong, and in the last round's
+// unused buffer: a word per block (status)
 size_t bkv_merge_reduce_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t n) {
     if (check_params(p) || n_seq < 0 || n < 0) return 0;
-    if (p->rounds <= 1) return align_up((size_t)n_seq * (n / 2) * 4, 256) + 256;   // survivor indices only
+    if (p->rounds <= 1) return align_up((size_t)n_seq * (n / 2) * 4, 256) + 256;   // survivor indices, or a word per block (status)
     const size_t rb = (size_t)row_bytes(p);
     size_t bytes = 0;
     bytes += align_up((size_t)n_seq * (n / 2) * rb, 256);
