@@ -14,7 +14,7 @@
 //                 permute; fp32 elements are operands as they are.
 // So the pass needs no transposes, and a query's weights, running reference and sums stay in its own lanes.
 // What bounds it: with few queries per sequence the stream over K, V, w (1024 sequences x 8321 tokens x 4 queries, bf16:
-// 710 us = 6.2 TB/s); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
+// 632 us = 6.9 TB/s, 710 with the rows kept in the caches); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
 // tokens x 256 queries: 25 us; 114 us on the vector units, four queries per pass); short ranges the sum of two memory
 // round trips and the hand-over between workgroups (8 x 4357 tokens: 11.3 us in one launch; 14 us as pass + merge launches).
 #include <unistd.h>
