@@ -684,17 +684,9 @@ static AttendPlan attend_plan(int d, int elem, int64_t n_seq, int64_t count0, in
     // where a wavefront has a single group anyway.  fp32: eight, four take more registers and fewer of them are resident
     // (1024 x 2000 tokens, d = 64: 184 us against 196; 256 x 1000, d = 128: 43 against 47; one sequence of 65536, d = 64: 16.7
     // against 15.9).  32 queries take eight (one workgroup per compute unit, LDS).
+    // (Eight also where workgroups of eight fill the compute units once, 64 sequences x 4100 tokens 24.5 us for 25.1, 256 x 1000 21.6 for 24.2, would cut
+    // the ranges, and with them the order of the sums and the last bits of a decode, by how much of the chip a batch happens to fill.)
     p.waves = elem == 2 && p.nqt == 1 && all * wgs > kTargetWaves ? 4 : 8;
-    if (p.waves == 4) {
-        // Eight as well where such workgroups fill most of the compute units once (one each at a time): all start together and end together,
-        // and half as many partials are merged.  4 queries, 4 wavefronts / 8: 256 x 1000 tokens (256 workgroups) 24.2 / 21.6 us, 64 x 4100
-        // 25.1 / 24.5, caches read in turn 30.1 / 28.5, 256 x 8321 170.7 / 165.5, 32 x 8321 (224) 26.2 / 25.0, 16 x 16000 (208) 27.7 / 24.8, 64 x 2100
-        // (192) 17.1 / 16.2; not so with 300 (100 x 3000 27.7 / 37.3) or four rounds of them (1024 x 1000 81.5 / 85.8).
-        const int64_t steps8 = (all * wgs + kTargetWaves - 1) / kTargetWaves, n_cu = compute_units();
-        int64_t ns8 = 0;
-        for (int k = 0; k < 2; ++k) ns8 += ((cnt[k] + keys - 1) / keys + steps8 * 8 - 1) / (steps8 * 8);
-        if (wgs * ns8 <= n_cu && 4 * wgs * ns8 >= 3 * n_cu) p.waves = 8;
-    }
     const size_t row_bytes = (size_t)p.rows * (d + kRowPad) * sizeof(float);
     int64_t most = (int64_t)(max_bytes / ((size_t)wgs * row_bytes));          // splits whose partials fit the buffer
     int64_t steps = (all * wgs + kTargetWaves - 1) / kTargetWaves;             // per wavefront

@@ -960,10 +960,10 @@ def test_attend_edges(bk, dtype, d, n_seq, count, g, nq):
 @pytest.mark.parametrize("dtype,d,n_seq,count,stride,g", [
     (torch.bfloat16, 128, 64, 10301, 10310, 4), (torch.bfloat16, 128, 701, 999, 1000, 16), (torch.bfloat16, 64, 520, 2600, 2601, 5),      # more than the
     (torch.float32, 128, 41, 8193, 8200, 4), (torch.float32, 64, 90, 8190, 8192, 16),                                                     # caches hold
-    (torch.bfloat16, 128, 256, 97, 100, 1), (torch.bfloat16, 128, 200, 1001, 1001, 4), (torch.bfloat16, 64, 64, 4100, 4111, 2)])          # one round of eight
+    (torch.bfloat16, 128, 256, 97, 100, 1), (torch.bfloat16, 128, 200, 1001, 1001, 4), (torch.bfloat16, 64, 64, 4100, 4111, 2)])          # less than that
 def test_attend_of_many_sequences_equals_few(bk, dtype, d, n_seq, count, stride, g):
-    """Rows read past the caches, and workgroups of eight wavefronts where they fill the compute units once, against the same sequences eight
-    at a time (neither rule takes those).  Only the order of the sums differs: outputs to their own rounding (bf16: 2^-9 each) or to that
+    """Rows read past the caches (those of as many sequences as are too much for them), and sequences enough for several to be on their way in
+    a compute unit, against the same sequences eight at a time.  Only the order of the sums differs: outputs to their own rounding (bf16: 2^-9 each) or to that
     of fp32 sums, lse to that of fp32 sums."""
     gen = torch.Generator(device="cuda").manual_seed(count)
     K = torch.randn(n_seq, stride, d, generator=gen, device="cuda", dtype=torch.float32).mul_(2.0).to(dtype)
@@ -979,6 +979,21 @@ def test_attend_of_many_sequences_equals_few(bk, dtype, d, n_seq, count, stride,
         x, y = out[s].double(), ref.double()
         assert float((x - y).norm() / y.norm()) <= (1e-5 if dtype == torch.float32 else 4e-3)
         torch.testing.assert_close(lse[s], ref_lse, rtol=1e-6, atol=1e-5)
+
+
+@pytest.mark.parametrize("d,n_seq,more,count,g", [(128, 64, 66, 4100, 4), (64, 64, 66, 4111, 1), (128, 32, 37, 8321, 4)])
+def test_attend_cuts_decode_caches_as_ever(bk, d, n_seq, more, count, g):
+    """A sequence's token range is cut by the steps that a wavefront takes over all sequences, and by nothing else: a decode attend gives the bits
+    it gives among a few more sequences of as many steps (whatever part of the compute units either of them fills)."""
+    steps = lambda n: -(-n * -(-count // 32) // 2048)
+    assert steps(n_seq) == steps(more)
+    gen = torch.Generator(device="cuda").manual_seed(count)
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda").to(torch.bfloat16)
+    K, V, Q, w = rand(more, count, d), rand(more, count, d), rand(more, g, 1, d), torch.ones(more, count, device="cuda")
+    p = bk.make_params(d, 128, 2, torch.bfloat16, log_c=0.0)
+    ref, ref_lse = bk.attend_kv(p, K, V, w, Q)
+    out, lse = bk.attend_kv(p, K[:n_seq].contiguous(), V[:n_seq].contiguous(), w[:n_seq].contiguous(), Q[:n_seq].contiguous())
+    assert torch.equal(out, ref[:n_seq]) and torch.equal(lse, ref_lse[:n_seq])
 
 
 @pytest.mark.parametrize("n_seq,count,g,nq", [(8, 4357, 4, 1), (3, 2000, 1, 1), (8, 4096, 4, 16)])
