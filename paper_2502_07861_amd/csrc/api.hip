@@ -212,9 +212,11 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
     // The status words.  A round with room for a word per block sums its own up (the first one also clears the others'): the first round has
     // it in the key buffer of the second, the last one in the buffer it would write if it were not the last, with one round the workspace, if it
     // is there and does not hold the indices.  Not in a launch that will be replayed: its label would repeat.  Else they are cleared first
-    // and added to.  The sum is one trip to memory at the end of a launch, additions by many blocks wait for each other: the last round
+    // and added to.  The sum is a trip to memory at the end of a launch, two for the blocks that end last, additions by many blocks wait for each other: the last round
     // takes it from eight blocks a sequence on (two rounds, additions / sum: b = 512, 16 blocks 54.2 / 52.1 us, b = 128, 8 blocks 24.2 / 23.6, b = 64, 2
-    // blocks 19.8 / 20.2); the first round saves the launch that clears whatever it holds (3.3 us).
+    // blocks 19.8 / 20.2); the first round saves the launch that clears whatever it holds (3.3 us: one sequence of 256 blocks of 64 bf16 rows, d = 64, 13.7 / 10.2).
+    // Beyond kStatusWords blocks a sequence the words take more trips than that: with no bound one sequence of 1024 such blocks took 40 us for 38, of 4096
+    // 144 for 113, of 16384 815 for 413.
     bool may_sum = false;
     if (status_out && T <= 64) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -223,7 +225,7 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
     }
     auto words_of = [&](int r) -> unsigned long long* {
         const int64_t per_seq = (n >> r) / b;
-        if (!may_sum || (r > 0 && (r < T - 1 || per_seq < 8))) return nullptr;
+        if (!may_sum || per_seq > bkv::kStatusWords || (r > 0 && (r < T - 1 || per_seq < 8))) return nullptr;
         if (!bkv::compress_sums_status(p->dtype, p->d, b, (p->flags & BKV_VALUE_GRAM) != 0, n_seq * per_seq)) return nullptr;
         if (T > 1) return (unsigned long long*)kbuf[r == 0 ? 1 : r & 1];                      // (at least n_seq * n / 4 rows)
         return idx_out && workspace && aligned16(workspace) && ws_bytes >= (size_t)(n_seq * per_seq) * 8 ? (unsigned long long*)workspace : nullptr;

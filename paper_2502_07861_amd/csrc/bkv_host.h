@@ -39,6 +39,8 @@ struct StreamState {
     float erase2;             // (eps / (2n) * exp(-r^2 / sqrt d))^2, 0: nothing is erased
 };
 
+constexpr int kStatusWords = 256;         // most blocks of a sequence whose status words are summed up by the blocks
+
 struct CompressArgs {
     const char* K;            // input keys, dtype T
     const char* V;            // input values or null
@@ -50,8 +52,8 @@ struct CompressArgs {
     int8_t* signs_out;
     int32_t* status_out;
     float* stats_out;
-    // Tree mode, with status_out and no table: a word per block.  The launch then writes status_out instead of adding to it, and clears
-    // the entries of the rounds behind its own (see sum_status_words).
+    // Tree mode, with status_out and no table, at most kStatusWords blocks a sequence: a word per block.  The launch then writes status_out
+    // instead of adding to it, and clears the entries of the rounds behind its own (see sum_status_words).
     unsigned long long* status_words;
     unsigned long long status_label;   // 51 bits that no other launch has
     int32_t* sticky_err;      // or null: one word that collects BKV_STATUS_INTERNAL of every instance (never cleared by the kernel)

@@ -1768,7 +1768,8 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     // value factor: no Gram dump, value rows required; the values are staged in LDS when they fit next to the keys
     if (vgram && (emit_g || !a.V)) return hipErrorInvalidValue;
     if (a.k_by_idx && (!a.idx_in || emit_g)) return hipErrorInvalidValue;
-    if (a.status_words && (!a.tree_mode || !a.status_out || a.desc || a.carry_w || a.status_stride > 64 || a.round >= a.status_stride)) return hipErrorInvalidValue;
+    if (a.status_words && (!a.tree_mode || !a.status_out || a.desc || a.carry_w || a.status_stride > 64 || a.round >= a.status_stride ||
+                           a.blocks_per_seq > kStatusWords)) return hipErrorInvalidValue;
     if (a.carry_w && (!a.desc || !a.carry_idx || !a.carry_cnt || emit_g)) return hipErrorInvalidValue;
     // a streamed token: the workgroup of sequence i takes it in before its numerator's carry, other kernels would leave it out
     if (a.tok_k && (!a.tok_v || !a.carry_w || !vgram || n_inst != a.stream.n_seq)) return hipErrorInvalidValue;

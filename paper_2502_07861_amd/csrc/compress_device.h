@@ -175,17 +175,29 @@ __device__ __forceinline__ void put_status_word(unsigned long long* word, unsign
     const unsigned long long x = label << kLabelShift | (unsigned int)n_margin << 2 | (sync_failed ? 2u : 0u) | (any_fail ? 1u : 0u);
     __hip_atomic_store(word, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Called by the wavefront that has put its block's word.
+// Called by the wavefront that has put its block's word.  n: at most kStatusWords.  Workgroups start in order, so nearly every block finds
+// the last words missing and leaves after one load; the others follow together.
 __device__ __forceinline__ void sum_status_words(const unsigned long long* words, int n, unsigned long long label, int lane, int32_t* status) {
+    constexpr int kSteps = kStatusWords / 64;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int front = max(n - 64, 0);                       // words in front of the last 64
     bool there = true;
     unsigned int events = 0, near = 0;
-    for (int w0 = 0; w0 < n; w0 += 64) {
-        const unsigned long long x = __hip_atomic_load(words + min(w0 + lane, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    auto load = [&](int i) { return __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto take = [&](unsigned long long x, bool counts) {
         there &= x >> kLabelShift == label;
-        if (w0 + lane < n) { events |= (unsigned int)x & 3u; near += ((unsigned int)x & ((1u << kLabelShift) - 1u)) >> 2; }
-    }
+        if (counts) { events |= (unsigned int)x & 3u; near += ((unsigned int)x & ((1u << kLabelShift) - 1u)) >> 2; }
+    };
+    take(load(min(front + lane, n - 1)), front + lane < n);
     if (__ballot(!there) != 0ull) return;
+    if (front > 0) {
+        unsigned long long x[kSteps - 1];
+#pragma unroll
+        for (int k = 0; k < kSteps - 1; ++k) x[k] = load(min(64 * k + lane, front - 1));
+#pragma unroll
+        for (int k = 0; k < kSteps - 1; ++k) take(x[k], 64 * k + lane < front);
+        if (__ballot(!there) != 0ull) return;
+    }
     const int any_fail = __ballot(events & 1u) != 0ull, sync_failed = __ballot(events & 2u) != 0ull;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) near += __shfl_xor(near, o);

@@ -680,6 +680,37 @@ def test_status_words_without_clearing(bk, synth, dtype, d, b, T, n_seq, per_seq
         assert torch.equal(out["status"], ref["status"])
 
 
+@pytest.mark.parametrize("dtype,d,b,per_seq,value", [
+    (torch.bfloat16, 64, 64, 2, False), (torch.bfloat16, 64, 256, 64, False), (torch.bfloat16, 64, 256, 66, False), (torch.bfloat16, 64, 64, 256, False),
+    (torch.bfloat16, 64, 64, 258, False), (torch.bfloat16, 64, 64, 3000, False),                              # (beyond the words: added up)
+    (torch.float32, 128, 64, 130, False), (torch.bfloat16, 128, 64, 250, True), (torch.bfloat16, 128, 64, 1500, True)])
+def test_status_is_the_sum_over_the_blocks(bk, oracle, dtype, d, b, per_seq, value):
+    """One block of a sequence fails, another one in each (rows that are all alike in it, next to orthogonal elsewhere): the first, the last, the
+    first of the last 64, the one before, none.  Near ties and the bit are those of the blocks one by one, through words in any state."""
+    n_seq, n, seed = 5, per_seq * b, 77
+    gen = torch.Generator(device="cuda").manual_seed(per_seq)
+    K, V = (torch.randn(n_seq, per_seq, b, d, generator=gen, device="cuda") for _ in range(2))
+    failing = [0, per_seq - 1, max(per_seq - 64, 0), max(per_seq - 65, 0)]
+    for s, blk in enumerate(failing):
+        K[s, blk], V[s, blk] = K[s, blk, :1], V[s, blk, :1]
+    K, V = K.to(dtype).view(n_seq, n, d), V.to(dtype).view(n_seq, n, d)
+    p = bk.make_params(d, b, 1, dtype, log_c=-0.5, seed=seed, value_gram=value)
+    u = np.concatenate([oracle.uniform_fill(seed, 64 * s, 0, n) for s in range(n_seq)]).astype(np.float32).reshape(-1, b)
+    blocks = bk.compress_block(p, K.view(-1, b, d), V.view(-1, b, d), uniforms=torch.from_numpy(u).cuda())["status"].view(n_seq, per_seq).cpu()
+    assert [x.nonzero().flatten().tolist() for x in blocks & 1] == [[blk] for blk in failing] + [[]]
+    near = blocks >> 8
+    assert n_seq * n < 30000 or int((near > 0).sum(1).max()) > 1          # (2e-4 of the decisions)
+    want = (near.sum(1) << 8) | (blocks & 1).amax(1)
+    ws = torch.randint(0, 256, (bk.binding.merge_reduce_workspace_bytes(p, n_seq, n),), device="cuda", dtype=torch.uint8)
+    out = bk.merge_reduce(p, K, V, workspace=ws)
+    w = out["w"].clone()
+    for _ in range(3):
+        assert out["status"].flatten().tolist() == want.tolist()
+        assert bool((out["w"] == 2.0).all()) and torch.equal(out["w"], w)
+        out["status"].fill_(-1)
+        bk.merge_reduce(p, K, V, workspace=ws, out=out)
+
+
 @pytest.mark.parametrize("dtype,d,b,T,n_sink,n_recent,n_mid", [
     (torch.bfloat16, 128, 512, 2, 256, 256, 4096),      # the paper's windows, workload-2 blocks
     (torch.float32, 64, 128, 1, 40, 7, 512),            # ragged windows
