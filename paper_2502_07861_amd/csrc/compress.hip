@@ -709,12 +709,15 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
 
     // sigma starts at minus the threshold: the walk tests (sum of signed weights - threshold) < 0.  Integer work of about 1k clocks,
-    // done while the first rows are on their way.  (Every thread takes part in every step, the last token's again behind the
-    // end: a loop that lanes leave one by one ends with none of them active, and a register spilled there is lost.)
+    // done while the first rows are on their way, by whole wavefronts: one without tokens does nothing and leaves the vector unit to the others
+    // (3000 blocks of 64 bf16 rows, d = 64: 84.4 us when every wavefront went through it, the last token's again behind the end, 82.5 now; with
+    // the value factor 85.5 and 82.8).  With the values in memory every thread takes part in every step all the same: registers (256 blocks
+    // of 1024 bf16 rows, d = 128, 280 us by whole wavefronts, 275).  No loop that lanes leave one by one: it ends with none of them active, and a
+    // register spilled there is lost.
     auto thresholds = [&]() {
 #pragma unroll 1
-        for (int i0 = 0; i0 < b; i0 += kThreads) {
-            const int i = min(i0 + tid, b - 1);
+        for (int i0 = VG == 2 ? 0 : wave << 6; i0 < b; i0 += kThreads) {
+            const int i = VG == 2 ? min(i0 + tid, b - 1) : i0 + lane;
             sigma[i] = 0.f - threshold(i);                                       // never -0: the sign bit alone decides
         }
     };
@@ -733,8 +736,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
     const bool want_events = a.status_out || a.stats_out;
     // Chunks of up to so many panels leave all of them for the end: fp32 ones of two gain nothing (26.2 us for 4 x 512 tokens, d = 64, b = 128,
-    // two rounds, and 27.7), and with the values in memory the code beside the tiles costs registers that they have not got.
-    constexpr int kLateEvents = VG == 2 ? 16 : sizeof(T) == 4 ? 2 : 0;
+    // two rounds, and 27.7), and with the values in memory, or several chunks of bf16 rows, the code beside the tiles costs registers that
+    // they have not got (200 blocks of 1024 bf16 rows, d = 128: 71.9 us in the pipeline, 71.1 at the end).
+    constexpr int kLateEvents = VG == 2 || (MULTI && sizeof(T) == 2) ? 16 : sizeof(T) == 4 ? 2 : 0;
     // In blocks of several chunks with the values in memory the thresholds come before the loads: across them they cost those kernels registers
     // that the tiles' operands went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024
     // 318 -> 277 us, of 640 157 -> 134; blocks resident as one chunk gain nothing).
@@ -1112,8 +1116,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             const float rc = alpha * (mumu - A + a.cterm);       // row constant of the exponent
             if (has_row) narow[tid] = -pa_row;
             if (tid == 0) scal[1] = rc;
-            if (tid < 32) prog[tid] = 0;                        // progress counters of the first chunk's pipeline
-            if (tid < 4) events[tid] = tid == 0 ? 0x7f61b1e6u : 0u;   // 3e38: no margin seen yet
+            // progress counters of the first chunk's pipeline; in front of them the events (3e38: no margin seen yet)
+            if (VG == 2) { if (tid < 32) prog[tid] = 0; }
+            else if (tid < 36) events[tid] = tid == 0 ? 0x7f61b1e6u : 0u;
         }
         __syncthreads();
     }
@@ -1527,7 +1532,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
                     }
                 }
             }
-            if (VG != 2 && want_events && w < nPc && nPc > kLateEvents) {   // (signs of this panel have met the wavefront's own column: no wait to speak of)
+            if (kLateEvents < 8 && want_events && w < nPc && nPc > kLateEvents) {   // (signs of this panel have met the wavefront's own column: no wait to speak of)
                 await(eta_done, w, sync_err);
                 Events ev = {0, 0, 3.0e38f, 0.f};
                 panel_events(p0 + w - 1, ev);
@@ -1575,7 +1580,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         int32_t* status = o.tree_mode ? nullptr : o.status_out;
         float* stats = o.stats_out;
         const unsigned long long label = o.status_label;
-        Events ev = {(int)events[3], (int)events[2], __uint_as_float(events[0]), __uint_as_float(events[1])};
+        Events ev = {0, 0, 3.0e38f, 0.f};
+        if (VG != 2) ev = {(int)events[3], (int)events[2], __uint_as_float(events[0]), __uint_as_float(events[1])};
         for (int c = 0; c < n_chunks; ++c) {                       // the last panel of every chunk, or all of a short one
             const int p1 = min((c + 1) * CH, b) >> 6, short_chunk = p1 - ((c * CH) >> 6) <= kLateEvents;
             for (int p = short_chunk ? (c * CH) >> 6 : p1 - 1; p < p1; ++p) panel_events(p, ev);

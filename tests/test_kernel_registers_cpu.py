@@ -73,6 +73,14 @@ def test_blocks_with_values_in_memory(kernels):
         assert spilled <= 182, (name, spilled)
 
 
+@pytest.mark.parametrize("carry", [0, 1])
+def test_blocks_of_several_chunks(kernels, carry):
+    """bf16, d = 128, several chunks: the whole block is in flight in registers at the start.  What the walks have met is looked at behind the last
+    chunk: in the pipeline it cost two more spilled registers and 200 blocks of 1024 1 to 2 %."""
+    for name, (_, spilled) in _compress(kernels, "bf16", 128, 1, 0, carry).items():
+        assert spilled <= 4, (name, spilled)
+
+
 @pytest.mark.parametrize("dtype,d,most", [("bf16", 128, 52), ("f32", 128, 71), ("f32", 64, 48)])
 def test_carries_do_not_pay_for_the_token(kernels, dtype, d, most):
     """Resident carries with values in memory: taking a streamed token in is an instance of its own (last argument), which costs the others
