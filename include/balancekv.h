@@ -142,7 +142,8 @@ int bkv_kernel_weights(const bkv_params* p, const void* K, int64_t n_inst, float
  * status_out    [n_seq, T] int32 or NULL: per sequence and round, bit 0 = any FAIL, bits 8.. =
  *               total number of margin decisions (|u-p| < 1e-4).
  * workspace     bkv_merge_reduce_workspace_bytes() bytes; calls that overlap in time must not share
- *               one.  rounds == 0 copies the input.                                           */
+ *               one (one round with idx_out given neither needs nor touches it).  rounds == 0
+ *               copies the input.                                                             */
 size_t bkv_merge_reduce_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t n);
 int bkv_merge_reduce(const bkv_params* p, const void* K, const void* V, int64_t n_seq, int64_t n,
                      int64_t seq_base, void* K_out, void* V_out, float* w_out, int32_t* idx_out,

@@ -143,7 +143,7 @@ int bkv_kernel_weights(const bkv_params* p, const void* K, int64_t n_inst, float
 // unused buffer: a word per block (status)
 size_t bkv_merge_reduce_workspace_bytes(const bkv_params* p, int64_t n_seq, int64_t n) {
     if (check_params(p) || n_seq < 0 || n < 0) return 0;
-    if (p->rounds <= 1) return align_up((size_t)n_seq * (n / 2) * 4, 256) + 256;   // survivor indices, or a word per block (status)
+    if (p->rounds <= 1) return align_up((size_t)n_seq * (n / 2) * 4, 256) + 256;   // survivor indices only
     const size_t rb = (size_t)row_bytes(p);
     size_t bytes = 0;
     bytes += align_up((size_t)n_seq * (n / 2) * rb, 256);
@@ -210,28 +210,31 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
         }
     }
     // The status words.  A round with room for a word per block sums its own up (the first one also clears the others'): the first round has
-    // it in the key buffer of the second, the last one in the buffer it would write if it were not the last, with one round the workspace, if it
-    // is there and does not hold the indices.  Not in a launch that will be replayed: its label would repeat.  Else they are cleared first
-    // and added to.  The sum is a trip to memory at the end of a launch, two for the blocks that end last, additions by many blocks wait for each other: the last round
-    // takes it from eight blocks a sequence on (two rounds, additions / sum: b = 512, 16 blocks 54.2 / 52.1 us, b = 128, 8 blocks 24.2 / 23.6, b = 64, 2
-    // blocks 19.8 / 20.2); the first round saves the launch that clears whatever it holds (3.3 us: one sequence of 256 blocks of 64 bf16 rows, d = 64, 13.7 / 10.2).
-    // Beyond kStatusWords blocks a sequence the words take more trips than that: with no bound one sequence of 1024 such blocks took 40 us for 38, of 4096
-    // 144 for 113, of 16384 815 for 413.
+    // it in the key buffer of the second, the last one in the buffer it would write if it were not the last, the only one in the
+    // weights (see sum_status_words: with the indices given it needs no workspace, and leaves alone what another call may be using).  Not in a
+    // launch that will be replayed: its label would repeat.  Else they are cleared first and added to.  The sum is a trip to memory at the end of
+    // a launch, two for the blocks that end last, additions by many blocks wait for each other: where nothing has to be cleared the sum is taken
+    // from eight blocks a sequence on (two rounds, additions / sum: b = 512, 16 blocks 54.2 / 52.1 us, b = 128, 8 blocks 24.2 / 23.6, b = 64, 2
+    // blocks 19.8 / 20.2); else it saves the launch that clears (3.3 us: two rounds of one sequence of 256 blocks of 64 bf16 rows, d = 64, 23.4 / 19.7).
+    // Words in the weights up to 64 blocks (one load): every block that finds them all writes the weights back (64 blocks 10.5 us, 128 11.9, 256 14.6;
+    // cleared and added to 128 take 11.6, 256 13.5).  Beyond kStatusWords blocks a sequence the words take more trips than that: with no bound one
+    // sequence of 1024 such blocks took 40 us for 38, of 4096 144 for 113, of 16384 815 for 413.
     bool may_sum = false;
     if (status_out && T <= 64) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();       // (a launch says for itself what is wrong with the stream)
         else may_sum = capture == hipStreamCaptureStatusNone;
     }
+    const bool cleared = win && win->status_clear;
     auto words_of = [&](int r) -> unsigned long long* {
         const int64_t per_seq = (n >> r) / b;
-        if (!may_sum || per_seq > bkv::kStatusWords || (r > 0 && (r < T - 1 || per_seq < 8))) return nullptr;
+        if (!may_sum || per_seq > bkv::kStatusWords || (r > 0 && r < T - 1) || ((r > 0 || cleared) && per_seq < 8)) return nullptr;
         if (!bkv::compress_sums_status(p->dtype, p->d, b, (p->flags & BKV_VALUE_GRAM) != 0, n_seq * per_seq)) return nullptr;
         if (T > 1) return (unsigned long long*)kbuf[r == 0 ? 1 : r & 1];                      // (at least n_seq * n / 4 rows)
-        return idx_out && workspace && aligned16(workspace) && ws_bytes >= (size_t)(n_seq * per_seq) * 8 ? (unsigned long long*)workspace : nullptr;
+        return w_out && ((uintptr_t)w_out & 7) == 0 && out_stride % 2 == 0 && per_seq <= 64 ? (unsigned long long*)w_out : nullptr;
     };
     unsigned long long* words = words_of(0);
-    if (status_out && !words && !(win && win->status_clear) && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
+    if (status_out && !words && !cleared && (e = bkv::launch_fill_u32(status_out, 0u, n_seq * T, st)) != hipSuccess) return hip_fail(e);
 
     const char* k_in = (const char*)K;
     const int32_t* i_in = nullptr;
@@ -253,7 +256,10 @@ static int merge_reduce_impl(const bkv_params* p, const void* K, const void* V, 
         a.signs_out = signs_out ? signs_out + (size_t)n_seq * (size_t)(2 * n - ((2 * n) >> r)) : nullptr;
         a.status_out = status_out; a.status_stride = T; a.sticky_err = sticky_err;
         if (r > 0) words = words_of(r);
-        if (words) { a.status_words = words; a.status_label = bkv::status_label(); }
+        if (words) {
+            a.status_words = words; a.status_label = bkv::status_label();
+            if (words == (void*)w_out) { a.word_gap = out_stride / 2 - m / b; a.w_words = (int32_t)(2 * (m / b)); }
+        }
         a.in_seq_stride = r == 0 ? k_stride : m; a.out_seq_stride = last ? out_stride : m / 2;
         a.idx_out_seq_stride = (last && idx_out && win && win->idx_out_stride) ? win->idx_out_stride : m / 2;
         a.blocks_per_seq = (int32_t)(m / b);

@@ -54,8 +54,12 @@ struct CompressArgs {
     float* stats_out;
     // Tree mode, with status_out and no table, at most kStatusWords blocks a sequence: a word per block.  The launch then writes status_out
     // instead of adding to it, and clears the entries of the rounds behind its own (see sum_status_words).
+    // word_gap: words between the last one of a sequence and the first one of the next.  w_words > 0: the words are the first so many weights of
+    // a sequence (the same address as w_out, aligned to 8 bytes, an even stride), which are written when the sum is.
     unsigned long long* status_words;
     unsigned long long status_label;   // 51 bits that no other launch has
+    int64_t word_gap;
+    int32_t w_words;
     int32_t* sticky_err;      // or null: one word that collects BKV_STATUS_INTERNAL of every instance (never cleared by the kernel)
     const uint64_t* inst_ids;
     const float* uniforms;

@@ -1589,7 +1589,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         if (stats) { ev.least = wave_min(ev.least); ev.most = wave_max(ev.most); }
         fails = ev.fail; near_ties = ev.near;
         if (lane == 0) {
-            if (words) put_status_word(words + inst, label, fails, prog[3], near_ties);
+            if (words) put_status_word(words + inst + seq * o.word_gap, label, fails, prog[3], near_ties);
             if (status) status[inst] = (fails ? BKV_STATUS_FAIL : 0) | (prog[3] ? BKV_STATUS_INTERNAL : 0) | (near_ties << 8);
             if (stats) {
                 stats[2 * inst] = ev.least;
@@ -1675,8 +1675,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             }
         }
     }
+    const int in_words = CARRY ? 0 : a.w_words - (int)(out_tok0 - seq * a.out_seq_stride);       // weights of this block whose places hold words for now
     for (int r = tid; r < half; r += kThreads) {
-        if (a.w_out) a.w_out[out_tok0 + r] = a.w_out_val;
+        if (a.w_out && r >= in_words) a.w_out[out_tok0 + r] = a.w_out_val;
         if (a.idx_out) a.idx_out[idx_out0 + r] = (int32_t)src_token(r);
     }
     // (Behind the rows: an update takes trips to memory, one after the other for blocks that meet there, and rows that wait for it make
@@ -1688,7 +1689,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             asm volatile("" : "+s"(i));
             const unsigned int per = (unsigned int)o.blocks_per_seq, s = i / per;
             int32_t* status = o.status_out + (int64_t)s * o.status_stride;
-            sum_status_words(o.status_words + (int64_t)s * per, (int)per, o.status_label, lane, status + o.round);
+            sum_status_words(o.status_words + (int64_t)s * (per + o.word_gap), (int)per, o.w_words > 0 ? o.w_out_val : 0.f, o.status_label, lane, status + o.round);
             if (i == s * per && lane < o.status_stride && lane > o.round) status[lane] = 0;      // the rounds to come add to theirs
         } else if (lane == 0) add_status(o.status_out + seq * o.status_stride + o.round, fails, prog[3], near_ties);
     }
@@ -1776,6 +1777,7 @@ hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64
     if (a.k_by_idx && (!a.idx_in || emit_g)) return hipErrorInvalidValue;
     if (a.status_words && (!a.tree_mode || !a.status_out || a.desc || a.carry_w || a.status_stride > 64 || a.round >= a.status_stride ||
                            a.blocks_per_seq > kStatusWords)) return hipErrorInvalidValue;
+    if (a.w_words && (!a.status_words || (void*)a.w_out != (void*)a.status_words || ((uintptr_t)a.w_out & 7) || a.out_seq_stride % 2)) return hipErrorInvalidValue;
     if (a.carry_w && (!a.desc || !a.carry_idx || !a.carry_cnt || emit_g)) return hipErrorInvalidValue;
     // a streamed token: the workgroup of sequence i takes it in before its numerator's carry, other kernels would leave it out
     if (a.tok_k && (!a.tok_v || !a.carry_w || !vgram || n_inst != a.stream.n_seq)) return hipErrorInvalidValue;

@@ -176,8 +176,10 @@ __device__ __forceinline__ void put_status_word(unsigned long long* word, unsign
     __hip_atomic_store(word, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Called by the wavefront that has put its block's word.  n: at most kStatusWords.  Workgroups start in order, so nearly every block finds
-// the last words missing and leaves after one load; the others follow together.
-__device__ __forceinline__ void sum_status_words(const unsigned long long* words, int n, unsigned long long label, int lane, int32_t* status) {
+// the last words missing and leaves after one load; the others follow together.  Words that lie in the
+// weights (weight: their value, else 0) are replaced by them once all have been seen: a block that finds one gone knows that another has
+// seen all.
+__device__ __forceinline__ void sum_status_words(unsigned long long* words, int n, float weight, unsigned long long label, int lane, int32_t* status) {
     constexpr int kSteps = kStatusWords / 64;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const int front = max(n - 64, 0);                       // words in front of the last 64
@@ -202,6 +204,10 @@ __device__ __forceinline__ void sum_status_words(const unsigned long long* words
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) near += __shfl_xor(near, o);
     if (lane == 0) *status = (any_fail ? BKV_STATUS_FAIL : 0) | (sync_failed ? BKV_STATUS_INTERNAL : 0) | (int)(min(near, 0x7fffffu) << 8);
+    if (weight > 0.f) {
+        const unsigned long long w = __float_as_uint(weight), both = w << 32 | w;
+        for (int i = lane; i < n; i += 64) __hip_atomic_store(words + i, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 }  // namespace bkv

@@ -711,6 +711,27 @@ def test_status_is_the_sum_over_the_blocks(bk, oracle, dtype, d, b, per_seq, val
         bk.merge_reduce(p, K, V, workspace=ws, out=out)
 
 
+@pytest.mark.parametrize("dtype,d,b,per_seq,sink,recent", [
+    (torch.float32, 64, 256, 4, 0, 0), (torch.bfloat16, 64, 64, 130, 0, 0), (torch.bfloat16, 128, 64, 2, 0, 0), (torch.bfloat16, 128, 512, 600, 0, 0),
+    (torch.bfloat16, 64, 64, 16, 3, 4), (torch.bfloat16, 64, 64, 16, 2, 4)])
+def test_one_round_leaves_the_workspace_alone(bk, synth, dtype, d, b, per_seq, sink, recent):
+    """With the indices given a call of one round neither needs nor touches the workspace: two that overlap may have been given the same.  Odd windows
+    (weights that words do not fit) and even ones."""
+    n = per_seq * b + sink + recent
+    t = synth.clustered_layer_bf16(n_seq=3, n=n, d=d, g=1, nq=1, seed=3, device="cuda", dtype=dtype)
+    p = bk.make_params(d, b, 1, dtype, log_c=-8.0, seed=4, center=True)
+    pattern = torch.randint(0, 256, (bk.binding.merge_reduce_workspace_bytes(p, 3, per_seq * b) + 256,), device="cuda", dtype=torch.uint8)
+    ws = pattern.clone()
+    call = lambda w: bk.merge_reduce_protected(p, t["K"], t["V"], sink, recent, workspace=w) if sink else bk.merge_reduce(p, t["K"], t["V"], workspace=w)
+    out, none = call(ws), call(torch.empty(0, device="cuda", dtype=torch.uint8))
+    assert torch.equal(ws, pattern)
+    assert (out["status"] & 1).all()
+    for k in out:
+        assert torch.equal(out[k], none[k]), k
+    mid = out["w"][:, sink:out["w"].shape[1] - recent]
+    assert bool((mid == 2.0).all()) and out["w"].sum() == 2 * mid.numel() + 3 * (sink + recent)
+
+
 @pytest.mark.parametrize("dtype,d,b,T,n_sink,n_recent,n_mid", [
     (torch.bfloat16, 128, 512, 2, 256, 256, 4096),      # the paper's windows, workload-2 blocks
     (torch.float32, 64, 128, 1, 40, 7, 512),            # ragged windows
