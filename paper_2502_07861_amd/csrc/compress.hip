@@ -1574,9 +1574,12 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     // 4 x 4000 tokens, b = 256, 200 and 181.)
     constexpr bool kArgsHeld = VG == 2 && sizeof(T) == 2;
     int fails = 0, near_ties = 0;              // of the whole block (wavefront 2)
+    unsigned long long* words = nullptr;
+    int32_t* tree_status = nullptr;
     if (wave == 2 && want_events) {
         const CompressArgs& o = kArgsHeld ? a : *args_here();
-        unsigned long long* words = CARRY ? nullptr : o.status_words;
+        words = CARRY ? nullptr : o.status_words;
+        if (o.tree_mode && o.status_out) tree_status = o.status_out + seq * o.status_stride + o.round;
         int32_t* status = o.tree_mode ? nullptr : o.status_out;
         float* stats = o.stats_out;
         const unsigned long long label = o.status_label;
@@ -1682,16 +1685,16 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     }
     // (Behind the rows: an update takes trips to memory, one after the other for blocks that meet there, and rows that wait for it make
     // the block late.)
-    if (wave == 2 && a.tree_mode && a.status_out) {
-        const CompressArgs& o = kArgsHeld ? a : *args_here();
-        if (!CARRY && o.status_words) {
+    if (wave == 2 && tree_status) {
+        if (!CARRY && words) {
+            const CompressArgs& o = kArgsHeld ? a : *args_here();
             unsigned int i = blockIdx.x;                     // (the block's coordinates anew: kept through the pipeline they cost registers)
             asm volatile("" : "+s"(i));
             const unsigned int per = (unsigned int)o.blocks_per_seq, s = i / per;
             int32_t* status = o.status_out + (int64_t)s * o.status_stride;
             sum_status_words(o.status_words + (int64_t)s * (per + o.word_gap), (int)per, o.w_words > 0 ? o.w_out_val : 0.f, o.status_label, lane, status + o.round);
             if (i == s * per && lane < o.status_stride && lane > o.round) status[lane] = 0;      // the rounds to come add to theirs
-        } else if (lane == 0) add_status(o.status_out + seq * o.status_stride + o.round, fails, prog[3], near_ties);
+        } else if (lane == 0) add_status(tree_status, fails, prog[3], near_ties);
     }
     // A carry leaves the stream's state complete: as a launch of its own behind every round (survivors back from a buffer) the
     // same cost a launch per round and token whether or not anything carried.  An instance of its own: as a run-time choice these
