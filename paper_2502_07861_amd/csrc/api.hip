@@ -476,7 +476,7 @@ size_t bkv_attend_sets_workspace_bytes(const bkv_params* p, int64_t n_seq, int32
 
 }  // extern "C"
 
-// live: tokens that the numerator set holds at most and the ranges they lie in, 0: not known
+// live_tokens, live_ranges: tokens that the numerator set holds at most and the ranges they lie in, for an estimate of its groups; 0: not known
 static int attend_sets_impl(const bkv_params* p, const void* K_n, const void* V_n, const float* w_n, int64_t count_n, int64_t stride_n,
                     const void* K_d, const float* w_d, int64_t count_d, int64_t stride_d, int64_t n_seq, const void* Q,
                     int32_t g, int32_t nq, void* out, float* lse_out, void* workspace, size_t ws_bytes, int64_t live_tokens, int64_t live_ranges,

@@ -737,15 +737,21 @@ static bool attend_streams(int row_bytes, const AttendArgs& a) {
     return rows * row_bytes > ((int64_t)320 << 20);
 }
 
-// Two sets in one workgroup per sequence: sets whose places are mostly empty, of which the caller knows about how many tokens they hold
+// Two sets in one workgroup per sequence: sets whose places are mostly empty, of which the caller has an estimate of how many tokens they hold
 // (AttendArgs::live: a stream's), on a chip that is not full.  Splits, hand-over and merge cost about 4 us, more than such a workgroup's
 // few steps (8 regions x 256 places, bf16, d = 128, over 288 tokens, append and attend: 32 streams 18.2 -> 16.6 us a token, 200 over 200
-// tokens 35 -> 17.8).  The line: four steps a wavefront, a numerator's group counted as one, a denominator's as half; one workgroup a compute unit.
+// tokens 35 -> 17.8).  The line, in halves of a group of keys, a numerator's two and a denominator's one, over eight wavefronts; one
+// workgroup a compute unit.  From a quarter of the compute units on the splits have no others to go to: four groups a wavefront.  For
+// fewer sequences the splits take steps at the same time that one workgroup takes one after the other.  One workgroup / splits, 4 queries, halving once,
+// us (halves of a group): bf16, d = 128, 8 x 256 places, 1 stream 8.1 / 9.2 (36), 9.1 / 9.2 (46), 11.4 / 9.2 (62), 8 streams 8.8 / 9.4 (36), 9.9 / 9.4 (46),
+// 6 x 128 places 7.9 / 8.4 (32), 8.7 / 8.5 (37), 128 streams 8.7 / 18.2 (36), 13.3 / 19.1 (62); d = 64 7.5 / 8.0 (36), 8.9 / 8.1 (52); fp32, d = 128, 8 x 256, 1 stream
+// 9.0 / 10.5 (26), 11.5 / 10.6 (36), 13.0 / 10.6 (56), 128 streams 15.0 / 26.0 (56); d = 64 7.3 / 8.3 (26), 8.7 / 8.5 (36).
 static bool attend_in_one(const AttendArgs& a, const AttendPlan& p, int keys) {
     const int64_t g0 = (a.set[0].count + keys - 1) / keys, g1 = (a.set[1].count + keys - 1) / keys;
     if (p.nqt != 1 || a.set[0].count <= 0 || a.set[1].count <= 0 || !a.set[0].V || a.live <= 0 || g0 > kOneGroups || g1 > kOneGroups) return false;
-    const int64_t live0 = min(g0, a.live);
-    return a.n_seq <= compute_units() && 2 * live0 + g1 <= 2 * 4 * 8;
+    const int64_t live0 = min(g0, a.live), n_cu = compute_units();
+    const int64_t most = 4 * a.n_seq >= n_cu ? 64 : keys == 32 ? 36 : 30;
+    return a.n_seq <= n_cu && 2 * live0 + g1 <= most;
 }
 
 template <typename T, int D>

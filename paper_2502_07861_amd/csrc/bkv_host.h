@@ -202,7 +202,7 @@ struct AttendArgs {
     int64_t n_seq;
     int32_t n_q;
     float scale_log2;         // log2(e)/sqrt(d)
-    int64_t live;             // > 0: groups of set[0] (of 32 tokens, single precision 16) that hold a token at most; 0: not known
+    int64_t live;             // > 0: about how many groups of set[0] (of 32 tokens, single precision 16) hold a token (no bound); 0: not known
     // set by the launcher
     float* partial;           // workspace: [n_seq, n_qg, splits, rows, d + pad]
     unsigned long long* arrivals;      // workspace: a word per partial

@@ -273,11 +273,12 @@ def test_more_sequences_than_compute_units_equal_few(bk, synth, dtype, d):
 @pytest.mark.parametrize("dtype,d,n_seq,regions,cap_num,tokens,g,zero", [
     (torch.bfloat16, 128, 1, 6, 200, 1, 1, False), (torch.bfloat16, 128, 5, 8, 131, 97, 16, False), (torch.bfloat16, 64, 256, 6, 256, 70, 4, False),
     (torch.float32, 128, 3, 8, 256, 161, 5, False), (torch.float32, 64, 7, 6, 130, 129, 4, False), (torch.bfloat16, 128, 4, 8, 512, 40, 4, True),
-    (torch.bfloat16, 128, 257, 6, 200, 33, 4, False), (torch.bfloat16, 128, 2, 8, 520, 60, 17, False)])
+    (torch.float32, 128, 64, 8, 256, 161, 5, False), (torch.float32, 64, 3, 6, 130, 90, 16, False), (torch.bfloat16, 128, 64, 8, 256, 300, 4, False),
+    (torch.bfloat16, 128, 63, 8, 256, 300, 4, False), (torch.bfloat16, 128, 257, 6, 200, 33, 4, False), (torch.bfloat16, 128, 2, 8, 520, 60, 17, False)])
 def test_attend_of_a_short_stream_equals_attend_of_its_sets(bk, dtype, d, n_seq, regions, cap_num, tokens, g, zero):
     """A stream's mostly empty sets are taken by one workgroup a sequence; attend_sets on the same sets (which knows nothing of how many tokens
-    they hold) cuts them into splits.  Only the order of the sums differs.  (The last two take the splits as well: more sequences than compute
-    units, places or queries beyond the rule.)"""
+    they hold) cuts them into splits.  Only the order of the sums differs.  (The last three take the splits as well: too much for
+    few sequences, more sequences than compute units, places or queries beyond the rule.)"""
     gen = torch.Generator(device="cuda").manual_seed(tokens)
     rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
     k, v, Q = rand(tokens, n_seq, d).to(dtype), rand(tokens, n_seq, d) * 2.0 ** torch.randint(-1, 2, (tokens, n_seq, 1), generator=gen, device="cuda"), rand(n_seq, g, 1, d)
