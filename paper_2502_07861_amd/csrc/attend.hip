@@ -14,7 +14,7 @@
 //                 permute; fp32 elements are operands as they are.
 // So the pass needs no transposes, and a query's weights, running reference and sums stay in its own lanes.
 // What bounds it: with few queries per sequence the stream over K, V, w (1024 sequences x 8321 tokens x 4 queries, bf16:
-// 632 us = 6.9 TB/s, 710 with the rows kept in the caches); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
+// 631 to 649 us from box to box = 6.7 to 6.9 TB/s, 707 to 712 with the rows kept in the caches); with many (16 or 32 queries share every load) the latency of the loads from L2 and the merge (8 x 4096
 // tokens x 256 queries: 25 us; 114 us on the vector units, four queries per pass); short ranges the sum of two memory
 // round trips and the hand-over between workgroups (8 x 4357 tokens: 11.3 us in one launch; 14 us as pass + merge launches).
 #include <unistd.h>
@@ -730,7 +730,7 @@ size_t attend_scratch_bytes(int dtype, int d, int64_t n_seq, int64_t count, int 
 
 // Rows that are read once (up to 16 queries: one query group) and are more than the 256 MB that the cache in front of the memory
 // holds come back from memory the next time whatever is done, and keeping them costs.  Past the caches (4 queries, d = 128): bf16 1024 x 8321
-// tokens 707 -> 649 us, 1024 x 1000 (0.5 GB) 90.0 -> 81.5; fp32 256 x 8321 366 -> 340, 1024 x 1000 183 -> 175.  Below that they may still be
+// tokens 707 -> 649 us (on another box 711 -> 631), 1024 x 1000 (0.5 GB) 90.0 -> 81.5; fp32 256 x 8321 366 -> 340, 1024 x 1000 183 -> 175.  Below that they may still be
 // there (bf16 256 x 2000 tokens, 0.26 GB: 42.4 us when they are, 46.3 past the caches), so the line lies a little above what the cache holds.
 static bool attend_streams(int row_bytes, const AttendArgs& a) {
     const int64_t rows = a.n_seq * (2 * a.set[0].count + a.set[1].count);

@@ -736,9 +736,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     };
     const bool want_events = a.status_out || a.stats_out;
     // Chunks of up to so many panels leave all of them for the end: fp32 ones of two gain nothing (26.2 us for 4 x 512 tokens, d = 64, b = 128,
-    // two rounds, and 27.7), and with the values in memory, or several chunks of bf16 rows, the code beside the tiles costs registers that
-    // they have not got (200 blocks of 1024 bf16 rows, d = 128: 71.9 us in the pipeline, 71.1 at the end).
-    constexpr int kLateEvents = VG == 2 || (MULTI && sizeof(T) == 2) ? 16 : sizeof(T) == 4 ? 2 : 0;
+    // two rounds, and 27.7), and with the values in memory, or several chunks of bf16 rows of 256 bytes, the code beside the tiles costs
+    // registers that they have not got (200 blocks of 1024 bf16 rows, d = 128: 71.9 us in the pipeline, 71.1 at the end; d = 64 47.9 and 50.5).
+    constexpr int kLateEvents = VG == 2 || (MULTI && sizeof(T) == 2 && D == 128) ? 16 : sizeof(T) == 4 ? 2 : 0;
     // In blocks of several chunks with the values in memory the thresholds come before the loads: across them they cost those kernels registers
     // that the tiles' operands went to scratch memory for (bf16, d = 128, value factor, whole call: 256 blocks of 1024
     // 318 -> 277 us, of 640 157 -> 134; blocks resident as one chunk gain nothing).
@@ -1579,7 +1579,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
     if (wave == 2 && want_events) {
         const CompressArgs& o = kArgsHeld ? a : *args_here();
         words = CARRY ? nullptr : o.status_words;
-        if (o.tree_mode && o.status_out) tree_status = o.status_out + seq * o.status_stride + o.round;
+        if (VG != 2 && o.tree_mode && o.status_out) tree_status = o.status_out + seq * o.status_stride + o.round;
         int32_t* status = o.tree_mode ? nullptr : o.status_out;
         float* stats = o.stats_out;
         const unsigned long long label = o.status_label;
@@ -1611,8 +1611,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
         return a.idx_in ? (int64_t)a.idx_in[in_tok0 + kept] : tok_base + kept;
     };
     {
-        // Keys come from LDS when the whole block is still resident, else from global memory (L2); value rows
-        // always come from global memory.  All loads of a pass are issued before its first store.
+        // Keys come from LDS when the whole block is still resident, else from global memory (L2); value rows from LDS where they are
+        // resident beside the keys (VG = 1), else from global memory.  So neither area may be used for anything else before this.  All
+        // loads of a pass are issued before its first store.
         char* Ko = a.K_out ? a.K_out + out_tok0 * G::kRowBytes : nullptr;
         const bool do_v = a.V_out && a.V;
         const char* Vseq = do_v ? a.V + (size_t)seq * a.v_seq_stride * G::kRowBytes : nullptr;
@@ -1678,13 +1679,20 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const CompressArgs a
             }
         }
     }
-    const int in_words = CARRY ? 0 : a.w_words - (int)(out_tok0 - seq * a.out_seq_stride);       // weights of this block whose places hold words for now
+    // (fp32 with the values in memory has no register for these two: 150 blocks of 192 rows, d = 128, 57.5 us read here, 64.7 held; nor for where the
+    // status goes, below)
+    const CompressArgs& late = VG == 2 && !kArgsHeld ? *args_here() : a;
+    const int in_words = CARRY ? 0 : late.w_words - (int)(out_tok0 - seq * late.out_seq_stride);       // weights of this block whose places hold words for now
     for (int r = tid; r < half; r += kThreads) {
         if (a.w_out && r >= in_words) a.w_out[out_tok0 + r] = a.w_out_val;
         if (a.idx_out) a.idx_out[idx_out0 + r] = (int32_t)src_token(r);
     }
     // (Behind the rows: an update takes trips to memory, one after the other for blocks that meet there, and rows that wait for it make
     // the block late.)
+    if (VG == 2 && wave == 2 && a.tree_mode && a.status_out) {
+        const CompressArgs& o = kArgsHeld ? a : *args_here();
+        tree_status = o.status_out + seq * o.status_stride + o.round;
+    }
     if (wave == 2 && tree_status) {
         if (!CARRY && words) {
             const CompressArgs& o = kArgsHeld ? a : *args_here();
