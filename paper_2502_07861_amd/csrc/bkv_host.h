@@ -58,6 +58,7 @@ struct CompressArgs {
     // a sequence (the same address as w_out, aligned to 8 bytes, an even stride), which are written when the sum is.
     unsigned long long* status_words;
     unsigned long long status_label;   // 51 bits that no other launch has
+    int32_t raise_fetch;      // compress_pair_kernel, two chunks: the first rows and the statistics at a raised wave priority
     int64_t word_gap;
     int32_t w_words;
     int32_t* sticky_err;      // or null: one word that collects BKV_STATUS_INTERNAL of every instance (never cleared by the kernel)
@@ -113,7 +114,7 @@ bool compress_sums_status(int dtype, int d, int b, bool value_gram, int64_t n_in
 unsigned long long status_label();                                                      // a new one
 hipError_t launch_compress(int dtype, int d, bool emit_g, CompressArgs& a, int64_t n_inst, hipStream_t st);
 // two blocks per compute unit (compress_pair.hip): rows of 256 bytes, no weight dump, value factor, in-place carry or scattered rows
-hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t n_inst, hipStream_t st);
+hipError_t launch_compress_pair(int dtype, int d, CompressArgs& a, int64_t n_inst, hipStream_t st);
 hipError_t launch_fill_u32(void* p, uint32_t v, int64_t n, hipStream_t st);
 hipError_t launch_copy_rows(const void* src, void* dst, int64_t n_seq, int64_t src_seq_stride,
                             int64_t dst_seq_stride, int64_t rows, int row_bytes, hipStream_t st);

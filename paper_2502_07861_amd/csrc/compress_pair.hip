@@ -175,10 +175,11 @@ __global__ __launch_bounds__(kThreads, 4) void compress_pair_kernel(const Compre
     int l = flip ? 7 - wave : wave;                                 // this wavefront's column panel of the chunk
     // Blocks of two chunks fetch rows and form their statistics for a third of their time, beside a block that walks at raised priority and leaves
     // them the vector unit's gaps: 40 of 125 us, where the statistics take 2.3 by themselves.  One step up they are sooner done and the two
-    // blocks' phases lie better (256 x 32768 tokens, b = 1024, one round 2.04 -> 1.97 ms, 64 x 32768, two rounds 764 -> 740 us, b = 640 305 -> 296,
-    // 768 364 -> 362, 896 471 -> 458).  Three steps give less, raised for the output or the second chunk's rows as well nothing; blocks of one
+    // blocks' phases lie better (256 x 32768 tokens, b = 1024, one round 2.04 -> 1.97 ms, 64 x 32768, two rounds 764 -> 740 us); not in every launch
+    // (launch_compress_pair).  Three steps give less, raised for the output or the second chunk's rows as well nothing; blocks of one
     // chunk lose (b = 384 340 -> 352 us, 256 488 -> 495).
-    if constexpr (TWO) __builtin_amdgcn_s_setprio(1);
+    if constexpr (TWO)
+        if (a.raise_fetch) __builtin_amdgcn_s_setprio(1);
     // Two batches at a time are on their way: one straight into LDS, one into registers.
     fetch(0);
     uintx4 rows1[8], keep[TWO ? 8 : 1];
@@ -791,8 +792,14 @@ hipError_t launch_pair_t(const CompressArgs& a, int64_t n_inst, hipStream_t st) 
 
 }  // namespace
 
-hipError_t launch_compress_pair(int dtype, int d, const CompressArgs& a, int64_t n_inst, hipStream_t st) {
+hipError_t launch_compress_pair(int dtype, int d, CompressArgs& a, int64_t n_inst, hipStream_t st) {
     const bool two = a.b > 512, table = a.desc != nullptr;
+    const int64_t n_cu = compute_units();
+    // Raised / not, us.  Up to two blocks a compute unit: b = 640, 300 blocks 71 / 75, 512 85 / 90, b = 1024 116 / 119, 139 / 142.  Between two and three the last
+    // blocks are alone on theirs: b = 640, 600 blocks 135 / 126, 832 172 / 160, 1024 198 / 196, 700 blocks 214 / 209.  With more it depends on how long the
+    // second chunk walks: b = 576, 1200 blocks 213 / 197, 640 217 / 207, 704 4000 blocks 676 / 654; 768 800 blocks 174 / 179, 1200 239 / 239, 4000 737 / 719;
+    // 896 1200 blocks 284 / 290, 4000 875 / 919, 1024 330 / 338, 1048 / 1058.
+    a.raise_fetch = n_inst <= 2 * n_cu || (a.b >= 768 && n_inst > 3 * n_cu);
 #define BKV_PAIR(TT, DD, TWO) return table ? launch_pair_t<TT, DD, TWO, true>(a, n_inst, st) : launch_pair_t<TT, DD, TWO, false>(a, n_inst, st)
     if (dtype == BKV_BF16 && d == 128) { if (two) { BKV_PAIR(__bf16, 128, true); } else { BKV_PAIR(__bf16, 128, false); } }
     if (dtype == BKV_F32 && d == 64 && !two) { BKV_PAIR(float, 64, false); }
